@@ -19,9 +19,10 @@
 // the softmax, so they contribute exactly 0; blocks whose 1024 bits are all set skip the
 // masking.
 //
-// fp32 storage uses v_mfma_f32_32x32x2_f32 (true fp32 products), fp16 storage uses
-// v_mfma_f32_32x32x16_f16 with fp32 accumulation; P is rounded to fp16 only as the MFMA
-// operand, l is summed in fp32.
+// fp32 storage splits its operands into 16-bit parts whose products the 16-bit matrix cores sum
+// in fp32 (see ScoreOperand and ValueOperand; v_mfma_f32_32x32x2_f32 only where a tile holds an
+// infinity), fp16 storage uses v_mfma_f32_32x32x16_f16 with fp32 accumulation; P is rounded
+// to fp16 only as the MFMA operand, l is summed in fp32.
 //
 // Tiles with many edges (global-token rows) are cut into segments of their key-block span;
 // each segment is one more work item of the same launches, leaves a partial (m, l, acc)
@@ -544,28 +545,209 @@ struct SliceExchange {
 };
 
 // ---- fp32 storage ---------------------------------------------------------------------------
+// fp32 products on the 16-bit matrix cores (16 times the rate of the fp32 ones), by splitting
+// the operands into parts whose products are summed in fp32.
+//
+// Scores.  Every row of Q and K is scaled by a power of two that takes its largest element to
+// [2^14, 2^15), and an element x is written as hi + lo, hi = fp16(x), lo = fp16(x - hi) (the
+// difference is exact): the remainder is below 2^-24 |x|, half a unit in the last place of fp32,
+// or 2^-40 of the row's largest element where lo is subnormal.  A product is taken as
+//   lo.hi + hi.lo + hi.hi
+// and lo.lo, below 2^-24 |a.b|, is left out.  The scales return in the exponent of the softmax.
+//
+// Weights and values.  The numerators of the softmax have no largest element to scale by until
+// the row is done, and small ones count when there are many, so they keep the exponent range of
+// fp32: three bf16 parts, hi = bf16(x), mid = bf16(x - hi), lo = x - hi - mid, where both
+// differences are exact in fp32 and lo (at most 8 significant bits) is exact in bf16.  A product
+// is taken as
+//   lo.hi + hi.lo + mid.mid + mid.hi + hi.mid + hi.hi
+// and the terms left out (mid.lo, lo.mid, lo.lo) are below 2^-26 |a.b|.
+//
+// The smallest terms go first into an accumulator, so that only the last few of its additions
+// round at the size of the sum, where the fp32 matrix instruction (two channels or keys at a
+// time) rounds at every one: the error against 64-bit arithmetic is smaller than with
+// fp32 products (longformer mask, L = 65,536: 3.0e-7 instead of 4.1e-7 relative).
+//
+// Per 32 x 32 block: 36 matrix instructions of 32 cycles instead of 64 of 64, and about 380 vector
+// instructions for the splits.  Longformer mask, L = 65,536, 8 heads, prepared: 494 -> 395 us;
+// +-815 at d = 256, L = 16,301: 282 -> 210 us.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
+
+// Two values at a time: hi = fp16(x) packed into one register, x - hi by the mixed-precision
+// fma (the fp16 operand is read straight out of the packed pair, no conversion back), and the
+// remainders packed again: four instructions per pair.
+__device__ __forceinline__ void split_pair_f16(float x0, float x1, half2v& hi, half2v& lo) {
+  hi = half2v{(_Float16)x0, (_Float16)x1};
+  const uint32_t hp = __builtin_bit_cast(uint32_t, hi);
+  float r0, r1;
+  asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r0) : "v"(hp), "v"(x0));
+  asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r1) : "v"(hp), "v"(x1));
+  lo = half2v{(_Float16)r0, (_Float16)r1};
+}
+// One operand of the score products (8 values per lane).
+struct ScoreOperand {
+  half8 hi, lo;
+  __device__ __forceinline__ void split(const float* x, float factor) {
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+      half2v h2, l2;
+      split_pair_f16(x[e] * factor, x[e + 1] * factor, h2, l2);
+      hi[e] = h2[0]; hi[e + 1] = h2[1];
+      lo[e] = l2[0]; lo[e + 1] = l2[1];
+    }
+  }
+};
+// The scale of a row whose largest magnitude is `top`: `down` = 2^(15 - e) takes it below 2^15, `up` is
+// its inverse.  (An infinite row gets some scale; its products are no numbers.)
+struct RowScale {
+  float down, up;
+  __device__ __forceinline__ explicit RowScale(float top) {
+    int e = __builtin_amdgcn_frexp_expf(top);
+    e = e > -100 ? e : -100;
+    down = __builtin_bit_cast(float, (uint32_t)(127 + 15 - e) << 23);
+    up = __builtin_bit_cast(float, (uint32_t)(127 - 15 + e) << 23);
+  }
+};
+template <int kN>
+__device__ __forceinline__ float largest(const float* x) {
+  float top = 0.f;
+#pragma unroll
+  for (int e = 0; e < kN; e += 2) top = __builtin_fmaxf(__builtin_fmaxf(top, __builtin_fabsf(x[e])), __builtin_fabsf(x[e + 1]));
+  return top;
+}
+// Scores of 32 keys: S[key acc_row(r, h)] with the key's scale, factors[key], taken back (a power of
+// two: exact); the caller takes back the query's.
+__device__ __forceinline__ floatx16 split_scores(const ScoreOperand (&k)[4], const ScoreOperand (&q)[4],
+                                                 const float* factors, int h) {
+  floatx16 s = {0};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    s = __builtin_amdgcn_mfma_f32_32x32x16_f16(k[i].lo, q[i].hi, s, 0, 0, 0);
+    s = __builtin_amdgcn_mfma_f32_32x32x16_f16(k[i].hi, q[i].lo, s, 0, 0, 0);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_mfma_f32_32x32x16_f16(k[i].hi, q[i].hi, s, 0, 0, 0);
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const float4 f = *reinterpret_cast<const float4*>(factors + 8 * g + 4 * h);
+    s[4 * g] *= f.x; s[4 * g + 1] *= f.y; s[4 * g + 2] *= f.z; s[4 * g + 3] *= f.w;
+  }
+  return s;
+}
+
+__device__ __forceinline__ uint32_t round_pair_bf16(float x0, float x1) {
+  const float2v x = {x0, x1};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
+}
+// x0 and x1 less the two bf16 numbers packed in `pair`
+__device__ __forceinline__ void take_pair(float& x0, float& x1, uint32_t pair) {
+  x0 -= __builtin_bit_cast(float, pair << 16);
+  x1 -= __builtin_bit_cast(float, pair & 0xffff0000u);
+}
+// One operand of the products of weights and values (8 values per lane).
+struct ValueOperand {
+  bf16x8 hi, mid, lo;
+  __device__ __forceinline__ void split(const float* x) {
+    uint4v a, b, c;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float x0 = x[2 * e], x1 = x[2 * e + 1];
+      a[e] = round_pair_bf16(x0, x1);
+      take_pair(x0, x1, a[e]);
+      b[e] = round_pair_bf16(x0, x1);
+      take_pair(x0, x1, b[e]);
+      c[e] = round_pair_bf16(x0, x1);
+    }
+    hi = __builtin_bit_cast(bf16x8, a);
+    mid = __builtin_bit_cast(bf16x8, b);
+    lo = __builtin_bit_cast(bf16x8, c);
+  }
+};
+__device__ __forceinline__ floatx16 mfma_bf16(bf16x8 a, bf16x8 b, floatx16 acc) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
+}
+__device__ __forceinline__ floatx16 split_product(const ValueOperand& a, const ValueOperand& b, floatx16 acc) {
+  acc = mfma_bf16(a.lo, b.hi, acc);
+  acc = mfma_bf16(a.hi, b.lo, acc);
+  acc = mfma_bf16(a.mid, b.mid, acc);
+  acc = mfma_bf16(a.mid, b.hi, acc);
+  acc = mfma_bf16(a.hi, b.mid, acc);
+  return mfma_bf16(a.hi, b.hi, acc);
+}
+
+// True in a lane whose state holds an infinity or a NaN.
+__device__ __forceinline__ bool not_finite(const TileState& st) {
+  float z = st.l * 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    z = __builtin_fmaf(st.o[0][r], 0.f, z);
+    z = __builtin_fmaf(st.o[1][r], 0.f, z);
+  }
+  return !(z == 0.f);
+}
+
+// The split of an infinity is no number (nor is that of a finite value that rounds to an
+// infinite bf16), so the products of such inputs are not those of fp32.  A tile whose state
+// ends with an infinity or a NaN is therefore computed once more with fp32 products (run_exact),
+// which decide what such inputs give.
 template <int kD>
 struct CoreF32T {
   using Stage = StageMap<float, kD>;
-  float qf[32];   // Q[query n][h*32 + t] (of this wavefront's 64-channel slice)
+  ScoreOperand q2[4];         // Q[query n][h*32 + 8s .. +7], s = 0..3 (of this wavefront's 64-channel slice)
+  float q_up;                 // scale of this lane's query
+  const float* q_row;         // this lane's half row of Q, for run_exact
+  bool q_negate;
   SliceExchange<kD> xchg;   // used for kD > 64 only
 
-  __device__ void load_q(const float* Qrow, int h, bool negate) {
-    const float4* src = reinterpret_cast<const float4*>(Qrow + h * 32);
+  __device__ void load_qf(float (&qf)[32]) const {
+    const float4* src = reinterpret_cast<const float4*>(q_row);
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       const float4 v = src[t];
       qf[4 * t] = v.x; qf[4 * t + 1] = v.y; qf[4 * t + 2] = v.z; qf[4 * t + 3] = v.w;
     }
-    if (negate) {
+    if (q_negate) {
 #pragma unroll
       for (int t = 0; t < 32; ++t) qf[t] = -qf[t];
     }
   }
+  __device__ void load_q(const float* Qrow, int h, bool negate) {
+    q_row = Qrow + h * 32;
+    q_negate = negate;
+    float qf[32];
+    load_qf(qf);
+    const RowScale scale(row_top(qf, h));
+    q_up = scale.up;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) q2[s].split(qf + 8 * s, scale.down);
+  }
+  // largest magnitude of the row whose halves this lane and the one 32 positions away hold
+  __device__ static float row_top(const float (&x)[32], int h) {
+    const float top = largest<32>(x);
+    return __builtin_fmaxf(top, other_half(top, h));
+  }
+  // K fragment -> operands; the key's scale goes to `factors`
+  __device__ static void split_k(const float (&kf)[32], int n, int h, ScoreOperand (&k2)[4], float* factors) {
+    const RowScale scale(row_top(kf, h));
+    if (h == 0) factors[n] = scale.up;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) k2[s].split(kf + 8 * s, scale.down);
+  }
+  // scores; returns what takes them to log2 units
+  __device__ float scores(const ScoreOperand (&k2)[4], const float* factors, float c, int lane, floatx16& s) {
+    s = split_scores(k2, q2, factors, lane >> 5);
+    if (kD == kHeadDim) return q_up * c;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] *= q_up;             // (the slices of a row have scales of their own)
+    xchg.sum_slices(s, lane);
+    return c;
+  }
 
   // kf[t] = K[key n of the block][h*32 + t], straight from global memory: 128 contiguous bytes
-  // per lane, i.e. kFragLoads loads of 16 bytes (the widest load there is; the counted waits of
-  // run_regk rely on this number).  lane_off = byte offset of the lane's key row and half inside
+  // per lane, i.e. kFragLoads loads of 16 bytes (the widest load there is; the counted waits
+  // below rely on this number).  lane_off = byte offset of the lane's key row and half inside
   // a whole block.
   static constexpr int kFragLoads = 32 * (int)sizeof(float) / 16;
   __device__ static void load_k(const float* __restrict__ Kh, const BlockInfo& b, int64_t stride_bytes,
@@ -587,202 +769,168 @@ struct CoreF32T {
 
   static constexpr int kBlockBytes = kTile * kHeadDim * 4;   // one staged K or V block
 
-  // kf[t] = K[key n][h*32 + t] out of the staged block.  The global -> LDS copy moved keys
-  // 4i..4i+3 per instruction, 16 lanes per 256-byte row (whole cache lines), and stored the
-  // sixteen 16-byte chunks of a row XOR-swizzled: chunk c of key r lives at chunk slot
-  // c ^ (r & 15).  This read (each lane 128 contiguous bytes of its own key row, 16 at a time)
-  // then spreads 8 consecutive lanes over the 8 groups of 4 banks instead of hitting one.
-  __device__ static void read_k(const char* ldsk, int n, int h, float (&kf)[32]) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int slot = (8 * h + j) ^ (n & 15);
-      const float4 v = *reinterpret_cast<const float4*>(ldsk + (n * 16 + slot) * 16);
-      kf[4 * j] = v.x; kf[4 * j + 1] = v.y; kf[4 * j + 2] = v.z; kf[4 * j + 3] = v.w;
-    }
-  }
-
-  // S^T = K_blk Q^T, softmax, O^T += V_blk^T P^T for one block whose V rows are staged at ldsv.
-  // (kKeepMore, more: see wait_staged_v)
-  template <int kKeepMore>
-  __device__ void block_math(const float (&kf)[32], const BlockInfo& b, float c, int n, int h,
-                             TileState& st, const char* ldsv, bool more) {
-    floatx16 s = {0};
-#pragma unroll
-    for (int t = 0; t < 32; ++t)
-      s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[t], qf[t], s, 0, 0, 0);
-    if (kD > kHeadDim) xchg.sum_slices(s, 32 * h + n);
-    float p[16];
-    softmax_block(s, c, b, h, st, p);
-    wait_staged_v<kKeepMore>(more);
-    __builtin_amdgcn_wave_barrier();
+  // O^T += V_blk^T P^T with the V rows of the block staged (complete) at ldsv.  A operand:
+  // V^T[channel cb*32+n][key acc_row(r,h)] = staged V[key][channel], 8 keys per operand.
+  __device__ static void weigh_v(const float (&p)[16], const BlockInfo& b, int n, int h, TileState& st,
+                                 const char* ldsv) {
     const float* vread = reinterpret_cast<const float*>(ldsv) + h * 4 * kHeadDim + n;
-    if (b.full) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        // A operand: V^T[channel cb*32+n][key acc_row(r,h)] = staged V[key][channel]
-        const float v0 = vread[acc_row(r, 0) * kHeadDim];
-        const float v1 = vread[acc_row(r, 0) * kHeadDim + 32];
-        st.o[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(v0, p[r], st.o[0], 0, 0, 0);
-        st.o[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(v1, p[r], st.o[1], 0, 0, 0);
-      }
-    } else {
-      // A masked block: registers 4g..4g+3 hold the keys 8g..8g+7 of the block; a group of keys
-      // that no query of the tile attends (p = 0 in every lane) is skipped, which is exact
-      // (e.g. the upper half of a block that holds 16 global tokens).
+    for (int u = 0; u < 2; ++u) {
+      // registers 8u .. 8u+7 hold the keys 16u .. 16u+15 of the block: if no query of the tile
+      // attends one of them (p = 0 in every lane) they are skipped, which is exact (e.g. the
+      // upper half of a block that holds 16 global tokens)
+      if (!b.full && __builtin_amdgcn_ballot_w64(((b.word >> (16 * u)) & 0xffffu) != 0) == 0) continue;
+      ValueOperand pb;
+      pb.split(p + 8 * u);
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        if (__builtin_amdgcn_ballot_w64(((b.word >> (8 * g)) & 0xffu) != 0) == 0) continue;
+      for (int cb = 0; cb < 2; ++cb) {
+        float v[8];
 #pragma unroll
-        for (int r = 4 * g; r < 4 * g + 4; ++r) {
-          const float v0 = vread[acc_row(r, 0) * kHeadDim];
-          const float v1 = vread[acc_row(r, 0) * kHeadDim + 32];
-          st.o[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(v0, p[r], st.o[0], 0, 0, 0);
-          st.o[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(v1, p[r], st.o[1], 0, 0, 0);
-        }
+        for (int e = 0; e < 8; ++e) v[e] = vread[acc_row(8 * u + e, 0) * kHeadDim + cb * 32];
+        ValueOperand va;
+        va.split(v);
+        st.o[cb] = split_product(va, pb, st.o[cb]);
       }
     }
   }
 
-  // Variant with the K block staged in LDS (many blocks per tile).  Both K and V blocks travel
-  // global -> LDS without registers, as whole rows (coalesced).  Per block k: the V copy is
-  // issued first; the K fragment (copied during block k-1) is read into registers and the K
-  // copy of block k+1 is issued at once, so it lands behind the matrix work of block k; block
-  // ids / mask words are fetched two blocks ahead.
+  // The pipeline: the K fragment of block k+1 is loaded global -> registers (each lane reads 128
+  // contiguous bytes of its key row) into the registers that block k's fragment left when it was
+  // split, the V block k is copied global -> LDS behind the S^T matrix work.
   template <typename Src>
-  __device__ void run_ldsk(const float* __restrict__ Kh, const float* __restrict__ Vh, const Src& src,
-                      int k0, int k1, float c, int lane, TileState& st, char* lds) {
-    if (k0 >= k1) return;
-    const int n = lane & 31, h = lane >> 5;
-    Stage sm;
-    sm.init(src.key_stride(), lane);
-    char* ldsk = lds;
-    char* ldsv = lds + kBlockBytes;
-    BlockInfo b = src.get(k0, n);
-    BlockInfo b1 = src.get(k0 + 1 < k1 ? k0 + 1 : k0, n);
-    src.resolve(b);
-    __builtin_amdgcn_wave_barrier();     // reads of both buffers by an earlier work item are done
-    sm.stage_k(Kh, b, lane, ldsk);
-    for (int k = k0; k < k1; ++k) {
-      const bool more = k + 1 < k1;      // wave-uniform
-      src.resolve(b1);
-      __builtin_amdgcn_wave_barrier();   // the previous block's reads of the staged V are done
-      sm.stage_v(Vh, b, lane, ldsv);
-      BlockInfo b2 = b1;
-      if (k + 2 < k1) b2 = src.get(k + 2, n);
-      wait_k_block<8, Src::kGetLoads>(k + 2 < k1);   // K block k: older than the V copies (and the record loads)
-      __builtin_amdgcn_wave_barrier();
-      float kf[32];
-      read_k(ldsk, n, h, kf);
-      wait_lds_reads();                  // the K buffer may be overwritten now
-      __builtin_amdgcn_wave_barrier();
-      if (more) sm.stage_k(Kh, b1, lane, ldsk);
-      // V block k is older than the 8 K copies issued above (if any)
-      block_math<8>(kf, b, c, n, h, st, ldsv, more);
-      b = b1;
-      b1 = b2;
-    }
-  }
-
-  // Variant with the K fragment in registers (few blocks per tile): the K fragment of block k+1 is
-  // prefetched global -> registers (each lane reads 128 contiguous bytes of its key row), the V
-  // block k is copied global -> LDS behind the S^T matrix work, and block ids / mask words are
-  // fetched two blocks ahead, so no load sits on the critical path of the matrix cores.  The
-  // loop is unrolled over two fragment buffers, so the prefetched fragment is never copied.
-  template <typename Src>
-  __device__ void run_regk(const float* __restrict__ Kh, const float* __restrict__ Vh, const Src& src,
-                      int k0, int k1, float c, int lane, TileState& st, char* lds) {
-    if (k0 >= k1) return;
+  __device__ void run_split(const float* __restrict__ Kh, const float* __restrict__ Vh, const Src& src,
+                            int k0, int k1, float c, int lane, TileState& st, char* lds) {
     const int n = lane & 31, h = lane >> 5;
     Stage sm;
     sm.init(src.key_stride(), lane);
     const uint32_t klane = (uint32_t)(n * sm.stride_bytes) + h * 128;
+    float* factors = reinterpret_cast<float*>(lds + kBlockBytes + 512);
     BlockInfo b = src.get(k0, n);
-    BlockInfo b1 = src.get(k0 + 1 < k1 ? k0 + 1 : k0, n);
     src.resolve(b);
-    float kfa[32], kfb[32];
-    load_k(Kh, b, sm.stride_bytes, klane, n, h, kfa);
-    auto step = [&](int k, float (&kf)[32], float (&kf_next)[32]) {
+    float kf[32];
+    load_k(Kh, b, sm.stride_bytes, klane, n, h, kf);
+    for (int k = k0; k < k1; ++k) {
+      const bool more = k + 1 < k1;      // wave-uniform
+      ScoreOperand k2[4];
+      split_k(kf, n, h, k2, factors);
+      BlockInfo b1 = src.get(more ? k + 1 : k, n);
       src.resolve(b1);
-      if (k + 1 < k1) load_k(Kh, b1, sm.stride_bytes, klane, n, h, kf_next);
       __builtin_amdgcn_wave_barrier();   // the previous block's reads of the staged V are done
       sm.stage_v(Vh, b, lane, lds);
-      BlockInfo b2 = b1;
-      if (k + 2 < k1) b2 = src.get(k + 2, n);
-      block_math<0>(kf, b, c, n, h, st, lds, false);
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0); // (the counted wait below relies on this order)
+      if (more) load_k(Kh, b1, sm.stride_bytes, klane, n, h, kf);
+      floatx16 s;
+      const float up = scores(k2, factors, c, lane, s);
+      float p[16];
+      softmax_block(s, up, b, h, st, p);
+      wait_staged_v<kFragLoads>(more);   // V block k is older than the K fragment loads (if any)
+      __builtin_amdgcn_wave_barrier();
+      weigh_v(p, b, n, h, st, lds);
       b = b1;
-      b1 = b2;
-    };
-    for (int k = k0; k < k1; k += 2) {
-      step(k, kfa, kfb);
-      if (k + 1 >= k1) break;
-      step(k + 1, kfb, kfa);
     }
   }
 
-  // Explicit block lists: as run_regk, with the block ids read through the scalar path and the
-  // mask words of block k+1 copied global -> LDS while block k is computed (two 256-byte slots
-  // behind the V block), as in CoreF16T::run_ldsk.  The only loads into vector registers are the
-  // K fragments, and the step's own waits are counted: V block k, then the words of block k+1,
-  // then the K fragment of block k+1 are issued in this order, so the fragment may still be in
-  // flight during the PV products.  (Workload 2, measured side by side: 4 % faster than with the records loaded
-  // into vector registers two blocks ahead.)
-  __device__ void run_regk(const float* __restrict__ Kh, const float* __restrict__ Vh,
-                           const ExplicitBlocks& src, int k0, int k1, float c, int lane, TileState& st,
-                           char* lds) {
-    if (k0 >= k1) return;
+  // Explicit block lists: the block ids are read through the scalar path and the mask words of
+  // block k+1 are copied global -> LDS while block k is computed (two 256-byte slots behind the V
+  // block), as in CoreF16T::run_ldsk.  The only loads into vector registers are the K fragments.
+  __device__ void run_split(const float* __restrict__ Kh, const float* __restrict__ Vh,
+                            const ExplicitBlocks& src, int k0, int k1, float c, int lane, TileState& st,
+                            char* lds) {
     const int n = lane & 31, h = lane >> 5;
     Stage sm;
     sm.init(1, lane);
     const uint32_t klane = (uint32_t)(n * sm.stride_bytes) + h * 128;
     char* ldsw = lds + kBlockBytes;              // two slots of 64 mask words (both half-waves)
+    float* factors = reinterpret_cast<float*>(lds + kBlockBytes + 512);
     const uint32_t* wsrc = src.mask + n;         // this lane's word of block k: wsrc[32 k]
     BlockInfo b = src.block(k0);
     BlockInfo b1 = src.block(k0 + 1 < k1 ? k0 + 1 : k0);
     src.resolve(b);
     __builtin_amdgcn_wave_barrier();     // reads of the buffers by an earlier work item are done
     copy4_to_lds(wsrc + (int64_t)k0 * kTile, ldsw + (k0 & 1) * 256);
-    float kfa[32], kfb[32];
-    load_k(Kh, b, sm.stride_bytes, klane, n, h, kfa);
-    auto step = [&](int k, float (&kf)[32], float (&kf_next)[32]) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    float kf[32];
+    load_k(Kh, b, sm.stride_bytes, klane, n, h, kf);
+    for (int k = k0; k < k1; ++k) {
       const bool more = k + 1 < k1;      // wave-uniform
       src.resolve(b1);
-      __builtin_amdgcn_wave_barrier();   // the previous block's reads of V and of the other word slot are done
-      sm.stage_v(Vh, b, lane, lds);
-      if (more) {
-        copy4_to_lds(wsrc + (int64_t)(k + 1) * kTile, ldsw + ((k + 1) & 1) * 256);
-        load_k(Kh, b1, sm.stride_bytes, klane, n, h, kf_next);
-      }
-      BlockInfo b2 = b1;
-      if (k + 2 < k1) b2 = src.block(k + 2);
-      // the words and the K fragment of block k are older than the operations above: the V copies
-      // and, if a block follows, its word copy and fragment loads
-      if (more) wait_loads_except<Stage::kCopies + 1 + kFragLoads>(); else wait_loads_except<Stage::kCopies>();
+      ScoreOperand k2[4];
+      split_k(kf, n, h, k2, factors);
+      wait_loads_except<0>();            // the words of block k are older than its K fragment
       __builtin_amdgcn_wave_barrier();
       b.word = *reinterpret_cast<const uint32_t*>(ldsw + (k & 1) * 256 + lane * 4);
-      // V block k is older than the word copy and the fragment loads (if any)
-      block_math<1 + kFragLoads>(kf, b, c, n, h, st, lds, more);
+      sm.stage_v(Vh, b, lane, lds);
+      if (more) copy4_to_lds(wsrc + (int64_t)(k + 1) * kTile, ldsw + ((k + 1) & 1) * 256);
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0); // (the counted wait below relies on this order)
+      if (more) load_k(Kh, b1, sm.stride_bytes, klane, n, h, kf);
+      BlockInfo b2 = b1;
+      if (k + 2 < k1) b2 = src.block(k + 2);
+      floatx16 s;
+      const float up = scores(k2, factors, c, lane, s);
+      float p[16];
+      softmax_block(s, up, b, h, st, p);
+      wait_staged_v<kFragLoads>(more);   // V block k is older than the K fragment loads (if any)
+      __builtin_amdgcn_wave_barrier();
+      weigh_v(p, b, n, h, st, lds);
       b = b1;
       b1 = b2;
-    };
-    for (int k = k0; k < k1; k += 2) {
-      step(k, kfa, kfb);
-      if (k + 1 >= k1) break;
-      step(k + 1, kfb, kfa);
     }
   }
 
-  // kLdsK selects the pipeline: K block staged in LDS (coalesced whole-row copies; best with many
-  // blocks per tile) or K fragment loaded straight into registers (no LDS round trip before the
-  // first product; best with two or three blocks per tile).
+  // The same tile with v_mfma_f32_32x32x2_f32 (true fp32 products), one block after the other.
+  template <typename Src>
+  __device__ void run_exact(const float* __restrict__ Kh, const float* __restrict__ Vh, const Src& src,
+                            int k0, int k1, float c, int lane, TileState& st, char* lds) {
+    const int n = lane & 31, h = lane >> 5;
+    Stage sm;
+    sm.init(src.key_stride(), lane);
+    const uint32_t klane = (uint32_t)(n * sm.stride_bytes) + h * 128;
+    float qf[32];
+    load_qf(qf);
+    for (int k = k0; k < k1; ++k) {
+      BlockInfo b = src.get(k, n);
+      src.resolve(b);
+      __builtin_amdgcn_wave_barrier();   // the previous block's reads of the staged V are done
+      sm.stage_v(Vh, b, lane, lds);
+      float kf[32];
+      load_k(Kh, b, sm.stride_bytes, klane, n, h, kf);
+      floatx16 s = {0};
+#pragma unroll
+      for (int t = 0; t < 32; ++t) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[t], qf[t], s, 0, 0, 0);
+      if (kD > kHeadDim) xchg.sum_slices(s, lane);
+      float p[16];
+      softmax_block(s, c, b, h, st, p);
+      wait_loads_except<0>();
+      __builtin_amdgcn_wave_barrier();
+      const float* vread = reinterpret_cast<const float*>(lds) + h * 4 * kHeadDim + n;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float v0 = vread[acc_row(r, 0) * kHeadDim];
+        const float v1 = vread[acc_row(r, 0) * kHeadDim + 32];
+        st.o[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(v0, p[r], st.o[0], 0, 0, 0);
+        st.o[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(v1, p[r], st.o[1], 0, 0, 0);
+      }
+    }
+  }
+
   template <int kPipe>
-  static constexpr int lds_bytes() { return kPipe == kPipeRegK ? kBlockBytes + 512 : 2 * kBlockBytes; }
+  static constexpr int lds_bytes() { return kBlockBytes + 512 + kTile * 4; }     // V block, mask words, factors of the keys
 
   template <int kPipe, typename Src>
   __device__ void run(const float* __restrict__ Kh, const float* __restrict__ Vh, const Src& src,
                       int k0, int k1, float c, int lane, TileState& st, char* lds) {
-    static_assert(kPipe == kPipeRegK || kPipe == kPipeLdsK, "fp32 pipelines");
-    if (kPipe == kPipeLdsK) run_ldsk(Kh, Vh, src, k0, k1, c, lane, st, lds);
-    else run_regk(Kh, Vh, src, k0, k1, c, lane, st, lds);
+    static_assert(kPipe == kPipeRegK, "fp32 pipeline");
+    if (k0 >= k1) return;                // (for a wide tile the same in every slice)
+    run_split(Kh, Vh, src, k0, k1, c, lane, st, lds);
+    bool again = __any(not_finite(st));
+    if constexpr (kD > kHeadDim) again = __syncthreads_or(again);
+    if (again) {
+      st.init();
+      run_exact(Kh, Vh, src, k0, k1, c, lane, st, lds);
+    }
   }
 
   // Orow = acc * inv, or w_prev * Orow + acc * inv when the call continues an earlier state.
@@ -1092,25 +1240,11 @@ struct CoreSplit {
   static constexpr int kBlockBytes = kTile * kHeadDim * 4;
   half8 qh[4], ql[4];   // Q[query n][h*32 + 8s .. +7], high and low parts
 
-  typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-
-  // Two values at a time: hi = fp16(x) packed into one register, x - hi by the mixed-precision
-  // fma (the fp16 operand is read straight out of the packed pair, no conversion back), and the
-  // remainders packed again: four instructions per pair.
-  __device__ static void split2(float x0, float x1, half2v& hi, half2v& lo) {
-    hi = half2v{(_Float16)x0, (_Float16)x1};
-    const uint32_t hp = __builtin_bit_cast(uint32_t, hi);
-    float r0, r1;
-    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r0) : "v"(hp), "v"(x0));
-    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r1) : "v"(hp), "v"(x1));
-    lo = half2v{(_Float16)r0, (_Float16)r1};
-  }
-
   __device__ static void split8(const float* x, half8& hi, half8& lo) {
 #pragma unroll
     for (int e = 0; e < 8; e += 2) {
       half2v h2, l2;
-      split2(x[e], x[e + 1], h2, l2);
+      split_pair_f16(x[e], x[e + 1], h2, l2);
       hi[e] = h2[0]; hi[e + 1] = h2[1];
       lo[e] = l2[0]; lo[e + 1] = l2[1];
     }
@@ -1130,6 +1264,20 @@ struct CoreSplit {
     }
 #pragma unroll
     for (int s = 0; s < 4; ++s) split8(q + 8 * s, qh[s], ql[s]);
+  }
+
+  // kf[t] = K[key n][h*32 + t] out of the staged block.  The global -> LDS copy moved keys
+  // 4i..4i+3 per instruction, 16 lanes per 256-byte row (whole cache lines), and stored the
+  // sixteen 16-byte chunks of a row XOR-swizzled: chunk c of key r lives at chunk slot
+  // c ^ (r & 15).  This read (each lane 128 contiguous bytes of its own key row, 16 at a time)
+  // then spreads 8 consecutive lanes over the 8 groups of 4 banks instead of hitting one.
+  __device__ static void read_k(const char* ldsk, int n, int h, float (&kf)[32]) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int slot = (8 * h + j) ^ (n & 15);
+      const float4 v = *reinterpret_cast<const float4*>(ldsk + (n * 16 + slot) * 16);
+      kf[4 * j] = v.x; kf[4 * j + 1] = v.y; kf[4 * j + 2] = v.z; kf[4 * j + 3] = v.w;
+    }
   }
 
   template <int kPipe>
@@ -1165,7 +1313,7 @@ struct CoreSplit {
       half8 kh[4], kl[4];
       {
         float kf[32];
-        CoreF32::read_k(ldsk, n, h, kf);
+        read_k(ldsk, n, h, kf);
         wait_lds_reads();                // the K buffer may be overwritten now
         __builtin_amdgcn_wave_barrier();
         if (more) sm.stage_k(Kh, b1, lane, ldsk);
@@ -1204,7 +1352,7 @@ struct CoreSplit {
 #pragma unroll
           for (int e = 0; e < 4; e += 2) {
             half2v h2, l2;
-            split2(vraw[4 * i + e], vraw[4 * i + e + 1], h2, l2);
+            split_pair_f16(vraw[4 * i + e], vraw[4 * i + e + 1], h2, l2);
             vh[e] = h2[0]; vh[e + 1] = h2[1];
             vl[e] = l2[0]; vl[e + 1] = l2[1];
           }

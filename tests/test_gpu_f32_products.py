@@ -1,0 +1,85 @@
+"""fp32 storage on the matrix cores: the operands are split into 16-bit parts (scaled per row for the
+scores), so the cases here are the ones where a split can go wrong: rows of very different
+magnitude in one key block, values near the ends of the fp32 range, huge values in keys that a
+query does not attend, and infinities.  The per-row kernels, which use fp32 arithmetic throughout,
+are the reference; each of them is compared with the oracle in test_gpu_attention.py."""
+import pytest
+
+import paper_2502_01659_amd as sga
+from sga_inputs import MaskSpec, KIND_SLIDING, torch_qkv
+from gpu_util import TOL
+
+pytestmark = pytest.mark.gpu
+
+# (head dimension, explicit CSR, length, window): window tiles, wide tiles and work items; a ragged
+# length, a window inside one key block and one of many blocks
+FORMS = [(64, False, 333, 20), (64, False, 5003, 700), (64, True, 333, 20), (64, True, 4100, 300),
+         (128, False, 333, 40), (256, True, 300, 20)]
+
+
+def _both(form, Q, K, V, scale):
+    d, explicit, L, W = form
+    spec = MaskSpec(KIND_SLIDING, L, window=W)
+    if explicit:
+        rp, ci = sga.build_mask(spec)
+        ws = sga.alloc_workspace(L, Q.shape[0], d, "f32", ci.numel())
+        return [sga.attention_forward(Q, K, V, rp, ci, scale, workspace=ws, path=p, want_lse=True)
+                for p in (sga.PATH_TILE, sga.PATH_GATHER)]
+    ws = sga.alloc_workspace(L, Q.shape[0], d, "f32", -1)
+    return [sga.attention_forward_implicit(Q, K, V, spec, scale, workspace=ws, path=p, want_lse=True)
+            for p in (sga.PATH_TILE, sga.PATH_GATHER)]
+
+
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("q_exp,k_exp,v_exp", [(0, 0, 0), (60, -60, 100), (-90, 90, -60), (-30, 24, 0)])
+def test_rows_of_different_magnitude(form, q_exp, k_exp, v_exp):
+    """Rows scaled by powers of two: q_exp + k_exp + up to 6 per key stays near 0, the values reach
+    2^+-100.  Bar: twice the fp32 tolerance relative to the largest value (a weighted mean of values
+    rounds at their size), raised by the size of the scores, which round at 2^-24 of themselves."""
+    import torch
+    d, _, L, _ = form
+    Q, K, V = torch_qkv(2, L, d, "f32", 1.0, 5, "cuda:0")
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(9)
+    per_key = torch.randint(-12, 3, (2, L, 1), generator=g, device="cuda:0").float()
+    Q = Q * 2.0 ** q_exp
+    K = K * torch.exp2(per_key + k_exp)
+    V = V * 2.0 ** v_exp
+    (O1, l1), (O2, l2) = _both(form, Q, K, V, d ** -0.5)
+    assert torch.isfinite(O1).all()
+    top = V.abs().max().item()
+    assert (O1.double() - O2.double()).abs().max().item() <= 2 * TOL["f32"] * 4 * top
+    assert (l1 - l2).abs().max().item() <= 1e-4
+
+
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("huge", [1e30, 3.39e38])
+def test_huge_keys_outside_the_mask(form, huge):
+    """A key nobody attends (its row is taken out of every comparison) shares key blocks with keys
+    that count: its size must not reach them."""
+    import torch
+    d, _, L, W = form
+    Q, K, V = torch_qkv(1, L, d, "f32", 1.0, 6, "cuda:0")
+    O0, _ = _both(form, Q, K, V, d ** -0.5)[0]
+    K2 = K.clone()
+    j = L // 2
+    K2[:, j] = huge
+    O1, _ = _both(form, Q, K2, V, d ** -0.5)[0]
+    far = (torch.arange(L, device="cuda:0") - j).abs() > W
+    assert far.any()
+    assert (O1[:, far] - O0[:, far]).abs().max().item() <= TOL["f32"]
+
+
+@pytest.mark.parametrize("form", FORMS)
+def test_minus_infinity_scores_weigh_nothing(form):
+    """Keys with an infinite channel whose product is -inf for every query: weight 0, as on the per-row
+    kernels."""
+    import torch
+    d, _, L, _ = form
+    Q, K, V = torch_qkv(1, L, d, "f32", 1.0, 7, "cuda:0")
+    Q[:, :, 3] = Q[:, :, 3].abs() + 0.25
+    K[:, ::7, 3] = -float("inf")
+    (O1, l1), (O2, l2) = _both(form, Q, K, V, d ** -0.5)
+    assert torch.isfinite(O2).all() and torch.isfinite(O1).all()
+    assert (O1 - O2).abs().max().item() <= 2 * TOL["f32"]
+    assert (l1 - l2).abs().max().item() <= 1e-4
