@@ -566,7 +566,7 @@ struct SliceExchange {
 // The smallest terms go first into an accumulator, so that only the last few of its additions
 // round at the size of the sum, where the fp32 matrix instruction (two channels or keys at a
 // time) rounds at every one: the error against 64-bit arithmetic is smaller than with
-// fp32 products (longformer mask, L = 65,536: 3.0e-7 instead of 4.1e-7 relative).
+// fp32 products (longformer mask, L = 65,536: 1.8e-7 instead of 4.1e-7 relative).
 //
 // Per 32 x 32 block: 36 matrix instructions of 32 cycles instead of 64 of 64, and about 380 vector
 // instructions for the splits.  Longformer mask, L = 65,536, 8 heads, prepared: 494 -> 395 us;
@@ -676,6 +676,26 @@ __device__ __forceinline__ floatx16 split_product(const ValueOperand& a, const V
   acc = mfma_bf16(a.hi, b.mid, acc);
   return mfma_bf16(a.hi, b.hi, acc);
 }
+// O^T += V_blk^T P^T for one block; value(u, cb) is the operand V^T[channel cb*32+n][keys 16u ..].
+// The products of a block are summed by themselves and added to O once: one rounding at the size
+// of O per block (chained into O they round 12 times, the fp32 instruction 16 times, which is
+// what the error of rows of thousands of keys comes from: +-16,383, relative error 1.15e-6 with
+// fp32 products, 1.03e-6 chained, 0.32e-6 so; the 32 additions cost nothing measurable).
+// No branch here: skipping the halves of a masked block that no query attends made two versions
+// of this code, whose registers cost more than the products saved (247 -> 331 us at +-128).
+template <typename Value>
+__device__ __forceinline__ void weigh_values(const float (&p)[16], const BlockInfo& b, TileState& st, Value value) {
+  ValueOperand pb[2];
+  pb[0].split(p);
+  pb[1].split(p + 8);
+#pragma unroll
+  for (int cb = 0; cb < 2; ++cb) {
+    floatx16 part = split_product(value(0, cb), pb[0], floatx16{0});
+    part = split_product(value(1, cb), pb[1], part);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) st.o[cb][r] += part[r];
+  }
+}
 
 // True in a lane whose state holds an infinity or a NaN.
 __device__ __forceinline__ bool not_finite(const TileState& st) {
@@ -774,24 +794,14 @@ struct CoreF32T {
   __device__ static void weigh_v(const float (&p)[16], const BlockInfo& b, int n, int h, TileState& st,
                                  const char* ldsv) {
     const float* vread = reinterpret_cast<const float*>(ldsv) + h * 4 * kHeadDim + n;
+    weigh_values(p, b, st, [&](int u, int cb) {
+      float v[8];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      // registers 8u .. 8u+7 hold the keys 16u .. 16u+15 of the block: if no query of the tile
-      // attends one of them (p = 0 in every lane) they are skipped, which is exact (e.g. the
-      // upper half of a block that holds 16 global tokens)
-      if (!b.full && __builtin_amdgcn_ballot_w64(((b.word >> (16 * u)) & 0xffffu) != 0) == 0) continue;
-      ValueOperand pb;
-      pb.split(p + 8 * u);
-#pragma unroll
-      for (int cb = 0; cb < 2; ++cb) {
-        float v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = vread[acc_row(8 * u + e, 0) * kHeadDim + cb * 32];
-        ValueOperand va;
-        va.split(v);
-        st.o[cb] = split_product(va, pb, st.o[cb]);
-      }
-    }
+      for (int e = 0; e < 8; ++e) v[e] = vread[acc_row(8 * u + e, 0) * kHeadDim + cb * 32];
+      ValueOperand va;
+      va.split(v);
+      return va;
+    });
   }
 
   // The pipeline: the K fragment of block k+1 is loaded global -> registers (each lane reads 128
@@ -2044,7 +2054,7 @@ __device__ __forceinline__ void tile_attend_body(
 }
 
 template <typename T, int kPipe>
-__global__ __launch_bounds__(256) void tile_attend_kernel(
+__global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) void tile_attend_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
     float* __restrict__ lse, const int64_t* __restrict__ row_ptr, int64_t L, float scale, void* ws,
     size_t ws_bytes, int accumulate) {
@@ -2338,6 +2348,166 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) voi
     finish_tile_rows<T>(O + hoff, lse ? lse + hd * L : nullptr, s * u0 + p, s,
                         Lc - u0 < kTile ? (int)(Lc - u0) : kTile, st, lane, lds);
   }
+}
+
+// ---- fp32 storage, key blocks shared by a workgroup ------------------------------------------------
+// Four tiles (one per wavefront) walk one list of key blocks together.  Each block of K and V is
+// loaded once per workgroup, split once (16 values per thread), and left in LDS as five planes of
+// 16-bit parts in the layouts CoreF16 reads: two of K (32 keys x 64 channels, the 16-byte chunks
+// of a row swizzled), three of V (row-major, for the LDS transpose read).  The wavefronts take
+// their matrix-core operands from there.  Splitting a block costs about as much vector time as its
+// products cost matrix time; shared by four tiles it is a quarter of that.
+struct SharedBlock {
+  static constexpr int kPlane = kTile * kHeadDim * 2;
+  static constexpr int kValues = 2 * kPlane;               // offset of the first V plane
+  static constexpr int kFactors = 5 * kPlane;              // ... of the keys' scales (see split_scores)
+  static constexpr int kBytes = 5 * kPlane + kTile * 4;
+  float k[8], v[8];        // this thread's share: key threadIdx.x / 8, channels 8 * (threadIdx.x % 8) ..
+  __device__ __forceinline__ void load(const char* k_at, const char* v_at) {
+    const float4 a = reinterpret_cast<const float4*>(k_at)[0], b = reinterpret_cast<const float4*>(k_at)[1];
+    const float4 c = reinterpret_cast<const float4*>(v_at)[0], d = reinterpret_cast<const float4*>(v_at)[1];
+    k[0] = a.x; k[1] = a.y; k[2] = a.z; k[3] = a.w; k[4] = b.x; k[5] = b.y; k[6] = b.z; k[7] = b.w;
+    v[0] = c.x; v[1] = c.y; v[2] = c.z; v[3] = c.w; v[4] = d.x; v[5] = d.y; v[6] = d.z; v[7] = d.w;
+  }
+  template <int CTRL>
+  __device__ static __forceinline__ float dpp(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, false));
+  }
+  __device__ __forceinline__ void store(char* planes) const {
+    const int r = threadIdx.x >> 3, j = threadIdx.x & 7;
+    float top = largest<8>(k);                             // of the key's row: its eight threads are neighbours
+    top = __builtin_fmaxf(top, dpp<0xB1>(top));            // quad_perm [1,0,3,2]
+    top = __builtin_fmaxf(top, dpp<0x4E>(top));            // quad_perm [2,3,0,1]
+    top = __builtin_fmaxf(top, dpp<0x141>(top));           // row_half_mirror
+    const RowScale scale(top);
+    if (j == 0) reinterpret_cast<float*>(planes + kFactors)[r] = scale.up;
+    ScoreOperand x;
+    x.split(k, scale.down);
+    char* at = planes + (r * 8 + (j ^ (r & 7))) * 16;
+    *reinterpret_cast<half8*>(at) = x.hi;
+    *reinterpret_cast<half8*>(at + kPlane) = x.lo;
+    ValueOperand y;
+    y.split(v);
+    at = planes + kValues + r * (kHeadDim * 2) + j * 16;
+    *reinterpret_cast<bf16x8*>(at) = y.hi;
+    *reinterpret_cast<bf16x8*>(at + kPlane) = y.mid;
+    *reinterpret_cast<bf16x8*>(at + 2 * kPlane) = y.lo;
+  }
+  // One block step of a wavefront's tile against the planes of a block (the operations of
+  // CoreF32T::run_split in the same order: the same result bit for bit).
+  __device__ static __forceinline__ void attend(CoreF32& core, const char* planes, const BlockInfo& b, float c, int lane,
+                                                TileState& st) {
+    const int n = lane & 31, h = lane >> 5;
+    ScoreOperand k2[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const char* at = planes + (n * 8 + ((4 * h + s) ^ (n & 7))) * 16;
+      k2[s].hi = *reinterpret_cast<const half8*>(at);
+      k2[s].lo = *reinterpret_cast<const half8*>(at + kPlane);
+    }
+    floatx16 s;
+    const float up = core.scores(k2, reinterpret_cast<const float*>(planes + kFactors), c, lane, s);
+    float p[16];
+    softmax_block(s, up, b, h, st, p);
+    const char* vt = CoreF16::vt_base(planes + kValues, lane, h);
+    weigh_values(p, b, st, [&](int u, int cb) {
+      ValueOperand va;
+      va.hi = __builtin_bit_cast(bf16x8, CoreF16::read_va(vt, u, cb));
+      va.mid = __builtin_bit_cast(bf16x8, CoreF16::read_va(vt + kPlane, u, cb));
+      va.lo = __builtin_bit_cast(bf16x8, CoreF16::read_va(vt + 2 * kPlane, u, cb));
+      return va;
+    });
+  }
+};
+// Every wavefront is done with its LDS reads and writes and has met the others.  (Loads into
+// registers stay in flight across it.)
+__device__ __forceinline__ void workgroup_lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// Implicit window masks, fp32: 128 consecutive queries of a class per workgroup, 32 per wavefront,
+// over the key blocks of the whole 128 (grid mapping, ranges of key blocks and partial states as
+// in tile_window_kernel).  Block k is computed from one of two LDS buffers while block k+1, whose
+// values have arrived in registers, is split into the other one and block k+2 is requested.
+// Bound by matrix cores (56 % busy) and vector unit (60 %) together, a quarter of the time both
+// at once; 160 registers and 41 KB keep three wavefronts per SIMD (two were 4 % slower).  +-1359,
+// L = 262,144, 4 heads: 6.51 ms with fp32 products -> 3.28 ms; +-128, L = 65,536, 8 heads: 385 ->
+// 247 us; L = 2,000,000, one head, +-16: 526 -> 433 us.
+__global__ __attribute__((amdgpu_waves_per_eu(3, 3))) __launch_bounds__(256) void tile_window_f32_kernel(
+    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, float* __restrict__ O,
+    float* __restrict__ lse, int64_t L, int64_t W, int64_t s, int64_t n_groups, float scale, int accumulate,
+    int64_t seg_len, int nsplit, float* __restrict__ parts) {
+  __shared__ __attribute__((aligned(16))) char planes[2 * SharedBlock::kBytes];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int n = lane & 31, h = lane >> 5;
+  const int64_t chunk = gridDim.x / 8;
+  const int64_t bid_all = (int64_t)(blockIdx.x % 8) * chunk + blockIdx.x / 8;
+  const int64_t bid = bid_all / nsplit;
+  const int part = (int)(bid_all - bid * nsplit);
+  WindowSlot slot;
+  if (!locate_window_slot(bid, L, s, n_groups, seg_len, slot)) return;      // (the whole workgroup leaves)
+  const int64_t p = slot.p, Lc = slot.Lc;
+  const int64_t q0 = slot.grp * (4 * kTile);
+  if (q0 >= Lc) return;
+  const int64_t hd = blockIdx.y;
+  const int64_t hoff = hd * L * kHeadDim;
+  const int64_t u0 = q0 + (int64_t)wave * kTile;
+  const int64_t vfirst = q0 - W > 0 ? q0 - W : 0;
+  const int64_t vlast = q0 + 4 * kTile - 1 + W < Lc - 1 ? q0 + 4 * kTile - 1 + W : Lc - 1;
+  const int nblk = (int)((vlast - vfirst) / kTile + 1);
+  const int k0 = (int)((int64_t)nblk * part / nsplit), k1 = (int)((int64_t)nblk * (part + 1) / nsplit);
+  // a wavefront whose queries lie past the end of the class still copies and meets the barriers;
+  // classify() then reports no block as its own
+  const WindowBlocks src{vfirst, Lc, s, p, u0, W};
+  const int64_t u = u0 + n;
+  const bool exists = u < Lc;
+  const int64_t qrow = s * (exists ? u : Lc - 1) + p;
+  const float c = softmax_factor(scale);
+  TileState st;
+  st.init();
+  CoreF32 core;
+  const uint32_t key_bytes = (uint32_t)(s * kHeadDim * 4);       // (at most 2^27, the host checks)
+  const int r_own = threadIdx.x >> 3;
+  SharedBlock next;
+  auto request = [&](int k) {                                    // (past the last block: the last one again)
+    const int64_t v0 = vfirst + (int64_t)(k < k1 ? k : k1 - 1) * kTile;
+    const int64_t left = Lc - v0;
+    const int last = left < kTile ? (int)left - 1 : kTile - 1;   // keys past the end re-read the last one (masked off)
+    const uint32_t at = (uint32_t)(r_own < last ? r_own : last) * key_bytes + (threadIdx.x & 7) * 32;
+    const int64_t base = hoff * 4 + (s * v0 + p) * (kHeadDim * 4);
+    next.load(reinterpret_cast<const char*>(K) + base + at, reinterpret_cast<const char*>(V) + base + at);
+  };
+  if (k0 < k1) {
+    request(k0);
+    core.load_q(Q + hoff + qrow * kHeadDim, h, scale < 0.f);
+    next.store(planes + (k0 & 1) * SharedBlock::kBytes);
+    request(k0 + 1);
+    workgroup_lds_barrier();
+    for (int k = k0; k < k1; ++k) {
+      next.store(planes + ((k + 1) & 1) * SharedBlock::kBytes);
+      request(k + 2);
+      const int cls = src.classify(k);                           // wave-uniform
+      if (cls) {
+        BlockInfo b = src.get(k, n);
+        b.full = cls == 2;
+        SharedBlock::attend(core, planes + (k & 1) * SharedBlock::kBytes, b, c, lane, st);
+      }
+      workgroup_lds_barrier();
+    }
+    if (__any(not_finite(st))) {         // (see CoreF32T)
+      int ka = k0, kb = k1;
+      while (ka < kb && src.classify(ka) == 0) ++ka;
+      while (kb > ka && src.classify(kb - 1) == 0) --kb;
+      st.init();
+      core.run_exact(K + hoff, V + hoff, src, ka, kb, c, lane, st, planes + wave * CoreF32::kBlockBytes);
+    }
+  }
+  if (u0 >= Lc) return;
+  if (nsplit > 1)
+    store_partial(parts + (((bid * 4 + wave) * gridDim.y + hd) * nsplit + part) * (int64_t)kTilePartialFloats, st, n, h);
+  else
+    finish_tile<float>(O + hoff, lse ? lse + hd * L : nullptr, qrow, qrow, exists, st, h, accumulate != 0);
 }
 
 // Key blocks of the non-local mask (global tokens 0..g-1 without the window, Section IV-B
@@ -3723,6 +3893,8 @@ sga_status run_tile_implicit_wide(const AttnArgs& a) {
   return SGA_ERR_UNSUPPORTED;
 }
 
+constexpr int64_t kSharedSteps = 8192;
+
 sga_status run_tile_implicit(const AttnArgs& a) {
   if (a.d != kHeadDim)
     return a.dtype == SGA_F32 ? run_tile_implicit_wide<float>(a) : run_tile_implicit_wide<__half>(a);
@@ -3741,10 +3913,11 @@ sga_status run_tile_implicit(const AttnArgs& a) {
   const dim3 grid((unsigned)n_wg, (unsigned)a.H);
   const int acc = a.accumulate ? 1 : 0;
   if (a.dtype == SGA_F32) clear_unselected_rows<float>(a); else clear_unselected_rows<__half>(a);
-  const int nb_max = (int)((4 * kTile - 1 + 2 * (int64_t)a.window) / kTile + 1);   // key blocks of 128 queries
+  const int64_t nb_max = (4 * kTile - 1 + 2 * (int64_t)a.window) / kTile + 1;   // key blocks of 128 queries
   const bool kv = wg && nb_max >= kKvMinBlocks;
-  profile_mark_begin(a.stream, kv ? "tile_window_kv_kernel" : wg ? "tile_window_wg_kernel"
-                               : pair ? "tile_window_band_kernel" : "tile_window_kernel");
+  const char* window_kernel = kv ? "tile_window_kv_kernel" : wg ? "tile_window_wg_kernel"
+                              : pair ? "tile_window_band_kernel" : "tile_window_kernel";
+  if (wg || pair) profile_mark_begin(a.stream, window_kernel);
   if (wg) {
     int64_t Lq = a.L / s, Lr = a.L % s;             // class lengths, see the kernel
     if (shape.seg_len > 0) {
@@ -3756,12 +3929,12 @@ sga_status run_tile_implicit(const AttnArgs& a) {
       hipLaunchKernelGGL(tile_window_kv_kernel, grid, dim3(256), (size_t)(nb_max > 5 ? nb_max : 5) * CoreF16::kBlockBytes,
                          a.stream, static_cast<const __half*>(a.Q), static_cast<const __half*>(a.K),
                          static_cast<const __half*>(a.V), static_cast<__half*>(a.O), a.lse, a.L,
-                         (int64_t)a.window, s, n_groups, a.scale, acc, nb_max, shape.seg_len, Lq, Lr);
+                         (int64_t)a.window, s, n_groups, a.scale, acc, (int)nb_max, shape.seg_len, Lq, Lr);
     else
       hipLaunchKernelGGL(tile_window_wg_kernel, grid, dim3(256), (size_t)nb_max * 2 * CoreF16::kBlockBytes,
                          a.stream, static_cast<const __half*>(a.Q), static_cast<const __half*>(a.K),
                          static_cast<const __half*>(a.V), static_cast<__half*>(a.O), a.lse, a.L,
-                         (int64_t)a.window, s, n_groups, a.scale, acc, nb_max, shape.seg_len, Lq, Lr);
+                         (int64_t)a.window, s, n_groups, a.scale, acc, (int)nb_max, shape.seg_len, Lq, Lr);
   } else if (pair) {
     hipLaunchKernelGGL(tile_window_band_kernel, grid, dim3(256), 0, a.stream,
                        static_cast<const __half*>(a.Q), static_cast<const __half*>(a.K),
@@ -3770,7 +3943,18 @@ sga_status run_tile_implicit(const AttnArgs& a) {
   } else {
     float* parts = nullptr;
     const int nsplit = choose_window_split(a, n_wg * 4 * a.H, 2048, &parts);
-    auto kernel = a.split ? tile_window_kernel<float, kPipeSplit> : tile_window_kernel<float, kPipeRegK>;
+    // Key blocks that the workgroups of 128 queries step through in total: from kSharedSteps on the
+    // kernel that shares them (tile_window_f32_kernel) is the faster one, below it a step's latency
+    // counts, which the shared form lengthens.  (One head, us, own blocks / shared: L = 32,768, +-64
+    // 16 / 21, +-500 68 / 60; L = 98,304, +-32 28 / 30, +-128 54 / 50; L = 131,072, +-32 35 / 40;
+    // L = 200,000, +-32 65 / 61.)
+    const int64_t class_blocks = (Lc + kTile - 1) / kTile;
+    const int64_t steps = n_groups * shape.n_slots * a.H * (nb_max < class_blocks ? nb_max : class_blocks);
+    const bool shared = !a.split && steps >= kSharedSteps;
+    if (shared) window_kernel = "tile_window_f32_kernel";
+    profile_mark_begin(a.stream, window_kernel);
+    auto kernel = a.split ? tile_window_kernel<float, kPipeSplit>
+                  : shared ? tile_window_f32_kernel : tile_window_kernel<float, kPipeRegK>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(n_wg * nsplit), (unsigned)a.H), dim3(256), 0, a.stream,
                        static_cast<const float*>(a.Q), static_cast<const float*>(a.K),
                        static_cast<const float*>(a.V), static_cast<float*>(a.O), a.lse, a.L,

@@ -11,10 +11,11 @@ from gpu_util import TOL
 
 pytestmark = pytest.mark.gpu
 
-# (head dimension, explicit CSR, length, window): window tiles, wide tiles and work items; a ragged
-# length, a window inside one key block and one of many blocks
-FORMS = [(64, False, 333, 20), (64, False, 5003, 700), (64, True, 333, 20), (64, True, 4100, 300),
-         (128, False, 333, 40), (256, True, 300, 20)]
+# (head dimension, explicit CSR, length, window): window tiles of a small call and of one whose
+# workgroups share their key blocks (cut into ranges: 3,333 and 30,001), wide tiles, work items; ragged
+# lengths, a window inside one key block and one of many blocks
+FORMS = [(64, False, 333, 20), (64, False, 3333, 3000), (64, False, 30001, 700), (64, False, 140003, 70),
+         (64, True, 333, 20), (64, True, 4100, 300), (128, False, 333, 40), (256, True, 300, 20)]
 
 
 def _both(form, Q, K, V, scale):
@@ -62,7 +63,7 @@ def test_huge_keys_outside_the_mask(form, huge):
     Q, K, V = torch_qkv(1, L, d, "f32", 1.0, 6, "cuda:0")
     O0, _ = _both(form, Q, K, V, d ** -0.5)[0]
     K2 = K.clone()
-    j = L // 2
+    j = 5
     K2[:, j] = huge
     O1, _ = _both(form, Q, K2, V, d ** -0.5)[0]
     far = (torch.arange(L, device="cuda:0") - j).abs() > W
