@@ -292,9 +292,9 @@ __global__ __launch_bounds__(256) void clear_workspace_kernel(void* ws, size_t w
        t += (int64_t)gridDim.x * blockDim.x)
     bad[t] = 0;
   uint32_t* next = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + pl.off_work_next);
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < 2 * (int64_t)H;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < (int64_t)H;
        i += (int64_t)gridDim.x * blockDim.x)
-    next[i] = 0;          // claim counters and exit counters of the heads
+    next[i] = 0;          // claim counters of the heads
 }
 
 // One thread per row: rows that are split reserve their partial slots and enter the list of

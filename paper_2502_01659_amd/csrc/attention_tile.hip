@@ -1528,7 +1528,8 @@ __device__ __forceinline__ int64_t lower_bound_col(const int32_t* __restrict__ c
 // index >= segments are idle.
 struct WorkId {
   int64_t tile;
-  int32_t seg, nseg;
+  int32_t seg, nseg;       // seg >= nseg: idle
+  bool together;           // see tile_cut
 };
 
 // (Called by a whole wavefront with the same w.)  f is increasing, and for masks of even density
@@ -1576,10 +1577,17 @@ __device__ __forceinline__ WorkId locate_work(const int64_t* __restrict__ row_pt
     }
     f0 = work_first(row_ptr, L, sh, lo);
   }
+  const TileCut cut = tile_cut(row_ptr, L, sh, lo);
   WorkId id;
   id.tile = lo;
   id.seg = (int32_t)(w - f0);
-  id.nseg = tile_segments(row_ptr, L, sh, lo);
+  id.nseg = cut.nseg;
+  id.together = cut.together;
+  if (cut.together && cut.nseg > 1) {
+    const int64_t j = w - cut.first;
+    id.tile = (lo & ~int64_t(3)) + (j & 3);
+    id.seg = j >= 0 && (j >> 2) < cut.nseg ? (int32_t)(j >> 2) : cut.nseg;
+  }
   return id;
 }
 
@@ -1617,24 +1625,6 @@ __global__ __launch_bounds__(256) void tile_analyze_kernel(const int64_t* __rest
     if (id.seg >= id.nseg) {          // spare item of a tile whose edge range crosses a multiple of S
       if (lane == 0) items[w].tile = -1;
       continue;
-    }
-    if (id.nseg > 1) {
-      // Four neighbouring tiles that are all cut into the same number of segments (rows of global
-      // tokens: every tile spans the whole key range) trade segments among their items so that
-      // consecutive items hold the same segment of the four tiles.  The items of a workgroup
-      // of the static schedule then stream the same K and V blocks at the same time, instead of
-      // each tile passing over all keys on its own (workload 4: the four global tiles of a head
-      // otherwise fetch K and V four times).  The j-th (tile, segment) pair of the quad in
-      // tile-major order computes pair number j in segment-major order: a permutation of the
-      // same 4 * nseg pairs, a function of the mask alone.
-      const int64_t g = id.tile & ~int64_t(3);
-      bool same = g + 3 < pl.n_tiles;
-      for (int64_t q = g; same && q < g + 4; ++q) same = tile_segments(row_ptr, L, pl.seg_shift, q) == id.nseg;
-      if (same) {
-        const int64_t j = (id.tile - g) * id.nseg + id.seg;
-        id.tile = g + (j & 3);
-        id.seg = (int32_t)(j >> 2);
-      }
     }
     const int64_t t = id.tile;
     const int64_t row_first = t * kTile;
@@ -1908,14 +1898,13 @@ __global__ __launch_bounds__(256) void tile_analyze_kernel(const int64_t* __rest
       }
     }
     if (lane == 0) {
-      TileItem it;
-      it.tile = (int32_t)t;
-      it.nblk = overflow ? -1 : nblk;
-      it.seg = id.seg;
-      it.nseg = id.nseg;
-      it.slot0 = slot0;
-      it.pad = 0;
-      items[w] = it;
+      *reinterpret_cast<int4*>(items + w) = make_int4((int32_t)t, overflow ? -1 : nblk, id.seg, id.nseg);
+      items[w].slot0 = slot0;
+      // Segment items in groups of four consecutive items: the same segment of four tiles, or
+      // four segments of one tile.  (The order of the list is that of arrival; it only orders
+      // the claims of the attention kernel.)
+      if (id.nseg > 1 && ((id.together ? (int)t : id.seg) & 3) == 0)
+        items[atomicAdd(&ctr[kCtrMultiItems], 1u)].group = w;
       if (overflow && atomicOr(&tile_bad[t], 1) == 0) {
         // (the per-row kernels walk this list instead of testing every row of the sequence)
         const uint32_t bi = atomicAdd(&ctr[kCtrTilesBad], 1u);
@@ -1941,16 +1930,17 @@ __device__ __forceinline__ bool tile_parts_fit(const WorkspacePlan& pl, const vo
   return (int64_t) reinterpret_cast<const uint32_t*>(ws)[kCtrTilePartsNeeded] <= pl.cap_tparts;
 }
 
-// A claimant (wavefront or workgroup) of the dynamic schedule found no item left.  The last of
-// the head's `claimants` to arrive puts the head's claim counter and this exit counter back to
-// zero (every other claimant has made its last claim by then), so the next call on the same
-// workspace starts from a clean schedule without a clearing launch of its own.  One lane calls.
-__device__ __forceinline__ void claim_exit(uint32_t* work_next, int32_t H, uint32_t claimants) {
-  uint32_t* done = work_next + H;
-  if (atomicAdd(done, 1u) == claimants - 1) {
-    atomicExch(work_next, 0u);
-    atomicExch(done, 0u);
-  }
+// Dynamic schedule: of n items of a head, claimant i (a wavefront or a workgroup) takes item i first
+// and then claims from the head's counter, which hands out the items from `claimants` on.  Once n
+// is passed every claimant fails exactly once, and the last to fail, the n-th claim in all, puts
+// the counter back to zero: the next call on the same workspace starts from a clean schedule
+// without a clearing launch of its own.  With no more items than claimants nobody touches the
+// counter.  (Claims are atomic operations on one address, about 17 ns each: with a claim for every
+// item and an exit counter they took 40 of the 67 us of 1,307 items.)  One lane calls.
+__device__ __forceinline__ int64_t claim_next(uint32_t* work_next, int64_t n, uint32_t claimants) {
+  const uint32_t c = atomicAdd(work_next, 1u);
+  if (c == (uint32_t)n - 1) atomicExch(work_next, 0u);
+  return (int64_t)claimants + c;
 }
 
 constexpr uint32_t kXcdRun = 4;   // consecutive workgroups of the static schedule that share an XCD
@@ -1963,9 +1953,8 @@ template <typename T, int kPipe>
 __device__ __forceinline__ void tile_attend_body(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
     float* __restrict__ lse, const int64_t* __restrict__ row_ptr, int64_t L, float scale, void* ws,
-    size_t ws_bytes, int accumulate) {
-  constexpr int kLds = CoreFor<T, kPipe>::type::template lds_bytes<kPipe>();
-  __shared__ __attribute__((aligned(16))) char lds_all[4 * kLds];
+    size_t ws_bytes, int accumulate, char* lds_all) {
+  constexpr int kLds = CoreFor<T, kPipe>::type::template lds_bytes<kPipe>();       // (lds_all: 4 of them)
   const int32_t H = (int32_t)gridDim.x;   // head-major grid: the long work items of every head are dispatched first
   const WorkspacePlan pl = plan_workspace(L, H, row_ptr[L], DtypeOf<T>::code);
   if (pl.total_bytes > ws_bytes) return;
@@ -2002,21 +1991,18 @@ __device__ __forceinline__ void tile_attend_body(
   // neighbouring tiles at the same time (static stride), so that the key blocks they share are
   // fetched together and hit the CU's L1.
   int64_t w_static = (int64_t)ywg * 4 + wave;
-  while (true) {
-    int64_t w_cur;
-    if (kDynamic) {
-      uint32_t claimed = 0;
-      if (lane == 0) claimed = atomicAdd(work_next, 1u);
-      w_cur = __builtin_amdgcn_readfirstlane(claimed);
-      if (w_cur >= pl.n_work) {
-        if (lane == 0) claim_exit(work_next, H, gridDim.y * 4);
-        break;
-      }
-    } else {
-      w_cur = w_static;
+  const uint32_t claimants = gridDim.y * 4;
+  for (bool first = true;; first = false) {
+    int64_t w_cur = w_static;
+    if (!kDynamic) {
       w_static += (int64_t)gridDim.y * 4;
-      if (w_cur >= pl.n_work) break;
+    } else if (!first) {
+      if (pl.n_work <= claimants) break;
+      uint32_t claimed = 0;
+      if (lane == 0) claimed = (uint32_t)claim_next(work_next, pl.n_work, claimants);
+      w_cur = __builtin_amdgcn_readfirstlane(claimed);
     }
+    if (w_cur >= pl.n_work) break;
     // the whole record in one uniform 32-byte read
     const int4 r0 = reinterpret_cast<const int4*>(items + w_cur)[0];
     const int64_t slot_raw = reinterpret_cast<const int64_t*>(items + w_cur)[2];
@@ -2058,7 +2044,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) voi
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
     float* __restrict__ lse, const int64_t* __restrict__ row_ptr, int64_t L, float scale, void* ws,
     size_t ws_bytes, int accumulate) {
-  tile_attend_body<T, kPipe>(Q, K, V, O, lse, row_ptr, L, scale, ws, ws_bytes, accumulate);
+  __shared__ __attribute__((aligned(16))) char lds[4 * CoreFor<T, kPipe>::type::template lds_bytes<kPipe>()];
+  tile_attend_body<T, kPipe>(Q, K, V, O, lse, row_ptr, L, scale, ws, ws_bytes, accumulate, lds);
 }
 
 // fp16 storage: the same body held to the registers of four wavefronts per SIMD (the fp16 items
@@ -2068,7 +2055,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(4, 4))) __launch_bounds__(256) voi
     const __half* __restrict__ Q, const __half* __restrict__ K, const __half* __restrict__ V,
     __half* __restrict__ O, float* __restrict__ lse, const int64_t* __restrict__ row_ptr, int64_t L,
     float scale, void* ws, size_t ws_bytes, int accumulate) {
-  tile_attend_body<__half, kPipeLdsK>(Q, K, V, O, lse, row_ptr, L, scale, ws, ws_bytes, accumulate);
+  __shared__ __attribute__((aligned(16))) char lds[4 * CoreF16::lds_bytes<kPipeLdsK>()];
+  tile_attend_body<__half, kPipeLdsK>(Q, K, V, O, lse, row_ptr, L, scale, ws, ws_bytes, accumulate, lds);
 }
 
 // Head dimensions 128 and 256: one workgroup of kD / 64 wavefronts per work item, wavefront w
@@ -2104,15 +2092,16 @@ __global__ __launch_bounds__(kD) void tile_attend_wide_kernel(
   uint32_t* work_next = reinterpret_cast<uint32_t*>(base_ws + pl.off_work_next) + head;
   Core core;
   core.xchg.init(lds_all + kSlices * kLds, slice);
-  while (true) {
-    __syncthreads();           // every wavefront has read the previous claim and left its item
-    if (threadIdx.x == 0) claim = atomicAdd(work_next, 1u);
-    __syncthreads();
-    const int64_t w_cur = __builtin_amdgcn_readfirstlane(claim);
-    if (w_cur >= pl.n_work) {
-      if (threadIdx.x == 0) claim_exit(work_next, H, gridDim.y);
-      break;
+  for (bool first = true;; first = false) {
+    int64_t w_cur = blockIdx.y;
+    if (!first) {
+      if (pl.n_work <= gridDim.y) break;
+      __syncthreads();         // every wavefront has read the previous claim and left its item
+      if (threadIdx.x == 0) claim = (uint32_t)claim_next(work_next, pl.n_work, gridDim.y);
+      __syncthreads();
+      w_cur = __builtin_amdgcn_readfirstlane(claim);
     }
+    if (w_cur >= pl.n_work) break;
     const int4 r0 = reinterpret_cast<const int4*>(items + w_cur)[0];
     const int64_t slot_raw = reinterpret_cast<const int64_t*>(items + w_cur)[2];
     const int32_t t = __builtin_amdgcn_readfirstlane(r0.x);
@@ -2419,6 +2408,8 @@ struct SharedBlock {
     });
   }
 };
+constexpr int64_t kSharedSteps = 8192;      // steps of a call from which sharing pays, see run_tile_implicit
+
 // Every wavefront is done with its LDS reads and writes and has met the others.  (Loads into
 // registers stay in flight across it.)
 __device__ __forceinline__ void workgroup_lds_barrier() {
@@ -2508,6 +2499,231 @@ __global__ __attribute__((amdgpu_waves_per_eu(3, 3))) __launch_bounds__(256) voi
     store_partial(parts + (((bid * 4 + wave) * gridDim.y + hd) * nsplit + part) * (int64_t)kTilePartialFloats, st, n, h);
   else
     finish_tile<float>(O + hoff, lse ? lse + hd * L : nullptr, qrow, qrow, exists, st, h, accumulate != 0);
+}
+
+// The block lists of four work items, merged: advance() names the lists' smallest block not taken
+// yet (kDone past the end) and moves every list that holds it one entry on.  Everything is
+// wave-uniform (the ids are read through the scalar path) and the same in all four wavefronts.
+struct MergedLists {
+  typedef const int32_t __attribute__((address_space(4)))* Ids;
+  static constexpr int kDone = kFullBit - 1;
+  Ids at[4];
+  int left[4], head[4];      // entries behind the head, the head's record
+  struct Step {
+    int block;               // key block, or kDone
+    int own;                 // this wavefront's record of it (block | full flag), or -1
+  };
+  __device__ __forceinline__ void start(int i, const int32_t* ids, int n) {
+    at[i] = (Ids)ids;
+    left[i] = n;
+    head[i] = n > 0 ? *at[i] : kDone;
+  }
+  __device__ __forceinline__ Step advance(int wave) {
+    int m = kDone;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) m = min(m, head[i] & ~kFullBit);
+    Step s{m, -1};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if ((head[i] & ~kFullBit) != m || m == kDone) continue;
+      if (wave == i) s.own = head[i];
+      --left[i];
+      ++at[i];
+      head[i] = left[i] > 0 ? *at[i] : kDone;
+    }
+    return s;
+  }
+};
+
+// Explicit masks, fp32: a workgroup takes four work items, one per wavefront, over the union of
+// their block lists: four neighbouring tiles share most of their blocks (a block only some of them
+// hold is skipped by the others), and so do the same segments of four tiles cut alike.  The pipeline
+// is that of tile_window_f32_kernel.  Items whose lists have little in common (four segments of one
+// tile, tiles whose blocks are mostly random ones) run side by side, each wavefront with the split
+// of its own blocks; both forms do the same operations in the same order.
+// Resident workgroups claim from the head's counter: first the groups of segment items that the
+// CSR -> tile pass listed (the long ones), then the tiles in fours.  A call with fewer claims than
+// kSharedClaims leaves CUs without a workgroup: there every wavefront claims items by itself
+// (+-100, one head, us, that / fours: L = 8,192 23.7 / 26.8, L = 16,301 33.0 / 28.1).
+// Bound like that kernel, at two wavefronts per SIMD (256 registers, for the wavefronts on lists
+// of their own).  us, fp32 products -> own lists only -> this: longformer mask, L = 65,536, 8 heads,
+// prepared 495 -> 397 -> 355; +-300, L = 200,000, 2 heads 670 -> 530 -> 421; random, a quarter
+// of the pairs, L = 24,576 2,008 -> 1,359 -> 788.
+constexpr int64_t kSharedClaims = 128;
+
+__global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) void tile_attend_f32_kernel(
+    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, float* __restrict__ O,
+    float* __restrict__ lse, const int64_t* __restrict__ row_ptr, int64_t L, float scale, void* ws, size_t ws_bytes,
+    int accumulate) {
+  constexpr int kOwnLds = CoreF32::lds_bytes<kPipeRegK>();
+  static_assert(4 * kOwnLds <= 2 * SharedBlock::kBytes, "four wavefronts' own blocks fit the shared planes");
+  __shared__ __attribute__((aligned(16))) char planes[2 * SharedBlock::kBytes];
+  __shared__ uint32_t claim;
+  const int32_t H = (int32_t)gridDim.x;   // head-major grid: the long work items of every head are dispatched first
+  const WorkspacePlan pl = plan_workspace(L, H, row_ptr[L], SGA_F32);
+  if (pl.total_bytes > ws_bytes) return;
+  char* base_ws = static_cast<char*>(ws);
+  const int64_t n_groups = reinterpret_cast<const uint32_t*>(ws)[kCtrMultiItems];
+  const int64_t n_claims = n_groups + (pl.n_tiles + 3) / 4;
+  if (n_claims * H < kSharedClaims) {
+    tile_attend_body<float, kPipeRegK>(Q, K, V, O, lse, row_ptr, L, scale, ws, ws_bytes, accumulate, planes);
+    return;
+  }
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int n = lane & 31, h = lane >> 5;
+  const float c = softmax_factor(scale);
+  const TileItem* items = reinterpret_cast<const TileItem*>(base_ws + pl.off_items_rec);
+  const int32_t* tile_bad = reinterpret_cast<const int32_t*>(base_ws + pl.off_tile_bad);
+  const int32_t* tile_pbase = reinterpret_cast<const int32_t*>(base_ws + pl.off_tile_pbase);
+  const int32_t* pair_blk = reinterpret_cast<const int32_t*>(base_ws + pl.off_pair_blk);
+  const uint32_t* pair_mask = reinterpret_cast<const uint32_t*>(base_ws + pl.off_pair_mask);
+  const bool parts_fit = tile_parts_fit(pl, ws);
+  const int64_t head = blockIdx.x;
+  const int64_t hoff = head * L * kHeadDim;
+  const char* Kb = reinterpret_cast<const char*>(K + hoff);
+  const char* Vb = reinterpret_cast<const char*>(V + hoff);
+  uint32_t* work_next = reinterpret_cast<uint32_t*>(base_ws + pl.off_work_next) + head;
+  const int r_own = threadIdx.x >> 3;
+  SharedBlock next;
+  auto request = [&](int block) {
+    const int64_t v0 = (int64_t)block * kTile;
+    const int64_t left = L - v0;
+    const int last = left < kTile ? (int)left - 1 : kTile - 1;   // keys past the end re-read the last one (masked off)
+    const uint32_t at = (uint32_t)(r_own < last ? r_own : last) * (kHeadDim * 4) + (threadIdx.x & 7) * 32;
+    next.load(Kb + v0 * (kHeadDim * 4) + at, Vb + v0 * (kHeadDim * 4) + at);
+  };
+  for (bool first = true;; first = false) {
+    int64_t cl = blockIdx.y;
+    if (!first) {
+      if (n_claims <= gridDim.y) break;
+      __syncthreads();                   // every wavefront has read the previous claim and left the LDS of its item
+      if (threadIdx.x == 0) claim = (uint32_t)claim_next(work_next, n_claims, gridDim.y);
+      __syncthreads();
+      cl = __builtin_amdgcn_readfirstlane(claim);
+    }
+    if (cl >= n_claims) break;
+    const bool segments = cl < n_groups;
+    const int64_t group = segments ? uniform64(items[cl].group) : 0;
+    MergedLists lists;
+    const int32_t* ids[4];
+    int32_t nb[4], ti[4], t = -1, seg = 0, nseg = 1, nblk = 0;
+    int64_t slot0 = 0;
+    int held = 0, first_seg = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      int64_t w;
+      bool there;
+      if (segments) {
+        w = group + i;
+        there = w < pl.n_work;
+      } else {
+        const int64_t tile = (cl - n_groups) * 4 + i;
+        there = tile < pl.n_tiles;
+        w = there ? work_first(row_ptr, L, pl.seg_shift, tile) : 0;
+      }
+      const TileItem* rec = items + (there ? w : 0);
+      ti[i] = __builtin_amdgcn_readfirstlane(rec->tile);
+      nb[i] = __builtin_amdgcn_readfirstlane(rec->nblk);
+      const int32_t si = __builtin_amdgcn_readfirstlane(rec->seg), ns = __builtin_amdgcn_readfirstlane(rec->nseg);
+      const int64_t slot = uniform64(rec->slot0);
+      there = there && ti[i] >= 0 && nb[i] >= 0;                 // (a tile without edges still writes its rows)
+      if (segments) {
+        // of the group: the same segment of the next tile, or the next segment of the same one
+        there = there && ns > 1 && parts_fit && !tile_bad[ti[i]] &&
+                (i == 0 || ti[i] == ti[0] || (ti[i] == ti[0] + i && si == first_seg));
+      } else if (there) {
+        there = ns == 1;
+      }
+      if (i == 0) first_seg = si;
+      if (!there) nb[i] = 0;
+      ids[i] = pair_blk + slot;
+      held += there;
+      if (wave == i) {
+        t = there ? ti[i] : -1;
+        seg = si;
+        nseg = ns;
+        nblk = nb[i];
+        slot0 = slot;
+      }
+    }
+    // Lists worth merging: their blocks a quarter, half, three quarters and all of the way down lie
+    // close together, in a call of enough steps (see kSharedSteps).  (us, every wavefront on its own
+    // list / merged: 32-token blocks with two random ones per row, 4 heads, L = 65,536, 147 / 240;
+    // longformer mask with 16 global tokens, 373 / 365, its global tokens merged as well 476;
+    // +-300, L = 200,000, 2 heads, 476 / 426; random, a quarter of the pairs, L = 24,576, 1,003 / 810;
+    // +-30, L = 100,000, 37 / 49.)
+    int most = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) most = max(most, nb[i]);
+    bool alike = held > 1 && most > 0 && n_claims * H * most >= kSharedSteps;
+#pragma unroll
+    for (int f = 1; f <= 4; ++f) {
+      int lo = INT32_MAX, hi = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (nb[i] == 0) continue;
+        const int id = ((MergedLists::Ids)ids[i])[(int)((int64_t)(nb[i] - 1) * f / 4)] & ~kFullBit;
+        lo = min(lo, id);
+        hi = max(hi, id);
+      }
+      alike = alike && hi - lo <= 4 + most / 8;
+    }
+    const int64_t row_first = (int64_t)(t < 0 ? 0 : t) * kTile;
+    const int64_t qrow = row_first + n;
+    const bool exists = qrow < L;
+    CoreF32 core;
+    core.load_q(Q + hoff + (exists ? qrow : L - 1) * kHeadDim, h, scale < 0.f);
+    TileState st;
+    st.init();
+    const ExplicitBlocks src{pair_blk + slot0, pair_mask + slot0 * kTile, L};
+    if (alike) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) lists.start(i, ids[i], nb[i]);
+      MergedLists::Step cur = lists.advance(wave);               // (some list holds a block)
+      request(cur.block);
+      const uint32_t* words = src.mask + n;                      // this lane's word of the item's next block
+      uint32_t word = nblk > 0 ? *words : 0u;
+      int to_go = nblk;
+      MergedLists::Step ahead = lists.advance(wave);
+      next.store(planes);
+      request(ahead.block != MergedLists::kDone ? ahead.block : cur.block);
+      workgroup_lds_barrier();
+      for (int k = 0; cur.block != MergedLists::kDone; ++k) {
+        next.store(planes + ((k + 1) & 1) * SharedBlock::kBytes);
+        const MergedLists::Step after = lists.advance(wave);
+        request(after.block != MergedLists::kDone ? after.block : cur.block);
+        if (cur.own >= 0) {
+          BlockInfo b;
+          b.row0 = 0;
+          b.raw = 0;
+          b.nvalid = kTile;
+          b.word = word;
+          b.full = cur.own & kFullBit;
+          words += kTile;
+          if (--to_go > 0) word = *words;
+          SharedBlock::attend(core, planes + (k & 1) * SharedBlock::kBytes, b, c, lane, st);
+        }
+        workgroup_lds_barrier();
+        cur = ahead;
+        ahead = after;
+      }
+      if (__any(not_finite(st))) {         // (see CoreF32T)
+        st.init();
+        core.run_exact(K + hoff, V + hoff, src, 0, nblk, c, lane, st, planes + wave * CoreF32::kBlockBytes);
+      }
+    } else {
+      core.run<kPipeRegK>(K + hoff, V + hoff, src, 0, nblk, c, lane, st, planes + wave * kOwnLds);
+    }
+    if (t < 0) continue;
+    if (nseg > 1) {
+      float* part = reinterpret_cast<float*>(base_ws + pl.off_tpartials) +
+                    (((int64_t)tile_pbase[t] + seg) * H + head) * (int64_t)kTilePartialFloats;
+      store_partial(part, st, n, h);
+    } else {
+      finish_tile<float>(O + hoff, lse ? lse + head * L : nullptr, qrow, qrow, exists, st, h, accumulate != 0);
+    }
+  }
 }
 
 // Key blocks of the non-local mask (global tokens 0..g-1 without the window, Section IV-B
@@ -2794,14 +3010,16 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) voi
   sm.init(1, lane);
   const char* vt0 = Core::vt_base(ldsv, lane, h);
   float* lse_h = lse ? lse + head * L : nullptr;
-  while (true) {
-    uint32_t claimed = 0;
-    if (lane == 0) claimed = atomicAdd(work_next, 1u);
-    const int64_t w_cur = __builtin_amdgcn_readfirstlane(claimed);
-    if (w_cur >= pl.n_work) {
-      if (lane == 0) claim_exit(work_next, H, gridDim.y * 4);
-      break;
+  const uint32_t claimants = gridDim.y * 4;
+  for (bool first = true;; first = false) {
+    int64_t w_cur = (int64_t)blockIdx.y * 4 + wave;
+    if (!first) {
+      if (pl.n_work <= claimants) break;
+      uint32_t claimed = 0;
+      if (lane == 0) claimed = (uint32_t)claim_next(work_next, pl.n_work, claimants);
+      w_cur = __builtin_amdgcn_readfirstlane(claimed);
     }
+    if (w_cur >= pl.n_work) break;
     const int4 r0 = reinterpret_cast<const int4*>(items + w_cur)[0];
     const int64_t slot_raw = reinterpret_cast<const int64_t*>(items + w_cur)[2];
     const int32_t t = __builtin_amdgcn_readfirstlane(r0.x);
@@ -3704,6 +3922,16 @@ __global__ __launch_bounds__(256) void tile_window_kv_kernel(
 template <typename T>
 sga_status run_tile_explicit_wide(const AttnArgs& a);
 
+// Workgroups per row and head of the merge of multi-segment tiles, each of which walks the merge list:
+// one per tile where a prepared graph knows their number, up to four rounds of the chip's 2,048
+// workgroups.  (768 tiles of six segments, one head: 96 us with 16 workgroups per row.)
+unsigned merge_tiles(const AttnArgs& a) {
+  const int64_t most = 8192 / (kTile * (int64_t)a.H);
+  int64_t n = a.prepared ? (int64_t)a.plan_multi_tiles : 16;
+  if (n > most) n = most;
+  return (unsigned)(n < 16 ? (a.prepared && a.plan_multi_tiles < 16 ? a.plan_multi_tiles : 16) : n);
+}
+
 template <typename T>
 sga_status run_tile_explicit(const AttnArgs& a) {
   if (a.d != kHeadDim) return run_tile_explicit_wide<T>(a);
@@ -3723,7 +3951,7 @@ sga_status run_tile_explicit(const AttnArgs& a) {
   if (a.dtype == SGA_F32) {
     per_head = 512 / a.H;
     if (per_head < 1) per_head = 1;
-    if (per_head > nwg) per_head = nwg;
+    if (per_head > n_tiles + 64) per_head = n_tiles + 64;
   }
   // fp32 tiles keep the K fragment in registers; fp16 tiles stage K in LDS (measured best)
   const dim3 grid((unsigned)a.H, (unsigned)per_head);
@@ -3732,15 +3960,15 @@ sga_status run_tile_explicit(const AttnArgs& a) {
     hipLaunchKernelGGL(tile_attend_f16_kernel, grid, dim3(256), 0, a.stream, Q, K, V, O, a.lse, a.row_ptr,
                        a.L, a.scale, a.ws, a.ws_bytes, a.accumulate ? 1 : 0);
   } else {
-    profile_mark_begin(a.stream, "tile_attend_kernel");
-    auto kernel = a.split ? tile_attend_kernel<T, kPipeSplit> : tile_attend_kernel<T, kPipeRegK>;
+    profile_mark_begin(a.stream, a.split ? "tile_attend_kernel" : "tile_attend_f32_kernel");
+    auto kernel = a.split ? tile_attend_kernel<T, kPipeSplit> : tile_attend_f32_kernel;
     hipLaunchKernelGGL(kernel, grid, dim3(256), 0, a.stream, Q, K, V, O, a.lse, a.row_ptr, a.L, a.scale, a.ws,
                        a.ws_bytes, a.accumulate ? 1 : 0);
   }
   profile_mark_end(a.stream);
   // (a prepared graph knows whether any tile was cut into segments)
   if (!a.prepared || a.plan_multi_tiles > 0)
-    hipLaunchKernelGGL((tile_merge_kernel<T, kHeadDim>), dim3(16, (unsigned)a.H, kTile), dim3(256), 0,
+    hipLaunchKernelGGL((tile_merge_kernel<T, kHeadDim>), dim3(merge_tiles(a), (unsigned)a.H, kTile), dim3(256), 0,
                        a.stream, O, a.lse, a.row_ptr, a.L, a.ws, a.ws_bytes, a.accumulate ? 1 : 0);
   return hip_status(hipGetLastError());
 }
@@ -3775,7 +4003,7 @@ sga_status run_tile_explicit_wide_d(const AttnArgs& a) {
   }
   profile_mark_end(a.stream);
   if (!a.prepared || a.plan_multi_tiles > 0)
-    hipLaunchKernelGGL((tile_merge_kernel<T, kD>), dim3(16, (unsigned)a.H, kTile), dim3(256), 0, a.stream,
+    hipLaunchKernelGGL((tile_merge_kernel<T, kD>), dim3(merge_tiles(a), (unsigned)a.H, kTile), dim3(256), 0, a.stream,
                        O, a.lse, a.row_ptr, a.L, a.ws, a.ws_bytes, a.accumulate ? 1 : 0);
   return hip_status(hipGetLastError());
 }
@@ -3892,8 +4120,6 @@ sga_status run_tile_implicit_wide(const AttnArgs& a) {
   if (a.d == 256) return run_tile_implicit_wide_d<T, 256>(a);
   return SGA_ERR_UNSUPPORTED;
 }
-
-constexpr int64_t kSharedSteps = 8192;
 
 sga_status run_tile_implicit(const AttnArgs& a) {
   if (a.d != kHeadDim)

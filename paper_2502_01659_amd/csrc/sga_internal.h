@@ -82,10 +82,22 @@ __host__ __device__ inline int split_chunk(int64_t nnz, int32_t H) {
   return c;
 }
 __host__ __device__ inline int seg_shift_min(int32_t dtype) { return dtype == SGA_F32 ? 12 : 15; }
-__host__ __device__ inline int seg_shift(int32_t dtype, int64_t nnz, int32_t H) {
+// fp32 masks that fill a sixteenth of the L x L pairs and more spread their edges over all blocks:
+// S is then the edges of about 64 blocks at that fill, and the call gets up to 4096 items.  (A
+// workgroup shares the key blocks of four items, so there are a quarter as many claims for 512
+// resident workgroups.  Uniformly random mask, a quarter of the pairs, L = 24,576: 1,317 us with 128
+// blocks per item, three rounds of workgroups where 2.25 would do; half of the pairs, L = 8,192:
+// too few claims for all CUs.)
+__host__ __device__ inline int seg_shift(int32_t dtype, int64_t nnz, int32_t H, int64_t L) {
   int sh = dtype == SGA_F32 ? 15 : 18;
   const int64_t e = (nnz < 0 ? 0 : nnz) * (int64_t)H;
-  while (sh > seg_shift_min(dtype) && (e >> sh) < (dtype == SGA_F32 ? 1024 : 4096)) --sh;
+  int64_t items = dtype == SGA_F32 ? 1024 : 4096;
+  if (dtype == SGA_F32 && nnz > 0 && nnz / L >= L / 16) {
+    items = 4096;
+    const int64_t per_row = 2 * (nnz / L);               // fill * 2 L: S = 2^15 at a fill of one half
+    for (int64_t half = L + L / 2; sh > 13 && 2 * per_row <= half; half >>= 1) --sh;
+  }
+  while (sh > seg_shift_min(dtype) && (e >> sh) < items) --sh;
   return sh;
 }
 
@@ -103,8 +115,7 @@ __host__ __device__ inline int seg_shift(int32_t dtype, int64_t nnz, int32_t H) 
 //                     [row_ptr[32t]/128, row_ptr[32(t+1)]/128), split evenly among its segments
 // pair_mask           cap_pairs x 32 x uint32: bit j of word r = edge (row 32t+r, key 32b+j)
 // tpartials           cap_tparts x H x max(1, d / 64) x kTilePartialFloats floats
-// work_next           H x uint32: next unclaimed tile work item of each head (dynamic scheduling),
-//                     then H x uint32: wavefronts (workgroups) of the head that found no item left
+// work_next           H x uint32: claims of tile work items made so far of each head (dynamic scheduling)
 enum WsCounter : int {
   kCtrChunksNeeded = 0,   // sum of chunk counts of all long rows
   kCtrItemsAlloc = 1,     // bump allocator over the partial slots of split rows
@@ -117,6 +128,7 @@ enum WsCounter : int {
   kCtrFineNeeded = 8,       // the same three for the finer split (see row_split_shape)
   kCtrFineAlloc = 9,
   kCtrMaxChunksFine = 10,
+  kCtrMultiItems = 11,      // groups of up to four segment items (see TileItem::group)
   kNumCounters = 64
 };
 
@@ -128,7 +140,7 @@ struct alignas(32) TileItem {
   int32_t seg;      // segment of the tile's key-block span ...
   int32_t nseg;     // ... out of this many
   int64_t slot0;    // first (tile, key block) pair slot of the list
-  int64_t pad;
+  int64_t group;    // (no part of this item: entry of the list of groups, see tile_attend_f32_kernel)
 };
 
 struct WorkspacePlan {
@@ -159,7 +171,7 @@ __host__ __device__ inline WorkspacePlan plan_workspace(int64_t L, int32_t H, in
                                                         int32_t dtype, int32_t d = kHeadDim,
                                                         int force_shift = -1) {
   WorkspacePlan p{};
-  p.seg_shift = force_shift >= 0 ? force_shift : seg_shift(dtype, nnz, H);
+  p.seg_shift = force_shift >= 0 ? force_shift : seg_shift(dtype, nnz, H, L);
   p.split_chunk = force_shift >= 0 ? kSplitChunkMin : split_chunk(nnz, H);
   size_t off = 256;   // counters
   const int64_t e = nnz < 0 ? 0 : nnz;
@@ -207,7 +219,7 @@ __host__ __device__ inline WorkspacePlan plan_workspace(int64_t L, int32_t H, in
   const int64_t slices = d > kHeadDim ? d / kHeadDim : 1;   // a wide tile leaves one record per 64 channels
   off = (off + (size_t)p.cap_tparts * H * slices * kTilePartialFloats * sizeof(float) + 255) & ~size_t(255);
   p.off_work_next = off;
-  off = (off + (tiles ? (size_t)H * 8 : 0) + 255) & ~size_t(255);
+  off = (off + (tiles ? (size_t)H * 4 : 0) + 255) & ~size_t(255);
   // implicit window masks: partial states of cut tiles (short sequences only)
   p.cap_wparts = 0;
   if (nnz < 0 && d >= kHeadDim) {
@@ -256,12 +268,49 @@ __device__ __forceinline__ int64_t work_first(const int64_t* __restrict__ row_pt
 
 // Segments tile t is cut into: max(1, edges(t) / S); a tile below kCutEdges edges (every tile of
 // a window mask up to +-255) stays whole also where a small call has S below that.
-__device__ __forceinline__ int32_t tile_segments(const int64_t* __restrict__ row_ptr, int64_t L,
-                                                 int sh, int64_t t) {
-  const int64_t r0 = t * kTile, r1 = r0 + kTile < L ? r0 + kTile : L;
-  const int64_t e = row_ptr[r1] - row_ptr[r0];
-  const int64_t n = e >> sh;
-  return n < 1 || e < kCutEdges ? 1 : (int32_t)n;
+//
+// Four neighbouring tiles 4g .. 4g+3 of similar size (the largest at most twice the smallest) are
+// cut into the same number of segments, so that segment s of the four covers the same range of keys:
+// four consecutive work items, starting at a multiple of four, hold the same segment of the four
+// tiles, and a workgroup streams or shares the key blocks of one range.  Of the items the four
+// own, [f(4g), f(4g+4)), item first + 4 s + i then is segment s of tile 4g + i and the others are idle.
+struct TileCut {
+  int32_t nseg;
+  bool together;       // the four tiles are cut alike
+  int64_t first;       // ... and this is their first item (nseg > 1 only)
+};
+__device__ __forceinline__ TileCut tile_cut(const int64_t* __restrict__ row_ptr, int64_t L, int sh, int64_t t) {
+  const int64_t g = t & ~int64_t(3);
+  int64_t r[5];
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    const int64_t row = (g + i) * kTile;
+    r[i] = row_ptr[row < L ? row : L];
+  }
+  int64_t least = r[1] - r[0], most = least, own = least;
+#pragma unroll
+  for (int i = 1; i < 4; ++i) {
+    const int64_t e = r[i + 1] - r[i];
+    least = e < least ? e : least;
+    most = e > most ? e : most;
+    if (t - g == i) own = e;
+  }
+  TileCut cut{1, false, 0};
+  if ((g + 3) * kTile < L && 2 * least >= most) {
+    cut.together = true;
+    cut.first = (g + (r[0] >> sh) + 3) & ~int64_t(3);
+    const int64_t room = (((g + 4 + (r[4] >> sh)) & ~int64_t(3)) - cut.first) / 4;
+    int64_t n = ((r[4] - r[0]) >> 2) >> sh;
+    n = n < room ? n : room;
+    if (n > 1 && most >= kCutEdges) cut.nseg = (int32_t)n;
+  } else {
+    const int64_t n = own >> sh;
+    if (n > 1 && own >= kCutEdges) cut.nseg = (int32_t)n;
+  }
+  return cut;
+}
+__device__ __forceinline__ int32_t tile_segments(const int64_t* __restrict__ row_ptr, int64_t L, int sh, int64_t t) {
+  return tile_cut(row_ptr, L, sh, t).nseg;
 }
 
 // True when the tile path of this call produces the rows of tile t: its block lists fitted

@@ -12,10 +12,12 @@ from gpu_util import TOL
 pytestmark = pytest.mark.gpu
 
 # (head dimension, explicit CSR, length, window): window tiles of a small call and of one whose
-# workgroups share their key blocks (cut into ranges: 3,333 and 30,001), wide tiles, work items; ragged
-# lengths, a window inside one key block and one of many blocks
+# workgroups share their key blocks (cut into ranges: 3,333 and 30,001); work items claimed one by one,
+# in fours on lists of their own and in fours on merged lists; wide tiles; ragged lengths, windows
+# inside one key block and of many blocks
 FORMS = [(64, False, 333, 20), (64, False, 3333, 3000), (64, False, 30001, 700), (64, False, 140003, 70),
-         (64, True, 333, 20), (64, True, 4100, 300), (128, False, 333, 40), (256, True, 300, 20)]
+         (64, True, 333, 20), (64, True, 4100, 300), (64, True, 16421, 20), (64, True, 40003, 250),
+         (128, False, 333, 40), (256, True, 300, 20)]
 
 
 def _both(form, Q, K, V, scale):
@@ -84,3 +86,30 @@ def test_minus_infinity_scores_weigh_nothing(form):
     assert torch.isfinite(O2).all() and torch.isfinite(O1).all()
     assert (O1 - O2).abs().max().item() <= 2 * TOL["f32"]
     assert (l1 - l2).abs().max().item() <= 1e-4
+
+
+@pytest.mark.parametrize("L,density,H", [(1500, 0.6, 3), (4100, 0.3, 1), (8200, 0.5, 2), (6001, 1.0, 1)])
+def test_tiles_cut_alike(L, density, H):
+    """Dense random masks: every tile is cut into segments, four tiles alike (the last tiles of a ragged
+    length are not), with a band of empty rows and three tiles of a quarter of the edges.  The
+    prepared graph, whose claims start from what the call before left, repeats the call bit for bit."""
+    import torch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(L)
+    dense = torch.rand((L, L), generator=g, device="cuda:0") < density
+    dense[200:232] = False
+    dense[640:736, L // 4:] = False
+    rp = torch.zeros(L + 1, dtype=torch.int64, device="cuda:0")
+    rp[1:] = dense.sum(dim=1).cumsum(0)
+    ci = dense.nonzero()[:, 1].to(torch.int32).contiguous()
+    Q, K, V = torch_qkv(H, L, 64, "f32", 1.0, 3, "cuda:0")
+    ws = sga.alloc_workspace(L, H, 64, "f32", ci.numel())
+    O1, l1 = sga.attention_forward(Q, K, V, rp, ci, 0.125, workspace=ws, path=sga.PATH_TILE, want_lse=True)
+    O2, l2 = sga.attention_forward(Q, K, V, rp, ci, 0.125, workspace=ws, path=sga.PATH_GATHER, want_lse=True)
+    assert (O1 - O2).abs().max().item() <= 2 * TOL["f32"]
+    some = torch.isfinite(l2)
+    assert torch.equal(some, torch.isfinite(l1)) and (l1 - l2)[some].abs().max().item() <= 1e-4
+    plan = sga.graph_prepare(rp, ci, H, 64, "f32", ws)
+    for _ in range(3):
+        O3 = sga.attention_forward_prepared(Q, K, V, rp, ci, 0.125, plan, ws, O=torch.full_like(Q, 7.0))
+        assert torch.equal(O3, O1)
