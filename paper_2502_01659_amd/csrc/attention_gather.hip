@@ -500,24 +500,67 @@ __global__ __launch_bounds__(256) void gather_runs_kernel(
   finish_row<T, D>(O + hoff + i * D, lse ? lse + h * L + i : nullptr, lane, st, accumulate != 0);
 }
 
+// Partial states p0[c * step + ...] = {acc[D], m, l}, c < n, reduced in order to one; one wavefront, lane c
+// owns channels c, c + 64, ...  The maxima are read 64 partials at a time and the states eight
+// at a time, so that a row of a thousand chunks does not wait for a thousand loads one after the
+// other; the sums run in chunk order all the same.  (The 256 partials of a global row of the
+// non-local mask, a quarter per wavefront: 20 us one after the other.)
+template <int D>
+__device__ __forceinline__ void reduce_partials(const float* p0, int64_t step, int n, int lane, float& M, float& l,
+                                                float (&acc)[(D + kWave - 1) / kWave]) {
+  constexpr int kCh = (D + kWave - 1) / kWave;
+  constexpr int kAhead = 8;
+  M = kMinusHuge;
+  for (int c = lane; c < n; c += kWave) M = fmaxf(M, p0[c * step + D]);
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) M = fmaxf(M, __shfl_xor(M, off, kWave));
+  l = 0.f;
+#pragma unroll
+  for (int k = 0; k < kCh; ++k) acc[k] = 0.f;
+  for (int c0 = 0; c0 < n; c0 += kAhead) {
+    float mm[kAhead], ll[kAhead], aa[kAhead][kCh];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const float* p = p0 + (c0 + u < n ? c0 + u : n - 1) * step;
+      mm[u] = p[D];
+      ll[u] = p[D + 1];
+#pragma unroll
+      for (int k = 0; k < kCh; ++k) aa[u][k] = lane + k * kWave < D ? p[lane + k * kWave] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      if (c0 + u < n) {
+        const float w = __builtin_amdgcn_exp2f(mm[u] - M);
+        l = __builtin_fmaf(ll[u], w, l);
+#pragma unroll
+        for (int k = 0; k < kCh; ++k) acc[k] = __builtin_fmaf(aa[u][k], w, acc[k]);
+      }
+    }
+  }
+}
+// ... and left as one partial state at `out`
+template <int D>
+__device__ __forceinline__ void combine_partials(const float* p0, int64_t step, int n, float* out, int lane) {
+  constexpr int kCh = (D + kWave - 1) / kWave;
+  float M, l, acc[kCh];
+  reduce_partials<D>(p0, step, n, lane, M, l, acc);
+#pragma unroll
+  for (int k = 0; k < kCh; ++k)
+    if (lane + k * kWave < D) out[lane + k * kWave] = acc[k];
+  if (lane == 0) {
+    out[D] = M;
+    out[D + 1] = l;
+  }
+}
+
 // Combine the n partial (m, l, acc) states of one row in their stored order (deterministic) and
 // write the row: one wavefront, lane c owns channels c, c + 64, ...
 template <typename T, int D>
 __device__ __forceinline__ void merge_row_partials(const float* p0, int64_t step, int n, T* Orow,
                                                    float* lse_i, int lane, bool accumulate) {
   constexpr int kCh = (D + kWave - 1) / kWave;
-  float M = kMinusHuge;
-  for (int c = 0; c < n; ++c) M = fmaxf(M, p0[c * step + D]);
-  float l = 0.f, acc[kCh];
-#pragma unroll
-  for (int k = 0; k < kCh; ++k) acc[k] = 0.f;
-  for (int c = 0; c < n; ++c) {
-    const float w = __builtin_amdgcn_exp2f(p0[c * step + D] - M);
-    l = __builtin_fmaf(p0[c * step + D + 1], w, l);
-#pragma unroll
-    for (int k = 0; k < kCh; ++k)
-      if (lane + k * kWave < D) acc[k] = __builtin_fmaf(p0[c * step + lane + k * kWave], w, acc[k]);
-  }
+  float M, l, acc[kCh];
+  reduce_partials<D>(p0, step, n, lane, M, l, acc);
   const bool empty = !(l > 0.f);
   const float inv = empty ? 0.f : 1.0f / l;
   float lse_row = empty ? -INFINITY : (M + __builtin_amdgcn_logf(l)) * kLn2;
@@ -585,7 +628,6 @@ __global__ __launch_bounds__(256) void nonlocal_merge_kernel(T* __restrict__ O, 
                                                              int64_t L, int32_t n_chunks,
                                                              const float* __restrict__ partials,
                                                              int accumulate) {
-  constexpr int kCh = (D + kWave - 1) / kWave;
   __shared__ float quarter[4][D + 4];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int64_t i = blockIdx.x, h = blockIdx.y, H = gridDim.y;
@@ -594,25 +636,7 @@ __global__ __launch_bounds__(256) void nonlocal_merge_kernel(T* __restrict__ O, 
   const int c0 = wave * per < n_chunks ? wave * per : n_chunks;
   const int c1 = c0 + per < n_chunks ? c0 + per : n_chunks;
   const float* p0 = partials + ((i * n_chunks + c0) * H + h) * (D + 4);
-  float M = kMinusHuge;
-  for (int c = 0; c < c1 - c0; ++c) M = fmaxf(M, p0[c * step + D]);
-  float l = 0.f, acc[kCh];
-#pragma unroll
-  for (int k = 0; k < kCh; ++k) acc[k] = 0.f;
-  for (int c = 0; c < c1 - c0; ++c) {
-    const float w = __builtin_amdgcn_exp2f(p0[c * step + D] - M);
-    l = __builtin_fmaf(p0[c * step + D + 1], w, l);
-#pragma unroll
-    for (int k = 0; k < kCh; ++k)
-      if (lane + k * kWave < D) acc[k] = __builtin_fmaf(p0[c * step + lane + k * kWave], w, acc[k]);
-  }
-#pragma unroll
-  for (int k = 0; k < kCh; ++k)
-    if (lane + k * kWave < D) quarter[wave][lane + k * kWave] = acc[k];
-  if (lane == 0) {
-    quarter[wave][D] = M;
-    quarter[wave][D + 1] = l;
-  }
+  combine_partials<D>(p0, step, c1 - c0, &quarter[wave][0], lane);
   __syncthreads();
   if (wave == 0)
     merge_row_partials<T, D>(&quarter[0][0], D + 4, 4, O + h * L * D + i * D, lse ? lse + h * L + i : nullptr, lane,
@@ -699,51 +723,6 @@ __global__ __launch_bounds__(256) void gather_rows_and_chunks_kernel(
                             gridDim.x - n_rows);
 }
 
-// Partial states p0[c * step + ...], c < n, combined in order into one partial state
-// (D accumulators, m, l) at `out`; one wavefront, lane c owns channels c, c + 64, ...  The
-// maxima are read 64 partials at a time and the states eight at a time, so that a row of a
-// thousand chunks does not wait for a thousand loads one after the other; the sums run in
-// chunk order all the same.
-template <int D>
-__device__ __forceinline__ void combine_partials(const float* p0, int64_t step, int n, float* out, int lane) {
-  constexpr int kCh = (D + kWave - 1) / kWave;
-  constexpr int kAhead = 8;
-  float M = kMinusHuge;
-  for (int c = lane; c < n; c += kWave) M = fmaxf(M, p0[c * step + D]);
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) M = fmaxf(M, __shfl_xor(M, off, kWave));
-  float l = 0.f, acc[kCh];
-#pragma unroll
-  for (int k = 0; k < kCh; ++k) acc[k] = 0.f;
-  for (int c0 = 0; c0 < n; c0 += kAhead) {
-    float mm[kAhead], ll[kAhead], aa[kAhead][kCh];
-#pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-      const float* p = p0 + (c0 + u < n ? c0 + u : n - 1) * step;
-      mm[u] = p[D];
-      ll[u] = p[D + 1];
-#pragma unroll
-      for (int k = 0; k < kCh; ++k) aa[u][k] = lane + k * kWave < D ? p[lane + k * kWave] : 0.f;
-    }
-#pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-      if (c0 + u < n) {
-        const float w = __builtin_amdgcn_exp2f(mm[u] - M);
-        l = __builtin_fmaf(ll[u], w, l);
-#pragma unroll
-        for (int k = 0; k < kCh; ++k) acc[k] = __builtin_fmaf(aa[u][k], w, acc[k]);
-      }
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < kCh; ++k)
-    if (lane + k * kWave < D) out[lane + k * kWave] = acc[k];
-  if (lane == 0) {
-    out[D] = M;
-    out[D + 1] = l;
-  }
-}
-
 // Rows of up to kMaxSplit chunks: one wavefront per (long row, head) combines the row's partials
 // in chunk order.  Rows of more chunks (cut by edge count into up to kMaxSplitLong): one
 // workgroup per row, each of its four wavefronts combines a quarter of the partials in chunk
@@ -818,7 +797,7 @@ sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
     hipLaunchKernelGGL((gather_rows_and_chunks_kernel<T, D>), dim3(n_rows + chunk_wgs, (unsigned)a.H), dim3(256), 0,
                        a.stream, Q, K, V, O, a.lse, a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes, 1,
                        a.accumulate ? 1 : 0, n_rows);
-  } else {
+  } else if (!(a.prepared && a.plan_long_rows == a.L)) {       // (a prepared graph all of whose rows are split: 19 us of L = 24,576)
     if (mark && !mark_chunks) profile_mark_begin(a.stream, "gather_csr_kernel");
     hipLaunchKernelGGL((gather_csr_kernel<T, D>), grid, dim3(256), 0, a.stream, Q, K, V, O, a.lse,
                        a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes, split ? 1 : 0,

@@ -1229,6 +1229,40 @@ struct CoreF16T {
                                     reinterpret_cast<half8*>(Oh + (row0 + r * row_step) * kHeadDim + (lane & 7) * 8));
     }
   }
+
+  // The same for a call that continues an earlier state: O = w_prev O + inv acc on the rows r_lo <= r <
+  // n_rows (inv and w_prev are those of the lane's query).  The tile passes through LDS in fp32 and
+  // the earlier rows are read and written whole, where store_row moves 16 bytes of 32 rows per
+  // instruction (the non-local call of that mask: 25 us off).  lds = kCarryBytes bytes.
+  static constexpr int kCarryPitch = 64 * 4 + 16;
+  static constexpr int kCarryBytes = kTile * kCarryPitch;
+  __device__ static void store_tile_carry(__half* Oh, int64_t row0, int r_lo, int n_rows, const TileState& st, float inv,
+                                          float w_prev, int lane, char* lds) {
+    const int n = lane & 31, h = lane >> 5;
+    __builtin_amdgcn_wave_barrier();     // the last block's reads of the staged blocks are done
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<float4*>(lds + n * kCarryPitch + (cb * 32 + 8 * g + 4 * h) * 4) =
+            make_float4(st.o[cb][4 * g] * inv, st.o[cb][4 * g + 1] * inv, st.o[cb][4 * g + 2] * inv, st.o[cb][4 * g + 3] * inv);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = (lane >> 3) + 8 * i;
+      const float w = __shfl(w_prev, r, kWave);
+      const float4 a = reinterpret_cast<const float4*>(lds + r * kCarryPitch + (lane & 7) * 32)[0];
+      const float4 b = reinterpret_cast<const float4*>(lds + r * kCarryPitch + (lane & 7) * 32)[1];
+      if (r < r_lo || r >= n_rows) continue;
+      half8* at = reinterpret_cast<half8*>(Oh + (row0 + r) * kHeadDim + (lane & 7) * 8);
+      const half8 old = *at;
+      const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+      half8 out;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) out[e] = (_Float16)__builtin_fmaf(w, (float)old[e], v[e]);
+      __builtin_nontemporal_store(out, at);
+    }
+  }
 };
 using CoreF16 = CoreF16T<kHeadDim>;
 
@@ -2773,16 +2807,11 @@ struct NonlocalBlocks {
 // Implicit non-local mask, queries i >= g: one wavefront per 32 rows against the (g + 31) / 32
 // key blocks that hold the global tokens.
 template <typename T, int kPipe>
-__global__ __launch_bounds__(256) void tile_nonlocal_cols_kernel(
-    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
-    float* __restrict__ lse, int64_t L, int64_t W, int64_t g, float scale, int accumulate) {
-  constexpr int kLds = CoreFor<T, kPipe>::type::template lds_bytes<kPipe>();
-  __shared__ __attribute__((aligned(16))) char lds_all[4 * kLds];
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+__device__ __forceinline__ void nonlocal_cols(const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
+                                              T* __restrict__ O, float* __restrict__ lse, int64_t L, int64_t W,
+                                              int64_t g, int64_t tile, float scale, int accumulate, int lane, char* lds) {
   const int n = lane & 31, h = lane >> 5;
-  char* lds = lds_all + wave * kLds;
-  const int64_t row0 = (g / kTile + (int64_t)blockIdx.x * 4 + wave) * kTile;      // the first tile may start below g
+  const int64_t row0 = (g / kTile + tile) * kTile;           // the first tile may start below g
   if (row0 >= L) return;
   const int64_t hd = blockIdx.y;
   const int64_t hoff = hd * L * kHeadDim;
@@ -2795,22 +2824,33 @@ __global__ __launch_bounds__(256) void tile_nonlocal_cols_kernel(
   TileState st;
   st.init();
   core.template run<kPipe>(K + hoff, V + hoff, src, 0, nblk, softmax_factor(scale), lane, st, lds);
+  if constexpr (CoreOf<T>::type::kTileStore) {
+    static_assert(CoreF16::kCarryBytes <= CoreF16::lds_bytes<kPipeLdsK>(), "output tile fits the wavefront's LDS");
+    if (accumulate) {
+      const float l = st.l + other_half(st.l, h);
+      const bool empty = !(l > 0.f);
+      const float lse_row = empty ? -INFINITY : (st.m + __builtin_amdgcn_logf(l)) * kLn2;
+      const CarryWeights cw = carry_weights(lse[hd * L + (mine ? i : L - 1)], lse_row);
+      CoreF16::store_tile_carry(O + hoff, row0, g > row0 ? (int)(g - row0) : 0, L - row0 < kTile ? (int)(L - row0) : kTile,
+                                st, empty ? 0.f : 1.0f / l * cw.w_now, cw.w_prev, lane, lds);
+      if (mine && h == 0) lse[hd * L + i] = cw.lse;
+      return;
+    }
+  }
   finish_tile<T>(O + hoff, lse ? lse + hd * L : nullptr, i, i, mine, st, h, accumulate != 0);
 }
 
-// Implicit non-local mask, the g global rows: grid = (ranges of key blocks, tiles of global rows,
-// heads), one wavefront each, which leaves the partial state of its rows over its range in the
-// layout nonlocal_merge_kernel reads (row-major: D accumulators, m, l per (row, range, head)).
+// ... and the g global rows: one wavefront per (tile of global rows, range c of key blocks), which leaves
+// the partial state of its rows over its range in the layout nonlocal_merge_kernel reads
+// (row-major: D accumulators, m, l per (row, range, head)).
 template <typename T, int kPipe>
-__global__ __launch_bounds__(64) void tile_nonlocal_rows_kernel(
-    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, int64_t L, int64_t W,
-    int64_t g, int64_t blocks_per_range, float scale, float* __restrict__ partials) {
-  constexpr int kLds = CoreFor<T, kPipe>::type::template lds_bytes<kPipe>();
-  __shared__ __attribute__((aligned(16))) char lds[kLds];
-  const int lane = threadIdx.x;
+__device__ __forceinline__ void nonlocal_rows(const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
+                                              int64_t L, int64_t W, int64_t g, int64_t tile, int64_t c, int64_t n_ranges,
+                                              int64_t blocks_per_range, float scale, float* __restrict__ partials,
+                                              int lane, char* lds) {
   const int n = lane & 31, h = lane >> 5;
-  const int64_t c = blockIdx.x, n_ranges = gridDim.x, hd = blockIdx.z, H = gridDim.z;
-  const int64_t row0 = (int64_t)blockIdx.y * kTile;
+  const int64_t hd = blockIdx.y, H = gridDim.y;
+  const int64_t row0 = tile * kTile;
   const int64_t hoff = hd * L * kHeadDim;
   const int64_t nb_total = (L + kTile - 1) / kTile;
   const int64_t kb0 = c * blocks_per_range;
@@ -2835,6 +2875,32 @@ __global__ __launch_bounds__(64) void tile_nonlocal_rows_kernel(
   if (h == 0) {
     p[kHeadDim] = st.m;
     p[kHeadDim + 1] = l;
+  }
+}
+
+// Both parts in one launch (neither reads what the other writes): the first row_wgs workgroups of a
+// head take the ranges of the global rows, which are the long ones, the others the tiles of the rows
+// >= g, which wait for memory.  (longformer mask, L = 65,536, 8 heads, fp16: 56 and 22 us one
+// after the other; 58 us together, with the rows written whole.  268 MB of Q and O: 4.6 TB/s.)
+template <typename T, int kPipe>
+__global__ __launch_bounds__(256, 2) void tile_nonlocal_kernel(
+    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
+    float* __restrict__ lse, int64_t L, int64_t W, int64_t g, float scale, int accumulate, uint32_t row_wgs,
+    uint32_t n_ranges, int64_t blocks_per_range, float* __restrict__ partials) {
+  constexpr int kLds = CoreFor<T, kPipe>::type::template lds_bytes<kPipe>();
+  __shared__ __attribute__((aligned(16))) char lds_all[4 * kLds];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  char* lds = lds_all + wave * kLds;
+  if (blockIdx.x < row_wgs) {
+    const uint32_t unit = blockIdx.x * 4 + wave;             // (tile, range), ranges of a tile together
+    const uint32_t tile = unit / n_ranges;
+    if ((int64_t)tile * kTile >= g) return;
+    nonlocal_rows<T, kPipe>(Q, K, V, L, W, g, tile, unit - tile * n_ranges, n_ranges, blocks_per_range, scale, partials,
+                            lane, lds);
+  } else {
+    nonlocal_cols<T, kPipe>(Q, K, V, O, lse, L, W, g, (int64_t)(blockIdx.x - row_wgs) * 4 + wave, scale, accumulate,
+                            lane, lds);
   }
 }
 
@@ -3164,7 +3230,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) voi
 }
 
 // The implicit non-local mask at head dimensions 128 and 256: the two kernels of the 64-channel
-// form (tile_nonlocal_cols_kernel, tile_nonlocal_rows_kernel) with one workgroup of kD / 64
+// form (nonlocal_cols, nonlocal_rows) with one workgroup of kD / 64
 // wavefronts per tile, each on its 64-channel slice (see tile_attend_wide_kernel).
 template <typename T, int kD, int kPipe>
 __global__ __launch_bounds__(kD) void tile_nonlocal_cols_wide_kernel(
@@ -4231,28 +4297,26 @@ void run_tile_nonlocal(const AttnArgs& a, int64_t g, float* partials, int32_t* n
   const T* V = static_cast<const T*>(a.V);
   const int acc = a.accumulate ? 1 : 0;
   const int64_t first_tile = g / kTile, n_tiles = (a.L + kTile - 1) / kTile;
-  if (n_tiles > first_tile && a.L > g) {
-    profile_mark_begin(a.stream, "tile_nonlocal_cols_kernel");
-    hipLaunchKernelGGL((tile_nonlocal_cols_kernel<T, kPipe>), dim3((unsigned)((n_tiles - first_tile + 3) / 4), (unsigned)a.H),
-                       dim3(256), 0, a.stream, Q, K, V, static_cast<T*>(a.O), a.lse, a.L, (int64_t)a.window, g,
-                       a.scale, acc);
-    profile_mark_end(a.stream);
-  }
-  *n_chunks = 0;
+  const int64_t col_wgs = n_tiles > first_tile && a.L > g ? (n_tiles - first_tile + 3) / 4 : 0;
+  int64_t ranges = 0, per = 1, row_wgs = 0;
   if (g > 0) {
     // ranges of at least 8 key blocks, as many as the partial states of the workspace allow
     // (kMaxImplicitGlobal rows x kMaxSplit ranges in all: fewer global rows, more ranges each)
-    const int64_t g_rows = (g + kTile - 1) / kTile * kTile;
-    int64_t max_ranges = (int64_t)kMaxImplicitGlobal * kMaxSplit / g_rows;
+    const int64_t g_tiles = (g + kTile - 1) / kTile;
+    int64_t max_ranges = (int64_t)kMaxImplicitGlobal * kMaxSplit / (g_tiles * kTile);
     if (max_ranges > 256) max_ranges = 256;
-    int64_t per = (n_tiles + max_ranges - 1) / max_ranges;
+    per = (n_tiles + max_ranges - 1) / max_ranges;
     if (per < 8) per = 8;
-    const int64_t ranges = (n_tiles + per - 1) / per;
-    *n_chunks = (int32_t)ranges;
-    hipLaunchKernelGGL((tile_nonlocal_rows_kernel<T, kPipe>),
-                       dim3((unsigned)ranges, (unsigned)((g + kTile - 1) / kTile), (unsigned)a.H), dim3(64), 0, a.stream,
-                       Q, K, V, a.L, (int64_t)a.window, g, per, a.scale, partials);
+    ranges = (n_tiles + per - 1) / per;
+    row_wgs = (g_tiles * ranges + 3) / 4;
   }
+  *n_chunks = (int32_t)ranges;
+  if (row_wgs + col_wgs == 0) return;
+  profile_mark_begin(a.stream, "tile_nonlocal_kernel");
+  hipLaunchKernelGGL((tile_nonlocal_kernel<T, kPipe>), dim3((unsigned)(row_wgs + col_wgs), (unsigned)a.H), dim3(256), 0,
+                     a.stream, Q, K, V, static_cast<T*>(a.O), a.lse, a.L, (int64_t)a.window, g, a.scale, acc,
+                     (uint32_t)row_wgs, (uint32_t)ranges, per, partials);
+  profile_mark_end(a.stream);
 }
 }  // namespace
 
