@@ -297,40 +297,13 @@ __global__ __launch_bounds__(256) void clear_workspace_kernel(void* ws, size_t w
     next[i] = 0;          // claim counters of the heads
 }
 
-// One thread per row: rows that are split reserve their partial slots and enter the list of
-// long rows.
+// One thread per row, see split_prepass_row.
 __global__ __launch_bounds__(256) void split_prepass_kernel(const int64_t* __restrict__ row_ptr,
                                                             int64_t L, int32_t H, int32_t dtype,
                                                             int32_t d, void* ws, size_t ws_bytes,
                                                             int skip_tiled) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= L) return;
-  const int64_t deg = row_ptr[i + 1] - row_ptr[i];
-  if (deg <= kSplitThreshold / 2) return;           // (no rule splits a row this short)
-  const WorkspacePlan pl = plan_workspace(L, H, row_ptr[L], dtype, d);
-  if (pl.total_bytes > ws_bytes || !row_is_split(deg, pl)) return;
-  if (skip_tiled && (tiles_cover_everything(pl, ws) || tile_handled(pl, ws, row_ptr, L, dtype, i / kTile)))
-    return;
-  uint32_t* ctr = reinterpret_cast<uint32_t*>(ws);
-  int32_t n, len, nf, lenf;
-  row_split_shape(deg, pl, false, n, len);
-  row_split_shape(deg, pl, true, nf, lenf);
-  if (nf <= n) {
-    nf = n;
-    lenf = len;
-  }
-  atomicAdd(&ctr[kCtrChunksNeeded], (uint32_t)n);
-  atomicMax(&ctr[kCtrMaxChunks], (uint32_t)n);
-  atomicAdd(&ctr[kCtrFineNeeded], (uint32_t)nf);
-  atomicMax(&ctr[kCtrMaxChunksFine], (uint32_t)nf);
-  const uint32_t base = atomicAdd(&ctr[kCtrItemsAlloc], (uint32_t)n);
-  const uint32_t basef = atomicAdd(&ctr[kCtrFineAlloc], (uint32_t)nf);
-  if ((int64_t)base + n > pl.cap_items) return;
-  const uint32_t slot = atomicAdd(&ctr[kCtrLongRows], 1u);
-  int4* lr = reinterpret_cast<int4*>(static_cast<char*>(ws) + pl.off_long);
-  lr[slot] = make_int4((int)i, (int)base, n, len);
-  // (read only if the finer chunks of every row fit, and then basef + nf <= cap_items)
-  lr[pl.cap_items + slot] = make_int4((int)i, (int)basef, nf, lenf);
+  if (i < L) split_prepass_row(row_ptr, i, L, H, dtype, d, ws, ws_bytes, skip_tiled);
 }
 
 // The list of long rows that this call uses: the finer split if all its chunks fit.
@@ -779,7 +752,7 @@ sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
   T* O = static_cast<T*>(a.O);
   const bool split = allow_split && a.ws && a.ws_bytes >= 256 && a.L > kSplitThreshold;
   // (a prepared graph holds the chunk items of its split rows already)
-  if (split && !a.prepared) launch_split_prepass(a, skip_tiled);
+  if (split && !a.prepared && !a.prepass_done) launch_split_prepass(a, skip_tiled);
   // after the tile path only leftover rows remain: a grid of about one chip-full of wavefronts
   // over all heads strides over the rows (it returns at once when the tiles covered everything)
   int64_t nwg = (a.L + 3) / 4;

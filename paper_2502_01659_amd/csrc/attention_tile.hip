@@ -2025,18 +2025,25 @@ __device__ __forceinline__ void tile_attend_body(
   // neighbouring tiles at the same time (static stride), so that the key blocks they share are
   // fetched together and hit the CU's L1.
   int64_t w_static = (int64_t)ywg * 4 + wave;
-  const uint32_t claimants = gridDim.y * 4;
-  for (bool first = true;; first = false) {
-    int64_t w_cur = w_static;
-    if (!kDynamic) {
+  bool first = true;
+  while (true) {
+    int64_t w_cur;
+    if constexpr (kDynamic) {
+      const uint32_t claimants = gridDim.y * 4;
+      w_cur = w_static;
+      if (!first) {
+        if (pl.n_work <= claimants) break;
+        uint32_t claimed = 0;
+        if (lane == 0) claimed = (uint32_t)claim_next(work_next, pl.n_work, claimants);
+        w_cur = __builtin_amdgcn_readfirstlane(claimed);
+      }
+      first = false;
+      if (w_cur >= pl.n_work) break;
+    } else {
+      w_cur = w_static;
       w_static += (int64_t)gridDim.y * 4;
-    } else if (!first) {
-      if (pl.n_work <= claimants) break;
-      uint32_t claimed = 0;
-      if (lane == 0) claimed = (uint32_t)claim_next(work_next, pl.n_work, claimants);
-      w_cur = __builtin_amdgcn_readfirstlane(claimed);
+      if (w_cur >= pl.n_work) break;
     }
-    if (w_cur >= pl.n_work) break;
     // the whole record in one uniform 32-byte read
     const int4 r0 = reinterpret_cast<const int4*>(items + w_cur)[0];
     const int64_t slot_raw = reinterpret_cast<const int64_t*>(items + w_cur)[2];
@@ -2182,12 +2189,19 @@ __device__ __forceinline__ void store_out(__half* p, float v) { *p = __float2hal
 template <typename T, int kD>
 __global__ __launch_bounds__(256) void tile_merge_kernel(T* __restrict__ O, float* __restrict__ lse,
                                                          const int64_t* __restrict__ row_ptr, int64_t L,
-                                                         void* ws, size_t ws_bytes, int accumulate) {
+                                                         void* ws, size_t ws_bytes, int accumulate,
+                                                         uint32_t merge_wgs) {
   constexpr int kSlices = kD / kHeadDim;
   __shared__ float sm_acc[4][kD];
   __shared__ float sm_m[4], sm_l[4];
   const int32_t H = (int32_t)gridDim.y;
   constexpr int32_t dtype = DtypeOf<T>::code;
+  if (blockIdx.x >= merge_wgs) {
+    const int64_t wg = ((int64_t)(blockIdx.x - merge_wgs) * gridDim.y + blockIdx.y) * gridDim.z + blockIdx.z;
+    const int64_t i = wg * 256 + threadIdx.x;
+    if (i < L) split_prepass_row(row_ptr, i, L, H, dtype, kD, ws, ws_bytes, 1);
+    return;
+  }
   const WorkspacePlan pl = plan_workspace(L, H, row_ptr[L], dtype, kD);
   if (pl.total_bytes > ws_bytes || !tile_parts_fit(pl, ws)) return;
   char* base_ws = static_cast<char*>(ws);
@@ -2198,7 +2212,7 @@ __global__ __launch_bounds__(256) void tile_merge_kernel(T* __restrict__ O, floa
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
   const int64_t hd = blockIdx.y;
-  for (uint32_t i = blockIdx.x; i < n_multi; i += gridDim.x) {
+  for (uint32_t i = blockIdx.x; i < n_multi; i += merge_wgs) {
     const int4 rec = multi[i];
     const int64_t t = rec.x;
     if (tile_bad[t]) continue;
@@ -3998,6 +4012,12 @@ unsigned merge_tiles(const AttnArgs& a) {
   return (unsigned)(n < 16 ? (a.prepared && a.plan_multi_tiles < 16 ? a.plan_multi_tiles : 16) : n);
 }
 
+// ... and the columns of workgroups behind them that record the split rows (AttnArgs::prepass_done)
+unsigned prepass_columns(const AttnArgs& a) {
+  const int64_t per_column = 256 * (int64_t)kTile * a.H;
+  return a.prepass_done ? (unsigned)((a.L + per_column - 1) / per_column) : 0u;
+}
+
 template <typename T>
 sga_status run_tile_explicit(const AttnArgs& a) {
   if (a.d != kHeadDim) return run_tile_explicit_wide<T>(a);
@@ -4034,8 +4054,9 @@ sga_status run_tile_explicit(const AttnArgs& a) {
   profile_mark_end(a.stream);
   // (a prepared graph knows whether any tile was cut into segments)
   if (!a.prepared || a.plan_multi_tiles > 0)
-    hipLaunchKernelGGL((tile_merge_kernel<T, kHeadDim>), dim3(merge_tiles(a), (unsigned)a.H, kTile), dim3(256), 0,
-                       a.stream, O, a.lse, a.row_ptr, a.L, a.ws, a.ws_bytes, a.accumulate ? 1 : 0);
+    hipLaunchKernelGGL((tile_merge_kernel<T, kHeadDim>), dim3(merge_tiles(a) + prepass_columns(a), (unsigned)a.H, kTile),
+                       dim3(256), 0, a.stream, O, a.lse, a.row_ptr, a.L, a.ws, a.ws_bytes, a.accumulate ? 1 : 0,
+                       merge_tiles(a));
   return hip_status(hipGetLastError());
 }
 
@@ -4069,8 +4090,9 @@ sga_status run_tile_explicit_wide_d(const AttnArgs& a) {
   }
   profile_mark_end(a.stream);
   if (!a.prepared || a.plan_multi_tiles > 0)
-    hipLaunchKernelGGL((tile_merge_kernel<T, kD>), dim3(merge_tiles(a), (unsigned)a.H, kTile), dim3(256), 0, a.stream,
-                       O, a.lse, a.row_ptr, a.L, a.ws, a.ws_bytes, a.accumulate ? 1 : 0);
+    hipLaunchKernelGGL((tile_merge_kernel<T, kD>), dim3(merge_tiles(a) + prepass_columns(a), (unsigned)a.H, kTile),
+                       dim3(256), 0, a.stream, O, a.lse, a.row_ptr, a.L, a.ws, a.ws_bytes, a.accumulate ? 1 : 0,
+                       merge_tiles(a));
   return hip_status(hipGetLastError());
 }
 
@@ -4279,13 +4301,15 @@ void launch_tile_analyze(const AttnArgs& a) {
 sga_status launch_tile_explicit(const AttnArgs& a) {
   if (!a.ws || a.ws_bytes < 256) return launch_gather_explicit(a, false, false);
   // (a prepared graph in which no tile qualified goes straight to the per-row kernels)
+  AttnArgs b = a;
+  b.prepass_done = !a.prepared && a.L > kSplitThreshold;
   if (!(a.prepared && a.plan_no_tiles)) {
-    const sga_status st = a.dtype == SGA_F32 ? run_tile_explicit<float>(a) : run_tile_explicit<__half>(a);
+    const sga_status st = a.dtype == SGA_F32 ? run_tile_explicit<float>(b) : run_tile_explicit<__half>(b);
     if (st != SGA_OK) return st;
   }
   if (a.prepared && a.plan_tiles_cover_all) return SGA_OK;
   // rows of tiles that did not qualify (or everything, if the workspace is too small)
-  return launch_gather_explicit(a, true, true);
+  return launch_gather_explicit(b, true, true);
 }
 
 namespace {

@@ -330,6 +330,38 @@ __device__ __forceinline__ bool tiles_cover_everything(const WorkspacePlan& pl, 
   return ctr[kCtrTilesBad] == 0 && (int64_t)ctr[kCtrTilePartsNeeded] <= pl.cap_tparts;
 }
 
+// Row i of the per-row path's preparation: a row that is split reserves its partial slots and enters the
+// list of long rows.
+__device__ __forceinline__ void split_prepass_row(const int64_t* __restrict__ row_ptr, int64_t i, int64_t L, int32_t H,
+                                                  int32_t dtype, int32_t d, void* ws, size_t ws_bytes, int skip_tiled) {
+  const int64_t deg = row_ptr[i + 1] - row_ptr[i];
+  if (deg <= kSplitThreshold / 2) return;           // (no rule splits a row this short)
+  const WorkspacePlan pl = plan_workspace(L, H, row_ptr[L], dtype, d);
+  if (pl.total_bytes > ws_bytes || !row_is_split(deg, pl)) return;
+  if (skip_tiled && (tiles_cover_everything(pl, ws) || tile_handled(pl, ws, row_ptr, L, dtype, i / kTile)))
+    return;
+  uint32_t* ctr = reinterpret_cast<uint32_t*>(ws);
+  int32_t n, len, nf, lenf;
+  row_split_shape(deg, pl, false, n, len);
+  row_split_shape(deg, pl, true, nf, lenf);
+  if (nf <= n) {
+    nf = n;
+    lenf = len;
+  }
+  atomicAdd(&ctr[kCtrChunksNeeded], (uint32_t)n);
+  atomicMax(&ctr[kCtrMaxChunks], (uint32_t)n);
+  atomicAdd(&ctr[kCtrFineNeeded], (uint32_t)nf);
+  atomicMax(&ctr[kCtrMaxChunksFine], (uint32_t)nf);
+  const uint32_t base = atomicAdd(&ctr[kCtrItemsAlloc], (uint32_t)n);
+  const uint32_t basef = atomicAdd(&ctr[kCtrFineAlloc], (uint32_t)nf);
+  if ((int64_t)base + n > pl.cap_items) return;
+  const uint32_t slot = atomicAdd(&ctr[kCtrLongRows], 1u);
+  int4* lr = reinterpret_cast<int4*>(static_cast<char*>(ws) + pl.off_long);
+  lr[slot] = make_int4((int)i, (int)base, n, len);
+  // (read only if the finer chunks of every row fit, and then basef + nf <= cap_items)
+  lr[pl.cap_items + slot] = make_int4((int)i, (int)basef, nf, lenf);
+}
+
 template <typename T> struct DtypeOf;
 template <> struct DtypeOf<float> { static constexpr int32_t code = SGA_F32; };
 template <> struct DtypeOf<__half> { static constexpr int32_t code = SGA_F16; };
@@ -367,6 +399,7 @@ struct AttnArgs {
   size_t ws_bytes;
   // prepared graph (sga_graph_prepare): the workspace already holds the tile graph and the
   // chunk items of the split rows, and the host knows what they contain
+  bool prepass_done;           // the split rows were recorded by the launch that merges the tiles' segments
   bool prepared;
   uint32_t plan_multi_tiles;   // multi-segment tiles whose partial states fit (0: no merge launch)
   bool plan_tiles_cover_all;   // no row is left to the per-row kernels
