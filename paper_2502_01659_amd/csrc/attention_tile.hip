@@ -550,10 +550,12 @@ struct SliceExchange {
 //
 // Scores.  Every row of Q and K is scaled by a power of two that takes its largest element to
 // [2^14, 2^15), and an element x is written as hi + lo, hi = fp16(x), lo = fp16(x - hi) (the
-// difference is exact): the remainder is below 2^-24 |x|, half a unit in the last place of fp32,
-// or 2^-40 of the row's largest element where lo is subnormal.  A product is taken as
+// difference is exact): the remainder is at most 2^-23 |x|, a unit in the last place of fp32 (a
+// third of one on average), or 2^-40 of the row's largest element where lo is subnormal.  A
+// product is taken as
 //   lo.hi + hi.lo + hi.hi
-// and lo.lo, below 2^-24 |a.b|, is left out.  The scales return in the exponent of the softmax.
+// and lo.lo, at most 2^-22 |a.b| and 2^-25 on average, of either sign, is left out: less in a sum of
+// 64 products than the roundings of that sum.  The scales return in the exponent of the softmax.
 //
 // Weights and values.  The numerators of the softmax have no largest element to scale by until
 // the row is done, and small ones count when there are many, so they keep the exponent range of
@@ -561,7 +563,7 @@ struct SliceExchange {
 // differences are exact in fp32 and lo (at most 8 significant bits) is exact in bf16.  A product
 // is taken as
 //   lo.hi + hi.lo + mid.mid + mid.hi + hi.mid + hi.hi
-// and the terms left out (mid.lo, lo.mid, lo.lo) are below 2^-26 |a.b|.
+// and the terms left out (mid.lo, lo.mid, lo.lo) are together below 2^-24 |a.b|.
 //
 // The smallest terms go first into an accumulator, so that only the last few of its additions
 // round at the size of the sum, where the fp32 matrix instruction (two channels or keys at a
@@ -569,8 +571,9 @@ struct SliceExchange {
 // fp32 products (longformer mask, L = 65,536: 1.8e-7 instead of 4.1e-7 relative).
 //
 // Per 32 x 32 block: 36 matrix instructions of 32 cycles instead of 64 of 64, and about 380 vector
-// instructions for the splits.  Longformer mask, L = 65,536, 8 heads, prepared: 494 -> 395 us;
-// +-815 at d = 256, L = 16,301: 282 -> 210 us.
+// instructions for the splits (three quarters fewer where a workgroup shares them, SharedBlock).
+// With every wavefront splitting its own blocks: longformer mask, L = 65,536, 8 heads, prepared
+// 494 -> 399 us; +-815 at d = 256, L = 16,301 282 -> 205 us.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
