@@ -2022,8 +2022,8 @@ __device__ __forceinline__ void tile_attend_body(
   }
   const int64_t hoff = (int64_t)head * L * kHeadDim;
   uint32_t* work_next = reinterpret_cast<uint32_t*>(base_ws + pl.off_work_next) + head;
-  // fp32 items are long (4096 matrix-core cycles per block): wavefronts stay resident and claim
-  // the next item of their head from a device counter (greedy balance, no re-launch gaps).
+  // fp32 items are long (1,152 matrix-core cycles per block and the splits): wavefronts stay resident
+  // and claim the next item of their head from a device counter (greedy balance, no re-launch gaps).
   // fp16 items are short and bound by the memory path: the 4 wavefronts of a workgroup take 4
   // neighbouring tiles at the same time (static stride), so that the key blocks they share are
   // fetched together and hit the CU's L1.
