@@ -20,7 +20,7 @@
 // masking.
 //
 // fp32 storage splits its operands into 16-bit parts whose products the 16-bit matrix cores sum
-// in fp32 (see ScoreOperand and ValueOperand; v_mfma_f32_32x32x2_f32 only where a tile holds an
+// in fp32 (see SplitOperand; v_mfma_f32_32x32x2_f32 only where a tile holds an
 // infinity), fp16 storage uses v_mfma_f32_32x32x16_f16 with fp32 accumulation; P is rounded
 // to fp16 only as the MFMA operand, l is summed in fp32.
 //
@@ -548,97 +548,28 @@ struct SliceExchange {
 // fp32 products on the 16-bit matrix cores (16 times the rate of the fp32 ones), by splitting
 // the operands into parts whose products are summed in fp32.
 //
-// Scores.  Every row of Q and K is scaled by a power of two that takes its largest element to
-// [2^14, 2^15), and an element x is written as hi + lo, hi = fp16(x), lo = fp16(x - hi) (the
-// difference is exact): the remainder is at most 2^-23 |x|, a unit in the last place of fp32 (a
-// third of one on average), or 2^-40 of the row's largest element where lo is subnormal.  A
-// product is taken as
-//   lo.hi + hi.lo + hi.hi
-// and lo.lo, at most 2^-22 |a.b| and 2^-25 on average, of either sign, is left out: less in a sum of
-// 64 products than the roundings of that sum.  The scales return in the exponent of the softmax.
-//
-// Weights and values.  The numerators of the softmax have no largest element to scale by until
-// the row is done, and small ones count when there are many, so they keep the exponent range of
-// fp32: three bf16 parts, hi = bf16(x), mid = bf16(x - hi), lo = x - hi - mid, where both
-// differences are exact in fp32 and lo (at most 8 significant bits) is exact in bf16.  A product
-// is taken as
+// An element x of any operand (Q, K, the numerators of the softmax, V) becomes three bf16 parts,
+// hi = bf16(x), mid = bf16(x - hi), lo = x - hi - mid: both differences are exact in fp32 and lo (at
+// most 8 significant bits) is exact in bf16, so the parts hold x to its last bit and keep the exponent
+// range of fp32.  A product is taken as
 //   lo.hi + hi.lo + mid.mid + mid.hi + hi.mid + hi.hi
-// and the terms left out (mid.lo, lo.mid, lo.lo) are together below 2^-24 |a.b|.
+// and the terms left out (mid.lo, lo.mid, lo.lo) are together below 2^-24 |a.b|, whatever else the row
+// holds.  (Two fp16 parts under a scale per row take half the products for the scores, but an element
+// is then known to 2^-40 of the largest of its row only: one large channel costs the others their
+// accuracy, and the scales themselves can overflow.)
 //
 // The smallest terms go first into an accumulator, so that only the last few of its additions
 // round at the size of the sum, where the fp32 matrix instruction (two channels or keys at a
 // time) rounds at every one: the error against 64-bit arithmetic is smaller than with
-// fp32 products (longformer mask, L = 65,536: 1.8e-7 instead of 4.1e-7 relative).
+// fp32 products (longformer mask, L = 65,536: 1.5e-7 instead of 4.1e-7 relative).
 //
-// Per 32 x 32 block: 36 matrix instructions of 32 cycles instead of 64 of 64, and about 380 vector
+// Per 32 x 32 block: 48 matrix instructions of 32 cycles instead of 64 of 64, and about 440 vector
 // instructions for the splits (three quarters fewer where a workgroup shares them, SharedBlock).
 // With every wavefront splitting its own blocks: longformer mask, L = 65,536, 8 heads, prepared
-// 494 -> 399 us; +-815 at d = 256, L = 16,301 282 -> 205 us.
+// 494 -> 411 us; +-815 at d = 256, L = 16,301 282 -> 228 us.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
-
-// Two values at a time: hi = fp16(x) packed into one register, x - hi by the mixed-precision
-// fma (the fp16 operand is read straight out of the packed pair, no conversion back), and the
-// remainders packed again: four instructions per pair.
-__device__ __forceinline__ void split_pair_f16(float x0, float x1, half2v& hi, half2v& lo) {
-  hi = half2v{(_Float16)x0, (_Float16)x1};
-  const uint32_t hp = __builtin_bit_cast(uint32_t, hi);
-  float r0, r1;
-  asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r0) : "v"(hp), "v"(x0));
-  asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r1) : "v"(hp), "v"(x1));
-  lo = half2v{(_Float16)r0, (_Float16)r1};
-}
-// One operand of the score products (8 values per lane).
-struct ScoreOperand {
-  half8 hi, lo;
-  __device__ __forceinline__ void split(const float* x, float factor) {
-#pragma unroll
-    for (int e = 0; e < 8; e += 2) {
-      half2v h2, l2;
-      split_pair_f16(x[e] * factor, x[e + 1] * factor, h2, l2);
-      hi[e] = h2[0]; hi[e + 1] = h2[1];
-      lo[e] = l2[0]; lo[e + 1] = l2[1];
-    }
-  }
-};
-// The scale of a row whose largest magnitude is `top`: `down` = 2^(15 - e) takes it below 2^15, `up` is
-// its inverse.  (An infinite row gets some scale; its products are no numbers.)
-struct RowScale {
-  float down, up;
-  __device__ __forceinline__ explicit RowScale(float top) {
-    int e = __builtin_amdgcn_frexp_expf(top);
-    e = e > -100 ? e : -100;
-    down = __builtin_bit_cast(float, (uint32_t)(127 + 15 - e) << 23);
-    up = __builtin_bit_cast(float, (uint32_t)(127 - 15 + e) << 23);
-  }
-};
-template <int kN>
-__device__ __forceinline__ float largest(const float* x) {
-  float top = 0.f;
-#pragma unroll
-  for (int e = 0; e < kN; e += 2) top = __builtin_fmaxf(__builtin_fmaxf(top, __builtin_fabsf(x[e])), __builtin_fabsf(x[e + 1]));
-  return top;
-}
-// Scores of 32 keys: S[key acc_row(r, h)] with the key's scale, factors[key], taken back (a power of
-// two: exact); the caller takes back the query's.
-__device__ __forceinline__ floatx16 split_scores(const ScoreOperand (&k)[4], const ScoreOperand (&q)[4],
-                                                 const float* factors, int h) {
-  floatx16 s = {0};
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    s = __builtin_amdgcn_mfma_f32_32x32x16_f16(k[i].lo, q[i].hi, s, 0, 0, 0);
-    s = __builtin_amdgcn_mfma_f32_32x32x16_f16(k[i].hi, q[i].lo, s, 0, 0, 0);
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_mfma_f32_32x32x16_f16(k[i].hi, q[i].hi, s, 0, 0, 0);
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    const float4 f = *reinterpret_cast<const float4*>(factors + 8 * g + 4 * h);
-    s[4 * g] *= f.x; s[4 * g + 1] *= f.y; s[4 * g + 2] *= f.z; s[4 * g + 3] *= f.w;
-  }
-  return s;
-}
 
 __device__ __forceinline__ uint32_t round_pair_bf16(float x0, float x1) {
   const float2v x = {x0, x1};
@@ -649,8 +580,8 @@ __device__ __forceinline__ void take_pair(float& x0, float& x1, uint32_t pair) {
   x0 -= __builtin_bit_cast(float, pair << 16);
   x1 -= __builtin_bit_cast(float, pair & 0xffff0000u);
 }
-// One operand of the products of weights and values (8 values per lane).
-struct ValueOperand {
+// One operand of the products (8 values per lane).
+struct SplitOperand {
   bf16x8 hi, mid, lo;
   __device__ __forceinline__ void split(const float* x) {
     uint4v a, b, c;
@@ -671,7 +602,7 @@ struct ValueOperand {
 __device__ __forceinline__ floatx16 mfma_bf16(bf16x8 a, bf16x8 b, floatx16 acc) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
 }
-__device__ __forceinline__ floatx16 split_product(const ValueOperand& a, const ValueOperand& b, floatx16 acc) {
+__device__ __forceinline__ floatx16 split_product(const SplitOperand& a, const SplitOperand& b, floatx16 acc) {
   acc = mfma_bf16(a.lo, b.hi, acc);
   acc = mfma_bf16(a.hi, b.lo, acc);
   acc = mfma_bf16(a.mid, b.mid, acc);
@@ -679,16 +610,34 @@ __device__ __forceinline__ floatx16 split_product(const ValueOperand& a, const V
   acc = mfma_bf16(a.hi, b.mid, acc);
   return mfma_bf16(a.hi, b.hi, acc);
 }
+// Scores of 32 keys, S[key acc_row(r, h)].
+__device__ __forceinline__ floatx16 split_scores(const SplitOperand (&k)[4], const SplitOperand (&q)[4]) {
+  floatx16 s = {0};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    s = mfma_bf16(k[i].lo, q[i].hi, s);
+    s = mfma_bf16(k[i].hi, q[i].lo, s);
+    s = mfma_bf16(k[i].mid, q[i].mid, s);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    s = mfma_bf16(k[i].mid, q[i].hi, s);
+    s = mfma_bf16(k[i].hi, q[i].mid, s);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) s = mfma_bf16(k[i].hi, q[i].hi, s);
+  return s;
+}
 // O^T += V_blk^T P^T for one block; value(u, cb) is the operand V^T[channel cb*32+n][keys 16u ..].
 // The products of a block are summed by themselves and added to O once: one rounding at the size
 // of O per block (chained into O they round 12 times, the fp32 instruction 16 times, which is
-// what the error of rows of thousands of keys comes from: +-16,383, relative error 1.15e-6 with
-// fp32 products, 1.03e-6 chained, 0.32e-6 so; the 32 additions cost nothing measurable).
+// what the error of rows of thousands of keys comes from: +-16,383, L = 65,536, relative error 3.0e-6
+// with fp32 products, 0.66e-6 so; the 32 additions cost nothing measurable).
 // No branch here: skipping the halves of a masked block that no query attends made two versions
 // of this code, whose registers cost more than the products saved (247 -> 331 us at +-128).
 template <typename Value>
 __device__ __forceinline__ void weigh_values(const float (&p)[16], const BlockInfo& b, TileState& st, Value value) {
-  ValueOperand pb[2];
+  SplitOperand pb[2];
   pb[0].split(p);
   pb[1].split(p + 8);
 #pragma unroll
@@ -712,14 +661,13 @@ __device__ __forceinline__ bool not_finite(const TileState& st) {
 }
 
 // The split of an infinity is no number (nor is that of a finite value that rounds to an
-// infinite bf16), so the products of such inputs are not those of fp32.  A tile whose state
+// infinite bf16, from 3.39e38), so the products of such inputs are not those of fp32.  A tile whose state
 // ends with an infinity or a NaN is therefore computed once more with fp32 products (run_exact),
 // which decide what such inputs give.
 template <int kD>
 struct CoreF32T {
   using Stage = StageMap<float, kD>;
-  ScoreOperand q2[4];         // Q[query n][h*32 + 8s .. +7], s = 0..3 (of this wavefront's 64-channel slice)
-  float q_up;                 // scale of this lane's query
+  SplitOperand q3[4];         // Q[query n][h*32 + 8s .. +7], s = 0..3 (of this wavefront's 64-channel slice)
   const float* q_row;         // this lane's half row of Q, for run_exact
   bool q_negate;
   SliceExchange<kD> xchg;   // used for kD > 64 only
@@ -741,31 +689,13 @@ struct CoreF32T {
     q_negate = negate;
     float qf[32];
     load_qf(qf);
-    const RowScale scale(row_top(qf, h));
-    q_up = scale.up;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) q2[s].split(qf + 8 * s, scale.down);
+    for (int s = 0; s < 4; ++s) q3[s].split(qf + 8 * s);
   }
-  // largest magnitude of the row whose halves this lane and the one 32 positions away hold
-  __device__ static float row_top(const float (&x)[32], int h) {
-    const float top = largest<32>(x);
-    return __builtin_fmaxf(top, other_half(top, h));
-  }
-  // K fragment -> operands; the key's scale goes to `factors`
-  __device__ static void split_k(const float (&kf)[32], int n, int h, ScoreOperand (&k2)[4], float* factors) {
-    const RowScale scale(row_top(kf, h));
-    if (h == 0) factors[n] = scale.up;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) k2[s].split(kf + 8 * s, scale.down);
-  }
-  // scores; returns what takes them to log2 units
-  __device__ float scores(const ScoreOperand (&k2)[4], const float* factors, float c, int lane, floatx16& s) {
-    s = split_scores(k2, q2, factors, lane >> 5);
-    if (kD == kHeadDim) return q_up * c;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] *= q_up;             // (the slices of a row have scales of their own)
-    xchg.sum_slices(s, lane);
-    return c;
+  __device__ floatx16 scores(const SplitOperand (&k3)[4], int lane) {
+    floatx16 s = split_scores(k3, q3);
+    if (kD > kHeadDim) xchg.sum_slices(s, lane);
+    return s;
   }
 
   // kf[t] = K[key n of the block][h*32 + t], straight from global memory: 128 contiguous bytes
@@ -801,7 +731,7 @@ struct CoreF32T {
       float v[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] = vread[acc_row(8 * u + e, 0) * kHeadDim + cb * 32];
-      ValueOperand va;
+      SplitOperand va;
       va.split(v);
       return va;
     });
@@ -817,15 +747,15 @@ struct CoreF32T {
     Stage sm;
     sm.init(src.key_stride(), lane);
     const uint32_t klane = (uint32_t)(n * sm.stride_bytes) + h * 128;
-    float* factors = reinterpret_cast<float*>(lds + kBlockBytes + 512);
     BlockInfo b = src.get(k0, n);
     src.resolve(b);
     float kf[32];
     load_k(Kh, b, sm.stride_bytes, klane, n, h, kf);
     for (int k = k0; k < k1; ++k) {
       const bool more = k + 1 < k1;      // wave-uniform
-      ScoreOperand k2[4];
-      split_k(kf, n, h, k2, factors);
+      SplitOperand k3[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) k3[i].split(kf + 8 * i);
       BlockInfo b1 = src.get(more ? k + 1 : k, n);
       src.resolve(b1);
       __builtin_amdgcn_wave_barrier();   // the previous block's reads of the staged V are done
@@ -833,10 +763,9 @@ struct CoreF32T {
       asm volatile("" ::: "memory");
       __builtin_amdgcn_sched_barrier(0); // (the counted wait below relies on this order)
       if (more) load_k(Kh, b1, sm.stride_bytes, klane, n, h, kf);
-      floatx16 s;
-      const float up = scores(k2, factors, c, lane, s);
+      const floatx16 s = scores(k3, lane);
       float p[16];
-      softmax_block(s, up, b, h, st, p);
+      softmax_block(s, c, b, h, st, p);
       wait_staged_v<kFragLoads>(more);   // V block k is older than the K fragment loads (if any)
       __builtin_amdgcn_wave_barrier();
       weigh_v(p, b, n, h, st, lds);
@@ -855,7 +784,6 @@ struct CoreF32T {
     sm.init(1, lane);
     const uint32_t klane = (uint32_t)(n * sm.stride_bytes) + h * 128;
     char* ldsw = lds + kBlockBytes;              // two slots of 64 mask words (both half-waves)
-    float* factors = reinterpret_cast<float*>(lds + kBlockBytes + 512);
     const uint32_t* wsrc = src.mask + n;         // this lane's word of block k: wsrc[32 k]
     BlockInfo b = src.block(k0);
     BlockInfo b1 = src.block(k0 + 1 < k1 ? k0 + 1 : k0);
@@ -869,8 +797,9 @@ struct CoreF32T {
     for (int k = k0; k < k1; ++k) {
       const bool more = k + 1 < k1;      // wave-uniform
       src.resolve(b1);
-      ScoreOperand k2[4];
-      split_k(kf, n, h, k2, factors);
+      SplitOperand k3[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) k3[i].split(kf + 8 * i);
       wait_loads_except<0>();            // the words of block k are older than its K fragment
       __builtin_amdgcn_wave_barrier();
       b.word = *reinterpret_cast<const uint32_t*>(ldsw + (k & 1) * 256 + lane * 4);
@@ -881,10 +810,9 @@ struct CoreF32T {
       if (more) load_k(Kh, b1, sm.stride_bytes, klane, n, h, kf);
       BlockInfo b2 = b1;
       if (k + 2 < k1) b2 = src.block(k + 2);
-      floatx16 s;
-      const float up = scores(k2, factors, c, lane, s);
+      const floatx16 s = scores(k3, lane);
       float p[16];
-      softmax_block(s, up, b, h, st, p);
+      softmax_block(s, c, b, h, st, p);
       wait_staged_v<kFragLoads>(more);   // V block k is older than the K fragment loads (if any)
       __builtin_amdgcn_wave_barrier();
       weigh_v(p, b, n, h, st, lds);
@@ -930,7 +858,7 @@ struct CoreF32T {
   }
 
   template <int kPipe>
-  static constexpr int lds_bytes() { return kBlockBytes + 512 + kTile * 4; }     // V block, mask words, factors of the keys
+  static constexpr int lds_bytes() { return kBlockBytes + 512; }     // V block, mask words
 
   template <int kPipe, typename Src>
   __device__ void run(const float* __restrict__ Kh, const float* __restrict__ Vh, const Src& src,
@@ -1287,11 +1215,23 @@ struct CoreSplit {
   static constexpr int kBlockBytes = kTile * kHeadDim * 4;
   half8 qh[4], ql[4];   // Q[query n][h*32 + 8s .. +7], high and low parts
 
+  // Two values at a time: hi = fp16(x) packed into one register, x - hi by the mixed-precision
+  // fma (the fp16 operand is read straight out of the packed pair, no conversion back), and the
+  // remainders packed again: four instructions per pair.
+  __device__ static void split2(float x0, float x1, half2v& hi, half2v& lo) {
+    hi = half2v{(_Float16)x0, (_Float16)x1};
+    const uint32_t hp = __builtin_bit_cast(uint32_t, hi);
+    float r0, r1;
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r0) : "v"(hp), "v"(x0));
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r1) : "v"(hp), "v"(x1));
+    lo = half2v{(_Float16)r0, (_Float16)r1};
+  }
+
   __device__ static void split8(const float* x, half8& hi, half8& lo) {
 #pragma unroll
     for (int e = 0; e < 8; e += 2) {
       half2v h2, l2;
-      split_pair_f16(x[e], x[e + 1], h2, l2);
+      split2(x[e], x[e + 1], h2, l2);
       hi[e] = h2[0]; hi[e + 1] = h2[1];
       lo[e] = l2[0]; lo[e + 1] = l2[1];
     }
@@ -1399,7 +1339,7 @@ struct CoreSplit {
 #pragma unroll
           for (int e = 0; e < 4; e += 2) {
             half2v h2, l2;
-            split_pair_f16(vraw[4 * i + e], vraw[4 * i + e + 1], h2, l2);
+            split2(vraw[4 * i + e], vraw[4 * i + e + 1], h2, l2);
             vh[e] = h2[0]; vh[e + 1] = h2[1];
             vl[e] = l2[0]; vl[e + 1] = l2[1];
           }
@@ -2022,7 +1962,7 @@ __device__ __forceinline__ void tile_attend_body(
   }
   const int64_t hoff = (int64_t)head * L * kHeadDim;
   uint32_t* work_next = reinterpret_cast<uint32_t*>(base_ws + pl.off_work_next) + head;
-  // fp32 items are long (1,152 matrix-core cycles per block and the splits): wavefronts stay resident
+  // fp32 items are long (1,536 matrix-core cycles per block and the splits): wavefronts stay resident
   // and claim the next item of their head from a device counter (greedy balance, no re-launch gaps).
   // fp16 items are short and bound by the memory path: the 4 wavefronts of a workgroup take 4
   // neighbouring tiles at the same time (static stride), so that the key blocks they share are
@@ -2108,7 +2048,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(4, 4))) __launch_bounds__(256) voi
 // resident and claim items from the head's counter like the fp32 kernel above; wavefront 0
 // claims and the item index travels through LDS.
 template <typename T, int kD, int kPipe>
-__global__ __launch_bounds__(kD) void tile_attend_wide_kernel(
+__global__ __launch_bounds__(kD, 2) void tile_attend_wide_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
     float* __restrict__ lse, const int64_t* __restrict__ row_ptr, int64_t L, float scale, void* ws,
     size_t ws_bytes, int accumulate) {
@@ -2392,16 +2332,15 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) voi
 
 // ---- fp32 storage, key blocks shared by a workgroup ------------------------------------------------
 // Four tiles (one per wavefront) walk one list of key blocks together.  Each block of K and V is
-// loaded once per workgroup, split once (16 values per thread), and left in LDS as five planes of
-// 16-bit parts in the layouts CoreF16 reads: two of K (32 keys x 64 channels, the 16-byte chunks
+// loaded once per workgroup, split once (16 values per thread), and left in LDS as six planes of
+// 16-bit parts in the layouts CoreF16 reads: three of K (32 keys x 64 channels, the 16-byte chunks
 // of a row swizzled), three of V (row-major, for the LDS transpose read).  The wavefronts take
 // their matrix-core operands from there.  Splitting a block costs about as much vector time as its
 // products cost matrix time; shared by four tiles it is a quarter of that.
 struct SharedBlock {
   static constexpr int kPlane = kTile * kHeadDim * 2;
-  static constexpr int kValues = 2 * kPlane;               // offset of the first V plane
-  static constexpr int kFactors = 5 * kPlane;              // ... of the keys' scales (see split_scores)
-  static constexpr int kBytes = 5 * kPlane + kTile * 4;
+  static constexpr int kValues = 3 * kPlane;               // offset of the first V plane
+  static constexpr int kBytes = 6 * kPlane;
   float k[8], v[8];        // this thread's share: key threadIdx.x / 8, channels 8 * (threadIdx.x % 8) ..
   __device__ __forceinline__ void load(const char* k_at, const char* v_at) {
     const float4 a = reinterpret_cast<const float4*>(k_at)[0], b = reinterpret_cast<const float4*>(k_at)[1];
@@ -2409,24 +2348,15 @@ struct SharedBlock {
     k[0] = a.x; k[1] = a.y; k[2] = a.z; k[3] = a.w; k[4] = b.x; k[5] = b.y; k[6] = b.z; k[7] = b.w;
     v[0] = c.x; v[1] = c.y; v[2] = c.z; v[3] = c.w; v[4] = d.x; v[5] = d.y; v[6] = d.z; v[7] = d.w;
   }
-  template <int CTRL>
-  __device__ static __forceinline__ float dpp(float x) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, false));
-  }
   __device__ __forceinline__ void store(char* planes) const {
     const int r = threadIdx.x >> 3, j = threadIdx.x & 7;
-    float top = largest<8>(k);                             // of the key's row: its eight threads are neighbours
-    top = __builtin_fmaxf(top, dpp<0xB1>(top));            // quad_perm [1,0,3,2]
-    top = __builtin_fmaxf(top, dpp<0x4E>(top));            // quad_perm [2,3,0,1]
-    top = __builtin_fmaxf(top, dpp<0x141>(top));           // row_half_mirror
-    const RowScale scale(top);
-    if (j == 0) reinterpret_cast<float*>(planes + kFactors)[r] = scale.up;
-    ScoreOperand x;
-    x.split(k, scale.down);
+    SplitOperand x;
+    x.split(k);
     char* at = planes + (r * 8 + (j ^ (r & 7))) * 16;
-    *reinterpret_cast<half8*>(at) = x.hi;
-    *reinterpret_cast<half8*>(at + kPlane) = x.lo;
-    ValueOperand y;
+    *reinterpret_cast<bf16x8*>(at) = x.hi;
+    *reinterpret_cast<bf16x8*>(at + kPlane) = x.mid;
+    *reinterpret_cast<bf16x8*>(at + 2 * kPlane) = x.lo;
+    SplitOperand y;
     y.split(v);
     at = planes + kValues + r * (kHeadDim * 2) + j * 16;
     *reinterpret_cast<bf16x8*>(at) = y.hi;
@@ -2438,20 +2368,20 @@ struct SharedBlock {
   __device__ static __forceinline__ void attend(CoreF32& core, const char* planes, const BlockInfo& b, float c, int lane,
                                                 TileState& st) {
     const int n = lane & 31, h = lane >> 5;
-    ScoreOperand k2[4];
+    SplitOperand k3[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       const char* at = planes + (n * 8 + ((4 * h + s) ^ (n & 7))) * 16;
-      k2[s].hi = *reinterpret_cast<const half8*>(at);
-      k2[s].lo = *reinterpret_cast<const half8*>(at + kPlane);
+      k3[s].hi = *reinterpret_cast<const bf16x8*>(at);
+      k3[s].mid = *reinterpret_cast<const bf16x8*>(at + kPlane);
+      k3[s].lo = *reinterpret_cast<const bf16x8*>(at + 2 * kPlane);
     }
-    floatx16 s;
-    const float up = core.scores(k2, reinterpret_cast<const float*>(planes + kFactors), c, lane, s);
+    const floatx16 s = core.scores(k3, lane);
     float p[16];
-    softmax_block(s, up, b, h, st, p);
+    softmax_block(s, c, b, h, st, p);
     const char* vt = CoreF16::vt_base(planes + kValues, lane, h);
     weigh_values(p, b, st, [&](int u, int cb) {
-      ValueOperand va;
+      SplitOperand va;
       va.hi = __builtin_bit_cast(bf16x8, CoreF16::read_va(vt, u, cb));
       va.mid = __builtin_bit_cast(bf16x8, CoreF16::read_va(vt + kPlane, u, cb));
       va.lo = __builtin_bit_cast(bf16x8, CoreF16::read_va(vt + 2 * kPlane, u, cb));
@@ -2471,10 +2401,10 @@ __device__ __forceinline__ void workgroup_lds_barrier() {
 // over the key blocks of the whole 128 (grid mapping, ranges of key blocks and partial states as
 // in tile_window_kernel).  Block k is computed from one of two LDS buffers while block k+1, whose
 // values have arrived in registers, is split into the other one and block k+2 is requested.
-// Bound by matrix cores (56 % busy) and vector unit (60 %) together, a quarter of the time both
-// at once; 160 registers and 41 KB keep three wavefronts per SIMD (two were 4 % slower).  +-1359,
-// L = 262,144, 4 heads: 6.51 ms with fp32 products -> 3.28 ms; +-128, L = 65,536, 8 heads: 385 ->
-// 247 us; L = 2,000,000, one head, +-16: 526 -> 433 us.
+// Bound by matrix cores and vector unit together (see the profile of this kernel); 168 registers and
+// 48 KB keep three wavefronts per SIMD (two were 5 to 10 % slower).  +-1359, L = 262,144, 4 heads: 6.51
+// ms with fp32 products -> 3.64 ms; +-128, L = 65,536, 8 heads: 386 -> 270 us; L = 2,000,000, one head,
+// +-16: 524 -> 465 us.
 __global__ __attribute__((amdgpu_waves_per_eu(3, 3))) __launch_bounds__(256) void tile_window_f32_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, float* __restrict__ O,
     float* __restrict__ lse, int64_t L, int64_t W, int64_t s, int64_t n_groups, float scale, int accumulate,
@@ -2595,11 +2525,12 @@ struct MergedLists {
 // Resident workgroups claim from the head's counter: first the groups of segment items that the
 // CSR -> tile pass listed (the long ones), then the tiles in fours.  A call with fewer claims than
 // kSharedClaims leaves CUs without a workgroup: there every wavefront claims items by itself
-// (+-100, one head, us, that / fours: L = 8,192 23.7 / 26.8, L = 16,301 33.0 / 28.1).
+// (+-100, one head, us, that / fours: L = 8,192 26.5 / 28.4, L = 16,301 38.2 / 30.1).
 // Bound like that kernel, at two wavefronts per SIMD (256 registers, for the wavefronts on lists
-// of their own).  us, fp32 products -> own lists only -> this: longformer mask, L = 65,536, 8 heads,
-// prepared 495 -> 397 -> 355; +-300, L = 200,000, 2 heads 670 -> 530 -> 421; random, a quarter
-// of the pairs, L = 24,576 2,008 -> 1,359 -> 788.
+// of their own; 17 vector values spill outside the loops over blocks, 91 scalar ones to vector lanes).  us, fp32
+// products -> every wavefront by itself -> this: longformer mask, L = 65,536, 8 heads, prepared 494 ->
+// 411 -> 387; +-300, L = 200,000, 2 heads 670 -> 568 -> 465; random, a quarter of the pairs, L = 24,576
+// 2,014 -> 1,144 -> 893.
 constexpr int64_t kSharedClaims = 128;
 
 __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) void tile_attend_f32_kernel(
@@ -2700,10 +2631,10 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) voi
     }
     // Lists worth merging: their blocks a quarter, half, three quarters and all of the way down lie
     // close together, in a call of enough steps (see kSharedSteps).  (us, every wavefront on its own
-    // list / merged: 32-token blocks with two random ones per row, 4 heads, L = 65,536, 147 / 240;
-    // longformer mask with 16 global tokens, 373 / 365, its global tokens merged as well 476;
-    // +-300, L = 200,000, 2 heads, 476 / 426; random, a quarter of the pairs, L = 24,576, 1,003 / 810;
-    // +-30, L = 100,000, 37 / 49.)
+    // list / merged: 32-token blocks with two random ones per row, 4 heads, L = 65,536, 122 / 158;
+    // longformer mask with 16 global tokens, 406 / 379, its global tokens merged as well 506;
+    // +-300, L = 200,000, 2 heads, 540 / 456; random, a quarter of the pairs, L = 24,576, 1,163 / 890;
+    // +-30, L = 100,000, 42 / 51.)
     int most = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) most = max(most, nb[i]);
@@ -4263,8 +4194,8 @@ sga_status run_tile_implicit(const AttnArgs& a) {
     // Key blocks that the workgroups of 128 queries step through in total: from kSharedSteps on the
     // kernel that shares them (tile_window_f32_kernel) is the faster one, below it a step's latency
     // counts, which the shared form lengthens.  (One head, us, own blocks / shared: L = 32,768, +-64
-    // 16 / 21, +-500 68 / 60; L = 98,304, +-32 28 / 30, +-128 54 / 50; L = 131,072, +-32 35 / 40;
-    // L = 200,000, +-32 65 / 61.)
+    // 18 / 23, +-500 78 / 65; L = 98,304, +-32 31 / 32, +-128 63 / 54; L = 131,072, +-32 40 / 42;
+    // L = 200,000, +-32 69 / 65.)
     const int64_t class_blocks = (Lc + kTile - 1) / kTile;
     const int64_t steps = n_groups * shape.n_slots * a.H * (nb_max < class_blocks ? nb_max : class_blocks);
     const bool shared = !a.split && steps >= kSharedSteps;

@@ -1,7 +1,7 @@
-"""fp32 storage on the matrix cores: the operands are split into 16-bit parts (scaled per row for the
-scores), so the cases here are the ones where a split can go wrong: rows of very different
-magnitude in one key block, values near the ends of the fp32 range, huge values in keys that a
-query does not attend, and infinities.  The per-row kernels, which use fp32 arithmetic throughout,
+"""fp32 storage on the matrix cores: the operands are split into 16-bit parts, so the cases here
+are the ones where a split can go wrong: rows of very different magnitude in one key block, channels
+of very different magnitude in one row, values near the ends of the fp32 range, huge values in keys
+that a query does not attend, and infinities.  The per-row kernels, which use fp32 arithmetic throughout,
 are the reference; each of them is compared with the oracle in test_gpu_attention.py."""
 import pytest
 
@@ -113,3 +113,41 @@ def test_tiles_cut_alike(L, density, H):
     for _ in range(3):
         O3 = sga.attention_forward_prepared(Q, K, V, rp, ci, 0.125, plan, ws, O=torch.full_like(Q, 7.0))
         assert torch.equal(O3, O1)
+
+
+def _form_qkv(form, H, seed):
+    d, _, L, _ = form
+    return torch_qkv(H, L, d, "f32", 1.0, seed, "cuda:0")
+
+
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("q_exp,k_exp", [(-100, 112), (112, -100), (-115, 115), (-124, 125), (125, -124), (0, 13)])
+def test_scores_of_one_sign(form, q_exp, k_exp):
+    """Every product of Q and K is the same negative number, up to -2^19 after scaling: the scores of a row
+    are equal, no weight may vanish, and O is the mean of the attended V."""
+    import torch
+    d = form[0]
+    Q, K, V = _form_qkv(form, 2, 11)
+    Q = torch.full_like(Q, 2.0 ** q_exp)
+    K = torch.full_like(K, -2.0 ** k_exp)
+    (O1, l1), (O2, l2) = _both(form, Q, K, V, d ** -0.5)
+    assert torch.isfinite(l2).all()
+    # lse = score + ln(neighbours): rounds at the size of the score
+    assert ((l1 - l2).abs() <= 1e-4 + 2.0 ** -22 * l2.abs()).all()
+    assert (O1 - O2).abs().max().item() <= 2 * TOL["f32"]
+
+
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("big,in_k", [(1e6, True), (1e8, True), (1e12, True), (1e8, False), (1e12, False), (1e30, True)])
+def test_one_large_channel(form, big, in_k):
+    """One channel of K (or of Q) is larger than the others by any factor and meets a channel of Q (or of K)
+    that is smaller by the same factor: all channels count alike in the scores."""
+    import torch
+    d = form[0]
+    Q, K, V = _form_qkv(form, 2, 12)
+    large, small = (K, Q) if in_k else (Q, K)
+    large[:, :, 3] *= big
+    small[:, :, 3] /= big
+    (O1, l1), (O2, l2) = _both(form, Q, K, V, d ** -0.5)
+    assert (O1 - O2).abs().max().item() <= 2 * TOL["f32"]
+    assert (l1 - l2).abs().max().item() <= 1e-4
