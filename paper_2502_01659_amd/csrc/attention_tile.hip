@@ -847,10 +847,18 @@ struct CoreF32T {
       wait_loads_except<0>();
       __builtin_amdgcn_wave_barrier();
       const float* vread = reinterpret_cast<const float*>(lds) + h * 4 * kHeadDim + n;
+      // The values of keys that no query of the tile attends count as 0, so an infinity or a NaN among them
+      // (padding behind a mask) stays out of the sums, where 0 * inf would spoil the whole tile.
+      uint32_t seen = b.word;
+#pragma unroll
+      for (int off = 1; off < kTile; off <<= 1) seen |= __shfl_xor(seen, off, kWave);
+      if (b.full) seen = ~0u;
+      seen >>= 4 * h;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float v0 = vread[acc_row(r, 0) * kHeadDim];
-        const float v1 = vread[acc_row(r, 0) * kHeadDim + 32];
+        const bool used = (seen >> acc_row(r, 0)) & 1u;
+        const float v0 = used ? vread[acc_row(r, 0) * kHeadDim] : 0.f;
+        const float v1 = used ? vread[acc_row(r, 0) * kHeadDim + 32] : 0.f;
         st.o[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(v0, p[r], st.o[0], 0, 0, 0);
         st.o[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(v1, p[r], st.o[1], 0, 0, 0);
       }

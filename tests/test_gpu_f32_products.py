@@ -151,3 +151,45 @@ def test_one_large_channel(form, big, in_k):
     (O1, l1), (O2, l2) = _both(form, Q, K, V, d ** -0.5)
     assert (O1 - O2).abs().max().item() <= 2 * TOL["f32"]
     assert (l1 - l2).abs().max().item() <= 1e-4
+
+
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_values_nobody_attends(form, value):
+    """An infinite or undefined value in keys that no query of a 32-query tile attends leaves the tile alone,
+    also where the tile attends other keys of their block.  Explicit forms: a mask without the columns
+    from `first` on, which hold the value.  Window forms: the keys from `first` on hold it, and the
+    tiles out of their reach are compared."""
+    import torch
+    d, explicit, L, W = form
+    H = 2
+    Q, K, V = _form_qkv(form, H, 13)
+    V2 = V.clone()
+    if explicit:
+        rp, ci = sga.build_mask(MaskSpec(KIND_SLIDING, L, window=W))
+        first = (L - 1) // 32 * 32 - 21                 # inside a key block
+        row = torch.repeat_interleave(torch.arange(L, device="cuda:0"), rp[1:] - rp[:-1])
+        keep = ci < first
+        ci = ci[keep].contiguous()
+        rp = torch.zeros_like(rp)
+        rp[1:] = torch.bincount(row[keep], minlength=L).cumsum(0)
+        ws = sga.alloc_workspace(L, H, d, "f32", ci.numel())
+        run = lambda v: sga.attention_forward(Q, K, v, rp, ci, d ** -0.5, workspace=ws, path=sga.PATH_TILE)
+        V2[:, first:] = value
+        alone = torch.ones(L, dtype=torch.bool, device="cuda:0")
+    else:
+        spec = MaskSpec(KIND_SLIDING, L, window=W)
+        ws = sga.alloc_workspace(L, H, d, "f32", -1)
+        run = lambda v: sga.attention_forward_implicit(Q, K, v, spec, d ** -0.5, workspace=ws, path=sga.PATH_TILE)
+        # the first key past the reach of a tile in the middle (of the first tile, if the window is wider)
+        u0 = (max(W, L // 2) + 127) // 128 * 128
+        if u0 + 32 + W >= L:
+            u0 = 0
+        first = u0 + 32 + W
+        assert first < L
+        V2[:, first:] = value
+        alone = torch.arange(L, device="cuda:0") < u0 + 32
+    O0, O1 = run(V), run(V2)
+    assert alone.any()
+    assert torch.isfinite(O1[:, alone]).all()
+    assert (O1[:, alone] - O0[:, alone]).abs().max().item() <= TOL["f32"]
