@@ -83,11 +83,14 @@ __host__ __device__ inline int split_chunk(int64_t nnz, int32_t H) {
 }
 __host__ __device__ inline int seg_shift_min(int32_t dtype) { return dtype == SGA_F32 ? 12 : 15; }
 // fp32 masks that fill a sixteenth of the L x L pairs and more spread their edges over all blocks:
-// S is then the edges of about 64 blocks at that fill, and the call gets up to 4096 items.  (A
-// workgroup shares the key blocks of four items, so there are a quarter as many claims for 512
-// resident workgroups.  Uniformly random mask, a quarter of the pairs, L = 24,576: 1,317 us with 128
-// blocks per item, three rounds of workgroups where 2.25 would do; half of the pairs, L = 8,192:
+// S is then the edges of about 64 blocks at that fill, and less until the call has 4096 items.  (At
+// d = 64 a workgroup shares the key blocks of four items, so there are a quarter as many claims for
+// 512 resident workgroups.  Uniformly random mask, a quarter of the pairs, L = 24,576: 1,317 us with
+// 128 blocks per item, three rounds of workgroups where 2.25 would do; half of the pairs, L = 8,192:
 // too few claims for all CUs.)
+// The partial states of all segments must fit kMaxTilePartials, or every cut tile goes to the
+// per-row kernels: no shorter items where nnz / S, which bounds their number, would pass that.
+// (+-3,000, L = 65,536: 0.76 ms with S = 2^14; 31 ms with 2^13, whose partial states do not fit.)
 __host__ __device__ inline int seg_shift(int32_t dtype, int64_t nnz, int32_t H, int64_t L) {
   int sh = dtype == SGA_F32 ? 15 : 18;
   const int64_t e = (nnz < 0 ? 0 : nnz) * (int64_t)H;
@@ -95,7 +98,7 @@ __host__ __device__ inline int seg_shift(int32_t dtype, int64_t nnz, int32_t H, 
   if (dtype == SGA_F32 && nnz > 0 && nnz / L >= L / 16) {
     items = 4096;
     const int64_t per_row = 2 * (nnz / L);               // fill * 2 L: S = 2^15 at a fill of one half
-    for (int64_t half = L + L / 2; sh > 13 && 2 * per_row <= half; half >>= 1) --sh;
+    for (int64_t half = L + L / 2; sh > 13 && 2 * per_row <= half && (nnz >> (sh - 1)) <= kMaxTilePartials; half >>= 1) --sh;
   }
   while (sh > seg_shift_min(dtype) && (e >> sh) < items) --sh;
   return sh;

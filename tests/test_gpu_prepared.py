@@ -220,3 +220,22 @@ def test_implicit_forward_replays_from_a_hip_graph(spec, dtype):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(O, want[0]) and torch.equal(lse, want[1]), seed
+
+
+def test_dense_mask_stays_on_the_tiles():
+    """+-3,000 at L = 65,536 (384 million edges, every tile cut): the partial states of all segments fit, and
+    the prepared call agrees with the implicit one, which stores no graph and cuts nothing."""
+    import torch
+    L, W = 65536, 3000
+    spec = MaskSpec(KIND_SLIDING, L, window=W)
+    rp, ci = sga.build_mask(spec)
+    ws = sga.alloc_workspace(L, 1, 64, "f32", ci.numel())
+    plan = sga.graph_prepare(rp, ci, 1, 64, "f32", ws)
+    assert plan.multi_tiles > 0 and plan.tiles_left == 0
+    assert plan.flags & sga.GRAPH_TILES_COVER_ALL
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    Q, K, V = (torch.randn((1, L, 64), generator=g, device="cuda") for _ in range(3))
+    O = sga.attention_forward_prepared(Q, K, V, rp, ci, 0.125, plan, ws)
+    O2 = sga.attention_forward_implicit(Q, K, V, spec, 0.125)
+    assert (O - O2).abs().max().item() <= TOL["f32"]
