@@ -83,19 +83,21 @@ __host__ __device__ inline int split_chunk(int64_t nnz, int32_t H) {
 }
 __host__ __device__ inline int seg_shift_min(int32_t dtype) { return dtype == SGA_F32 ? 12 : 15; }
 // fp32 masks that fill a sixteenth of the L x L pairs and more spread their edges over all blocks:
-// S is then the edges of about 64 blocks at that fill, and less until the call has 4096 items.  (At
-// d = 64 a workgroup shares the key blocks of four items, so there are a quarter as many claims for
-// 512 resident workgroups.  Uniformly random mask, a quarter of the pairs, L = 24,576: 1,317 us with
-// 128 blocks per item, three rounds of workgroups where 2.25 would do; half of the pairs, L = 8,192:
-// too few claims for all CUs.)
+// at d = 64 and 128, S is then the edges of about 64 blocks at that fill, and less until the call has
+// 4096 items.  (At d = 64 a workgroup shares the key blocks of four items, so there are a quarter as
+// many claims for 512 resident workgroups.  Uniformly random mask, a quarter of the pairs, L = 24,576:
+// 1,317 us with 128 blocks per item, three rounds of workgroups where 2.25 would do; half of the
+// pairs, L = 8,192: too few claims for all CUs.  One workgroup per item, us without / with the rule:
+// d = 128, +-1,500, L = 16,384 390 / 327, four heads 863 / 910, random as above 2,840 / 2,645; d = 256,
+// +-600, L = 8,192 166 / 172, random, a quarter, L = 8,192 752 / 779.)
 // The partial states of all segments must fit kMaxTilePartials, or every cut tile goes to the
 // per-row kernels: no shorter items where nnz / S, which bounds their number, would pass that.
 // (+-3,000, L = 65,536: 0.76 ms with S = 2^14; 31 ms with 2^13, whose partial states do not fit.)
-__host__ __device__ inline int seg_shift(int32_t dtype, int64_t nnz, int32_t H, int64_t L) {
+__host__ __device__ inline int seg_shift(int32_t dtype, int64_t nnz, int32_t H, int64_t L, int32_t d) {
   int sh = dtype == SGA_F32 ? 15 : 18;
   const int64_t e = (nnz < 0 ? 0 : nnz) * (int64_t)H;
   int64_t items = dtype == SGA_F32 ? 1024 : 4096;
-  if (dtype == SGA_F32 && nnz > 0 && nnz / L >= L / 16) {
+  if (dtype == SGA_F32 && d <= 2 * kHeadDim && nnz > 0 && nnz / L >= L / 16) {
     items = 4096;
     const int64_t per_row = 2 * (nnz / L);               // fill * 2 L: S = 2^15 at a fill of one half
     for (int64_t half = L + L / 2; sh > 13 && 2 * per_row <= half && (nnz >> (sh - 1)) <= kMaxTilePartials; half >>= 1) --sh;
@@ -174,7 +176,7 @@ __host__ __device__ inline WorkspacePlan plan_workspace(int64_t L, int32_t H, in
                                                         int32_t dtype, int32_t d = kHeadDim,
                                                         int force_shift = -1) {
   WorkspacePlan p{};
-  p.seg_shift = force_shift >= 0 ? force_shift : seg_shift(dtype, nnz, H, L);
+  p.seg_shift = force_shift >= 0 ? force_shift : seg_shift(dtype, nnz, H, L, d);
   p.split_chunk = force_shift >= 0 ? kSplitChunkMin : split_chunk(nnz, H);
   size_t off = 256;   // counters
   const int64_t e = nnz < 0 ? 0 : nnz;

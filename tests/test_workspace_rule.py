@@ -58,3 +58,15 @@ def test_segments_of_dense_masks_fit_their_partial_states(plans):
             assert nnz >> shift <= cap, (L, nnz, H, d, shift, cap)
             fitted += nnz >> 15 > 8192
     assert fitted > 0
+
+
+def test_items_of_thin_and_of_half_precision_masks(plans):
+    """Masks below a sixteenth of the pairs, d = 256 and fp16: items are halved from 2^15 (2^18) edges until
+    a call has 1024 (4096) of them."""
+    for dtype, longest, shortest, items in ((0, 15, 12, 1024), (1, 18, 15, 4096)):
+        cases = [c for c in _grid(dtype) if dtype == 1 or c[4] == 256 or c[1] // c[0] < c[0] // 16]
+        for (L, nnz, H, _, d), (shift, _, _) in zip(cases, plans(cases)):
+            want = longest
+            while want > shortest and (nnz * H >> want) < items:
+                want -= 1
+            assert shift == want, (L, nnz, H, d, shift, want)
