@@ -82,26 +82,25 @@ __host__ __device__ inline int split_chunk(int64_t nnz, int32_t H) {
   return c;
 }
 __host__ __device__ inline int seg_shift_min(int32_t dtype) { return dtype == SGA_F32 ? 12 : 15; }
-// fp32 masks that fill a sixteenth of the L x L pairs and more spread their edges over all blocks:
-// at d = 64 and 128, S is then the edges of about 64 blocks at that fill, and less until the call has
-// 4096 items.  (At d = 64 a workgroup shares the key blocks of four items, so there are a quarter as
-// many claims for 512 resident workgroups.  Uniformly random mask, a quarter of the pairs, L = 24,576:
-// 1,317 us with 128 blocks per item, three rounds of workgroups where 2.25 would do; half of the
-// pairs, L = 8,192: too few claims for all CUs.  One workgroup per item, us without / with the rule:
-// d = 128, +-1,500, L = 16,384 390 / 327, four heads 863 / 910, random as above 2,840 / 2,645; d = 256,
-// +-600, L = 8,192 166 / 172, random, a quarter, L = 8,192 752 / 779.)
-// The partial states of all segments must fit kMaxTilePartials, or every cut tile goes to the
-// per-row kernels: no shorter items where nnz / S, which bounds their number, would pass that.
-// (+-3,000, L = 65,536: 0.76 ms with S = 2^14; 31 ms with 2^13, whose partial states do not fit.)
+// fp32 masks that fill a sixteenth of the L x L pairs and more, at d = 64 and 128: 2^14 instead of 2^15
+// edges where the average tile is cut at 2^15 already (2^16 edges) and the call has 1024 to 8191
+// such items, so that 512 (d = 64: for four items each) to 1024 resident workgroups come out even.
+// Nothing shorter, and no tile cut for this: the blocks of a random mask are as thin as its
+// fill, but those of a band or of block masks are full, and an item of 2^13 edges is then eight of
+// them and one partial state.  8192 items also bound the partial states, far below
+// kMaxTilePartials (beyond which every cut tile would go to the per-row kernels).
+// (us, 2^15 / 2^14 (/ 2^13): random, a quarter, L = 24,576 982 / 895; half, L = 12,000 356 / 280; a
+// quarter, L = 24,576, d = 128 2,840 / 2,675; +-1,500, L = 20,000 199 / 166 / 170, L = 16,384, d = 128
+// 390 / 320 / 327.  Outside the rule: +-1,000, L = 20,000, two heads 179 / 241 / 235, eight heads
+// 499 / 827 / 910; +-3,000, L = 65,536 720 / 757 / 31,000 (no room for the partial states); 64-token
+// blocks, 5 to 8 per row, L = 11,072, eight heads 139 / - / 311; d = 256, +-600, L = 8,192 166 / - / 172.)
 __host__ __device__ inline int seg_shift(int32_t dtype, int64_t nnz, int32_t H, int64_t L, int32_t d) {
   int sh = dtype == SGA_F32 ? 15 : 18;
   const int64_t e = (nnz < 0 ? 0 : nnz) * (int64_t)H;
-  int64_t items = dtype == SGA_F32 ? 1024 : 4096;
-  if (dtype == SGA_F32 && d <= 2 * kHeadDim && nnz > 0 && nnz / L >= L / 16) {
-    items = 4096;
-    const int64_t per_row = 2 * (nnz / L);               // fill * 2 L: S = 2^15 at a fill of one half
-    for (int64_t half = L + L / 2; sh > 13 && 2 * per_row <= half && (nnz >> (sh - 1)) <= kMaxTilePartials; half >>= 1) --sh;
-  }
+  const int64_t items = dtype == SGA_F32 ? 1024 : 4096;
+  if (dtype == SGA_F32 && d <= 2 * kHeadDim && nnz > 0 && nnz / L >= L / 16 && nnz / L * kTile >= int64_t(1) << 16 &&
+      (e >> 15) >= 1024 && (e >> 15) < 8192)
+    sh = 14;
   while (sh > seg_shift_min(dtype) && (e >> sh) < items) --sh;
   return sh;
 }

@@ -60,13 +60,21 @@ def test_segments_of_dense_masks_fit_their_partial_states(plans):
     assert fitted > 0
 
 
-def test_items_of_thin_and_of_half_precision_masks(plans):
-    """Masks below a sixteenth of the pairs, d = 256 and fp16: items are halved from 2^15 (2^18) edges until
-    a call has 1024 (4096) of them."""
+def test_items_are_shortened_only_where_tiles_are_cut(plans):
+    """Items are halved from 2^15 (fp16: 2^18) edges until a call has 1024 (4096) of them.  The only shorter
+    ones are 2^14 edges, fp32, d = 64 and 128, in masks of a sixteenth of the pairs whose average tile has
+    two segments at 2^15 already, in calls of fewer than 8192 items: a band or a block mask would be cut into
+    segments of a few full blocks otherwise."""
+    shorter = 0
     for dtype, longest, shortest, items in ((0, 15, 12, 1024), (1, 18, 15, 4096)):
-        cases = [c for c in _grid(dtype) if dtype == 1 or c[4] == 256 or c[1] // c[0] < c[0] // 16]
+        cases = list(_grid(dtype))
         for (L, nnz, H, _, d), (shift, _, _) in zip(cases, plans(cases)):
             want = longest
             while want > shortest and (nnz * H >> want) < items:
                 want -= 1
-            assert shift == want, (L, nnz, H, d, shift, want)
+            if shift == want:
+                continue
+            assert (dtype, want, shift) == (0, 15, 14) and d <= 128, (L, nnz, H, d, shift, want)
+            assert 32 * nnz >= L << 16 and 16 * nnz >= L * (L - 15) and nnz * H < 8192 << 15, (L, nnz, H, d)
+            shorter += 1
+    assert shorter > 0
