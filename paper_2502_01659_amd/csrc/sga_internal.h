@@ -82,25 +82,30 @@ __host__ __device__ inline int split_chunk(int64_t nnz, int32_t H) {
   return c;
 }
 __host__ __device__ inline int seg_shift_min(int32_t dtype) { return dtype == SGA_F32 ? 12 : 15; }
-// fp32 masks that fill a sixteenth of the L x L pairs and more, at d = 64 and 128: 2^14 instead of 2^15
-// edges where the average tile is cut at 2^15 already (2^16 edges) and the call has 1024 to 8191
-// such items, so that 512 (d = 64: for four items each) to 1024 resident workgroups come out even.
-// Nothing shorter, and no tile cut for this: the blocks of a random mask are as thin as its
-// fill, but those of a band or of block masks are full, and an item of 2^13 edges is then eight of
-// them and one partial state.  8192 items also bound the partial states, far below
-// kMaxTilePartials (beyond which every cut tile would go to the per-row kernels).
-// (us, 2^15 / 2^14 (/ 2^13): random, a quarter, L = 24,576 982 / 895; half, L = 12,000 356 / 280; a
-// quarter, L = 24,576, d = 128 2,840 / 2,675; +-1,500, L = 20,000 199 / 166 / 170, L = 16,384, d = 128
-// 390 / 320 / 327.  Outside the rule: +-1,000, L = 20,000, two heads 179 / 241 / 235, eight heads
-// 499 / 827 / 910; +-3,000, L = 65,536 720 / 757 / 31,000 (no room for the partial states); 64-token
-// blocks, 5 to 8 per row, L = 11,072, eight heads 139 / - / 311; d = 256, +-600, L = 8,192 166 / - / 172.)
+// fp32 masks that fill a sixteenth of the L x L pairs and more, at d = 64 and 128, whose average tile is
+// cut at 2^15 already (kTwiceCutEdges): 2^14 where that makes fewer than 16,384 items, 2^13 where 2^14
+// makes fewer than 4096, so that the 512 (d = 64: for four items each) to 1024 resident workgroups
+// come out even.  No tile is cut for this: the blocks of a random mask are as thin as its fill, but those
+// of a band or of block masks are full, and an item of 2^13 edges is then eight of them and one
+// partial state.  16,384 items also bound the partial states, far below kMaxTilePartials (beyond
+// which every cut tile would go to the per-row kernels).
+// (us, 2^15 / 2^14 / 2^13, prepared, one head where not said.  Inside: random, a quarter, L = 24,576
+// 982 / 895 / -, L = 10,972 394 / 330 / 260; half, L = 12,000 356 / 280 / 292; a fifth, L = 14,000
+// 522 / 448 / 377; +-4,000, L = 9,000 373 / 383 / 250, d = 128 644 / 708 / 582; +-1,100, L = 14,000
+// 186 / 139 / 116; +-2,000, L = 16,000, two heads 289 / 270 / 321; against it +-2,000, L = 9,000
+// 175 / 216 / 240.  Outside: +-1,000, L = 20,000, two heads 179 / 241 / 235, eight heads 499 / 827 / 910;
+// +-3,000, L = 65,536 720 / 757 / 31,000 (no room for the partial states); 64-token blocks, 5 to 8 per
+// row, L = 11,072, eight heads 139 / - / 311; d = 256, +-600, L = 8,192 166 / - / 172.)
+// kTwiceCutEdges is 2^16 less a margin for masks of random rows, whose tiles fall on both sides of their
+// average (a quarter of the pairs, L = 8,192, four heads, uncut / cut 613 / 468).
+constexpr int64_t kTwiceCutEdges = 65024;
 __host__ __device__ inline int seg_shift(int32_t dtype, int64_t nnz, int32_t H, int64_t L, int32_t d) {
   int sh = dtype == SGA_F32 ? 15 : 18;
   const int64_t e = (nnz < 0 ? 0 : nnz) * (int64_t)H;
   const int64_t items = dtype == SGA_F32 ? 1024 : 4096;
-  if (dtype == SGA_F32 && d <= 2 * kHeadDim && nnz > 0 && nnz / L >= L / 16 && nnz / L * kTile >= int64_t(1) << 16 &&
-      (e >> 15) >= 1024 && (e >> 15) < 8192)
-    sh = 14;
+  if (dtype == SGA_F32 && d <= 2 * kHeadDim && nnz > 0 && nnz / L >= L / 16 && nnz / L * kTile >= kTwiceCutEdges &&
+      (e >> 14) < 16384)
+    sh = (e >> 14) < 4096 ? 13 : 14;
   while (sh > seg_shift_min(dtype) && (e >> sh) < items) --sh;
   return sh;
 }

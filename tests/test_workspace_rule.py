@@ -61,11 +61,11 @@ def test_segments_of_dense_masks_fit_their_partial_states(plans):
 
 
 def test_items_are_shortened_only_where_tiles_are_cut(plans):
-    """Items are halved from 2^15 (fp16: 2^18) edges until a call has 1024 (4096) of them.  The only shorter
-    ones are 2^14 edges, fp32, d = 64 and 128, in masks of a sixteenth of the pairs whose average tile has
-    two segments at 2^15 already, in calls of fewer than 8192 items: a band or a block mask would be cut into
-    segments of a few full blocks otherwise."""
-    shorter = 0
+    """Items are halved from 2^15 (fp16: 2^18) edges until a call has 1024 (4096) of them.  Shorter ones, 2^14
+    or 2^13 edges, are taken only with fp32, d = 64 and 128, in masks of a sixteenth of the pairs whose average
+    tile has two segments at 2^15 already, and only until a call has 16,384 (4096 before the last halving): a
+    band or a block mask would be cut into segments of a few full blocks otherwise."""
+    shorter = set()
     for dtype, longest, shortest, items in ((0, 15, 12, 1024), (1, 18, 15, 4096)):
         cases = list(_grid(dtype))
         for (L, nnz, H, _, d), (shift, _, _) in zip(cases, plans(cases)):
@@ -74,7 +74,8 @@ def test_items_are_shortened_only_where_tiles_are_cut(plans):
                 want -= 1
             if shift == want:
                 continue
-            assert (dtype, want, shift) == (0, 15, 14) and d <= 128, (L, nnz, H, d, shift, want)
-            assert 32 * nnz >= L << 16 and 16 * nnz >= L * (L - 15) and nnz * H < 8192 << 15, (L, nnz, H, d)
-            shorter += 1
-    assert shorter > 0
+            assert dtype == 0 and d <= 128 and 13 <= shift < want, (L, nnz, H, d, shift, want)
+            assert 32 * nnz >= 65024 * L and 16 * nnz >= L * (L - 15), (L, nnz, H, d)
+            assert nnz * H >> (shift + 1) < (8192 if shift == 14 else 4096), (L, nnz, H, d, shift)
+            shorter.add(shift)
+    assert shorter == {13, 14}
