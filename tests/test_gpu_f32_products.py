@@ -3,21 +3,52 @@ are the ones where a split can go wrong: rows of very different magnitude in one
 of very different magnitude in one row, values near the ends of the fp32 range, huge values in keys
 that a query does not attend, and infinities.  The per-row kernels, which use fp32 arithmetic throughout,
 are the reference; each of them is compared with the oracle in test_gpu_attention.py."""
+import os
+import re
+
 import pytest
 
 import paper_2502_01659_amd as sga
-from sga_inputs import MaskSpec, KIND_SLIDING, torch_qkv
+from sga_inputs import MaskSpec, KIND_SLIDING, KIND_NONLOCAL, torch_qkv
 from gpu_util import TOL
 
 pytestmark = pytest.mark.gpu
 
-# (head dimension, explicit CSR, length, window): window tiles of a small call and of one whose
-# workgroups share their key blocks (cut into ranges: 3,333 and 30,001); work items claimed one by one,
-# in fours on lists of their own and in fours on merged lists; wide tiles; ragged lengths, windows
-# inside one key block and of many blocks
-FORMS = [(64, False, 333, 20), (64, False, 3333, 3000), (64, False, 30001, 700), (64, False, 140003, 70),
+# (head dimension, explicit CSR, length, window), run with H heads: window tiles of a small call and of
+# one whose workgroups share their key blocks (cut into ranges: 3,333 and 15,001); work items claimed one
+# by one, in fours on lists of their own and in fours on merged lists; wide tiles; ragged lengths,
+# windows inside one key block and of many blocks
+H = 2
+FORMS = [(64, False, 333, 20), (64, False, 3333, 3000), (64, False, 30001, 700), (64, False, 15001, 1500),
+         (64, False, 140003, 70),
          (64, True, 333, 20), (64, True, 4100, 300), (64, True, 16421, 20), (64, True, 40003, 250),
          (128, False, 333, 40), (256, True, 300, 20)]
+
+
+# the route of the d = 64 forms: (explicit, claims in fours, key blocks shared by a workgroup)
+ROUTES = [(False, None, False), (False, None, False), (False, None, True), (False, None, True), (False, None, True),
+          (True, False, None), (True, False, None), (True, True, False), (True, True, True)]
+
+
+def test_forms_take_the_routes_they_are_for():
+    """The lines of the dispatch as the kernels' source states them, against the sizes of FORMS: a line that
+    moves must not leave a kernel untested."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    source = open(os.path.join(root, "paper_2502_01659_amd", "csrc", "attention_tile.hip")).read()
+    line = {n: int(re.search(r"constexpr int64_t %s = (\d+);" % n, source).group(1)) for n in ("kSharedSteps", "kSharedClaims")}
+    for (d, explicit, L, W), (is_explicit, fours, shared) in zip(FORMS, ROUTES):
+        assert d == 64 and explicit == is_explicit
+        tiles = (L + 31) // 32
+        if explicit:                    # (no tile of these windows is cut into segments)
+            claims = (tiles + 3) // 4 * H
+            blocks = 2 * W // 32 + 1    # of a tile's list, at least
+            assert (claims >= line["kSharedClaims"]) == fours
+            if fours:
+                assert (claims * blocks >= line["kSharedSteps"]) == shared
+                assert shared or claims * (blocks + 3) < line["kSharedSteps"]
+        else:
+            steps = (L + 127) // 128 * H * min((127 + 2 * W) // 32 + 1, tiles)
+            assert (steps >= line["kSharedSteps"]) == shared
 
 
 def _both(form, Q, K, V, scale):
@@ -41,10 +72,10 @@ def test_rows_of_different_magnitude(form, q_exp, k_exp, v_exp):
     rounds at their size), raised by the size of the scores, which round at 2^-24 of themselves."""
     import torch
     d, _, L, _ = form
-    Q, K, V = torch_qkv(2, L, d, "f32", 1.0, 5, "cuda:0")
+    Q, K, V = torch_qkv(H, L, d, "f32", 1.0, 5, "cuda:0")
     g = torch.Generator(device="cuda:0")
     g.manual_seed(9)
-    per_key = torch.randint(-12, 3, (2, L, 1), generator=g, device="cuda:0").float()
+    per_key = torch.randint(-12, 3, (H, L, 1), generator=g, device="cuda:0").float()
     Q = Q * 2.0 ** q_exp
     K = K * torch.exp2(per_key + k_exp)
     V = V * 2.0 ** v_exp
@@ -62,7 +93,7 @@ def test_huge_keys_outside_the_mask(form, huge):
     that count: its size must not reach them."""
     import torch
     d, _, L, W = form
-    Q, K, V = torch_qkv(1, L, d, "f32", 1.0, 6, "cuda:0")
+    Q, K, V = torch_qkv(H, L, d, "f32", 1.0, 6, "cuda:0")
     O0, _ = _both(form, Q, K, V, d ** -0.5)[0]
     K2 = K.clone()
     j = 5
@@ -79,7 +110,7 @@ def test_minus_infinity_scores_weigh_nothing(form):
     kernels."""
     import torch
     d, _, L, _ = form
-    Q, K, V = torch_qkv(1, L, d, "f32", 1.0, 7, "cuda:0")
+    Q, K, V = torch_qkv(H, L, d, "f32", 1.0, 7, "cuda:0")
     Q[:, :, 3] = Q[:, :, 3].abs() + 0.25
     K[:, ::7, 3] = -float("inf")
     (O1, l1), (O2, l2) = _both(form, Q, K, V, d ** -0.5)
@@ -115,7 +146,7 @@ def test_tiles_cut_alike(L, density, H):
         assert torch.equal(O3, O1)
 
 
-def _form_qkv(form, H, seed):
+def _form_qkv(form, seed):
     d, _, L, _ = form
     return torch_qkv(H, L, d, "f32", 1.0, seed, "cuda:0")
 
@@ -127,7 +158,7 @@ def test_scores_of_one_sign(form, q_exp, k_exp):
     are equal, no weight may vanish, and O is the mean of the attended V."""
     import torch
     d = form[0]
-    Q, K, V = _form_qkv(form, 2, 11)
+    Q, K, V = _form_qkv(form, 11)
     Q = torch.full_like(Q, 2.0 ** q_exp)
     K = torch.full_like(K, -2.0 ** k_exp)
     (O1, l1), (O2, l2) = _both(form, Q, K, V, d ** -0.5)
@@ -144,7 +175,7 @@ def test_one_large_channel(form, big, in_k):
     that is smaller by the same factor: all channels count alike in the scores."""
     import torch
     d = form[0]
-    Q, K, V = _form_qkv(form, 2, 12)
+    Q, K, V = _form_qkv(form, 12)
     large, small = (K, Q) if in_k else (Q, K)
     large[:, :, 3] *= big
     small[:, :, 3] /= big
@@ -162,8 +193,7 @@ def test_values_nobody_attends(form, value):
     tiles out of their reach are compared."""
     import torch
     d, explicit, L, W = form
-    H = 2
-    Q, K, V = _form_qkv(form, H, 13)
+    Q, K, V = _form_qkv(form, 13)
     V2 = V.clone()
     if explicit:
         rp, ci = sga.build_mask(MaskSpec(KIND_SLIDING, L, window=W))
@@ -193,3 +223,25 @@ def test_values_nobody_attends(form, value):
     assert alone.any()
     assert torch.isfinite(O1[:, alone]).all()
     assert (O1[:, alone] - O0[:, alone]).abs().max().item() <= TOL["f32"]
+
+
+@pytest.mark.parametrize("d,L,g", [(64, 3001, 16), (64, 9000, 64), (128, 700, 5)])
+@pytest.mark.parametrize("case", ["one_sign", "large_channel"])
+def test_nonlocal_mask(d, L, g, case):
+    """The same inputs on the kernels of the implicit non-local mask."""
+    import torch
+    Q, K, V = torch_qkv(H, L, d, "f32", 1.0, 14, "cuda:0")
+    if case == "one_sign":
+        Q = torch.full_like(Q, 2.0 ** -100)
+        K = torch.full_like(K, -2.0 ** 112)
+    else:
+        K[:, :, 3] *= 1e8
+        Q[:, :, 3] /= 1e8
+    spec = MaskSpec(KIND_NONLOCAL, L, window=40, n_global=g)
+    ws = sga.alloc_workspace(L, H, d, "f32", -1)
+    (O1, l1), (O2, l2) = [sga.attention_forward_implicit(Q, K, V, spec, d ** -0.5, workspace=ws, path=p, want_lse=True)
+                          for p in (sga.PATH_TILE, sga.PATH_GATHER)]
+    some = torch.isfinite(l2)
+    assert some.any() and torch.equal(some, torch.isfinite(l1))
+    assert ((l1 - l2).abs() <= 1e-4 + 2.0 ** -22 * l2.abs())[some].all()
+    assert (O1 - O2).abs().max().item() <= 2 * TOL["f32"]
