@@ -331,7 +331,7 @@ __device__ __forceinline__ bool row_done_by_tiles(const int64_t* row_ptr, int64_
                                                   size_t ws_bytes, int64_t i) {
   const WorkspacePlan pl = plan_workspace(L, H, row_ptr[L], dtype, d);
   if (pl.total_bytes > ws_bytes) return false;
-  return tile_handled(pl, ws, row_ptr, L, dtype, i / kTile);
+  return tile_handled(pl, ws, row_ptr, L, i / kTile);
 }
 
 // (wg of n_wg: this workgroup's place among those that share the rows of a head)

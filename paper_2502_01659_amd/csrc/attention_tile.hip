@@ -636,7 +636,7 @@ __device__ __forceinline__ floatx16 split_scores(const SplitOperand (&k)[4], con
 // No branch here: skipping the halves of a masked block that no query attends made two versions
 // of this code, whose registers cost more than the products saved (247 -> 331 us at +-128).
 template <typename Value>
-__device__ __forceinline__ void weigh_values(const float (&p)[16], const BlockInfo& b, TileState& st, Value value) {
+__device__ __forceinline__ void weigh_values(const float (&p)[16], TileState& st, Value value) {
   SplitOperand pb[2];
   pb[0].split(p);
   pb[1].split(p + 8);
@@ -724,10 +724,9 @@ struct CoreF32T {
 
   // O^T += V_blk^T P^T with the V rows of the block staged (complete) at ldsv.  A operand:
   // V^T[channel cb*32+n][key acc_row(r,h)] = staged V[key][channel], 8 keys per operand.
-  __device__ static void weigh_v(const float (&p)[16], const BlockInfo& b, int n, int h, TileState& st,
-                                 const char* ldsv) {
+  __device__ static void weigh_v(const float (&p)[16], int n, int h, TileState& st, const char* ldsv) {
     const float* vread = reinterpret_cast<const float*>(ldsv) + h * 4 * kHeadDim + n;
-    weigh_values(p, b, st, [&](int u, int cb) {
+    weigh_values(p, st, [&](int u, int cb) {
       float v[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] = vread[acc_row(8 * u + e, 0) * kHeadDim + cb * 32];
@@ -768,7 +767,7 @@ struct CoreF32T {
       softmax_block(s, c, b, h, st, p);
       wait_staged_v<kFragLoads>(more);   // V block k is older than the K fragment loads (if any)
       __builtin_amdgcn_wave_barrier();
-      weigh_v(p, b, n, h, st, lds);
+      weigh_v(p, n, h, st, lds);
       b = b1;
     }
   }
@@ -815,7 +814,7 @@ struct CoreF32T {
       softmax_block(s, c, b, h, st, p);
       wait_staged_v<kFragLoads>(more);   // V block k is older than the K fragment loads (if any)
       __builtin_amdgcn_wave_barrier();
-      weigh_v(p, b, n, h, st, lds);
+      weigh_v(p, n, h, st, lds);
       b = b1;
       b1 = b2;
     }
@@ -938,7 +937,7 @@ struct CoreF16T {
 
   // kf[s] = K[key n][h*32 + 8s .. +7] out of the staged block: keys 8i..8i+7 per copy, 8 lanes
   // per 128-byte row, the eight 16-byte chunks of a row XOR-swizzled with the row index (see
-  // CoreF32::read_k) so that these reads are free of bank conflicts.
+  // CoreSplit::read_k) so that these reads are free of bank conflicts.
   __device__ static void read_k(const char* ldsk, int n, int h, half8 (&kf)[4]) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
@@ -1006,7 +1005,10 @@ struct CoreF16T {
         st.o[cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(read_va(vt, u, cb), ph[u], st.o[cb], 0, 0, 0);
   }
 
-  // Same pipeline as CoreF32::run_ldsk.
+  // K and V blocks travel global -> LDS without registers, as whole rows (coalesced).  Per block k:
+  // the V copy is issued first; the K fragment (copied during block k-1) is read into registers and the K
+  // copy of block k+1 is issued at once, so it lands behind the matrix work of block k; block ids / mask
+  // words are fetched two blocks ahead.
   template <typename Src>
   __device__ void run_ldsk(const __half* __restrict__ Kh, const __half* __restrict__ Vh, const Src& src,
                       int k0, int k1, float c, int lane, TileState& st, char* lds) {
@@ -1210,12 +1212,12 @@ using CoreF16 = CoreF16T<kHeadDim>;
 // exact in fp32), and a product a.b is evaluated as hi_a.hi_b + hi_a.lo_b + lo_a.hi_b on the
 // fp16 matrix cores, all three terms into the same fp32 accumulator.  The dropped term
 // lo_a.lo_b and the rounding of lo are below 2^-22 |a.b|, the size of an fp32 rounding error,
-// so results match the true-fp32 kernels to their tolerance while the matrix work drops from
-// 64 fp32 MFMAs (4096 cycles) to 24 fp16 MFMAs (768 cycles) per block.  lo is a subnormal fp16
+// so results match the kernels that hold every bit of the operands (CoreF32T: 48 matrix instructions
+// per block) to their tolerance, with 24 (768 cycles).  lo is a subnormal fp16
 // number for |x| < 0.25 (the matrix cores do not flush them); below |x| ~ 2^-13 it loses bits,
 // an absolute error of at most 2^-25 per operand.  Inputs must lie inside the fp16 range
 // (|x| < 65504); the caller opts in (SGA_PATH_TILE_SPLIT).
-// K and V blocks travel global -> LDS as raw fp32 (as in CoreF32::run_ldsk); K is split when
+// K and V blocks travel global -> LDS as raw fp32 (as in CoreF16T::run_ldsk); K is split when
 // its fragment is read, V is split in registers and written back over its own staged block as
 // two row-major fp16 blocks, which the PV products read with the LDS transpose read.
 struct CoreSplit {
@@ -2388,7 +2390,7 @@ struct SharedBlock {
     float p[16];
     softmax_block(s, c, b, h, st, p);
     const char* vt = CoreF16::vt_base(planes + kValues, lane, h);
-    weigh_values(p, b, st, [&](int u, int cb) {
+    weigh_values(p, st, [&](int u, int cb) {
       SplitOperand va;
       va.hi = __builtin_bit_cast(bf16x8, CoreF16::read_va(vt, u, cb));
       va.mid = __builtin_bit_cast(bf16x8, CoreF16::read_va(vt + kPlane, u, cb));

@@ -325,8 +325,7 @@ __device__ __forceinline__ int32_t tile_segments(const int64_t* __restrict__ row
 // True when the tile path of this call produces the rows of tile t: its block lists fitted
 // their slots and, if it is a multi-segment tile, the call's partial states fitted theirs.
 __device__ __forceinline__ bool tile_handled(const WorkspacePlan& pl, const void* ws,
-                                             const int64_t* __restrict__ row_ptr, int64_t L,
-                                             int32_t dtype, int64_t t) {
+                                             const int64_t* __restrict__ row_ptr, int64_t L, int64_t t) {
   const char* base = static_cast<const char*>(ws);
   if (reinterpret_cast<const int32_t*>(base + pl.off_tile_bad)[t] != 0) return false;
   if (tile_segments(row_ptr, L, pl.seg_shift, t) == 1) return true;
@@ -347,7 +346,7 @@ __device__ __forceinline__ void split_prepass_row(const int64_t* __restrict__ ro
   if (deg <= kSplitThreshold / 2) return;           // (no rule splits a row this short)
   const WorkspacePlan pl = plan_workspace(L, H, row_ptr[L], dtype, d);
   if (pl.total_bytes > ws_bytes || !row_is_split(deg, pl)) return;
-  if (skip_tiled && (tiles_cover_everything(pl, ws) || tile_handled(pl, ws, row_ptr, L, dtype, i / kTile)))
+  if (skip_tiled && (tiles_cover_everything(pl, ws) || tile_handled(pl, ws, row_ptr, L, i / kTile)))
     return;
   uint32_t* ctr = reinterpret_cast<uint32_t*>(ws);
   int32_t n, len, nf, lenf;
