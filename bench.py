@@ -23,6 +23,10 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBPS = 8000.0          # MI355X HBM3E
 MFMA_F32_PEAK_TFLOPS = 157.3    # dense fp32 MFMA
+# fp32 products as six bf16 products each (2.5 PFLOP/s dense), and the kernels that take them so
+MFMA_F32_SIX_TERM_PEAK_TFLOPS = 2500.0 / 6
+SIX_TERM_KERNELS = ("tile_attend_f32_kernel", "tile_window_f32_kernel", "tile_window_kernel", "tile_attend_wide_kernel",
+                    "tile_window_wide_kernel", "tile_nonlocal_kernel", "tile_nonlocal_cols_wide_kernel")
 ALU_F32_PEAK_TFLOPS = 78.6      # 256 CUs x 4 SIMDs x 16 lanes x 2 flop x 2.4 GHz (unpacked fp32 FMA)
 kWarmSeconds = 0.05             # minimum untimed warm-up under load before the timed steps
 FLOPS_PER_EDGE = 256            # 2d (q.k) + 2d (p*v accumulate), d = 64
@@ -35,15 +39,15 @@ DEFAULT_WORKLOAD = "cfg5_sliding_160m"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 
 
-def measured_traffic(name, prepared=False):
+def measured_traffic(name, prepared=False, kernel=None):
     """-> (bytes of the dominant kernel per launch, bytes of all kernels of one forward), or
-    (None, None) where no counter run is on file."""
+    (None, None) where no counter run is on file, or the one on file is of another kernel."""
     try:
         with open(TRAFFIC_FILE) as f:
             rec = json.load(f).get(name + ("/prepared" if prepared else ""))
     except (OSError, ValueError):
         rec = None
-    if not rec:
+    if not rec or (kernel and rec.get("dominant_kernel", "").split("<")[0] != kernel):
         return None, None
     return rec.get("dominant_kernel_bytes"), rec.get("forward_bytes")
 
@@ -233,7 +237,8 @@ def roofline_of(wl, nnz, kern_ms, fwd_ms, path_used, kernel, prepared=False):
     Dominant kernel: `achieved` counts only what that kernel touches -- for fp16 storage the
     tensor bytes (Q, K, V read once, O written once; the tile kernel of an explicit mask reads
     the tile graph, not col_idx, so no index bytes are counted for it), for fp32 storage the
-    256 flops per edge.  Forward level (`forward`): the algorithmic bytes of the call (tensor
+    256 flops per edge, against the rate at which the matrix cores can do fp32 products the way the
+    kernel does them.  Forward level (`forward`): the algorithmic bytes of the call (tensor
     bytes plus, for an unprepared explicit call, 4 B per edge of col_idx and 8 B per row of
     row_ptr) and the same flops, over the duration of the whole call."""
     edges = nnz * wl.H
@@ -245,7 +250,8 @@ def roofline_of(wl, nnz, kern_ms, fwd_ms, path_used, kernel, prepared=False):
     kbytes = tensor_bytes(wl)
     fbytes = kbytes if prepared else algorithmic_bytes(wl, nnz)
     if wl.dtype == "f32" and not split:
-        bound, peak = ("alu", ALU_F32_PEAK_TFLOPS) if path_used == "gather" else ("mfma", MFMA_F32_PEAK_TFLOPS)
+        bound, peak = ("alu", ALU_F32_PEAK_TFLOPS) if path_used == "gather" else \
+            ("mfma", MFMA_F32_SIX_TERM_PEAK_TFLOPS if kernel in SIX_TERM_KERNELS else MFMA_F32_PEAK_TFLOPS)
         ach, ach_f, unit = flops / t / 1e12, flops / tf / 1e12, "TFLOP/s"
     else:
         # fp16 storage, and fp32 storage on the split-precision path (three fp16 matrix-core
@@ -253,7 +259,7 @@ def roofline_of(wl, nnz, kern_ms, fwd_ms, path_used, kernel, prepared=False):
         # 77 us the compulsory bytes take): bound by HBM
         bound, peak, unit = "hbm", HBM_PEAK_GBPS, "GB/s"
         ach, ach_f = kbytes / t / 1e9, fbytes / tf / 1e9
-    traffic_kernel, traffic_forward = measured_traffic(wl.name, prepared)
+    traffic_kernel, traffic_forward = measured_traffic(wl.name, prepared, kernel)
     return {"bound": bound, "achieved": ach, "peak": peak, "unit": unit, "frac": ach / peak,
             "traffic": traffic_kernel,
             "kernel": kernel, "kernel_ms": kern_ms,
@@ -846,7 +852,7 @@ def main():
         w2 = WORKLOADS["cfg2_longformer_64k"]
         if args.path == "auto":
             # workload 2 through the opt-in split-precision path (fp32 storage, three fp16
-            # matrix-core products per product): reported beside the true-fp32 figures, never as them
+            # matrix-core products per product): reported beside the default path's figures, never as them
             try:
                 r = Runner(w2, 3)
                 ms, f, b, km = r.timed(20, 5)

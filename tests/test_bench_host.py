@@ -107,3 +107,18 @@ def test_traffic_summary_from_counter_files(tmp_path, monkeypatch):
     assert rec["forward_bytes"] == int(1100 * 1024 * 2.0 + 60 * 1024)
     assert bench.measured_traffic("cfg4_bigbird_1m") == (rec["dominant_kernel_bytes"], rec["forward_bytes"])
     assert bench.measured_traffic("cfg4_bigbird_1m", prepared=True) == (None, None)
+
+
+def test_fp32_tiles_are_priced_by_the_products_they_issue(tmp_path, monkeypatch):
+    """Six bf16 products per fp32 product; recorded traffic of another kernel is not reported."""
+    import json
+    wl = WORKLOADS["cfg2_longformer_64k"]
+    nnz = sga.mask_nnz(wl.mask)
+    (tmp_path / "t.json").write_text(json.dumps({wl.name: {"dominant_kernel": "tile_attend_f32_kernel<float>",
+                                                           "dominant_kernel_bytes": 5, "forward_bytes": 7}}))
+    monkeypatch.setattr(bench, "TRAFFIC_FILE", str(tmp_path / "t.json"))
+    r = bench.roofline_of(wl, nnz, 0.5, 0.6, "auto", "tile_attend_f32_kernel")
+    assert r["bound"] == "mfma" and abs(r["peak"] - 2500 / 6) < 1e-9
+    assert r["traffic"] == 5 and r["forward"]["traffic"] == 7
+    r = bench.roofline_of(wl, nnz, 0.5, 0.6, "gather", "gather_csr_kernel")
+    assert r["bound"] == "alu" and r["traffic"] is None and r["forward"]["traffic"] is None
