@@ -21,7 +21,7 @@
 //
 // fp32 storage splits its operands into 16-bit parts whose products the 16-bit matrix cores sum
 // in fp32 (see SplitOperand; v_mfma_f32_32x32x2_f32 only where a tile holds an
-// infinity), fp16 storage uses v_mfma_f32_32x32x16_f16 with fp32 accumulation; P is rounded
+// infinity or numbers near the smallest), fp16 storage uses v_mfma_f32_32x32x16_f16 with fp32 accumulation; P is rounded
 // to fp16 only as the MFMA operand, l is summed in fp32.
 //
 // Tiles with many edges (global-token rows) are cut into segments of their key-block span;
@@ -649,27 +649,33 @@ __device__ __forceinline__ void weigh_values(const float (&p)[16], TileState& st
   }
 }
 
-// True in a lane whose state holds an infinity or a NaN.
-__device__ __forceinline__ bool not_finite(const TileState& st) {
-  float z = st.l * 0.f;
+// Inputs whose split is not exact: an infinity or a finite value that rounds to an infinite bf16 (from
+// 3.39e38), whose parts are no numbers, and values below 2^-109, whose low parts fall below the subnormal
+// numbers of bf16 (an error of 2^-134: it counts in the scores where the other operand is that large, and
+// in O where all values are that small).  A tile that may have met one is computed once more with
+// fp32 products (run_exact), which decide what such inputs give.  All of this is seen per tile, not
+// per block: in the state a tile ends with, and in its queries (small ones themselves, large ones
+// because the keys they meet may be small).
+constexpr float kSplitSmall = 0x1p-108f, kSplitLarge = 0x1p96f;
+// True in a lane whose state holds an infinity or a NaN, or no value of a size that V's split keeps.
+__device__ __forceinline__ bool beyond_split(const TileState& st) {
+  float z = st.l * 0.f, top = 0.f;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     z = __builtin_fmaf(st.o[0][r], 0.f, z);
     z = __builtin_fmaf(st.o[1][r], 0.f, z);
+    top = __builtin_fmaxf(__builtin_fmaxf(top, __builtin_fabsf(st.o[0][r])), __builtin_fabsf(st.o[1][r]));
   }
-  return !(z == 0.f);
+  return !(z == 0.f) || (top > 0.f && top < st.l * (kSplitSmall * 16.f));
 }
 
-// The split of an infinity is no number (nor is that of a finite value that rounds to an
-// infinite bf16, from 3.39e38), so the products of such inputs are not those of fp32.  A tile whose state
-// ends with an infinity or a NaN is therefore computed once more with fp32 products (run_exact),
-// which decide what such inputs give.
 template <int kD>
 struct CoreF32T {
   using Stage = StageMap<float, kD>;
   SplitOperand q3[4];         // Q[query n][h*32 + 8s .. +7], s = 0..3 (of this wavefront's 64-channel slice)
   const float* q_row;         // this lane's half row of Q, for run_exact
   bool q_negate;
+  bool q_beyond;              // the tile's queries call for run_exact, see beyond_split (wave-uniform)
   SliceExchange<kD> xchg;   // used for kD > 64 only
 
   __device__ void load_qf(float (&qf)[32]) const {
@@ -689,9 +695,20 @@ struct CoreF32T {
     q_negate = negate;
     float qf[32];
     load_qf(qf);
+    // (twice a number's bits, less one: the order of the magnitudes, with the zeros at the top)
+    float most = 0.f;
+    uint32_t least = ~0u;
+#pragma unroll
+    for (int t = 0; t < 32; ++t) {
+      most = __builtin_fmaxf(most, __builtin_fabsf(qf[t]));
+      const uint32_t order = (__builtin_bit_cast(uint32_t, qf[t]) << 1) - 1u;
+      least = order < least ? order : least;
+    }
+    q_beyond = __any(least < (__builtin_bit_cast(uint32_t, kSplitSmall) << 1) - 1u || most > kSplitLarge);
 #pragma unroll
     for (int s = 0; s < 4; ++s) q3[s].split(qf + 8 * s);
   }
+  __device__ bool again(const TileState& st) const { return q_beyond || __any(beyond_split(st)); }
   __device__ floatx16 scores(const SplitOperand (&k3)[4], int lane) {
     floatx16 s = split_scores(k3, q3);
     if (kD > kHeadDim) xchg.sum_slices(s, lane);
@@ -873,9 +890,9 @@ struct CoreF32T {
     static_assert(kPipe == kPipeRegK, "fp32 pipeline");
     if (k0 >= k1) return;                // (for a wide tile the same in every slice)
     run_split(Kh, Vh, src, k0, k1, c, lane, st, lds);
-    bool again = __any(not_finite(st));
-    if constexpr (kD > kHeadDim) again = __syncthreads_or(again);
-    if (again) {
+    bool once_more = again(st);
+    if constexpr (kD > kHeadDim) once_more = __syncthreads_or(once_more);
+    if (once_more) {
       st.init();
       run_exact(Kh, Vh, src, k0, k1, c, lane, st, lds);
     }
@@ -2477,7 +2494,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(3, 3))) __launch_bounds__(256) voi
       }
       workgroup_lds_barrier();
     }
-    if (__any(not_finite(st))) {         // (see CoreF32T)
+    if (core.again(st)) {                // (see beyond_split)
       int ka = k0, kb = k1;
       while (ka < kb && src.classify(ka) == 0) ++ka;
       while (kb > ka && src.classify(kb - 1) == 0) --kb;
@@ -2537,7 +2554,7 @@ struct MergedLists {
 // kSharedClaims leaves CUs without a workgroup: there every wavefront claims items by itself
 // (+-100, one head, us, that / fours: L = 8,192 26.5 / 28.4, L = 16,301 38.2 / 30.1).
 // Bound like that kernel, at two wavefronts per SIMD (256 registers, for the wavefronts on lists
-// of their own; 17 vector values spill outside the loops over blocks, 91 scalar ones to vector lanes).  us, fp32
+// of their own; 18 vector values spill outside the loops over blocks, 92 scalar ones to vector lanes).  us, fp32
 // products -> every wavefront by itself -> this: longformer mask, L = 65,536, 8 heads, prepared 494 ->
 // 411 -> 387; +-300, L = 200,000, 2 heads 670 -> 568 -> 465; random, a quarter of the pairs, L = 24,576
 // 2,014 -> 1,144 -> 893.
@@ -2700,7 +2717,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) voi
         cur = ahead;
         ahead = after;
       }
-      if (__any(not_finite(st))) {         // (see CoreF32T)
+      if (core.again(st)) {                // (see beyond_split)
         st.init();
         core.run_exact(K + hoff, V + hoff, src, 0, nblk, c, lane, st, planes + wave * CoreF32::kBlockBytes);
       }

@@ -185,6 +185,18 @@ def test_one_large_channel(form, big, in_k):
 
 
 @pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("q_exp,k_exp,v_exp", [(-116, 116, 0), (116, -116, 0), (-121, 121, 0), (0, 0, -116), (0, 0, -121)])
+def test_operands_near_the_smallest_numbers(form, q_exp, k_exp, v_exp):
+    """Values whose low parts lie below the subnormal numbers of bf16: the bar is that of ordinary inputs,
+    relative to the largest value."""
+    import torch
+    Q, K, V = _form_qkv(form, 15)
+    (O1, l1), (O2, l2) = _both(form, Q * 2.0 ** q_exp, K * 2.0 ** k_exp, V * 2.0 ** v_exp, form[0] ** -0.5)
+    assert (O1.double() - O2.double()).abs().max().item() <= 2 * TOL["f32"] * 2.0 ** v_exp
+    assert (l1 - l2).abs().max().item() <= 1e-5
+
+
+@pytest.mark.parametrize("form", FORMS)
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])
 def test_values_nobody_attends(form, value):
     """An infinite or undefined value in keys that no query of a 32-query tile attends leaves the tile alone,
