@@ -232,7 +232,7 @@ struct WindowBlocks {
 // The mask words of WindowBlocks for a tile whose keys all lie within a few hundred positions of
 // its first key (the workgroup-staged kernel): the same quantities as 32-bit differences, so the
 // per-block arithmetic runs on the scalar unit.  d0 = u0 - vfirst, rem = min(Lc - vfirst, 2^20),
-// nq = queries of the tile that exist (clamped to 64), W <= 64.
+// nq = queries of the tile that exist (clamped to 64).
 struct WindowWordsNear {
   int d0, W, nq, rem;
   __device__ static int clamp(int v) { return v < -64 ? -64 : (v > 64 ? 64 : v); }
@@ -3698,8 +3698,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) voi
 }
 
 // fp16 window masks narrow enough that the keys of 128 consecutive queries fit the LDS
-// (128 + 2W <= 256 keys: 8 key blocks; this kernel takes the windows of up to 6 blocks, K and V
-// side by side in 48 KB at most, tile_window_kv_kernel those of 7 and 8).  A workgroup owns 128 queries
+// (this kernel takes the windows of up to 6 blocks, W <= 32, K and V side by side in 48 KB at most,
+// tile_window_kv_kernel those of 7 to 20, W <= 256).  A workgroup owns 128 queries
 // of one residue class: its four wavefronts first copy every K and V block the workgroup
 // needs global -> LDS, once (wavefront w copies blocks w, w+4), and after one barrier each
 // wavefront runs its own 32-query sub-tile entirely out of LDS.  Compared with one wavefront
@@ -3707,8 +3707,6 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) voi
 // times, and the block loop holds no memory instruction and no wait.  The LDS is sized to the
 // window at launch, so narrow windows run up to four workgroups per CU.  Grid mapping as in
 // tile_window_kernel.
-constexpr int kWgBlocks = 8;
-
 __global__ __launch_bounds__(256) void tile_window_wg_kernel(
     const __half* __restrict__ Q, const __half* __restrict__ K, const __half* __restrict__ V,
     __half* __restrict__ O, float* __restrict__ lse, int64_t L, int64_t W, int64_t s, int64_t n_groups,
@@ -3754,7 +3752,7 @@ __global__ __launch_bounds__(256) void tile_window_wg_kernel(
   const int64_t hoff = hd * L * kHeadDim;
   const int64_t vfirst = q0 - W > 0 ? q0 - W : 0;
   const int64_t vlast = q0 + 4 * kTile - 1 + W < Lc - 1 ? q0 + 4 * kTile - 1 + W : Lc - 1;
-  const int nb = (int)((vlast - vfirst) / kTile + 1);          // <= kWgBlocks
+  const int nb = (int)((vlast - vfirst) / kTile + 1);          // <= nb_max
   const int64_t u0 = q0 + (int64_t)wave * kTile;
   const int64_t u = u0 + n;
   const bool exists = u < Lc;
@@ -3827,25 +3825,31 @@ __device__ __forceinline__ void softmax_block_deferred(floatx16 sv, float c, boo
   }
 }
 
-// The same windows as tile_window_wg_kernel at their widest (7 or 8 key blocks per workgroup),
-// with K and V taking turns in ONE set of LDS blocks: the workgroup copies its K blocks, every
-// wavefront takes the scores and softmax numerators of its sub-tile against them (numerators and
-// the running max each block left behind stay in registers: at most kKvWaveBlocks blocks meet a
-// 32-query sub-tile), and after a barrier the V blocks are copied over the K blocks and the PV
-// products follow, O rescaled where the recorded max changes, exactly as the online form does.
-// Half the LDS (32 KB for 8 blocks) and under 128 registers: four workgroups per CU instead of
-// two, so that the copies of one workgroup overlap the arithmetic of three others.
+// Wider windows than those of tile_window_wg_kernel (7 to 20 key blocks per workgroup of 128 queries, W
+// up to kKvMaxWindow), with K and V taking turns in ONE set of LDS blocks: the workgroup copies its K
+// blocks, every wavefront takes the scores and softmax numerators of its sub-tile against them
+// (numerators and the running max each block left behind stay in registers: at most kWaveBlocks
+// blocks meet a 32-query sub-tile), and after a barrier the V blocks are copied over the K blocks
+// and the PV products follow, O rescaled where the recorded max changes, exactly as the online form does.
+// What it lives from is workgroups per CU: the copies of one run under the arithmetic of the
+// others.  4 KB of LDS per block and 9 registers per block of a sub-tile leave four workgroups up to W = 96
+// (40 KB, 116 registers), three up to 144 (52 KB, 152), two up to 256 (80 KB, 206).  The band kernel
+// that took W > 64 before has two, each of which waits for its first blocks, its Q and its output alone.
 // (blocks start at the workgroup's first key, W below it: sub-tile w covers blocks w .. w + (31 + 2W) / 32
-// of them, and in the first workgroup of a class, where the window is cut at key 0, at most
-// 2 * ceil(W / 32) + 1: five blocks at most for W <= 64)
-constexpr int kKvWaveBlocks = 5;
-constexpr int kKvMinBlocks = 7;     // windows of this many blocks per workgroup take this kernel
+// of them, and in the first workgroups of a class, where the window is cut at key 0, at most
+// 2 * ceil(W / 32) + 1: kWaveBlocks = 5 up to W = 64, 7 up to 96, 9 up to 128, 11 up to 160, 17 up to 256)
+// L = 1,048,576, 4 heads, us, band kernel -> this: W = 65 737 -> 446, 96 756 -> 475, 128 837 -> 558,
+// 144 872 -> 600, 160 923 -> 719, 192 980 -> 797, 256 1,076 -> 952; beyond, one workgroup per CU: 288
+// 1,136 -> 1,665.  W = 64 (2.1 GB, 5.1 TB/s): 412.
+constexpr int kKvMinBlocks = 7;        // windows of this many blocks per workgroup take this kernel
+constexpr int64_t kKvMaxWindow = 256;
 
+template <int kWaveBlocks>
 __global__ __launch_bounds__(256) void tile_window_kv_kernel(
     const __half* __restrict__ Q, const __half* __restrict__ K, const __half* __restrict__ V,
     __half* __restrict__ O, float* __restrict__ lse, int64_t L, int64_t W, int64_t s, int64_t n_groups,
     float scale, int accumulate, int nb_max, int64_t seg_len, int64_t Lq, int64_t Lr) {
-  extern __shared__ __attribute__((aligned(16))) char lds_wg[];      // max(nb_max, 5) blocks
+  extern __shared__ __attribute__((aligned(16))) char lds_wg[];      // nb_max blocks
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int n = lane & 31, h = lane >> 5;
@@ -3876,7 +3880,7 @@ __global__ __launch_bounds__(256) void tile_window_kv_kernel(
   const int64_t hoff = hd * L * kHeadDim;
   const int64_t vfirst = q0 - W > 0 ? q0 - W : 0;
   const int64_t vlast = q0 + 4 * kTile - 1 + W < Lc - 1 ? q0 + 4 * kTile - 1 + W : Lc - 1;
-  const int nb = (int)((vlast - vfirst) / kTile + 1);          // <= kWgBlocks
+  const int nb = (int)((vlast - vfirst) / kTile + 1);          // <= nb_max
   const int64_t u0 = q0 + (int64_t)wave * kTile;
   const int64_t u = u0 + n;
   const bool exists = u < Lc;
@@ -3902,7 +3906,7 @@ __global__ __launch_bounds__(256) void tile_window_kv_kernel(
   const int64_t lo_key = u0 - W > vfirst ? u0 - W : vfirst;
   const int64_t hi_key = u0 + kTile - 1 + W < vlast ? u0 + kTile - 1 + W : vlast;
   const int k_lo = (int)((lo_key - vfirst) / kTile);
-  const int k_hi = active ? (int)((hi_key - vfirst) / kTile) : k_lo - 1;     // k_hi - k_lo < kKvWaveBlocks
+  const int k_hi = active ? (int)((hi_key - vfirst) / kTile) : k_lo - 1;     // k_hi - k_lo < kWaveBlocks
   const float c = softmax_factor(scale);
   // K blocks of the workgroup, then this sub-tile's scores and numerators
   for (int j = wave; j < nb; j += 4) sm.stage_k(K + hoff, block_at(j), lane, lds_wg + j * CoreF16::kBlockBytes);
@@ -3910,10 +3914,10 @@ __global__ __launch_bounds__(256) void tile_window_kv_kernel(
   __syncthreads();
   TileState st;
   st.init();
-  half8 ph[kKvWaveBlocks][2];
-  float m_after[kKvWaveBlocks];
+  half8 ph[kWaveBlocks][2];
+  float m_after[kWaveBlocks];
 #pragma unroll
-  for (int j = 0; j < kKvWaveBlocks; ++j) {
+  for (int j = 0; j < kWaveBlocks; ++j) {
     const int k = k_lo + j;
     m_after[j] = st.m;
     if (k <= k_hi) {
@@ -3933,7 +3937,7 @@ __global__ __launch_bounds__(256) void tile_window_kv_kernel(
   __syncthreads();
   float m_run = m_after[0];
 #pragma unroll
-  for (int j = 0; j < kKvWaveBlocks; ++j) {
+  for (int j = 0; j < kWaveBlocks; ++j) {
     const int k = k_lo + j;
     if (k <= k_hi) {
       if (__any(m_after[j] != m_run)) {
@@ -4176,9 +4180,9 @@ sga_status run_tile_implicit(const AttnArgs& a) {
   const int64_t s = a.stride;
   const WindowShape shape = window_shape(a);
   const int64_t Lc = shape.Lc;
-  // fp16, 128 queries' key range fits the LDS: one workgroup stages it once (128 queries per
-  // workgroup, as in the fp32 kernel); wider fp16 windows: 64 queries per wavefront
-  const bool wg = a.dtype == SGA_F16 && 4 * kTile + 2 * (int64_t)a.window <= kWgBlocks * kTile;
+  // fp16, 128 queries' key range fits the LDS at two workgroups per CU or more: one workgroup stages
+  // it once (128 queries per workgroup, as in the fp32 kernel); wider fp16 windows: 64 queries per wavefront
+  const bool wg = a.dtype == SGA_F16 && a.window <= kKvMaxWindow;
   const bool pair = a.dtype == SGA_F16 && !wg;
   const int64_t per_wave = pair ? 2 * kTile : kTile;
   const int64_t n_tiles = (Lc + per_wave - 1) / per_wave;
@@ -4200,8 +4204,13 @@ sga_status run_tile_implicit(const AttnArgs& a) {
       Lq = (shape.seg_len + s - 1) / s;
       Lr = (last_len + s - 1) / s;
     }
+    const int64_t wave_blocks = 2 * ((a.window + kTile - 1) / kTile) + 1;
+    const auto kv_kernel = wave_blocks <= 5   ? tile_window_kv_kernel<5>
+                           : wave_blocks <= 7 ? tile_window_kv_kernel<7>
+                           : wave_blocks <= 9 ? tile_window_kv_kernel<9>
+                           : wave_blocks <= 11 ? tile_window_kv_kernel<11> : tile_window_kv_kernel<17>;
     if (kv)
-      hipLaunchKernelGGL(tile_window_kv_kernel, grid, dim3(256), (size_t)(nb_max > 5 ? nb_max : 5) * CoreF16::kBlockBytes,
+      hipLaunchKernelGGL(kv_kernel, grid, dim3(256), (size_t)nb_max * CoreF16::kBlockBytes,
                          a.stream, static_cast<const __half*>(a.Q), static_cast<const __half*>(a.K),
                          static_cast<const __half*>(a.V), static_cast<__half*>(a.O), a.lse, a.L,
                          (int64_t)a.window, s, n_groups, a.scale, acc, (int)nb_max, shape.seg_len, Lq, Lr);

@@ -236,6 +236,26 @@ def test_scattered_masks_tiles_agree_with_row_kernels_and_prepared_graphs(seed):
     _agree(O1, l1, O2, l2, dtype)
 
 
+@pytest.mark.parametrize("window", [65, 80, 96, 97, 128, 129, 144, 160, 161, 255, 256, 257])
+@pytest.mark.parametrize("kind,L,stride", [(KIND_SLIDING, 3011, 1), (KIND_SLIDING, 130, 1), (KIND_DILATED, 2705, 3)])
+def test_staged_windows_agree_with_row_kernels(window, kind, L, stride):
+    """fp16 windows on both sides of every number of blocks per sub-tile (5, 7, 9, 11, 17) and of the widest one
+    whose blocks are staged whole, on sequences with ragged ends and shorter than the window; forward, and
+    continuing a state."""
+    import torch
+    spec = MaskSpec(kind, L, window=window, stride=stride)
+    print("case", spec, flush=True)
+    Q, K, V = torch_qkv(2, L, 64, "f16", 0.8, window, "cuda:0")
+    O1, l1 = sga.attention_forward_implicit(Q, K, V, spec, 0.125, path=sga.PATH_TILE, want_lse=True)
+    O2, l2 = sga.attention_forward_implicit(Q, K, V, spec, 0.125, path=sga.PATH_GATHER, want_lse=True)
+    torch.cuda.synchronize()
+    _agree(O1, l1, O2, l2, "f16")
+    sga.attention_accumulate_implicit(Q, K, V, spec, 0.125, O1, l1, path=sga.PATH_TILE)
+    sga.attention_accumulate_implicit(Q, K, V, spec, 0.125, O2, l2, path=sga.PATH_GATHER)
+    torch.cuda.synchronize()
+    _agree(O1, l1, O2, l2, "f16", 2.0)
+
+
 @pytest.mark.parametrize("case", range(11))
 def test_d128_wide_bands_agree_with_row_kernels(case):
     """fp16, d = 128, windows wide enough and calls large enough for the kernel that gives a
