@@ -619,9 +619,11 @@ __global__ __launch_bounds__(256) void nonlocal_merge_kernel(T* __restrict__ O, 
 // One wavefront per (chunk of a long row, head): partial state of a slice of the row.  Chunk c
 // of every row is computed on XCD c % 8 (workgroups go to the XCDs round-robin in launch order
 // and gridDim.x is a multiple of 8): chunks are ranges of the rows' sorted neighbour lists, so
-// an XCD's L2 sees the same part of the key range from every row.  The work units of XCD x are
-// the pairs (long row s, j) with chunk c = x + 8j, numbered j * n_long + s (rows of few chunks
-// have no unit for the larger j) and dealt to the XCD's wavefronts in turn.
+// an XCD's L2 sees the same part of the key range from every row.  A row s whose z chunks are few and no
+// multiple of 8 starts at XCD (s z) % 8 instead, so that the rows together fill all of them: random
+// rows of 2,458 neighbours, cut in two, at L = 24,576, d = 128 had two XCDs to themselves (fp32 14.9 -> 4.8 ms, fp16 5.9 -> 2.8; d = 64, two heads 12.4 -> 4.7).
+// The work units of XCD x are the pairs (long row s, j) with chunk c = (x - s z) % 8 + 8j, numbered
+// j * n_long + s (rows of few chunks have no unit for the larger j) and dealt to the XCD's wavefronts in turn.
 template <typename T, int D>
 __device__ __forceinline__ void gather_chunk_body(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
@@ -643,8 +645,10 @@ __device__ __forceinline__ void gather_chunk_body(
   const uint64_t n_units = (uint64_t)n_long * ((max_chunks + 7) / 8);
   for (uint64_t u = (uint64_t)(wg >> 3) * waves + threadIdx.x / kWave; u < n_units;
        u += (uint64_t)(n_wg >> 3) * waves) {
-    const int4 rec = lr[u % n_long];                         // {row, first partial slot, chunks, chunk length}
-    const int32_t c = (int32_t)(xcd + 8 * (u / n_long));
+    const uint32_t s = (uint32_t)(u % n_long);
+    const int4 rec = lr[s];                                  // {row, first partial slot, chunks, chunk length}
+    const uint32_t turn = rec.z <= kMaxSplit ? s * (uint32_t)rec.z : 0;      // (0 mod 8 for a split by L2 share)
+    const int32_t c = (int32_t)(((xcd - turn) & 7) + 8 * (u / n_long));
     if (c >= rec.z) continue;
     const int64_t i = rec.x;
     const int64_t r0 = row_ptr[i], deg = row_ptr[i + 1] - r0;

@@ -383,6 +383,34 @@ def test_rows_split_by_l2_share(dtype, L, p):
             _close(O[h].cpu().numpy()[rows], lse[h].cpu().numpy()[rows], refs[h][0], refs[h][1], dtype)
 
 
+@pytest.mark.parametrize("d,dtype", [(32, "f32"), (64, "f32"), (128, "f16")])
+def test_rows_split_into_a_few_chunks(d, dtype):
+    """Rows of two and of three chunks, dealt over the XCDs in turn, beside whole ones: every row against the
+    same call without a workspace (no row is split then), sampled rows against the dense oracle."""
+    import torch
+    L, H = 5000, 2
+    rng = np.random.default_rng(78)
+    fill = np.where(np.arange(L) % 3 == 0, 0.04, np.where(np.arange(L) % 3 == 1, 0.5, 0.9))
+    mask = rng.random((L, L)) < fill[:, None]
+    rp, ci = R.csr_from_dense(mask)
+    deg = np.diff(rp)
+    assert int(rp[-1]) * H >= 2048 * 1024 and (deg[1::3] > 2048).all() and (deg[2::3] > 2 * 2048).all()
+    Q, K, V = numpy_qkv(H, L, d, dtype, 0.6, 32)
+    dQ, dK, dV = to_device(Q, K, V)
+    drp, dci = to_device(rp, ci)
+    ws = sga.alloc_workspace(L, H, d, dtype, int(rp[-1]))
+    O, lse = sga.attention_forward(dQ, dK, dV, drp, dci, 0.125, workspace=ws, path=sga.PATH_GATHER, want_lse=True)
+    O1, lse1 = sga.attention_forward(dQ, dK, dV, drp, dci, 0.125, path=sga.PATH_GATHER, want_lse=True)
+    torch.cuda.synchronize()
+    assert (O.float() - O1.float()).abs().max().item() <= 2 * TOL[dtype]
+    assert (lse - lse1).abs().max().item() <= 2 * LSE_TOL[dtype]
+    rows = np.unique(np.concatenate([np.arange(0, 20), np.arange(L - 20, L), rng.integers(0, L, 30)]))
+    for h in range(H):
+        O_ref, lse_ref = R.attention_dense(Q[h][rows].astype(np.float64), K[h].astype(np.float64),
+                                           V[h].astype(np.float64), mask[rows], 0.125)
+        _close(O[h].cpu().numpy()[rows], lse[h].cpu().numpy()[rows], O_ref, lse_ref, dtype)
+
+
 def test_explicit_and_implicit_paths_agree():
     """The same mask through the CSR entry point and the implicit entry point (the paper's
     own cross-check between its CSR and ordered-sparsity kernels, Section V-F)."""
