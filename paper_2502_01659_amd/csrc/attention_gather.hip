@@ -14,6 +14,7 @@
 // that separate wavefronts reduce to partial (m, l, acc) states; a merge kernel combines
 // the partials in chunk order, so the result is deterministic.
 #include "sga_internal.h"
+#include "tile_merge.h"
 
 namespace sga {
 namespace {
@@ -297,13 +298,14 @@ __global__ __launch_bounds__(256) void clear_workspace_kernel(void* ws, size_t w
     next[i] = 0;          // claim counters of the heads
 }
 
-// One thread per row, see split_prepass_row.
+// One thread per row, see record_split_row (calls on the per-row kernels alone).
 __global__ __launch_bounds__(256) void split_prepass_kernel(const int64_t* __restrict__ row_ptr,
                                                             int64_t L, int32_t H, int32_t dtype,
-                                                            int32_t d, void* ws, size_t ws_bytes,
-                                                            int skip_tiled) {
+                                                            int32_t d, void* ws, size_t ws_bytes) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < L) split_prepass_row(row_ptr, i, L, H, dtype, d, ws, ws_bytes, skip_tiled);
+  if (i >= L || row_ptr[i + 1] - row_ptr[i] <= kSplitThreshold / 2) return;      // (no rule splits a row this short)
+  const WorkspacePlan pl = plan_workspace(L, H, row_ptr[L], dtype, d);
+  if (pl.total_bytes <= ws_bytes) record_split_row(row_ptr, i, pl, ws);
 }
 
 // The list of long rows that this call uses: the finer split if all its chunks fit.
@@ -312,6 +314,12 @@ __device__ __forceinline__ const int4* long_rows(const WorkspacePlan& pl, const 
   const bool fine = (int64_t)ctr[kCtrFineNeeded] <= pl.cap_items;
   max_chunks = ctr[fine ? kCtrMaxChunksFine : kCtrMaxChunks];
   return reinterpret_cast<const int4*>(static_cast<const char*>(ws) + pl.off_long) + (fine ? pl.cap_items : 0);
+}
+
+// A recorded row that the tile path produced after all (skip_tiled: this call ran it), see tile_parts_in_doubt.
+__device__ __forceinline__ bool passed_over(const WorkspacePlan& pl, const void* ws, const int64_t* row_ptr, int64_t L,
+                                            int64_t i, int skip_tiled) {
+  return skip_tiled && tile_parts_in_doubt(pl) && tile_handled(pl, ws, row_ptr, L, i / kTile);
 }
 
 // True when the long rows of this call are handled by the chunk kernels.
@@ -628,7 +636,7 @@ template <typename T, int D>
 __device__ __forceinline__ void gather_chunk_body(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int64_t L, float scale,
-    void* ws, size_t ws_bytes, uint32_t wg, uint32_t n_wg) {
+    void* ws, size_t ws_bytes, int skip_tiled, uint32_t wg, uint32_t n_wg) {
   const int32_t H = (int32_t)gridDim.y;
   constexpr int32_t dtype = DtypeOf<T>::code;
   if (!split_active(row_ptr, L, H, dtype, D, ws, ws_bytes)) return;
@@ -651,6 +659,7 @@ __device__ __forceinline__ void gather_chunk_body(
     const int32_t c = (int32_t)(((xcd - turn) & 7) + 8 * (u / n_long));
     if (c >= rec.z) continue;
     const int64_t i = rec.x;
+    if (passed_over(pl, ws, row_ptr, L, i, skip_tiled)) continue;
     const int64_t r0 = row_ptr[i], deg = row_ptr[i + 1] - r0;
     const int64_t e0 = (int64_t)c * rec.w;
     const int64_t e1 = min(deg, e0 + rec.w);
@@ -679,25 +688,29 @@ template <typename T, int D>
 __global__ __launch_bounds__(256) void gather_chunk_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int64_t L, float scale,
-    void* ws, size_t ws_bytes) {
-  gather_chunk_body<T, D>(Q, K, V, row_ptr, col_idx, L, scale, ws, ws_bytes, blockIdx.x, gridDim.x);
+    void* ws, size_t ws_bytes, int skip_tiled) {
+  gather_chunk_body<T, D>(Q, K, V, row_ptr, col_idx, L, scale, ws, ws_bytes, skip_tiled, blockIdx.x, gridDim.x);
 }
 
-// The two kernels above in one launch (neither reads what the other writes): the first n_rows
-// workgroups of a head (a multiple of 8, so that the chunk workgroups keep their XCDs) take the
-// leftover rows, the others the chunks of the split rows.  For the call that does not know yet
-// whether anything is left for either: one launch that finds nothing to do instead of two.
+// What the tile path leaves over, in one launch for the call that does not know whether there is anything
+// (none reads what another writes): the first n_merge workgroups of a head merge the tiles' segments,
+// the next n_rows take the leftover rows, the others the chunks of the split rows.  (n_merge and
+// n_rows are multiples of 8, so that the chunk workgroups keep their XCDs.)  An empty launch costs 3 to 6
+// us of a small call: +-32, L = 4,096, fp32, mask build and forward, in three launches 42.0 us, in two 38.9.
 template <typename T, int D>
-__global__ __launch_bounds__(256) void gather_rows_and_chunks_kernel(
+__global__ __launch_bounds__(256) void leftovers_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
     float* __restrict__ lse, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
-    int64_t L, float scale, void* ws, size_t ws_bytes, int skip_tiled, int accumulate, uint32_t n_rows) {
-  if (blockIdx.x < n_rows)
-    gather_csr_body<T, D>(Q, K, V, O, lse, row_ptr, col_idx, L, scale, ws, ws_bytes, 1, skip_tiled, accumulate,
-                          blockIdx.x, n_rows);
+    int64_t L, float scale, void* ws, size_t ws_bytes, int use_split, int accumulate, uint32_t n_merge, uint32_t n_rows) {
+  if (blockIdx.x < n_merge)
+    tile_merge_body<T, D>(O, lse, row_ptr, L, ws, ws_bytes, accumulate, blockIdx.x / kTile, n_merge / kTile,
+                          blockIdx.x % kTile, kTile);
+  else if (blockIdx.x < n_merge + n_rows)
+    gather_csr_body<T, D>(Q, K, V, O, lse, row_ptr, col_idx, L, scale, ws, ws_bytes, use_split, 1, accumulate,
+                          blockIdx.x - n_merge, n_rows);
   else
-    gather_chunk_body<T, D>(Q, K, V, row_ptr, col_idx, L, scale, ws, ws_bytes, blockIdx.x - n_rows,
-                            gridDim.x - n_rows);
+    gather_chunk_body<T, D>(Q, K, V, row_ptr, col_idx, L, scale, ws, ws_bytes, 1, blockIdx.x - n_merge - n_rows,
+                            gridDim.x - n_merge - n_rows);
 }
 
 // Rows of up to kMaxSplit chunks: one wavefront per (long row, head) combines the row's partials
@@ -709,7 +722,7 @@ template <typename T, int D>
 __global__ __launch_bounds__(256) void gather_merge_kernel(T* __restrict__ O, float* __restrict__ lse,
                                                            const int64_t* __restrict__ row_ptr,
                                                            int64_t L, void* ws, size_t ws_bytes,
-                                                           int accumulate) {
+                                                           int skip_tiled, int accumulate) {
   __shared__ float quarter[4][D + 4];
   const int32_t H = (int32_t)gridDim.y;
   constexpr int32_t dtype = DtypeOf<T>::code;
@@ -727,6 +740,7 @@ __global__ __launch_bounds__(256) void gather_merge_kernel(T* __restrict__ O, fl
     const int4 rec = lr[r];
     if (rec.z > kMaxSplit) continue;
     const int64_t i = rec.x;
+    if (passed_over(pl, ws, row_ptr, L, i, skip_tiled)) continue;
     merge_row_partials<T, D>(partials + ((int64_t)rec.y * H + h) * (D + 4), step, rec.z, O + h * L * D + i * D,
                              lse ? lse + h * L + i : nullptr, lane, accumulate != 0);
   }
@@ -735,6 +749,7 @@ __global__ __launch_bounds__(256) void gather_merge_kernel(T* __restrict__ O, fl
     const int4 rec = lr[r];
     if (rec.z <= kMaxSplit) continue;
     const int64_t i = rec.x;
+    if (passed_over(pl, ws, row_ptr, L, i, skip_tiled)) continue;
     const float* p0 = partials + ((int64_t)rec.y * H + h) * (D + 4);
     T* Orow = O + h * L * D + i * D;
     float* lse_i = lse ? lse + h * L + i : nullptr;
@@ -748,6 +763,11 @@ __global__ __launch_bounds__(256) void gather_merge_kernel(T* __restrict__ O, fl
   }
 }
 
+void launch_split_prepass(const AttnArgs& a) {
+  hipLaunchKernelGGL(split_prepass_kernel, dim3((unsigned)((a.L + 255) / 256)), dim3(256), 0, a.stream,
+                     a.row_ptr, a.L, a.H, a.dtype, a.d, a.ws, a.ws_bytes);
+}
+
 template <typename T, int D>
 sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
   const T* Q = static_cast<const T*>(a.Q);
@@ -755,8 +775,8 @@ sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
   const T* V = static_cast<const T*>(a.V);
   T* O = static_cast<T*>(a.O);
   const bool split = allow_split && a.ws && a.ws_bytes >= 256 && a.L > kSplitThreshold;
-  // (a prepared graph holds the chunk items of its split rows already)
-  if (split && !a.prepared && !a.prepass_done) launch_split_prepass(a, skip_tiled);
+  // (after the tile path, and in a prepared graph, the CSR -> tile pass has recorded the split rows)
+  if (split && !skip_tiled) launch_split_prepass(a);
   // after the tile path only leftover rows remain: a grid of about one chip-full of wavefronts
   // over all heads strides over the rows (it returns at once when the tiles covered everything)
   int64_t nwg = (a.L + 3) / 4;
@@ -767,14 +787,20 @@ sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
   // kernel where a prepared graph has found every row left to it split
   const bool mark = !skip_tiled || (a.prepared && a.plan_no_tiles);
   const bool mark_chunks = mark && a.prepared && a.plan_long_rows > 0;
-  const unsigned chunk_wgs = skip_tiled && a.H >= 8 ? 128 : 1024;
-  const bool fused = split && skip_tiled && !a.prepared;     // (after the tile path, nothing known about what is left)
-  if (fused) {
-    const unsigned n_rows = ((unsigned)nwg + 7u) & ~7u;
-    hipLaunchKernelGGL((gather_rows_and_chunks_kernel<T, D>), dim3(n_rows + chunk_wgs, (unsigned)a.H), dim3(256), 0,
-                       a.stream, Q, K, V, O, a.lse, a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes, 1,
-                       a.accumulate ? 1 : 0, n_rows);
-  } else if (!(a.prepared && a.plan_long_rows == a.L)) {       // (a prepared graph all of whose rows are split: 19 us of L = 24,576)
+  const bool fused = D >= kHeadDim && skip_tiled && !a.prepared;     // (nothing known about what is left)
+  if constexpr (D >= kHeadDim) {
+    if (fused) {
+      // chunks: a chip-full of workgroups over the heads, fewer where L leaves little to split
+      int64_t chunk_wgs = split ? (a.L < 32768 ? a.L / 32 : 1024) / a.H : 0;
+      if (split && chunk_wgs < 128) chunk_wgs = 128;
+      chunk_wgs = (chunk_wgs + 7) & ~int64_t(7);
+      const unsigned n_rows = ((unsigned)nwg + 7u) & ~7u, n_merge = merge_tiles(a) * kTile;
+      hipLaunchKernelGGL((leftovers_kernel<T, D>), dim3(n_merge + n_rows + (unsigned)chunk_wgs, (unsigned)a.H), dim3(256),
+                         0, a.stream, Q, K, V, O, a.lse, a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes,
+                         split ? 1 : 0, a.accumulate ? 1 : 0, n_merge, n_rows);
+    }
+  }
+  if (!fused && !(a.prepared && a.plan_long_rows == a.L)) {       // (a prepared graph all of whose rows are split: 19 us of L = 24,576)
     if (mark && !mark_chunks) profile_mark_begin(a.stream, "gather_csr_kernel");
     hipLaunchKernelGGL((gather_csr_kernel<T, D>), grid, dim3(256), 0, a.stream, Q, K, V, O, a.lse,
                        a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes, split ? 1 : 0,
@@ -783,18 +809,19 @@ sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
   }
   if (split && (!a.prepared || a.plan_long_rows > 0)) {
     if (!fused) {
+      const unsigned chunk_wgs = skip_tiled && a.H >= 8 ? 128 : 1024;
       if (mark_chunks) profile_mark_begin(a.stream, "gather_chunk_kernel");
       hipLaunchKernelGGL((gather_chunk_kernel<T, D>), dim3(chunk_wgs, (unsigned)a.H), dim3(256), 0, a.stream, Q,
-                         K, V, a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes);
+                         K, V, a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes, skip_tiled ? 1 : 0);
       if (mark_chunks) profile_mark_end(a.stream);
     }
     // one wavefront per long row and head, one workgroup for a row of more than kMaxSplit
     // chunks; a prepared graph knows how many rows there are
-    int64_t merge_wgs = a.prepared ? (int64_t)a.plan_long_rows : (a.L + 3) / 4;
+    int64_t merge_wgs = a.prepared ? (int64_t)a.plan_long_rows : (a.L + 15) / 16;
     const int64_t merge_cap = 4096 / a.H > 64 ? 4096 / a.H : 64;
     if (merge_wgs > merge_cap) merge_wgs = merge_cap;
     hipLaunchKernelGGL((gather_merge_kernel<T, D>), dim3((unsigned)merge_wgs, (unsigned)a.H), dim3(256), 0, a.stream, O,
-                       a.lse, a.row_ptr, a.L, a.ws, a.ws_bytes, a.accumulate ? 1 : 0);
+                       a.lse, a.row_ptr, a.L, a.ws, a.ws_bytes, skip_tiled ? 1 : 0, a.accumulate ? 1 : 0);
   }
   return hip_status(hipGetLastError());
 }
@@ -807,11 +834,6 @@ void clear_workspace(const AttnArgs& a, bool tile_flags) {
   if (nwg > 1024) nwg = 1024;
   hipLaunchKernelGGL(clear_workspace_kernel, dim3((unsigned)nwg), dim3(256), 0, a.stream, a.ws,
                      a.ws_bytes, a.row_ptr, a.L, a.H, a.dtype, a.d, tile_flags ? 1 : 0);
-}
-
-void launch_split_prepass(const AttnArgs& a, bool skip_tiled) {
-  hipLaunchKernelGGL(split_prepass_kernel, dim3((unsigned)((a.L + 255) / 256)), dim3(256), 0, a.stream,
-                     a.row_ptr, a.L, a.H, a.dtype, a.d, a.ws, a.ws_bytes, skip_tiled ? 1 : 0);
 }
 
 sga_status launch_gather_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {

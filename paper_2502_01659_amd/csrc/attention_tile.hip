@@ -30,6 +30,7 @@
 // Window masks on short sequences (few tiles, many key blocks each) are cut the same way by a
 // host rule, into ranges of key blocks whose partial states window_merge_kernel combines.
 #include "sga_internal.h"
+#include "tile_merge.h"
 
 #include <type_traits>
 
@@ -1901,6 +1902,7 @@ __global__ __launch_bounds__(256) void tile_analyze_kernel(const int64_t* __rest
         pos = q;
       }
     }
+    bool gives_up = false;            // this item is the first of its tile to be given up
     if (lane == 0) {
       *reinterpret_cast<int4*>(items + w) = make_int4((int32_t)t, overflow ? -1 : nblk, id.seg, id.nseg);
       items[w].slot0 = slot0;
@@ -1910,6 +1912,7 @@ __global__ __launch_bounds__(256) void tile_analyze_kernel(const int64_t* __rest
       if (id.nseg > 1 && ((id.together ? (int)t : id.seg) & 3) == 0)
         items[atomicAdd(&ctr[kCtrMultiItems], 1u)].group = w;
       if (overflow && atomicOr(&tile_bad[t], 1) == 0) {
+        gives_up = true;
         // (the per-row kernels walk this list instead of testing every row of the sequence)
         const uint32_t bi = atomicAdd(&ctr[kCtrTilesBad], 1u);
         reinterpret_cast<int32_t*>(base_ws + pl.off_bad_list)[bi] = (int32_t)t;
@@ -1927,6 +1930,10 @@ __global__ __launch_bounds__(256) void tile_analyze_kernel(const int64_t* __rest
           reinterpret_cast<int4*>(base_ws + pl.off_multi_tiles)[mi] = make_int4((int32_t)t, pbase, id.nseg, 0);
       }
     }
+    // the tile's rows that the per-row kernels split (L > kSplitThreshold; see tile_parts_in_doubt)
+    const bool in_doubt = id.nseg > 1 && tile_parts_in_doubt(pl);
+    if (L > kSplitThreshold && (in_doubt ? id.seg == 0 : __any(gives_up)) && lane < kTile && row < L)
+      record_split_row(row_ptr, row, pl, ws);
   }
 }
 
@@ -2143,111 +2150,13 @@ __global__ __launch_bounds__(kD, 2) void tile_attend_wide_kernel(
   }
 }
 
-__device__ __forceinline__ float load_out(const float* p) { return *p; }
-__device__ __forceinline__ float load_out(const __half* p) { return __half2float(*p); }
-__device__ __forceinline__ void store_out(float* p, float v) { *p = v; }
-__device__ __forceinline__ void store_out(__half* p, float v) { *p = __float2half_rn(v); }
-
-// Merge of a multi-segment tile's partial states.  grid = (tiles of the merge list, head,
-// rows of the tile in groups of 32 / gridDim.z).  Per row: the running maximum M over all
-// segments (every thread takes every 256th segment, so all loads are in flight together), the
-// weights 2^(m_c - M), and the weighted sums of l and of the accumulators.  The 4 wavefronts of
-// a workgroup take every 4th segment (lane = channel within each 64-channel slice; a partial
-// of a kD-wide tile is kD / 64 records, one per slice, with the same m and l), four segments per
-// trip so that their loads overlap, each in ascending segment order; the four results are added
-// in wavefront order, so the summation order is fixed.
+// Merge of the multi-segment tiles of a prepared graph (see tile_merge_body; other calls merge in the launch
+// of the leftover rows).
 template <typename T, int kD>
 __global__ __launch_bounds__(256) void tile_merge_kernel(T* __restrict__ O, float* __restrict__ lse,
                                                          const int64_t* __restrict__ row_ptr, int64_t L,
-                                                         void* ws, size_t ws_bytes, int accumulate,
-                                                         uint32_t merge_wgs) {
-  constexpr int kSlices = kD / kHeadDim;
-  __shared__ float sm_acc[4][kD];
-  __shared__ float sm_m[4], sm_l[4];
-  const int32_t H = (int32_t)gridDim.y;
-  constexpr int32_t dtype = DtypeOf<T>::code;
-  if (blockIdx.x >= merge_wgs) {
-    const int64_t wg = ((int64_t)(blockIdx.x - merge_wgs) * gridDim.y + blockIdx.y) * gridDim.z + blockIdx.z;
-    const int64_t i = wg * 256 + threadIdx.x;
-    if (i < L) split_prepass_row(row_ptr, i, L, H, dtype, kD, ws, ws_bytes, 1);
-    return;
-  }
-  const WorkspacePlan pl = plan_workspace(L, H, row_ptr[L], dtype, kD);
-  if (pl.total_bytes > ws_bytes || !tile_parts_fit(pl, ws)) return;
-  char* base_ws = static_cast<char*>(ws);
-  const uint32_t n_multi = reinterpret_cast<const uint32_t*>(ws)[kCtrMultiTiles];
-  const int4* multi = reinterpret_cast<const int4*>(base_ws + pl.off_multi_tiles);     // {tile, first partial slot, segments, -}
-  const int32_t* tile_bad = reinterpret_cast<const int32_t*>(base_ws + pl.off_tile_bad);
-  const float* parts = reinterpret_cast<const float*>(base_ws + pl.off_tpartials);
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
-  const int64_t hd = blockIdx.y;
-  for (uint32_t i = blockIdx.x; i < n_multi; i += merge_wgs) {
-    const int4 rec = multi[i];
-    const int64_t t = rec.x;
-    if (tile_bad[t]) continue;
-    const int nseg = rec.z;
-    const float* p0 = parts + ((int64_t)rec.y * H + hd) * (kSlices * kTilePartialFloats);
-    const int64_t step = (int64_t)H * (kSlices * kTilePartialFloats);
-    const int rows_per_wg = kTile / (int)gridDim.z;
-    for (int r = blockIdx.z * rows_per_wg; r < (int)(blockIdx.z + 1) * rows_per_wg; ++r) {
-      const int64_t row = t * kTile + r;
-      const float* pm = p0 + kTile * 64 + r;       // segment c: m = pm[c * step], l = pm[c * step + kTile]
-      float M = kMinusHuge;
-      for (int c = threadIdx.x; c < nseg; c += 256) M = fmaxf(M, pm[c * step]);
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, kWave));
-      __syncthreads();            // the previous row's combine has read the shared arrays
-      if (lane == 0) sm_m[wave] = M;
-      __syncthreads();
-      M = fmaxf(fmaxf(sm_m[0], sm_m[1]), fmaxf(sm_m[2], sm_m[3]));
-      float l = 0.f, acc[kSlices];
-#pragma unroll
-      for (int sl = 0; sl < kSlices; ++sl) acc[sl] = 0.f;
-      for (int c = wave; c < nseg; c += 16) {
-        float mc[4], lc[4], oc[4][kSlices];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int cc = c + 4 * u < nseg ? c + 4 * u : c;
-          mc[u] = pm[cc * step];
-          lc[u] = pm[cc * step + kTile];
-#pragma unroll
-          for (int sl = 0; sl < kSlices; ++sl) oc[u][sl] = p0[cc * step + sl * kTilePartialFloats + r * 64 + lane];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const float wgt = c + 4 * u < nseg ? __builtin_amdgcn_exp2f(mc[u] - M) : 0.f;
-          l = __builtin_fmaf(lc[u], wgt, l);
-#pragma unroll
-          for (int sl = 0; sl < kSlices; ++sl) acc[sl] = __builtin_fmaf(oc[u][sl], wgt, acc[sl]);
-        }
-      }
-#pragma unroll
-      for (int sl = 0; sl < kSlices; ++sl) sm_acc[wave][sl * 64 + lane] = acc[sl];
-      if (lane == 0) sm_l[wave] = l;
-      __syncthreads();
-      if (wave == 0 && row < L) {
-        const float lt = ((sm_l[0] + sm_l[1]) + sm_l[2]) + sm_l[3];
-        const bool empty = !(lt > 0.f);
-        float lse_row = empty ? -INFINITY : (M + __builtin_amdgcn_logf(lt)) * kLn2;
-        CarryWeights cw{0.f, 1.f, lse_row};
-        if (accumulate) {
-          cw = carry_weights(lse[hd * L + row], lse_row);
-          lse_row = cw.lse;
-        }
-#pragma unroll
-        for (int sl = 0; sl < kSlices; ++sl) {
-          const float at = ((sm_acc[0][sl * 64 + lane] + sm_acc[1][sl * 64 + lane]) +
-                            sm_acc[2][sl * 64 + lane]) + sm_acc[3][sl * 64 + lane];
-          T* dst = O + hd * L * kD + row * kD + sl * 64 + lane;
-          float o = empty ? 0.f : at / lt;
-          if (accumulate) o = cw.w_prev * load_out(dst) + cw.w_now * o;
-          store_out(dst, o);
-        }
-        if (lse && lane == 0) lse[hd * L + row] = lse_row;
-      }
-    }
-  }
+                                                         void* ws, size_t ws_bytes, int accumulate) {
+  tile_merge_body<T, kD>(O, lse, row_ptr, L, ws, ws_bytes, accumulate, blockIdx.x, gridDim.x, blockIdx.z, gridDim.z);
 }
 
 // A workgroup's place among the window tiles.  Whole-sequence masks (seg_len = 0): residue class
@@ -3967,22 +3876,6 @@ __global__ __launch_bounds__(256) void tile_window_kv_kernel(
 template <typename T>
 sga_status run_tile_explicit_wide(const AttnArgs& a);
 
-// Workgroups per row and head of the merge of multi-segment tiles, each of which walks the merge list:
-// one per tile where a prepared graph knows their number, up to four rounds of the chip's 2,048
-// workgroups.  (768 tiles of six segments, one head: 96 us with 16 workgroups per row.)
-unsigned merge_tiles(const AttnArgs& a) {
-  const int64_t most = 8192 / (kTile * (int64_t)a.H);
-  int64_t n = a.prepared ? (int64_t)a.plan_multi_tiles : 16;
-  if (n > most) n = most;
-  return (unsigned)(n < 16 ? (a.prepared && a.plan_multi_tiles < 16 ? a.plan_multi_tiles : 16) : n);
-}
-
-// ... and the columns of workgroups behind them that record the split rows (AttnArgs::prepass_done)
-unsigned prepass_columns(const AttnArgs& a) {
-  const int64_t per_column = 256 * (int64_t)kTile * a.H;
-  return a.prepass_done ? (unsigned)((a.L + per_column - 1) / per_column) : 0u;
-}
-
 template <typename T>
 sga_status run_tile_explicit(const AttnArgs& a) {
   if (a.d != kHeadDim) return run_tile_explicit_wide<T>(a);
@@ -4017,11 +3910,11 @@ sga_status run_tile_explicit(const AttnArgs& a) {
                        a.ws_bytes, a.accumulate ? 1 : 0);
   }
   profile_mark_end(a.stream);
-  // (a prepared graph knows whether any tile was cut into segments)
-  if (!a.prepared || a.plan_multi_tiles > 0)
-    hipLaunchKernelGGL((tile_merge_kernel<T, kHeadDim>), dim3(merge_tiles(a) + prepass_columns(a), (unsigned)a.H, kTile),
-                       dim3(256), 0, a.stream, O, a.lse, a.row_ptr, a.L, a.ws, a.ws_bytes, a.accumulate ? 1 : 0,
-                       merge_tiles(a));
+  // (a prepared graph knows whether any tile was cut into segments; otherwise the launch for the rows left
+  // over merges them)
+  if (a.prepared && a.plan_multi_tiles > 0)
+    hipLaunchKernelGGL((tile_merge_kernel<T, kHeadDim>), dim3(merge_tiles(a), (unsigned)a.H, kTile), dim3(256), 0,
+                       a.stream, O, a.lse, a.row_ptr, a.L, a.ws, a.ws_bytes, a.accumulate ? 1 : 0);
   return hip_status(hipGetLastError());
 }
 
@@ -4054,10 +3947,9 @@ sga_status run_tile_explicit_wide_d(const AttnArgs& a) {
                        a.accumulate ? 1 : 0);
   }
   profile_mark_end(a.stream);
-  if (!a.prepared || a.plan_multi_tiles > 0)
-    hipLaunchKernelGGL((tile_merge_kernel<T, kD>), dim3(merge_tiles(a) + prepass_columns(a), (unsigned)a.H, kTile),
-                       dim3(256), 0, a.stream, O, a.lse, a.row_ptr, a.L, a.ws, a.ws_bytes, a.accumulate ? 1 : 0,
-                       merge_tiles(a));
+  if (a.prepared && a.plan_multi_tiles > 0)
+    hipLaunchKernelGGL((tile_merge_kernel<T, kD>), dim3(merge_tiles(a), (unsigned)a.H, kTile), dim3(256), 0, a.stream, O,
+                       a.lse, a.row_ptr, a.L, a.ws, a.ws_bytes, a.accumulate ? 1 : 0);
   return hip_status(hipGetLastError());
 }
 
@@ -4271,15 +4163,13 @@ void launch_tile_analyze(const AttnArgs& a) {
 sga_status launch_tile_explicit(const AttnArgs& a) {
   if (!a.ws || a.ws_bytes < 256) return launch_gather_explicit(a, false, false);
   // (a prepared graph in which no tile qualified goes straight to the per-row kernels)
-  AttnArgs b = a;
-  b.prepass_done = !a.prepared && a.L > kSplitThreshold;
   if (!(a.prepared && a.plan_no_tiles)) {
-    const sga_status st = a.dtype == SGA_F32 ? run_tile_explicit<float>(b) : run_tile_explicit<__half>(b);
+    const sga_status st = a.dtype == SGA_F32 ? run_tile_explicit<float>(a) : run_tile_explicit<__half>(a);
     if (st != SGA_OK) return st;
   }
   if (a.prepared && a.plan_tiles_cover_all) return SGA_OK;
   // rows of tiles that did not qualify (or everything, if the workspace is too small)
-  return launch_gather_explicit(b, true, true);
+  return launch_gather_explicit(a, true, true);
 }
 
 namespace {

@@ -340,14 +340,10 @@ __device__ __forceinline__ bool tiles_cover_everything(const WorkspacePlan& pl, 
 
 // Row i of the per-row path's preparation: a row that is split reserves its partial slots and enters the
 // list of long rows.
-__device__ __forceinline__ void split_prepass_row(const int64_t* __restrict__ row_ptr, int64_t i, int64_t L, int32_t H,
-                                                  int32_t dtype, int32_t d, void* ws, size_t ws_bytes, int skip_tiled) {
+__device__ __forceinline__ void record_split_row(const int64_t* __restrict__ row_ptr, int64_t i, const WorkspacePlan& pl,
+                                                 void* ws) {
   const int64_t deg = row_ptr[i + 1] - row_ptr[i];
-  if (deg <= kSplitThreshold / 2) return;           // (no rule splits a row this short)
-  const WorkspacePlan pl = plan_workspace(L, H, row_ptr[L], dtype, d);
-  if (pl.total_bytes > ws_bytes || !row_is_split(deg, pl)) return;
-  if (skip_tiled && (tiles_cover_everything(pl, ws) || tile_handled(pl, ws, row_ptr, L, i / kTile)))
-    return;
+  if (!row_is_split(deg, pl)) return;
   uint32_t* ctr = reinterpret_cast<uint32_t*>(ws);
   int32_t n, len, nf, lenf;
   row_split_shape(deg, pl, false, n, len);
@@ -369,6 +365,12 @@ __device__ __forceinline__ void split_prepass_row(const int64_t* __restrict__ ro
   // (read only if the finer chunks of every row fit, and then basef + nf <= cap_items)
   lr[pl.cap_items + slot] = make_int4((int)i, (int)basef, nf, lenf);
 }
+
+// The split rows that the tile path leaves over are recorded by the CSR -> tile pass where it gives a tile
+// up.  Whether the partial states of the multi-segment tiles fit is known only after it: they do
+// unless the call has more edges than kMaxTilePartials items hold, and in such a call the rows of
+// every multi-segment tile are recorded, to be passed over if the tile path produced them.
+__host__ __device__ inline bool tile_parts_in_doubt(const WorkspacePlan& p) { return p.cap_tparts >= kMaxTilePartials; }
 
 template <typename T> struct DtypeOf;
 template <> struct DtypeOf<float> { static constexpr int32_t code = SGA_F32; };
@@ -407,7 +409,6 @@ struct AttnArgs {
   size_t ws_bytes;
   // prepared graph (sga_graph_prepare): the workspace already holds the tile graph and the
   // chunk items of the split rows, and the host knows what they contain
-  bool prepass_done;           // the split rows were recorded by the launch that merges the tiles' segments
   bool prepared;
   uint32_t plan_multi_tiles;   // multi-segment tiles whose partial states fit (0: no merge launch)
   bool plan_tiles_cover_all;   // no row is left to the per-row kernels
@@ -419,7 +420,8 @@ struct AttnArgs {
 // Zeroes the counters (and, when row_ptr is given, the per-tile flags of the tile path).
 void clear_workspace(const AttnArgs& a, bool tile_flags);
 // skip_tiled: rows whose 32-row tile was produced by the tile path (tile_bad == 0 in the
-// workspace) are skipped, and a small grid strides over the rows.
+// workspace) are skipped, and a small grid strides over the rows; without a prepared graph the same
+// launch merges the tiles' segments.
 sga_status launch_gather_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled);
 sga_status launch_gather_implicit(const AttnArgs& a);
 
@@ -427,8 +429,6 @@ sga_status launch_gather_implicit(const AttnArgs& a);
 sga_status launch_tile_explicit(const AttnArgs& a);
 // CSR -> tile graph pass alone (sga_graph_prepare); a.ws holds a full workspace
 void launch_tile_analyze(const AttnArgs& a);
-// reservation of the chunk items of the split rows the tile path leaves over (sga_graph_prepare)
-void launch_split_prepass(const AttnArgs& a, bool skip_tiled);
 sga_status launch_tile_implicit(const AttnArgs& a);
 // Implicit non-local mask on the tile kernels (d = 64, 128, 256): the rows >= g against the global keys,
 // and the partial states of the g global rows over *n_chunks ranges of the key blocks, in the

@@ -326,3 +326,28 @@ def test_explicit_d128_tiles_agree_with_row_kernels_and_prepared_graphs(seed):
     assert ((O4.float() - O1.float()).abs() / (1 + O1.float().abs())).max().item() <= 2 * TOL["f16"]
     if fin.any():
         assert (l4[fin] - l1[fin] - 0.6931472).abs().max().item() <= 2e-3
+
+
+@pytest.mark.parametrize("L", [32768, 33000])
+def test_dense_mask_at_the_limit_of_partial_states(L):
+    """fp32, every pair an edge: the segments of all tiles just fit the call's partial states (L = 32,768), or do not
+    (33,000: every tile goes to the per-row kernels, each row split).  The split rows are recorded in both, and
+    passed over in the first.  Explicit, prepared and implicit calls agree; no row is done twice."""
+    import torch
+    spec = MaskSpec(KIND_SLIDING, L, window=L)
+    print("case", L, flush=True)
+    Q, K, V = torch_qkv(1, L, 64, "f32", 0.5, 41, "cuda:0")
+    rp, ci = sga.build_mask(spec)
+    ws = sga.alloc_workspace(L, 1, 64, "f32", ci.numel())
+    O1, l1 = sga.attention_forward(Q, K, V, rp, ci, 0.125, workspace=ws, want_lse=True)
+    O2, l2 = sga.attention_forward_implicit(Q, K, V, spec, 0.125, want_lse=True)
+    plan = sga.graph_prepare(rp, ci, 1, 64, "f32", ws)
+    assert (plan.tile_parts <= 32768) == (L == 32768) and plan.long_rows == L
+    O3, l3 = sga.attention_forward_prepared(Q, K, V, rp, ci, 0.125, plan, ws, want_lse=True)
+    torch.cuda.synchronize()
+    assert torch.equal(O1, O3) and torch.equal(l1, l3)
+    _agree(O1, l1, O2, l2, "f32")
+    # a continued state would show a row merged by both paths
+    sga.attention_accumulate(Q, K, V, rp, ci, 0.125, O1, l1, workspace=ws)
+    torch.cuda.synchronize()
+    _agree(O1, l1 - 0.6931472, O2, l2, "f32")
