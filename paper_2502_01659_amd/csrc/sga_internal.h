@@ -247,7 +247,7 @@ __host__ __device__ inline WorkspacePlan plan_workspace(int64_t L, int32_t H, in
 __host__ __device__ inline bool row_is_split(int64_t deg, const WorkspacePlan& p) {
   return deg > kSplitThreshold || (p.l2_chunks && deg >= (int64_t)kL2ChunkEdges * p.l2_chunks);
 }
-// ... into nchunks chunks of len edges (the last one shorter), len a multiple of 32.
+// ... into nchunks chunks of len edges (the last one shorter), len a multiple of 32 where they are cut by edge count.
 // The slots are sized for chunks of split_chunk edges with every row of the mask split; where
 // the split rows hold a small part of the edges (a few dense rows beside a window), the same
 // slots take chunks of kSplitChunkMin edges: the call uses this finer split (fine = true)
@@ -261,9 +261,13 @@ __host__ __device__ inline void row_split_shape(int64_t deg, const WorkspacePlan
   if (n > kMaxSplitLong) n = kMaxSplitLong;
   // (a row of more than kMaxSplit chunks by edge count keeps them: there are few such rows in a
   // call, and each has to spread over the chip before it can share an L2 with its neighbours)
-  if (n <= kMaxSplit && p.l2_chunks && deg >= (int64_t)kL2ChunkEdges * p.l2_chunks) n = p.l2_chunks;
+  // By share every row has n chunks: in multiples of 32, 1,106 neighbours would be 7 chunks of 160, which leave
+  // an XCD idle and shift the chunks of one row against the key ranges of the next (random 4.5 %, L = 24,576, fp32,
+  // us: 648 with chunk 7 missing, 1,191 with the rows' seven in turn on all XCDs, 620 so).
+  const bool by_share = n <= kMaxSplit && p.l2_chunks && deg >= (int64_t)kL2ChunkEdges * p.l2_chunks;
+  if (by_share) n = p.l2_chunks;
   int64_t l = (deg + n - 1) / n;
-  l = (l + 31) / 32 * 32;
+  if (!by_share) l = (l + 31) / 32 * 32;
   len = (int32_t)l;
   nchunks = (int32_t)((deg + l - 1) / l);
 }

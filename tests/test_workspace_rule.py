@@ -1,5 +1,5 @@
-"""The rule that sizes the work items of the tile path (seg_shift), evaluated on the host as the kernels
-evaluate it: sga_internal.h is compiled for the host and asked over a grid of sizes."""
+"""The rules that size the work items of the tile path (seg_shift) and the chunks of split rows, evaluated on
+the host as the kernels evaluate them: sga_internal.h is compiled for the host and asked over a grid of sizes."""
 import os
 import subprocess
 
@@ -11,11 +11,13 @@ PROGRAM = r"""
 #include <stdio.h>
 #include "sga_internal.h"
 int main() {
-  long long L, nnz;
+  long long L, nnz, deg;
   int H, dtype, d;
-  while (scanf("%lld %lld %d %d %d", &L, &nnz, &H, &dtype, &d) == 5) {
+  while (scanf("%lld %lld %d %d %d %lld", &L, &nnz, &H, &dtype, &d, &deg) == 6) {
     const sga::WorkspacePlan p = sga::plan_workspace(L, H, nnz, dtype, d);
-    printf("%d %lld %lld\n", p.seg_shift, (long long)p.n_work, (long long)p.cap_tparts);
+    int chunks, len;
+    sga::row_split_shape(deg, p, false, chunks, len);
+    printf("%d %lld %lld %d %d %d\n", p.seg_shift, (long long)p.n_work, (long long)p.cap_tparts, p.l2_chunks, chunks, len);
   }
   return 0;
 }
@@ -32,7 +34,7 @@ def plans(tmp_path_factory):
                     str(work / "rule.hip"), "-o", exe], check=True)
 
     def ask(cases):
-        text = "".join("%d %d %d %d %d\n" % c for c in cases)
+        text = "".join("%d %d %d %d %d %d\n" % (c if len(c) == 6 else c + (1,)) for c in cases)
         out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
         return [tuple(int(x) for x in line.split()) for line in out.splitlines()]
     return ask
@@ -52,7 +54,7 @@ def test_segments_of_dense_masks_fit_their_partial_states(plans):
     the items chosen fit too (else every cut tile would run on the per-row kernels)."""
     cases = list(_grid(0))
     fitted = 0
-    for (L, nnz, H, _, d), (shift, n_work, cap) in zip(cases, plans(cases)):
+    for (L, nnz, H, _, d), (shift, n_work, cap, _, _, _) in zip(cases, plans(cases)):
         assert 12 <= shift <= 15
         if nnz >> 15 <= 32768:
             assert nnz >> shift <= cap, (L, nnz, H, d, shift, cap)
@@ -68,7 +70,7 @@ def test_items_are_shortened_only_where_tiles_are_cut(plans):
     shorter = set()
     for dtype, longest, shortest, items in ((0, 15, 12, 1024), (1, 18, 15, 4096)):
         cases = list(_grid(dtype))
-        for (L, nnz, H, _, d), (shift, _, _) in zip(cases, plans(cases)):
+        for (L, nnz, H, _, d), (shift, *_) in zip(cases, plans(cases)):
             want = longest
             while want > shortest and (nnz * H >> want) < items:
                 want -= 1
@@ -79,3 +81,17 @@ def test_items_are_shortened_only_where_tiles_are_cut(plans):
             assert nnz * H >> (shift + 1) < (8192 if shift == 14 else 4096), (L, nnz, H, d, shift)
             shorter.add(shift)
     assert shorter == {13, 14}
+
+
+def test_rows_cut_by_l2_share_have_all_their_chunks(plans):
+    """Chunk c of every such row runs on XCD c % 8 against the c-th part of the keys: with a chunk less, an
+    XCD idles and the others' parts no longer fit their L2."""
+    cases = [(L, L * L // 10, 1, dtype, 64, deg) for dtype, L in ((0, 7000), (0, 24576), (1, 13000), (1, 30000))
+             for deg in (1024, 1025, 1055, 1106, 1121, 1536, 1537, 2047, 2048, 2049, 2458, 5000, L)]
+    seen = 0
+    for (L, _, _, dtype, _, deg), (_, _, _, n, chunks, length) in zip(cases, plans(cases)):
+        assert (chunks - 1) * length < deg <= chunks * length
+        if n and deg >= 128 * n:
+            assert chunks == n, (L, dtype, deg, chunks)
+            seen += 1
+    assert seen >= 40
