@@ -13,6 +13,8 @@
 // Rows with more than kSplitThreshold neighbours (global tokens) are split into chunks
 // that separate wavefronts reduce to partial (m, l, acc) states; a merge kernel combines
 // the partials in chunk order, so the result is deterministic.
+#include <type_traits>
+
 #include "sga_internal.h"
 #include "tile_merge.h"
 
@@ -624,6 +626,36 @@ __global__ __launch_bounds__(256) void nonlocal_merge_kernel(T* __restrict__ O, 
                              accumulate != 0);
 }
 
+// Which calls run shared_chunk_kernel: those of dense enough random rows.  The host asks whether the mask may be one
+// (its workspace has room for that many edges; an empty launch costs a small call 3 us), the chunk kernels
+// of such a call then look at the mask itself.
+// Where rows are cut by L2 share the other kernel reads K and V from its XCD's L2, and the line lies at an 18th of
+// the pairs for fp32 (us, that / this kernel, L = 24,576, d = 64: 4.5 % 620 / 651, 5 % 627 / 625, 5.5 % 675 / 655,
+// 10 % 1,287 / 880; L = 12,001, 10 % 317 / 259; d = 128, L = 13,001, 10 % 668 / 603); fp16 stays there (L = 24,576,
+// d = 64, 10 % 765 / 880; d = 128, L = 13,001, 8 % 393 / 480).  Where the partial states of that split have no room,
+// this kernel is the faster one down to a 25th for fp16 and below a 30th for fp32 (fp32 / fp16, d = 64, two heads,
+// L = 24,576, 10 % 4,700 -> 1,535 / 1,909 -> 1,611; one head, L = 44,001, 5 % 3,975 -> 1,949 / 2,560 -> 1,999; L = 65,001,
+// 3.4 % 6,947 -> 3,313 / 3,825 -> 3,900; d = 128, L = 24,576, 10 % 4,971 -> 1,627 / 2,844 -> 1,360); with fewer edges
+// to a step the sums lose accuracy (L = 90,001, 2.5 %, fp32: 3.7e-7 against 3.4e-7).
+constexpr int64_t kSharedMaxKeys = int64_t(1) << 16;
+constexpr uint32_t kSharedMinRows = 2048;
+constexpr int64_t kSharedFillByShare = 18;
+__host__ __device__ constexpr int64_t shared_fill(int32_t dtype) { return dtype == SGA_F32 ? 30 : 25; }
+inline bool shared_chunks_possible(const AttnArgs& a) {
+  if (!(a.d == 64 || a.d == 128) || a.L > kSharedMaxKeys || l2_chunks(a.L, a.d, a.dtype) == 0) return false;
+  const int shift = seg_shift_min(a.dtype);
+  WorkspacePlan p = plan_workspace(a.L, a.H, a.L * (a.L / shared_fill(a.dtype)), a.dtype, a.d, shift);
+  if (p.l2_chunks && a.dtype == SGA_F32)
+    p = plan_workspace(a.L, a.H, a.L * (a.L / kSharedFillByShare), a.dtype, a.d, shift);
+  return p.total_bytes <= a.ws_bytes;
+}
+__device__ __forceinline__ bool shared_chunks(const WorkspacePlan& pl, const int64_t* row_ptr, int64_t L, int32_t dtype,
+                                              uint32_t n_long, uint32_t max_chunks) {
+  if (pl.l2_chunks && dtype == SGA_F16) return false;
+  return max_chunks <= (uint32_t)kMaxSplit && n_long >= kSharedMinRows &&
+         row_ptr[L] / L >= L / (pl.l2_chunks ? kSharedFillByShare : shared_fill(dtype));
+}
+
 // One wavefront per (chunk of a long row, head): partial state of a slice of the row.  Chunk c
 // of every row is computed on XCD c % 8 (workgroups go to the XCDs round-robin in launch order
 // and gridDim.x is a multiple of 8): chunks are ranges of the rows' sorted neighbour lists, so
@@ -636,7 +668,7 @@ template <typename T, int D>
 __device__ __forceinline__ void gather_chunk_body(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int64_t L, float scale,
-    void* ws, size_t ws_bytes, int skip_tiled, uint32_t wg, uint32_t n_wg) {
+    void* ws, size_t ws_bytes, int skip_tiled, int may_share, uint32_t wg, uint32_t n_wg) {
   const int32_t H = (int32_t)gridDim.y;
   constexpr int32_t dtype = DtypeOf<T>::code;
   if (!split_active(row_ptr, L, H, dtype, D, ws, ws_bytes)) return;
@@ -644,6 +676,7 @@ __device__ __forceinline__ void gather_chunk_body(
   const uint32_t n_long = reinterpret_cast<const uint32_t*>(ws)[kCtrLongRows];
   uint32_t max_chunks;
   const int4* lr = long_rows(pl, ws, max_chunks);
+  if (may_share && shared_chunks(pl, row_ptr, L, dtype, n_long, max_chunks)) return;      // (shared_chunk_kernel)
   float* partials = reinterpret_cast<float*>(static_cast<char*>(ws) + pl.off_partials);
   const int lane = threadIdx.x & (kWave - 1);
   const int waves = blockDim.x / kWave;
@@ -688,8 +721,324 @@ template <typename T, int D>
 __global__ __launch_bounds__(256) void gather_chunk_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int64_t L, float scale,
+    void* ws, size_t ws_bytes, int skip_tiled, int may_share) {
+  gather_chunk_body<T, D>(Q, K, V, row_ptr, col_idx, L, scale, ws, ws_bytes, skip_tiled, may_share, blockIdx.x, gridDim.x);
+}
+
+// ---- chunks of many split rows: K and V through LDS ---------------------------------------------
+// Every edge of gather_chunk_kernel draws its own K and V row through the vector L1 (30.9 GB at 21.9 TB/s for a
+// tenth of the pairs of L = 24,576, d = 64, fp32) and spends 8 vector instructions, most of them on sums and
+// softmax steps that the 16 lanes of a group repeat.  Where many rows are split and their neighbours
+// are dense enough, a workgroup takes the same chunk of kRows rows, 16 lanes each, and passes over the
+// key blocks of the chunk's range: a block's K and V rows are copied to LDS once and each row's
+// neighbours in it are read from there, up to 16 at a time.  The 16 partial dot products
+// of a lane are summed over the lanes by halves, so that lane e ends with the score of edge e: maximum,
+// exponential and sum cost one lane each, and the products with V take the numerator of
+// edge e from lane e (row_newbcast).  The chunk of a row is a part of the keys here, not of its edges: by
+// edges, the chunks of 64 rows spread over half as many blocks again (1,164 us).  The products of a step
+// are added to the row's state at once: 24 additions per chunk at that density where a group of
+// gather_chunk_kernel does 77.
+// That case: 1,276 -> 835 us (880 in a loop of nothing else), error 2.2e-7 -> 1.9e-7.  Bound by the vector unit (busy 82 % of the time): 13 of
+// 16 slots of a step hold an edge, and four rows of a wavefront wait for the longest.  d = 64: one buffer, two
+// workgroups per CU, 64 registers (7 spill outside the steps); two buffers and one workgroup 1,061 us.
+//
+// A row's steps are cut at its own key blocks (multiples of kKeys) and nowhere else, so its result does not
+// depend on the rows it shares a workgroup with, nor on whether the block came through LDS: where the
+// rows' ranges have little in common (kKeys keys copied for fewer edges) every row reads its own.
+template <typename T, int D>
+struct SharedChunk {
+  static constexpr int kVec = D / 16;                        // channels per lane
+  static constexpr int kRowBytes = D * (int)sizeof(T);
+  static constexpr int kBuffers = kVec > 4 ? 2 : 1;
+  static constexpr int kThreads = 1024;
+  static constexpr int kKeys = kRowBytes > 256 ? 64 : 128;   // 66 KB for K and V of a block (fp16, d = 64: 33)
+  static constexpr int kRows = kThreads / 16;
+  static constexpr int kBatch = 4;                           // edges whose rows are read together (registers)
+  static constexpr int kPlane = (kKeys + 1) * kRowBytes;     // the row of zeros behind the block stands in for edges that are not there
+
+  // Byte offset of a lane's channels inside a row, and the channel of its element k.  (fp32, d = 128: two
+  // 16-byte parts 256 bytes apart, so that every read of 16 lanes is 256 contiguous bytes.)
+  __device__ static uint32_t lane_bytes(int l16) { return l16 * (sizeof(T) == 2 && kVec == 4 ? 8 : 16); }
+  __device__ static int channel(int l16, int k) {
+    return sizeof(T) == 4 && kVec == 8 ? (k >> 2) * 64 + 4 * l16 + (k & 3) : kVec * l16 + k;
+  }
+  __device__ static void load(const char* p, float (&v)[kVec]) {
+    if constexpr (sizeof(T) == 4) {
+#pragma unroll
+      for (int i = 0; i < kVec / 4; ++i) {
+        const float4 t = *reinterpret_cast<const float4*>(p + i * 256);
+        v[4 * i] = t.x; v[4 * i + 1] = t.y; v[4 * i + 2] = t.z; v[4 * i + 3] = t.w;
+      }
+    } else {
+      using half_vec = _Float16 __attribute__((ext_vector_type(kVec)));
+      const half_vec t = *reinterpret_cast<const half_vec*>(p);
+#pragma unroll
+      for (int k = 0; k < kVec; ++k) v[k] = (float)t[k];
+    }
+  }
+};
+
+// the bits of a ballot that belong to this lane's 16
+__device__ __forceinline__ int count16(uint64_t ballot, int lane) {
+  return __popc(__builtin_amdgcn_ubfe(lane & 32 ? (uint32_t)(ballot >> 32) : (uint32_t)ballot, lane & 16, 16));
+}
+
+// lane u of each 16
+template <int U>
+__device__ __forceinline__ int bcast16(int x) {
+  return __builtin_amdgcn_mov_dpp(x, 0x150 + U, 0xf, 0xf, true);
+}
+template <int N, typename F>
+__device__ __forceinline__ void unrolled(const F& f) {
+  if constexpr (N > 0) {
+    unrolled<N - 1>(f);
+    f(std::integral_constant<int, N - 1>{});
+  }
+}
+
+// One step of a row's 16 lanes: up to 16 edges, lane e holding edge e (valid), its row `off` bytes into K and
+// V.  held: the valid lanes of the wavefront (a prefix of every 16).
+template <typename T, int D, bool kLds>
+__device__ __forceinline__ void attend_step(const char* Kb, const char* Vb, uint32_t off, bool valid, uint64_t held,
+                                            int l16, const float (&q)[D / 16], float& m, float& l,
+                                            float (&acc)[D / 16]) {
+  using S = SharedChunk<T, D>;
+  constexpr int kVec = S::kVec;
+  const uint32_t own = S::lane_bytes(l16);
+  auto load = [&](const char* base, uint32_t at, bool there, float (&v)[kVec]) {
+    if (kLds) {
+      S::load(base + at, v);
+      return;
+    }
+#pragma unroll
+    for (int k = 0; k < kVec; ++k) v[k] = 0.f;
+    if (there) S::load(base + at, v);
+  };
+  auto product = [&](auto edge) {           // of this lane's channels
+    constexpr int u = decltype(edge)::value;
+    float kf[kVec];
+    load(Kb, (uint32_t)bcast16<u>((int)off) + own, kLds || bcast16<u>(valid), kf);
+    float part = q[0] * kf[0];
+#pragma unroll
+    for (int k = 1; k < kVec; ++k) part = __builtin_fmaf(q[k], kf[k], part);
+    return part;
+  };
+  // halves: lane l and lane l ^ 8 add up edge u (lanes 0 to 7) and edge u + 8 (lanes 8 to 15), and so on
+  float a[8], b[4], c[2];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) a[u] = 0.f;
+  unrolled<8 / S::kBatch>([&](auto batch) {
+    constexpr int g = S::kBatch * decltype(batch)::value;
+    if (g > 0 && !(held & (0x0001000100010001ull << g))) return;
+    unrolled<S::kBatch>([&](auto i) { a[g + decltype(i)::value] = product(std::integral_constant<int, g + decltype(i)::value>{}); });
+    if (held & (0x0100010001000100ull << g)) {
+      unrolled<S::kBatch>([&](auto i) {
+        constexpr int u = g + decltype(i)::value;
+        const float upper = product(std::integral_constant<int, u + 8>{});
+        a[u] = (l16 & 8 ? upper : a[u]) + dpp<0x128>(l16 & 8 ? a[u] : upper);                     // row_ror:8
+      });
+    } else {
+      unrolled<S::kBatch>([&](auto i) { a[g + decltype(i)::value] += dpp<0x128>(a[g + decltype(i)::value]); });
+    }
+  });
+#pragma unroll
+  for (int u = 0; u < 4; ++u) b[u] = (l16 & 4 ? a[u + 4] : a[u]) + dpp<0x141>(l16 & 4 ? a[u] : a[u + 4]);   // row_half_mirror
+#pragma unroll
+  for (int u = 0; u < 2; ++u) c[u] = (l16 & 2 ? b[u + 2] : b[u]) + dpp<0x4E>(l16 & 2 ? b[u] : b[u + 2]);    // quad_perm [2,3,0,1]
+  const float sum = (l16 & 1 ? c[1] : c[0]) + dpp<0xB1>(l16 & 1 ? c[0] : c[1]);                             // quad_perm [1,0,3,2]
+  const float score = valid ? sum : -INFINITY;
+  float most = fmaxf(score, dpp<0xB1>(score));
+  most = fmaxf(most, dpp<0x4E>(most));
+  most = fmaxf(most, dpp<0x141>(most));
+  most = fmaxf(most, dpp<0x140>(most));
+  most = fmaxf(m, most);
+  const float alpha = __builtin_amdgcn_exp2f(m - most);
+  const float p = __builtin_amdgcn_exp2f(score - most);
+  m = most;
+  l = __builtin_fmaf(l, alpha, p);
+  float now[kVec];
+#pragma unroll
+  for (int k = 0; k < kVec; ++k) now[k] = 0.f;
+  unrolled<16 / S::kBatch>([&](auto batch) {
+    constexpr int g = S::kBatch * decltype(batch)::value;
+    if (g > 0 && !(held & (0x0001000100010001ull << g))) return;
+    unrolled<S::kBatch>([&](auto i) {
+      constexpr int u = g + decltype(i)::value;
+      float vf[kVec];
+      load(Vb, (uint32_t)bcast16<u>((int)off) + own, kLds || bcast16<u>(valid), vf);
+      const float pu = __builtin_bit_cast(float, bcast16<u>(__builtin_bit_cast(int, p)));
+#pragma unroll
+      for (int k = 0; k < kVec; ++k) now[k] = __builtin_fmaf(pu, vf[k], now[k]);
+    });
+  });
+#pragma unroll
+  for (int k = 0; k < kVec; ++k) acc[k] = __builtin_fmaf(acc[k], alpha, now[k]);
+}
+
+// key[i] -> the first of the ascending cols[0 .. n) that is not below it (n: none), by the 16 lanes of a row.
+__device__ __forceinline__ void first_at_least(const int32_t* cols, int n, int (&key)[2], int lane) {
+  const int l16 = lane & 15;
+  int lo[2] = {0, 0}, hi[2] = {n, n};
+  while (__builtin_amdgcn_ballot_w64(lo[0] < hi[0] || lo[1] < hi[1])) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int step = (hi[i] - lo[i] + 15) / 16, at = lo[i] + (l16 + 1) * step - 1;
+      const bool below = at < hi[i] && step > 0 && cols[at] < key[i];
+      const int k = count16(__builtin_amdgcn_ballot_w64(below), lane);
+      hi[i] = step > 0 ? min(hi[i], lo[i] + (k + 1) * step - 1) : hi[i];
+      lo[i] += k * step;
+    }
+  }
+  key[0] = lo[0];
+  key[1] = lo[1];
+}
+
+template <typename T, int D>
+__global__ __attribute__((amdgpu_waves_per_eu((D == 64 ? 8 : 4), (D == 64 ? 8 : 4)))) __launch_bounds__((SharedChunk<T, D>::kThreads)) void shared_chunk_kernel(
+    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
+    const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int64_t L, float scale,
     void* ws, size_t ws_bytes, int skip_tiled) {
-  gather_chunk_body<T, D>(Q, K, V, row_ptr, col_idx, L, scale, ws, ws_bytes, skip_tiled, blockIdx.x, gridDim.x);
+  using S = SharedChunk<T, D>;
+  constexpr int kVec = S::kVec;
+  __shared__ __attribute__((aligned(16))) char planes[2 * S::kBuffers * S::kPlane];
+  __shared__ int range[3];                  // first and last key block of the unit, its edges
+  const int32_t H = (int32_t)gridDim.y;
+  constexpr int32_t dtype = DtypeOf<T>::code;
+  if (!split_active(row_ptr, L, H, dtype, D, ws, ws_bytes)) return;
+  const WorkspacePlan pl = plan_workspace(L, H, row_ptr[L], dtype, D);
+  const uint32_t n_long = reinterpret_cast<const uint32_t*>(ws)[kCtrLongRows];
+  uint32_t max_chunks;
+  const int4* lr = long_rows(pl, ws, max_chunks);
+  if (!shared_chunks(pl, row_ptr, L, dtype, n_long, max_chunks)) return;
+  float* partials = reinterpret_cast<float*>(static_cast<char*>(ws) + pl.off_partials);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int lane = threadIdx.x & (kWave - 1), l16 = lane & 15;
+  const int64_t h = blockIdx.y;
+  const char* Kb = reinterpret_cast<const char*>(K + h * L * D);
+  const char* Vb = reinterpret_cast<const char*>(V + h * L * D);
+  // (the rows of zeros stay)
+  if (threadIdx.x < S::kRowBytes / 4) {
+#pragma unroll
+    for (int i = 0; i < 2 * S::kBuffers; ++i)
+      reinterpret_cast<uint32_t*>(planes + i * S::kPlane + S::kKeys * S::kRowBytes)[threadIdx.x] = 0;
+  }
+  const uint32_t cohorts = (n_long + S::kRows - 1) / S::kRows;
+  // as in gather_chunk_kernel: chunk c on XCD c % 8, or, where there are fewer than 8, all units on all XCDs in turn
+  const bool few = max_chunks < 8;
+  const uint64_t n_units = few ? (uint64_t)cohorts * max_chunks : 8 * (uint64_t)cohorts * ((max_chunks + 7) / 8);
+  for (uint64_t u = blockIdx.x; u < n_units; u += gridDim.x) {
+    const uint32_t cohort = (uint32_t)(few ? u / max_chunks : (u >> 3) % cohorts);
+    const int c = (int)(few ? u % max_chunks : (u & 7) + 8 * ((u >> 3) / cohorts));
+    const uint32_t r = cohort * S::kRows + threadIdx.x / 16;
+    const int4 rec = r < n_long ? lr[r] : make_int4(0, 0, 0, 0);        // {row, first partial slot, chunks, chunk length}
+    const bool active = c < rec.z && !passed_over(pl, ws, row_ptr, L, rec.x, skip_tiled);
+    const int64_t r0 = row_ptr[rec.x];
+    const int deg = (int)(row_ptr[rec.x + 1] - r0);
+    const int32_t* cols = col_idx + r0;
+    // this row's edges: those of the c-th of rec.z equal parts of the key blocks, found by 16-way searches
+    const int n_blocks = (int)((L + S::kKeys - 1) / S::kKeys);
+    int bound[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) bound[i] = active ? (int)((int64_t)(c + i) * n_blocks / rec.z) * S::kKeys : 0;
+    first_at_least(cols, active ? deg : 0, bound, lane);
+    int e = bound[0];                       // the next edge
+    const int e1 = bound[1];
+    const int last = max(e1 - 1, 0);
+    __syncthreads();                        // the previous unit's range has been read
+    if (threadIdx.x == 0) {
+      range[0] = INT32_MAX;
+      range[1] = -1;
+      range[2] = 0;
+    }
+    __syncthreads();
+    if (l16 == 0 && e < e1) {
+      atomicMin(&range[0], cols[e] / S::kKeys);
+      atomicMax(&range[1], cols[last] / S::kKeys);
+      atomicAdd(&range[2], e1 - e);
+    }
+    __syncthreads();
+    const int b0 = __builtin_amdgcn_readfirstlane(range[0]), b1 = __builtin_amdgcn_readfirstlane(range[1]);
+    const int edges = __builtin_amdgcn_readfirstlane(range[2]);
+    float q[kVec], acc[kVec], m = kMinusHuge, l = 0.f;
+    S::load(reinterpret_cast<const char*>(Q + (h * L + rec.x) * D) + S::lane_bytes(l16), q);
+    const float scale2 = scale * kLog2e;
+#pragma unroll
+    for (int k = 0; k < kVec; ++k) {
+      q[k] *= scale2;
+      acc[k] = 0.f;
+    }
+    // (a row without edges in this unit reads no column: its loads are of the call's first, which exists)
+    const int32_t* own_cols = e < e1 ? cols : col_idx;
+    if (edges > 0 && (int64_t)(b1 - b0 + 1) * S::kKeys <= edges) {
+      auto stage = [&](int blk) {
+        char* const to = planes + ((blk - b0) & (S::kBuffers - 1)) * 2 * S::kPlane;
+        const int64_t first = (int64_t)blk * S::kKeys * S::kRowBytes, left = L * S::kRowBytes - first;
+        const uint32_t end = (uint32_t)min(left, (int64_t)S::kKeys * S::kRowBytes) - 16;    // (bytes past the last key are not read back)
+#pragma unroll
+        for (int i = 0; i < S::kKeys * S::kRowBytes / (16 * S::kThreads); ++i) {
+          const int part = (i * S::kThreads + wave * kWave) * 16;       // this wavefront's 1,024 bytes
+          const uint32_t at = min((uint32_t)(part + lane * 16), end);
+          copy16_to_lds_untracked(Kb + first + at, to + part);
+          copy16_to_lds_untracked(Vb + first + at, to + S::kPlane + part);
+        }
+      };
+      if (S::kBuffers > 1) stage(b0);
+      int32_t c0 = own_cols[min(e + l16, last)], c1 = own_cols[min(e + 16 + l16, last)];
+      __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wavefront's copies are there
+      __syncthreads();
+      for (int blk = b0; blk <= b1; ++blk) {
+        if (S::kBuffers > 1) {
+          if (blk < b1) stage(blk + 1);
+        } else {
+          stage(blk);
+          __builtin_amdgcn_s_waitcnt(0x0F70);
+          __syncthreads();
+        }
+        const char* const lds_k = planes + ((blk - b0) & (S::kBuffers - 1)) * 2 * S::kPlane;
+        const int key0 = blk * S::kKeys;
+        uint64_t held1;
+        do {
+          // the next 32 columns of the row, those of this block among them (the block's end, or the row's, ends them)
+          const int k0 = c0 - key0, k1 = c1 - key0;
+          const bool v0 = e + l16 < e1 && (uint32_t)k0 < (uint32_t)S::kKeys;
+          const bool v1 = e + 16 + l16 < e1 && (uint32_t)k1 < (uint32_t)S::kKeys;
+          const uint64_t held0 = __builtin_amdgcn_ballot_w64(v0);
+          held1 = __builtin_amdgcn_ballot_w64(v1);
+          e += count16(held0, lane) + count16(held1, lane);
+          c0 = own_cols[min(e + l16, last)];
+          c1 = own_cols[min(e + 16 + l16, last)];
+          if (held0)
+            attend_step<T, D, true>(lds_k, lds_k + S::kPlane, (uint32_t)((v0 ? k0 : S::kKeys) * S::kRowBytes), v0, held0, l16,
+                                    q, m, l, acc);
+          if (held1)
+            attend_step<T, D, true>(lds_k, lds_k + S::kPlane, (uint32_t)((v1 ? k1 : S::kKeys) * S::kRowBytes), v1, held1, l16,
+                                    q, m, l, acc);
+        } while (held1 & 0x8000800080008000ull);      // some row may go on in this block
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        __syncthreads();                    // the next block is there and every wavefront has left this one
+      }
+    } else {
+      while (true) {                        // every row at its own block
+        const int at = e + l16;
+        const int32_t col = own_cols[min(at, last)];
+        const bool valid = at < e1 && col / S::kKeys == bcast16<0>(col) / S::kKeys;
+        const uint64_t held = __builtin_amdgcn_ballot_w64(valid);
+        if (held == 0) break;
+        attend_step<T, D, false>(Kb, Vb, (uint32_t)col * S::kRowBytes, valid, held, l16, q, m, l, acc);
+        e += count16(held, lane);
+      }
+    }
+    l = group_sum<16>(l);
+    if (active) {
+      float* p = partials + ((int64_t)(rec.y + c) * H + h) * (D + 4);
+#pragma unroll
+      for (int k = 0; k < kVec; ++k) p[S::channel(l16, k)] = acc[k];
+      if (l16 == 0) {
+        p[D] = m;
+        p[D + 1] = l;
+      }
+    }
+  }
 }
 
 // What the tile path leaves over, in one launch for the call that does not know whether there is anything
@@ -701,7 +1050,8 @@ template <typename T, int D>
 __global__ __launch_bounds__(256) void leftovers_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
     float* __restrict__ lse, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
-    int64_t L, float scale, void* ws, size_t ws_bytes, int use_split, int accumulate, uint32_t n_merge, uint32_t n_rows) {
+    int64_t L, float scale, void* ws, size_t ws_bytes, int use_split, int may_share, int accumulate,
+    uint32_t n_merge, uint32_t n_rows) {
   if (blockIdx.x < n_merge)
     tile_merge_body<T, D>(O, lse, row_ptr, L, ws, ws_bytes, accumulate, blockIdx.x / kTile, n_merge / kTile,
                           blockIdx.x % kTile, kTile);
@@ -709,7 +1059,7 @@ __global__ __launch_bounds__(256) void leftovers_kernel(
     gather_csr_body<T, D>(Q, K, V, O, lse, row_ptr, col_idx, L, scale, ws, ws_bytes, use_split, 1, accumulate,
                           blockIdx.x - n_merge, n_rows);
   else
-    gather_chunk_body<T, D>(Q, K, V, row_ptr, col_idx, L, scale, ws, ws_bytes, 1, blockIdx.x - n_merge - n_rows,
+    gather_chunk_body<T, D>(Q, K, V, row_ptr, col_idx, L, scale, ws, ws_bytes, 1, may_share, blockIdx.x - n_merge - n_rows,
                             gridDim.x - n_merge - n_rows);
 }
 
@@ -788,6 +1138,7 @@ sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
   const bool mark = !skip_tiled || (a.prepared && a.plan_no_tiles);
   const bool mark_chunks = mark && a.prepared && a.plan_long_rows > 0;
   const bool fused = D >= kHeadDim && skip_tiled && !a.prepared;     // (nothing known about what is left)
+  const bool may_share = split && shared_chunks_possible(a) && (!a.prepared || a.plan_long_rows >= kSharedMinRows);
   if constexpr (D >= kHeadDim) {
     if (fused) {
       // chunks: a chip-full of workgroups over the heads, fewer where L leaves little to split
@@ -797,7 +1148,7 @@ sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
       const unsigned n_rows = ((unsigned)nwg + 7u) & ~7u, n_merge = merge_tiles(a) * kTile;
       hipLaunchKernelGGL((leftovers_kernel<T, D>), dim3(n_merge + n_rows + (unsigned)chunk_wgs, (unsigned)a.H), dim3(256),
                          0, a.stream, Q, K, V, O, a.lse, a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes,
-                         split ? 1 : 0, a.accumulate ? 1 : 0, n_merge, n_rows);
+                         split ? 1 : 0, may_share ? 1 : 0, a.accumulate ? 1 : 0, n_merge, n_rows);
     }
   }
   if (!fused && !(a.prepared && a.plan_long_rows == a.L)) {       // (a prepared graph all of whose rows are split: 19 us of L = 24,576)
@@ -812,9 +1163,17 @@ sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
       const unsigned chunk_wgs = skip_tiled && a.H >= 8 ? 128 : 1024;
       if (mark_chunks) profile_mark_begin(a.stream, "gather_chunk_kernel");
       hipLaunchKernelGGL((gather_chunk_kernel<T, D>), dim3(chunk_wgs, (unsigned)a.H), dim3(256), 0, a.stream, Q,
-                         K, V, a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes, skip_tiled ? 1 : 0);
-      if (mark_chunks) profile_mark_end(a.stream);
+                         K, V, a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes, skip_tiled ? 1 : 0, may_share ? 1 : 0);
     }
+    if constexpr (D == 64 || D == 128) {
+      if (may_share) {
+        using S = SharedChunk<T, D>;
+        const unsigned wgs = D == 64 ? 512 : 256;        // what the chip holds
+        hipLaunchKernelGGL((shared_chunk_kernel<T, D>), dim3(wgs, (unsigned)a.H), dim3(S::kThreads), 0, a.stream, Q, K, V,
+                           a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes, skip_tiled ? 1 : 0);
+      }
+    }
+    if (mark_chunks) profile_mark_end(a.stream);
     // one wavefront per long row and head, one workgroup for a row of more than kMaxSplit
     // chunks; a prepared graph knows how many rows there are
     int64_t merge_wgs = a.prepared ? (int64_t)a.plan_long_rows : (a.L + 15) / 16;

@@ -420,6 +420,24 @@ struct AttnArgs {
   uint32_t plan_long_rows;     // split rows among the leftover rows whose chunk items fit
 };
 
+// Global -> LDS copy of 16 bytes per lane without passing through registers: lane l's 16 bytes
+// land at dst + 16*l (dst is wave-uniform).  Completion is tracked by vmcnt.
+__device__ __forceinline__ void copy16_to_lds(const void* src, char* dst) {
+  __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)src,
+                                   (void __attribute__((address_space(3)))*)dst, 16, 0, 0);
+}
+// copy16_to_lds issued behind the compiler's back.  While it knows of copies in flight, the
+// compiler waits for all of them before any LDS read it cannot prove to be elsewhere; the
+// caller of this one orders the reads itself, by counted waits.
+__device__ __forceinline__ void copy16_to_lds_untracked(const void* src, char* dst) {
+  const uint32_t at = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(char __attribute__((address_space(3)))*)dst);
+  uint32_t m0_kept;    // (M0 holds the LDS address of the copy; the compiler's own value is put back)
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\t"
+               "s_mov_b32 m0, %0"
+               : "=&s"(m0_kept) : "s"(at), "v"(src) : "memory");
+}
+
 // gather path (attention_gather.hip)
 // Zeroes the counters (and, when row_ptr is given, the per-tile flags of the tile path).
 void clear_workspace(const AttnArgs& a, bool tile_flags);

@@ -411,6 +411,67 @@ def test_rows_split_into_a_few_chunks(d, dtype):
         _close(O[h].cpu().numpy()[rows], lse[h].cpu().numpy()[rows], O_ref, lse_ref, dtype)
 
 
+@pytest.mark.parametrize("d,dtype,L,H", [(64, "f32", 9001, 1), (64, "f32", 16321, 2), (64, "f16", 18017, 2),
+                                         (128, "f32", 8961, 1), (128, "f32", 18001, 1), (128, "f16", 18049, 1)])
+@pytest.mark.parametrize("even", [True, False])
+def test_many_split_rows_share_their_key_blocks(d, dtype, L, H, even):
+    """Random rows dense enough for shared_chunk_kernel, cut into 2 and into 8 chunks: lengths that end inside a
+    key block, short and empty rows in between, and (even = False) a quarter of the keys that only every 100th
+    row sees, where each row reads its own.  Values of keys nobody attends are NaN and stay out.  Every row
+    against the same call without a workspace (no row is split then), sampled rows against the dense oracle,
+    a rerun and a prepared graph bit for bit."""
+    import torch
+    print("case shared chunks", d, dtype, L, H, even, flush=True)
+    rng = np.random.default_rng(79)
+    cols, deg = [], np.zeros(L, dtype=np.int64)
+    for r0 in range(0, L, 1000):
+        n = min(1000, L - r0)
+        block = rng.random((n, L), dtype=np.float32) < 0.122
+        i = np.arange(r0, r0 + n)
+        block[i % 50 == 7] &= rng.random((L,), dtype=np.float32) < 0.02
+        block[i == 11] = False
+        block[:, 3] = False                            # a key of no row
+        if not even:
+            block[i % 100 != 0, : L // 4] = False
+            block[i % 100 != 0, L // 4 :] |= rng.random((1, L - L // 4), dtype=np.float32) < 0.04
+            block[:, 3] = False
+        deg[r0:r0 + n] = block.sum(1)
+        cols.append(np.nonzero(block)[1].astype(np.int32))
+    rp = np.concatenate([[0], deg.cumsum()])
+    ci = np.concatenate(cols)
+    kv = 2 * L * d * (4 if dtype == "f32" else 2)
+    assert kv > 3 << 20 and rp[-1] // L >= L // 18 and (deg >= 8 * 128).sum() > 2048
+    Q, K, V = numpy_qkv(H, L, d, dtype, 0.6, 33)
+    K[:, 3], V[:, 3] = np.nan, np.nan
+    dQ, dK, dV = to_device(Q, K, V)
+    drp, dci = to_device(rp, ci)
+    ws = sga.alloc_workspace(L, H, d, dtype, int(rp[-1]))
+    O1, lse1 = sga.attention_forward(dQ, dK, dV, drp, dci, 0.125, path=sga.PATH_GATHER, want_lse=True)
+    rows = np.unique(np.concatenate([np.arange(0, 20), np.arange(L - 20, L), rng.integers(0, L, 30)]))
+    mask = np.zeros((len(rows), L), dtype=bool)
+    for k, i in enumerate(rows):
+        mask[k, ci[rp[i]:rp[i + 1]]] = True
+    K[:, 3], V[:, 3] = 0, 0
+    for path in (sga.PATH_GATHER, sga.PATH_AUTO):
+        O, lse = sga.attention_forward(dQ, dK, dV, drp, dci, 0.125, workspace=ws, path=path, want_lse=True)
+        O2 = sga.attention_forward(dQ, dK, dV, drp, dci, 0.125, workspace=ws, path=path)
+        torch.cuda.synchronize()
+        assert torch.equal(O, O2)
+        assert (O.float() - O1.float()).abs().max().item() <= 2 * TOL[dtype]
+        some = deg > 0
+        some = torch.from_numpy(some).cuda()
+        assert (lse - lse1)[:, some].abs().max().item() <= 2 * LSE_TOL[dtype]
+        assert bool(torch.isneginf(lse[:, ~some]).all())
+        for h in range(H):
+            O_ref, lse_ref = R.attention_dense(Q[h][rows].astype(np.float64), K[h].astype(np.float64),
+                                               V[h].astype(np.float64), mask, 0.125)
+            _close(O[h].cpu().numpy()[rows], lse[h].cpu().numpy()[rows], O_ref, lse_ref, dtype)
+    plan = sga.graph_prepare(drp, dci, H, d, dtype, ws)
+    O3 = sga.attention_forward_prepared(dQ, dK, dV, drp, dci, 0.125, plan, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(O3, O2)
+
+
 def test_explicit_and_implicit_paths_agree():
     """The same mask through the CSR entry point and the implicit entry point (the paper's
     own cross-check between its CSR and ordered-sparsity kernels, Section V-F)."""
