@@ -357,6 +357,7 @@ sga_status sga_graph_prepare(const int64_t* row_ptr, const int32_t* col_idx, int
   a.ws = workspace; a.ws_bytes = workspace_bytes;
   clear_workspace(a, true);
   launch_tile_analyze(a);
+  if (L > kSplitThreshold && tile_parts_in_doubt(pl)) launch_split_prepass(a, true);
   uint32_t ctr[kNumCounters];
   if (hipGetLastError() != hipSuccess ||
       hipMemcpyAsync(ctr, workspace, sizeof(ctr), hipMemcpyDeviceToHost, st) != hipSuccess ||

@@ -300,14 +300,17 @@ __global__ __launch_bounds__(256) void clear_workspace_kernel(void* ws, size_t w
     next[i] = 0;          // claim counters of the heads
 }
 
-// One thread per row, see record_split_row (calls on the per-row kernels alone).
+// One thread per row, see record_split_row: the rows of a call on the per-row kernels alone, or (after_tiles) the rows
+// that the tile path left over where the CSR -> tile pass could not tell (tile_parts_in_doubt).
 __global__ __launch_bounds__(256) void split_prepass_kernel(const int64_t* __restrict__ row_ptr,
                                                             int64_t L, int32_t H, int32_t dtype,
-                                                            int32_t d, void* ws, size_t ws_bytes) {
+                                                            int32_t d, void* ws, size_t ws_bytes, int after_tiles) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= L || row_ptr[i + 1] - row_ptr[i] <= kSplitThreshold / 2) return;      // (no rule splits a row this short)
   const WorkspacePlan pl = plan_workspace(L, H, row_ptr[L], dtype, d);
-  if (pl.total_bytes <= ws_bytes) record_split_row(row_ptr, i, pl, ws);
+  if (pl.total_bytes > ws_bytes) return;
+  if (after_tiles && (!tile_parts_in_doubt(pl) || tile_handled(pl, ws, row_ptr, L, i / kTile))) return;
+  record_split_row(row_ptr, i, pl, ws);
 }
 
 // The list of long rows that this call uses: the finer split if all its chunks fit.
@@ -316,12 +319,6 @@ __device__ __forceinline__ const int4* long_rows(const WorkspacePlan& pl, const 
   const bool fine = (int64_t)ctr[kCtrFineNeeded] <= pl.cap_items;
   max_chunks = ctr[fine ? kCtrMaxChunksFine : kCtrMaxChunks];
   return reinterpret_cast<const int4*>(static_cast<const char*>(ws) + pl.off_long) + (fine ? pl.cap_items : 0);
-}
-
-// A recorded row that the tile path produced after all (skip_tiled: this call ran it), see tile_parts_in_doubt.
-__device__ __forceinline__ bool passed_over(const WorkspacePlan& pl, const void* ws, const int64_t* row_ptr, int64_t L,
-                                            int64_t i, int skip_tiled) {
-  return skip_tiled && tile_parts_in_doubt(pl) && tile_handled(pl, ws, row_ptr, L, i / kTile);
 }
 
 // True when the long rows of this call are handled by the chunk kernels.
@@ -668,7 +665,7 @@ template <typename T, int D>
 __device__ __forceinline__ void gather_chunk_body(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int64_t L, float scale,
-    void* ws, size_t ws_bytes, int skip_tiled, int may_share, uint32_t wg, uint32_t n_wg) {
+    void* ws, size_t ws_bytes, int may_share, uint32_t wg, uint32_t n_wg) {
   const int32_t H = (int32_t)gridDim.y;
   constexpr int32_t dtype = DtypeOf<T>::code;
   if (!split_active(row_ptr, L, H, dtype, D, ws, ws_bytes)) return;
@@ -692,7 +689,6 @@ __device__ __forceinline__ void gather_chunk_body(
     const int32_t c = (int32_t)(((xcd - turn) & 7) + 8 * (u / n_long));
     if (c >= rec.z) continue;
     const int64_t i = rec.x;
-    if (passed_over(pl, ws, row_ptr, L, i, skip_tiled)) continue;
     const int64_t r0 = row_ptr[i], deg = row_ptr[i + 1] - r0;
     const int64_t e0 = (int64_t)c * rec.w;
     const int64_t e1 = min(deg, e0 + rec.w);
@@ -721,8 +717,8 @@ template <typename T, int D>
 __global__ __launch_bounds__(256) void gather_chunk_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int64_t L, float scale,
-    void* ws, size_t ws_bytes, int skip_tiled, int may_share) {
-  gather_chunk_body<T, D>(Q, K, V, row_ptr, col_idx, L, scale, ws, ws_bytes, skip_tiled, may_share, blockIdx.x, gridDim.x);
+    void* ws, size_t ws_bytes, int may_share) {
+  gather_chunk_body<T, D>(Q, K, V, row_ptr, col_idx, L, scale, ws, ws_bytes, may_share, blockIdx.x, gridDim.x);
 }
 
 // ---- chunks of many split rows: K and V through LDS ---------------------------------------------
@@ -897,7 +893,7 @@ template <typename T, int D>
 __global__ __attribute__((amdgpu_waves_per_eu((D == 64 ? 8 : 4), (D == 64 ? 8 : 4)))) __launch_bounds__((SharedChunk<T, D>::kThreads)) void shared_chunk_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int64_t L, float scale,
-    void* ws, size_t ws_bytes, int skip_tiled) {
+    void* ws, size_t ws_bytes) {
   using S = SharedChunk<T, D>;
   constexpr int kVec = S::kVec;
   __shared__ __attribute__((aligned(16))) char planes[2 * S::kBuffers * S::kPlane];
@@ -931,7 +927,7 @@ __global__ __attribute__((amdgpu_waves_per_eu((D == 64 ? 8 : 4), (D == 64 ? 8 : 
     const int c = (int)(few ? u % max_chunks : (u & 7) + 8 * ((u >> 3) / cohorts));
     const uint32_t r = cohort * S::kRows + threadIdx.x / 16;
     const int4 rec = r < n_long ? lr[r] : make_int4(0, 0, 0, 0);        // {row, first partial slot, chunks, chunk length}
-    const bool active = c < rec.z && !passed_over(pl, ws, row_ptr, L, rec.x, skip_tiled);
+    const bool active = c < rec.z;
     const int64_t r0 = row_ptr[rec.x];
     const int deg = (int)(row_ptr[rec.x + 1] - r0);
     const int32_t* cols = col_idx + r0;
@@ -1059,7 +1055,7 @@ __global__ __launch_bounds__(256) void leftovers_kernel(
     gather_csr_body<T, D>(Q, K, V, O, lse, row_ptr, col_idx, L, scale, ws, ws_bytes, use_split, 1, accumulate,
                           blockIdx.x - n_merge, n_rows);
   else
-    gather_chunk_body<T, D>(Q, K, V, row_ptr, col_idx, L, scale, ws, ws_bytes, 1, may_share, blockIdx.x - n_merge - n_rows,
+    gather_chunk_body<T, D>(Q, K, V, row_ptr, col_idx, L, scale, ws, ws_bytes, may_share, blockIdx.x - n_merge - n_rows,
                             gridDim.x - n_merge - n_rows);
 }
 
@@ -1072,7 +1068,7 @@ template <typename T, int D>
 __global__ __launch_bounds__(256) void gather_merge_kernel(T* __restrict__ O, float* __restrict__ lse,
                                                            const int64_t* __restrict__ row_ptr,
                                                            int64_t L, void* ws, size_t ws_bytes,
-                                                           int skip_tiled, int accumulate) {
+                                                           int accumulate) {
   __shared__ float quarter[4][D + 4];
   const int32_t H = (int32_t)gridDim.y;
   constexpr int32_t dtype = DtypeOf<T>::code;
@@ -1090,7 +1086,6 @@ __global__ __launch_bounds__(256) void gather_merge_kernel(T* __restrict__ O, fl
     const int4 rec = lr[r];
     if (rec.z > kMaxSplit) continue;
     const int64_t i = rec.x;
-    if (passed_over(pl, ws, row_ptr, L, i, skip_tiled)) continue;
     merge_row_partials<T, D>(partials + ((int64_t)rec.y * H + h) * (D + 4), step, rec.z, O + h * L * D + i * D,
                              lse ? lse + h * L + i : nullptr, lane, accumulate != 0);
   }
@@ -1099,7 +1094,6 @@ __global__ __launch_bounds__(256) void gather_merge_kernel(T* __restrict__ O, fl
     const int4 rec = lr[r];
     if (rec.z <= kMaxSplit) continue;
     const int64_t i = rec.x;
-    if (passed_over(pl, ws, row_ptr, L, i, skip_tiled)) continue;
     const float* p0 = partials + ((int64_t)rec.y * H + h) * (D + 4);
     T* Orow = O + h * L * D + i * D;
     float* lse_i = lse ? lse + h * L + i : nullptr;
@@ -1113,11 +1107,6 @@ __global__ __launch_bounds__(256) void gather_merge_kernel(T* __restrict__ O, fl
   }
 }
 
-void launch_split_prepass(const AttnArgs& a) {
-  hipLaunchKernelGGL(split_prepass_kernel, dim3((unsigned)((a.L + 255) / 256)), dim3(256), 0, a.stream,
-                     a.row_ptr, a.L, a.H, a.dtype, a.d, a.ws, a.ws_bytes);
-}
-
 template <typename T, int D>
 sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
   const T* Q = static_cast<const T*>(a.Q);
@@ -1125,8 +1114,9 @@ sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
   const T* V = static_cast<const T*>(a.V);
   T* O = static_cast<T*>(a.O);
   const bool split = allow_split && a.ws && a.ws_bytes >= 256 && a.L > kSplitThreshold;
-  // (after the tile path, and in a prepared graph, the CSR -> tile pass has recorded the split rows)
-  if (split && !skip_tiled) launch_split_prepass(a);
+  // (after the tile path the CSR -> tile pass has recorded the split rows of most calls, and a prepared graph holds them)
+  if (split && !a.prepared && (!skip_tiled || tile_parts_may_be_in_doubt(a.dtype, a.ws_bytes)))
+    launch_split_prepass(a, skip_tiled);
   // after the tile path only leftover rows remain: a grid of about one chip-full of wavefronts
   // over all heads strides over the rows (it returns at once when the tiles covered everything)
   int64_t nwg = (a.L + 3) / 4;
@@ -1163,14 +1153,14 @@ sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
       const unsigned chunk_wgs = skip_tiled && a.H >= 8 ? 128 : 1024;
       if (mark_chunks) profile_mark_begin(a.stream, "gather_chunk_kernel");
       hipLaunchKernelGGL((gather_chunk_kernel<T, D>), dim3(chunk_wgs, (unsigned)a.H), dim3(256), 0, a.stream, Q,
-                         K, V, a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes, skip_tiled ? 1 : 0, may_share ? 1 : 0);
+                         K, V, a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes, may_share ? 1 : 0);
     }
     if constexpr (D == 64 || D == 128) {
       if (may_share) {
         using S = SharedChunk<T, D>;
         const unsigned wgs = D == 64 ? 512 : 256;        // what the chip holds
         hipLaunchKernelGGL((shared_chunk_kernel<T, D>), dim3(wgs, (unsigned)a.H), dim3(S::kThreads), 0, a.stream, Q, K, V,
-                           a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes, skip_tiled ? 1 : 0);
+                           a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes);
       }
     }
     if (mark_chunks) profile_mark_end(a.stream);
@@ -1180,7 +1170,7 @@ sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
     const int64_t merge_cap = 4096 / a.H > 64 ? 4096 / a.H : 64;
     if (merge_wgs > merge_cap) merge_wgs = merge_cap;
     hipLaunchKernelGGL((gather_merge_kernel<T, D>), dim3((unsigned)merge_wgs, (unsigned)a.H), dim3(256), 0, a.stream, O,
-                       a.lse, a.row_ptr, a.L, a.ws, a.ws_bytes, skip_tiled ? 1 : 0, a.accumulate ? 1 : 0);
+                       a.lse, a.row_ptr, a.L, a.ws, a.ws_bytes, a.accumulate ? 1 : 0);
   }
   return hip_status(hipGetLastError());
 }
@@ -1193,6 +1183,11 @@ void clear_workspace(const AttnArgs& a, bool tile_flags) {
   if (nwg > 1024) nwg = 1024;
   hipLaunchKernelGGL(clear_workspace_kernel, dim3((unsigned)nwg), dim3(256), 0, a.stream, a.ws,
                      a.ws_bytes, a.row_ptr, a.L, a.H, a.dtype, a.d, tile_flags ? 1 : 0);
+}
+
+void launch_split_prepass(const AttnArgs& a, bool after_tiles) {
+  hipLaunchKernelGGL(split_prepass_kernel, dim3((unsigned)((a.L + 255) / 256)), dim3(256), 0, a.stream,
+                     a.row_ptr, a.L, a.H, a.dtype, a.d, a.ws, a.ws_bytes, after_tiles ? 1 : 0);
 }
 
 sga_status launch_gather_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {

@@ -372,9 +372,15 @@ __device__ __forceinline__ void record_split_row(const int64_t* __restrict__ row
 
 // The split rows that the tile path leaves over are recorded by the CSR -> tile pass where it gives a tile
 // up.  Whether the partial states of the multi-segment tiles fit is known only after it: they do
-// unless the call has more edges than kMaxTilePartials items hold, and in such a call the rows of
-// every multi-segment tile are recorded, to be passed over if the tile path produced them.
+// unless the call has more edges than kMaxTilePartials items hold, and such a call records its rows in a
+// launch of its own behind that pass (split_prepass_kernel).
 __host__ __device__ inline bool tile_parts_in_doubt(const WorkspacePlan& p) { return p.cap_tparts >= kMaxTilePartials; }
+// What the host can tell of a call whose edge count it does not know: that many edges make items of the
+// longest kind, whatever L, H and d, and a workspace that holds their pair lists.
+inline bool tile_parts_may_be_in_doubt(int32_t dtype, size_t ws_bytes) {
+  const size_t least = size_t(kMaxTilePartials - 1) << (dtype == SGA_F32 ? 15 : 18);
+  return ws_bytes >= least / kPairEdges * (sizeof(int32_t) + kTile * sizeof(uint32_t));
+}
 
 template <typename T> struct DtypeOf;
 template <> struct DtypeOf<float> { static constexpr int32_t code = SGA_F32; };
@@ -451,6 +457,8 @@ sga_status launch_gather_implicit(const AttnArgs& a);
 sga_status launch_tile_explicit(const AttnArgs& a);
 // CSR -> tile graph pass alone (sga_graph_prepare); a.ws holds a full workspace
 void launch_tile_analyze(const AttnArgs& a);
+// records the split rows that this pass has not (after_tiles), or all of a call without tiles
+void launch_split_prepass(const AttnArgs& a, bool after_tiles);
 sga_status launch_tile_implicit(const AttnArgs& a);
 // Implicit non-local mask on the tile kernels (d = 64, 128, 256): the rows >= g against the global keys,
 // and the partial states of the g global rows over *n_chunks ranges of the key blocks, in the

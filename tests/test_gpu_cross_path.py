@@ -331,8 +331,9 @@ def test_explicit_d128_tiles_agree_with_row_kernels_and_prepared_graphs(seed):
 @pytest.mark.parametrize("L", [32768, 33000])
 def test_dense_mask_at_the_limit_of_partial_states(L):
     """fp32, every pair an edge: the segments of all tiles just fit the call's partial states (L = 32,768), or do not
-    (33,000: every tile goes to the per-row kernels, each row split).  The split rows are recorded in both, and
-    passed over in the first.  Explicit, prepared and implicit calls agree; no row is done twice."""
+    (33,000: every tile goes to the per-row kernels, each row split).  A plan counts the split rows that are left to
+    the per-row kernels: none in the first, all in the second.  Explicit, prepared and implicit calls agree; no
+    row is done twice."""
     import torch
     spec = MaskSpec(KIND_SLIDING, L, window=L)
     print("case", L, flush=True)
@@ -342,7 +343,8 @@ def test_dense_mask_at_the_limit_of_partial_states(L):
     O1, l1 = sga.attention_forward(Q, K, V, rp, ci, 0.125, workspace=ws, want_lse=True)
     O2, l2 = sga.attention_forward_implicit(Q, K, V, spec, 0.125, want_lse=True)
     plan = sga.graph_prepare(rp, ci, 1, 64, "f32", ws)
-    assert (plan.tile_parts <= 32768) == (L == 32768) and plan.long_rows == L
+    assert (plan.tile_parts <= 32768) == (L == 32768)
+    assert (plan.long_rows, plan.row_chunks > 0) == ((0, False) if L == 32768 else (L, True))
     O3, l3 = sga.attention_forward_prepared(Q, K, V, rp, ci, 0.125, plan, ws, want_lse=True)
     torch.cuda.synchronize()
     assert torch.equal(O1, O3) and torch.equal(l1, l3)

@@ -17,7 +17,8 @@ int main() {
     const sga::WorkspacePlan p = sga::plan_workspace(L, H, nnz, dtype, d);
     int chunks, len;
     sga::row_split_shape(deg, p, false, chunks, len);
-    printf("%d %lld %lld %d %d %d\n", p.seg_shift, (long long)p.n_work, (long long)p.cap_tparts, p.l2_chunks, chunks, len);
+    printf("%d %lld %lld %d %d %d %d %d\n", p.seg_shift, (long long)p.n_work, (long long)p.cap_tparts, p.l2_chunks, chunks, len,
+           sga::tile_parts_in_doubt(p), sga::tile_parts_may_be_in_doubt(dtype, p.total_bytes));
   }
   return 0;
 }
@@ -33,10 +34,10 @@ def plans(tmp_path_factory):
                     "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2502_01659_amd", "csrc"),
                     str(work / "rule.hip"), "-o", exe], check=True)
 
-    def ask(cases):
+    def ask(cases, first=0, last=6):
         text = "".join("%d %d %d %d %d %d\n" % (c if len(c) == 6 else c + (1,)) for c in cases)
         out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
-        return [tuple(int(x) for x in line.split()) for line in out.splitlines()]
+        return [tuple(int(x) for x in line.split())[first:last] for line in out.splitlines()]
     return ask
 
 
@@ -95,3 +96,19 @@ def test_rows_cut_by_l2_share_have_all_their_chunks(plans):
             assert chunks == n, (L, dtype, deg, chunks)
             seen += 1
     assert seen >= 40
+
+
+def test_doubtful_calls_are_recognised_by_their_workspace(plans):
+    """A call whose partial states may not fit records its split rows in a launch of its own, which the host adds
+    by the size of the workspace alone: every such call has one that large, and calls of ordinary size do not."""
+    doubtful = ordinary = 0
+    for dtype, shift in ((0, 15), (1, 18)):
+        least = 32767 << shift
+        cases = [(L, nnz, H, dtype, d) for L in (32768, 100000, 1 << 20, 1 << 24) for H in (1, 3, 64) for d in (64, 128, 256)
+                 for nnz in (least // 64, least - 1, least, least + (1 << shift), 3 * least) if nnz <= L * L]
+        for case, (sure, maybe) in zip(cases + list(_grid(dtype)), plans(cases + list(_grid(dtype)), 6, 8)):
+            assert maybe or not sure, case
+            assert sure == (case[1] >= least), case
+            doubtful += sure
+            ordinary += case[1] < least // 2 and case[2] == 1 and not maybe
+    assert doubtful > 50 and ordinary > 50
