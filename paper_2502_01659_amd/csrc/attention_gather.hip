@@ -1039,24 +1039,31 @@ __global__ __attribute__((amdgpu_waves_per_eu((D == 64 ? 8 : 4), (D == 64 ? 8 : 
 
 // What the tile path leaves over, in one launch for the call that does not know whether there is anything
 // (none reads what another writes): the first n_merge workgroups of a head merge the tiles' segments,
-// the next n_rows take the leftover rows, the others the chunks of the split rows.  (n_merge and
-// n_rows are multiples of 8, so that the chunk workgroups keep their XCDs.)  An empty launch costs 3 to 6
+// the others take the leftover rows and then the chunks of the split rows.  (n_merge and the others
+// are multiples of 8, so that the chunks keep their XCDs.)  An empty launch costs 3 to 6
 // us of a small call: +-32, L = 4,096, fp32, mask build and forward, in three launches 42.0 us, in two 38.9.
+// The same workgroups for rows and chunks: a chip-full for either, whichever a call has, and no more to start for
+// one that has neither.  (us, 1,024 workgroups of a head more for the chunks / L / 32 over the heads more / these:
+// random 10 %, fp16, L = 13,001 290 / 443 / 298, two heads 489 / 949 / 510, L = 24,576 907 / 1,085 / 890; +-16,
+// fp32, L = 4,096, eight heads 51.9 / 49.2 / 44.1, L = 16,384, one head 49.6 / 39.4 / 36.7.)
+// Four wavefronts per SIMD: fp32 at d = 256 has registers for five, which start on a second head's K and V
+// while the first is in the L2s (11.5 %, L = 9,001, two heads 3,182 against 2,932).
 template <typename T, int D>
-__global__ __launch_bounds__(256) void leftovers_kernel(
+__global__ __attribute__((amdgpu_waves_per_eu(1, 4))) __launch_bounds__(256) void leftovers_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
     float* __restrict__ lse, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
     int64_t L, float scale, void* ws, size_t ws_bytes, int use_split, int may_share, int accumulate,
-    uint32_t n_merge, uint32_t n_rows) {
-  if (blockIdx.x < n_merge)
+    uint32_t n_merge) {
+  if (blockIdx.x < n_merge) {
     tile_merge_body<T, D>(O, lse, row_ptr, L, ws, ws_bytes, accumulate, blockIdx.x / kTile, n_merge / kTile,
                           blockIdx.x % kTile, kTile);
-  else if (blockIdx.x < n_merge + n_rows)
-    gather_csr_body<T, D>(Q, K, V, O, lse, row_ptr, col_idx, L, scale, ws, ws_bytes, use_split, 1, accumulate,
-                          blockIdx.x - n_merge, n_rows);
-  else
-    gather_chunk_body<T, D>(Q, K, V, row_ptr, col_idx, L, scale, ws, ws_bytes, may_share, blockIdx.x - n_merge - n_rows,
-                            gridDim.x - n_merge - n_rows);
+    return;
+  }
+  gather_csr_body<T, D>(Q, K, V, O, lse, row_ptr, col_idx, L, scale, ws, ws_bytes, use_split, 1, accumulate,
+                        blockIdx.x - n_merge, gridDim.x - n_merge);
+  if (use_split && reinterpret_cast<const uint32_t*>(ws)[kCtrLongRows] > 0)
+    gather_chunk_body<T, D>(Q, K, V, row_ptr, col_idx, L, scale, ws, ws_bytes, may_share, blockIdx.x - n_merge,
+                            gridDim.x - n_merge);
 }
 
 // Rows of up to kMaxSplit chunks: one wavefront per (long row, head) combines the row's partials
@@ -1119,9 +1126,7 @@ sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
     launch_split_prepass(a, skip_tiled);
   // after the tile path only leftover rows remain: a grid of about one chip-full of wavefronts
   // over all heads strides over the rows (it returns at once when the tiles covered everything)
-  int64_t nwg = (a.L + 3) / 4;
-  const int64_t leftover_wgs = 2048 / a.H > 256 ? 2048 / a.H : 256;
-  if (skip_tiled && nwg > leftover_wgs) nwg = leftover_wgs;
+  const int64_t nwg = skip_tiled ? leftover_workgroups(a.L, a.H) : (a.L + 3) / 4;
   const dim3 grid((unsigned)nwg, (unsigned)a.H);
   // the benchmark hook brackets the kernel that does the work: the row kernel, or the chunk
   // kernel where a prepared graph has found every row left to it split
@@ -1131,14 +1136,10 @@ sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
   const bool may_share = split && shared_chunks_possible(a) && (!a.prepared || a.plan_long_rows >= kSharedMinRows);
   if constexpr (D >= kHeadDim) {
     if (fused) {
-      // chunks: a chip-full of workgroups over the heads, fewer where L leaves little to split
-      int64_t chunk_wgs = split ? (a.L < 32768 ? a.L / 32 : 1024) / a.H : 0;
-      if (split && chunk_wgs < 128) chunk_wgs = 128;
-      chunk_wgs = (chunk_wgs + 7) & ~int64_t(7);
-      const unsigned n_rows = ((unsigned)nwg + 7u) & ~7u, n_merge = merge_tiles(a) * kTile;
-      hipLaunchKernelGGL((leftovers_kernel<T, D>), dim3(n_merge + n_rows + (unsigned)chunk_wgs, (unsigned)a.H), dim3(256),
-                         0, a.stream, Q, K, V, O, a.lse, a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes,
-                         split ? 1 : 0, may_share ? 1 : 0, a.accumulate ? 1 : 0, n_merge, n_rows);
+      const unsigned n_merge = merge_tiles(a) * kTile;
+      hipLaunchKernelGGL((leftovers_kernel<T, D>), dim3(n_merge + (unsigned)nwg, (unsigned)a.H), dim3(256), 0, a.stream, Q, K, V, O,
+                         a.lse, a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes, split ? 1 : 0, may_share ? 1 : 0,
+                         a.accumulate ? 1 : 0, n_merge);
     }
   }
   if (!fused && !(a.prepared && a.plan_long_rows == a.L)) {       // (a prepared graph all of whose rows are split: 19 us of L = 24,576)

@@ -272,6 +272,13 @@ __host__ __device__ inline void row_split_shape(int64_t deg, const WorkspacePlan
   nchunks = (int32_t)((deg + l - 1) / l);
 }
 
+// Workgroups (of four wavefronts) of a head that stride over what the tile path leaves over: about one chip-full over
+// the heads, a multiple of 8 so that workgroup i runs on XCD i % 8 behind any other such number.
+__host__ __device__ inline int64_t leftover_workgroups(int64_t L, int32_t H) {
+  const int64_t rows = (L + 3) / 4, full = 2048 / H > 256 ? 2048 / H : 256;
+  return ((rows < full ? rows : full) + 7) & ~int64_t(7);
+}
+
 // First work item of tile t: f(t) = t + row_ptr[min(32t, L)] / S.
 __device__ __forceinline__ int64_t work_first(const int64_t* __restrict__ row_ptr, int64_t L,
                                               int sh, int64_t t) {

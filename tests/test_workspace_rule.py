@@ -17,8 +17,9 @@ int main() {
     const sga::WorkspacePlan p = sga::plan_workspace(L, H, nnz, dtype, d);
     int chunks, len;
     sga::row_split_shape(deg, p, false, chunks, len);
-    printf("%d %lld %lld %d %d %d %d %d\n", p.seg_shift, (long long)p.n_work, (long long)p.cap_tparts, p.l2_chunks, chunks, len,
-           sga::tile_parts_in_doubt(p), sga::tile_parts_may_be_in_doubt(dtype, p.total_bytes));
+    printf("%d %lld %lld %d %d %d %d %d %d\n", p.seg_shift, (long long)p.n_work, (long long)p.cap_tparts, p.l2_chunks, chunks, len,
+           sga::tile_parts_in_doubt(p), sga::tile_parts_may_be_in_doubt(dtype, p.total_bytes),
+           (int)sga::leftover_workgroups(L, H));
   }
   return 0;
 }
@@ -112,3 +113,14 @@ def test_doubtful_calls_are_recognised_by_their_workspace(plans):
             doubtful += sure
             ordinary += case[1] < least // 2 and case[2] == 1 and not maybe
     assert doubtful > 50 and ordinary > 50
+
+
+def test_rows_left_over_have_a_chip_full_of_workgroups(plans):
+    """Without a plan the same workgroups take the rows that the tiles leave over and the chunks of split rows.  In a
+    scattered mask those are all rows: a wavefront each, or the 1,024 workgroups that the chip holds; chunk c
+    runs on XCD c % 8, which a multiple of 8 keeps."""
+    cases = [(L, L * L // 20, H, dtype, 64) for dtype in (0, 1) for H in (1, 2, 4, 8, 64, 1000)
+             for L in (1, 31, 2049, 3001, 5000, 13001, 16384, 24576, 1 << 20)]
+    for (L, _, H, _, _), (wgs,) in zip(cases, plans(cases, 8, 9)):
+        assert wgs % 8 == 0 and 4 * wgs >= min(L, 4096 // H), (L, H, wgs)
+        assert wgs * H <= 2048 + 264 * H, (L, H, wgs)
