@@ -113,12 +113,16 @@ __device__ __forceinline__ void tile_merge_body(T* __restrict__ O, float* __rest
 
 // Workgroups per row and head of the merge of multi-segment tiles, each of which walks the merge list:
 // one per tile where a prepared graph knows their number, up to four rounds of the chip's 2,048
-// workgroups.  (768 tiles of six segments, one head: 96 us with 16 workgroups per row.)
+// workgroups.  (768 tiles of six segments, one head: 96 us with 16 workgroups per row.)  A call that does not
+// know whether there are any has 16, and fewer where the heads alone make four rounds: the launch that also takes
+// the rows left over holds four wavefronts per SIMD, and starting 512 idle workgroups of it per head cost more than a
+// kernel of its own (+-16, fp32, L = 1,000, 64 heads, us: that 120.8, 127.3, with four 85.6).
 inline unsigned merge_tiles(const AttnArgs& a) {
   const int64_t most = 8192 / (kTile * (int64_t)a.H);
-  int64_t n = a.prepared ? (int64_t)a.plan_multi_tiles : 16;
+  if (!a.prepared) return (unsigned)(most > 16 ? 16 : most < 1 ? 1 : most);
+  int64_t n = (int64_t)a.plan_multi_tiles;
   if (n > most) n = most;
-  return (unsigned)(n < 16 ? (a.prepared && a.plan_multi_tiles < 16 ? a.plan_multi_tiles : 16) : n);
+  return (unsigned)(n < 16 ? (a.plan_multi_tiles < 16 ? a.plan_multi_tiles : 16) : n);
 }
 
 }  // namespace

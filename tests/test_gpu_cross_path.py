@@ -353,3 +353,23 @@ def test_dense_mask_at_the_limit_of_partial_states(L):
     sga.attention_accumulate(Q, K, V, rp, ci, 0.125, O1, l1, workspace=ws)
     torch.cuda.synchronize()
     _agree(O1, l1 - 0.6931472, O2, l2, "f32")
+
+
+@pytest.mark.parametrize("dtype,H", [("f32", 17), ("f32", 64), ("f16", 64), ("f32", 300)])
+def test_cut_tiles_of_many_heads(dtype, H):
+    """Global rows, whose tiles are cut into segments, with more heads than the merge has workgroups for sixteen tiles
+    each: with and without a plan bit for bit, and against the per-row kernels."""
+    import torch
+    spec = MaskSpec(KIND_GLOBAL_LOCAL, 2700, window=20, n_global=70)
+    print("case", dtype, H, flush=True)
+    Q, K, V = torch_qkv(H, spec.L, 64, dtype, 0.5, 43, "cuda:0")
+    rp, ci = sga.build_mask(spec)
+    ws = sga.alloc_workspace(spec.L, H, 64, dtype, ci.numel())
+    O1, l1 = sga.attention_forward(Q, K, V, rp, ci, 0.125, workspace=ws, want_lse=True)
+    O2, l2 = sga.attention_forward(Q, K, V, rp, ci, 0.125, path=sga.PATH_GATHER, want_lse=True)
+    plan = sga.graph_prepare(rp, ci, H, 64, dtype, ws)
+    assert plan.multi_tiles > 0
+    O3, l3 = sga.attention_forward_prepared(Q, K, V, rp, ci, 0.125, plan, ws, want_lse=True)
+    torch.cuda.synchronize()
+    assert torch.equal(O1, O3) and torch.equal(l1, l3)
+    _agree(O1, l1, O2, l2, dtype)

@@ -10,6 +10,12 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PROGRAM = r"""
 #include <stdio.h>
 #include "sga_internal.h"
+#include "tile_merge.h"
+int merge_of(int H) {
+  sga::AttnArgs a{};
+  a.H = H;
+  return (int)sga::merge_tiles(a);
+}
 int main() {
   long long L, nnz, deg;
   int H, dtype, d;
@@ -17,9 +23,9 @@ int main() {
     const sga::WorkspacePlan p = sga::plan_workspace(L, H, nnz, dtype, d);
     int chunks, len;
     sga::row_split_shape(deg, p, false, chunks, len);
-    printf("%d %lld %lld %d %d %d %d %d %d\n", p.seg_shift, (long long)p.n_work, (long long)p.cap_tparts, p.l2_chunks, chunks, len,
+    printf("%d %lld %lld %d %d %d %d %d %d %d\n", p.seg_shift, (long long)p.n_work, (long long)p.cap_tparts, p.l2_chunks, chunks, len,
            sga::tile_parts_in_doubt(p), sga::tile_parts_may_be_in_doubt(dtype, p.total_bytes),
-           (int)sga::leftover_workgroups(L, H));
+           (int)sga::leftover_workgroups(L, H), merge_of(H));
   }
   return 0;
 }
@@ -124,3 +130,12 @@ def test_rows_left_over_have_a_chip_full_of_workgroups(plans):
     for (L, _, H, _, _), (wgs,) in zip(cases, plans(cases, 8, 9)):
         assert wgs % 8 == 0 and 4 * wgs >= min(L, 4096 // H), (L, H, wgs)
         assert wgs * H <= 2048 + 264 * H, (L, H, wgs)
+
+
+def test_idle_merge_workgroups_do_not_grow_with_the_heads(plans):
+    """A call without a plan launches the merge of tiles that most calls do not have: four rounds of the
+    chip's 2,048 workgroups at most, and a workgroup for each row of a tile and head at least."""
+    cases = [(4096, 1 << 17, H, 0, 64) for H in (1, 2, 8, 16, 17, 32, 64, 128, 256, 1000, 65535)]
+    for (_, _, H, _, _), (tiles,) in zip(cases, plans(cases, 9, 10)):
+        assert 1 <= tiles <= 16 and (tiles == 1 or 32 * H * tiles <= 8192), (H, tiles)
+        assert H > 16 or tiles == 16
