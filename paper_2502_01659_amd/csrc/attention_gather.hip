@@ -623,36 +623,6 @@ __global__ __launch_bounds__(256) void nonlocal_merge_kernel(T* __restrict__ O, 
                              accumulate != 0);
 }
 
-// Which calls run shared_chunk_kernel: those of dense enough random rows.  The host asks whether the mask may be one
-// (its workspace has room for that many edges; an empty launch costs a small call 3 us), the chunk kernels
-// of such a call then look at the mask itself.
-// Where rows are cut by L2 share the other kernel reads K and V from its XCD's L2, and the line lies at an 18th of
-// the pairs for fp32 (us, that / this kernel, L = 24,576, d = 64: 4.5 % 620 / 651, 5 % 627 / 625, 5.5 % 675 / 655,
-// 10 % 1,287 / 880; L = 12,001, 10 % 317 / 259; d = 128, L = 13,001, 10 % 668 / 603); fp16 stays there (L = 24,576,
-// d = 64, 10 % 765 / 880; d = 128, L = 13,001, 8 % 393 / 480).  Where the partial states of that split have no room,
-// this kernel is the faster one down to a 25th for fp16 and below a 30th for fp32 (fp32 / fp16, d = 64, two heads,
-// L = 24,576, 10 % 4,700 -> 1,535 / 1,909 -> 1,611; one head, L = 44,001, 5 % 3,975 -> 1,949 / 2,560 -> 1,999; L = 65,001,
-// 3.4 % 6,947 -> 3,313 / 3,825 -> 3,900; d = 128, L = 24,576, 10 % 4,971 -> 1,627 / 2,844 -> 1,360); with fewer edges
-// to a step the sums lose accuracy (L = 90,001, 2.5 %, fp32: 3.7e-7 against 3.4e-7).
-constexpr int64_t kSharedMaxKeys = int64_t(1) << 16;
-constexpr uint32_t kSharedMinRows = 2048;
-constexpr int64_t kSharedFillByShare = 18;
-__host__ __device__ constexpr int64_t shared_fill(int32_t dtype) { return dtype == SGA_F32 ? 30 : 25; }
-inline bool shared_chunks_possible(const AttnArgs& a) {
-  if (!(a.d == 64 || a.d == 128) || a.L > kSharedMaxKeys || l2_chunks(a.L, a.d, a.dtype) == 0) return false;
-  const int shift = seg_shift_min(a.dtype);
-  WorkspacePlan p = plan_workspace(a.L, a.H, a.L * (a.L / shared_fill(a.dtype)), a.dtype, a.d, shift);
-  if (p.l2_chunks && a.dtype == SGA_F32)
-    p = plan_workspace(a.L, a.H, a.L * (a.L / kSharedFillByShare), a.dtype, a.d, shift);
-  return p.total_bytes <= a.ws_bytes;
-}
-__device__ __forceinline__ bool shared_chunks(const WorkspacePlan& pl, const int64_t* row_ptr, int64_t L, int32_t dtype,
-                                              uint32_t n_long, uint32_t max_chunks) {
-  if (pl.l2_chunks && dtype == SGA_F16) return false;
-  return max_chunks <= (uint32_t)kMaxSplit && n_long >= kSharedMinRows &&
-         row_ptr[L] / L >= L / (pl.l2_chunks ? kSharedFillByShare : shared_fill(dtype));
-}
-
 // One wavefront per (chunk of a long row, head): partial state of a slice of the row.  Chunk c
 // of every row is computed on XCD c % 8 (workgroups go to the XCDs round-robin in launch order
 // and gridDim.x is a multiple of 8): chunks are ranges of the rows' sorted neighbour lists, so
@@ -668,12 +638,12 @@ __device__ __forceinline__ void gather_chunk_body(
     void* ws, size_t ws_bytes, int may_share, uint32_t wg, uint32_t n_wg) {
   const int32_t H = (int32_t)gridDim.y;
   constexpr int32_t dtype = DtypeOf<T>::code;
-  if (!split_active(row_ptr, L, H, dtype, D, ws, ws_bytes)) return;
+  const uint32_t n_long = reinterpret_cast<const uint32_t*>(ws)[kCtrLongRows];      // (none where the plan has no room)
+  if (n_long == 0 || !split_active(row_ptr, L, H, dtype, D, ws, ws_bytes)) return;
   const WorkspacePlan pl = plan_workspace(L, H, row_ptr[L], dtype, D);
-  const uint32_t n_long = reinterpret_cast<const uint32_t*>(ws)[kCtrLongRows];
   uint32_t max_chunks;
   const int4* lr = long_rows(pl, ws, max_chunks);
-  if (may_share && shared_chunks(pl, row_ptr, L, dtype, n_long, max_chunks)) return;      // (shared_chunk_kernel)
+  if (may_share && shared_chunks(pl, row_ptr[L], L, dtype, n_long, max_chunks)) return;      // (shared_chunk_kernel)
   float* partials = reinterpret_cast<float*>(static_cast<char*>(ws) + pl.off_partials);
   const int lane = threadIdx.x & (kWave - 1);
   const int waves = blockDim.x / kWave;
@@ -900,12 +870,14 @@ __global__ __attribute__((amdgpu_waves_per_eu((D == 64 ? 8 : 4), (D == 64 ? 8 : 
   __shared__ int range[3];                  // first and last key block of the unit, its edges
   const int32_t H = (int32_t)gridDim.y;
   constexpr int32_t dtype = DtypeOf<T>::code;
-  if (!split_active(row_ptr, L, H, dtype, D, ws, ws_bytes)) return;
+  const uint32_t n_long = reinterpret_cast<const uint32_t*>(ws)[kCtrLongRows];      // (none where the plan has no room)
+  // (the count first: a call with nothing for this kernel launches it once per head, and every idle workgroup that worked
+  // out its plan cost +-200, L = 8,192, 32 heads, fp32 294 -> 463 us; so 276)
+  if (n_long < kSharedMinRows || !split_active(row_ptr, L, H, dtype, D, ws, ws_bytes)) return;
   const WorkspacePlan pl = plan_workspace(L, H, row_ptr[L], dtype, D);
-  const uint32_t n_long = reinterpret_cast<const uint32_t*>(ws)[kCtrLongRows];
   uint32_t max_chunks;
   const int4* lr = long_rows(pl, ws, max_chunks);
-  if (!shared_chunks(pl, row_ptr, L, dtype, n_long, max_chunks)) return;
+  if (!shared_chunks(pl, row_ptr[L], L, dtype, n_long, max_chunks)) return;
   float* partials = reinterpret_cast<float*>(static_cast<char*>(ws) + pl.off_partials);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int lane = threadIdx.x & (kWave - 1), l16 = lane & 15;
@@ -1061,7 +1033,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(1, 4))) __launch_bounds__(256) voi
   }
   gather_csr_body<T, D>(Q, K, V, O, lse, row_ptr, col_idx, L, scale, ws, ws_bytes, use_split, 1, accumulate,
                         blockIdx.x - n_merge, gridDim.x - n_merge);
-  if (use_split && reinterpret_cast<const uint32_t*>(ws)[kCtrLongRows] > 0)
+  if (use_split)
     gather_chunk_body<T, D>(Q, K, V, row_ptr, col_idx, L, scale, ws, ws_bytes, may_share, blockIdx.x - n_merge,
                             gridDim.x - n_merge);
 }
@@ -1079,9 +1051,9 @@ __global__ __launch_bounds__(256) void gather_merge_kernel(T* __restrict__ O, fl
   __shared__ float quarter[4][D + 4];
   const int32_t H = (int32_t)gridDim.y;
   constexpr int32_t dtype = DtypeOf<T>::code;
-  if (!split_active(row_ptr, L, H, dtype, D, ws, ws_bytes)) return;
+  const uint32_t n_long = reinterpret_cast<const uint32_t*>(ws)[kCtrLongRows];      // (none where the plan has no room)
+  if (n_long == 0 || !split_active(row_ptr, L, H, dtype, D, ws, ws_bytes)) return;
   const WorkspacePlan pl = plan_workspace(L, H, row_ptr[L], dtype, D);
-  const uint32_t n_long = reinterpret_cast<const uint32_t*>(ws)[kCtrLongRows];
   uint32_t max_chunks;
   const int4* lr = long_rows(pl, ws, max_chunks);
   const float* partials = reinterpret_cast<const float*>(static_cast<char*>(ws) + pl.off_partials);
@@ -1133,7 +1105,8 @@ sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
   const bool mark = !skip_tiled || (a.prepared && a.plan_no_tiles);
   const bool mark_chunks = mark && a.prepared && a.plan_long_rows > 0;
   const bool fused = D >= kHeadDim && skip_tiled && !a.prepared;     // (nothing known about what is left)
-  const bool may_share = split && shared_chunks_possible(a) && (!a.prepared || a.plan_long_rows >= kSharedMinRows);
+  const bool may_share = split && (!a.prepared || a.plan_long_rows >= kSharedMinRows) &&
+                         shared_chunks_possible(a.L, a.H, a.d, a.dtype, a.ws_bytes);
   if constexpr (D >= kHeadDim) {
     if (fused) {
       const unsigned n_merge = merge_tiles(a) * kTile;

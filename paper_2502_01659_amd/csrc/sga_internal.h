@@ -279,6 +279,43 @@ __host__ __device__ inline int64_t leftover_workgroups(int64_t L, int32_t H) {
   return ((rows < full ? rows : full) + 7) & ~int64_t(7);
 }
 
+// Which calls run shared_chunk_kernel: those of dense enough random rows.  The host asks whether the mask may be one
+// (shared_chunks_possible), the chunk kernels of such a call then look at the mask itself (shared_chunks).
+// Where rows are cut by L2 share the other kernel reads K and V from its XCD's L2, and the line lies at an 18th of
+// the pairs for fp32 (us, that / this kernel, L = 24,576, d = 64: 4.5 % 620 / 651, 5 % 627 / 625, 5.5 % 675 / 655,
+// 10 % 1,287 / 880; L = 12,001, 10 % 317 / 259; d = 128, L = 13,001, 10 % 668 / 603); fp16 stays there (L = 24,576,
+// d = 64, 10 % 765 / 880; d = 128, L = 13,001, 8 % 393 / 480).  Where the partial states of that split have no room,
+// this kernel is the faster one down to a 25th for fp16 and below a 30th for fp32 (fp32 / fp16, d = 64, two heads,
+// L = 24,576, 10 % 4,700 -> 1,535 / 1,909 -> 1,611; one head, L = 44,001, 5 % 3,975 -> 1,949 / 2,560 -> 1,999; L = 65,001,
+// 3.4 % 6,947 -> 3,313 / 3,825 -> 3,900; d = 128, L = 24,576, 10 % 4,971 -> 1,627 / 2,844 -> 1,360); with fewer edges
+// to a step the sums lose accuracy (L = 90,001, 2.5 %, fp32: 3.7e-7 against 3.4e-7).
+constexpr int64_t kSharedMaxKeys = int64_t(1) << 16;
+constexpr uint32_t kSharedMinRows = 2048;
+constexpr int64_t kSharedFillByShare = 18;
+__host__ __device__ constexpr int64_t shared_fill(int32_t dtype) { return dtype == SGA_F32 ? 30 : 25; }
+__host__ __device__ inline bool shared_chunks(const WorkspacePlan& pl, int64_t nnz, int64_t L, int32_t dtype,
+                                              uint32_t n_long, uint32_t max_chunks) {
+  if (pl.l2_chunks && dtype == SGA_F16) return false;
+  return max_chunks <= (uint32_t)kMaxSplit && n_long >= kSharedMinRows &&
+         nnz / L >= L / (pl.l2_chunks ? kSharedFillByShare : shared_fill(dtype));
+}
+// False where no mask that this workspace was sized for can take shared_chunks: an empty launch costs a
+// small call 2 us.  The fewest edges that can are, with the split by L2 share, those of its line (fp32 only), and
+// without it those of the other line or the first for which that split has no room; every workspace of
+// sga_workspace_bytes for such a mask, or larger, answers true.
+inline bool shared_chunks_possible(int64_t L, int32_t H, int32_t d, int32_t dtype, size_t ws_bytes) {
+  const int n = l2_chunks(L, d, dtype);
+  if (!(d == 64 || d == 128) || L > kSharedMaxKeys || n == 0) return false;
+  auto room = [&](int64_t nnz, bool by_share) {
+    const WorkspacePlan p = plan_workspace(L, H, nnz, dtype, d, seg_shift_min(dtype));
+    return (p.l2_chunks != 0) == by_share && p.total_bytes <= ws_bytes;
+  };
+  if (dtype == SGA_F32 && room(L * (L / kSharedFillByShare), true)) return true;
+  const int64_t rows = kL2PartialBudget / ((int64_t)n * H * (d + 4) * (int64_t)sizeof(float)) + 1;
+  const int64_t without = rows * kL2ChunkEdges * n, least = L * (L / shared_fill(dtype));
+  return rows <= L && room(without > least ? without : least, false);
+}
+
 // First work item of tile t: f(t) = t + row_ptr[min(32t, L)] / S.
 __device__ __forceinline__ int64_t work_first(const int64_t* __restrict__ row_ptr, int64_t L,
                                               int sh, int64_t t) {

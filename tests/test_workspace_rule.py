@@ -11,6 +11,12 @@ PROGRAM = r"""
 #include <stdio.h>
 #include "sga_internal.h"
 #include "tile_merge.h"
+int possible(long long L, int H, long long nnz, int dtype, int d) {
+  size_t bytes = sga::plan_workspace(L, H, nnz, dtype, d).total_bytes;
+  const size_t shortest = sga::plan_workspace(L, H, nnz, dtype, d, sga::seg_shift_min(dtype)).total_bytes;
+  if (bytes < shortest) bytes = shortest;
+  return sga::shared_chunks_possible(L, H, d, dtype, bytes);
+}
 int merge_of(int H) {
   sga::AttnArgs a{};
   a.H = H;
@@ -23,9 +29,11 @@ int main() {
     const sga::WorkspacePlan p = sga::plan_workspace(L, H, nnz, dtype, d);
     int chunks, len;
     sga::row_split_shape(deg, p, false, chunks, len);
-    printf("%d %lld %lld %d %d %d %d %d %d %d\n", p.seg_shift, (long long)p.n_work, (long long)p.cap_tparts, p.l2_chunks, chunks, len,
+    printf("%d %lld %lld %d %d %d %d %d %d %d %d %d %d\n", p.seg_shift, (long long)p.n_work, (long long)p.cap_tparts, p.l2_chunks, chunks, len,
            sga::tile_parts_in_doubt(p), sga::tile_parts_may_be_in_doubt(dtype, p.total_bytes),
-           (int)sga::leftover_workgroups(L, H), merge_of(H));
+           (int)sga::leftover_workgroups(L, H), merge_of(H), p.l2_chunks != 0 && dtype == SGA_F16 ? -1 : 0,
+           sga::l2_chunks(L, d, dtype) && L <= sga::kSharedMaxKeys && sga::shared_chunks(p, nnz, L, dtype, 1 << 16, 2),
+           possible(L, H, nnz, dtype, d));
   }
   return 0;
 }
@@ -139,3 +147,26 @@ def test_idle_merge_workgroups_do_not_grow_with_the_heads(plans):
     for (_, _, H, _, _), (tiles,) in zip(cases, plans(cases, 9, 10)):
         assert 1 <= tiles <= 16 and (tiles == 1 or 32 * H * tiles <= 8192), (H, tiles)
         assert H > 16 or tiles == 16
+
+
+def test_workspaces_tell_whether_split_rows_may_share_key_blocks(plans):
+    """Without a plan the host decides by the workspace whether the kernel that shares key blocks is launched, and the
+    mask whether it is used.  A workspace sized for a mask that uses it says yes, and so does any larger one (the same
+    call in the library's own scratch gives the same bits); fp16 calls whose rows are always cut by L2 share never say
+    yes."""
+    used = refused = 0
+    for dtype in (0, 1):
+        for d in (64, 128):
+            for H in (1, 2, 3, 8, 32):
+                for L in (6300, 7001, 9001, 12001, 13001, 16321, 18017, 20000, 24576, 33000, 44001, 65001, 65536):
+                    nnz = sorted({L * (L // f) for f in (31, 30, 29, 27, 26, 25, 24, 20, 19, 18, 17, 14, 10, 8, 5, 3, 2, 1)})
+                    found = plans([(L, n, H, dtype, d) for n in nnz], 10, 13)
+                    reached = False
+                    for n, (never, uses, possible) in zip(nnz, found):
+                        assert possible or not uses, (L, n, H, dtype, d)
+                        reached |= bool(uses)
+                        used += uses
+                    if dtype == 1 and all(never for never, _, _ in found):
+                        assert not any(possible for _, _, possible in found), (L, H, d)
+                        refused += 1
+    assert used > 200 and refused > 5
