@@ -626,10 +626,9 @@ __global__ __launch_bounds__(256) void nonlocal_merge_kernel(T* __restrict__ O, 
 // One wavefront per (chunk of a long row, head): partial state of a slice of the row.  Chunk c
 // of every row is computed on XCD c % 8 (workgroups go to the XCDs round-robin in launch order
 // and gridDim.x is a multiple of 8): chunks are ranges of the rows' sorted neighbour lists, so
-// an XCD's L2 sees the same part of the key range from every row.  A row s whose z chunks are few and no
-// multiple of 8 starts at XCD (s z) % 8 instead, so that the rows together fill all of them: random
-// rows of 2,458 neighbours, cut in two, at L = 24,576, d = 128 had two XCDs to themselves (fp32 14.9 -> 4.8 ms, fp16 5.9 -> 2.8; d = 64, two heads 12.4 -> 4.7).
-// The work units of XCD x are the pairs (long row s, j) with chunk c = (x - s z) % 8 + 8j, numbered
+// an XCD's L2 sees the same part of the key range from every row.  Rows of a few chunks start at an XCD of
+// their own instead (first_xcd).
+// The work units of XCD x are the pairs (long row s, j) with chunk c = (x - first_xcd) % 8 + 8j, numbered
 // j * n_long + s (rows of few chunks have no unit for the larger j) and dealt to the XCD's wavefronts in turn.
 template <typename T, int D>
 __device__ __forceinline__ void gather_chunk_body(
@@ -655,8 +654,7 @@ __device__ __forceinline__ void gather_chunk_body(
        u += (uint64_t)(n_wg >> 3) * waves) {
     const uint32_t s = (uint32_t)(u % n_long);
     const int4 rec = lr[s];                                  // {row, first partial slot, chunks, chunk length}
-    const uint32_t turn = rec.z <= kMaxSplit ? s * (uint32_t)rec.z : 0;      // (0 mod 8 for a split by L2 share)
-    const int32_t c = (int32_t)(((xcd - turn) & 7) + 8 * (u / n_long));
+    const int32_t c = (int32_t)(((xcd - first_xcd(s, rec.z)) & 7) + 8 * (u / n_long));
     if (c >= rec.z) continue;
     const int64_t i = rec.x;
     const int64_t r0 = row_ptr[i], deg = row_ptr[i + 1] - r0;

@@ -272,6 +272,17 @@ __host__ __device__ inline void row_split_shape(int64_t deg, const WorkspacePlan
   nchunks = (int32_t)((deg + l - 1) / l);
 }
 
+// The XCD of chunk 0 of split row s, which has z chunks (chunk c follows c XCDs further on).  Up to four chunks would
+// leave half the XCDs or more without work, so such rows take them in turn; rows of more chunks all
+// start at XCD 0, where the same part of the keys stays in an L2 for every row.  (us, all rows from XCD 0 / in
+// turn, 3,200 rows of L = 51,200 split, fp32, d = 64, four heads: 2 chunks 6,021 / 2,777, 3 5,428 / 4,705,
+// 4 5,995 / 4,468, 5 5,173 / 7,664, 1,600 rows: 6 2,354 / 3,994, 7 2,217 / 4,983, 9 4,124 / 6,607, 12 4,151 / 5,376,
+// 15 4,128 / 9,669; L = 20,000, fp16, eight heads: 2 2,180 / 1,066, 4 2,162 / 1,241, 5 2,051 / 2,796.)
+constexpr int kXcdTurnChunks = 4;
+__host__ __device__ inline uint32_t first_xcd(uint32_t s, int32_t z) {
+  return z <= kXcdTurnChunks ? s * (uint32_t)z & 7u : 0u;
+}
+
 // Workgroups (of four wavefronts) of a head that stride over what the tile path leaves over: about one chip-full over
 // the heads, a multiple of 8 so that workgroup i runs on XCD i % 8 behind any other such number.
 __host__ __device__ inline int64_t leftover_workgroups(int64_t L, int32_t H) {

@@ -29,11 +29,11 @@ int main() {
     const sga::WorkspacePlan p = sga::plan_workspace(L, H, nnz, dtype, d);
     int chunks, len;
     sga::row_split_shape(deg, p, false, chunks, len);
-    printf("%d %lld %lld %d %d %d %d %d %d %d %d %d %d\n", p.seg_shift, (long long)p.n_work, (long long)p.cap_tparts, p.l2_chunks, chunks, len,
+    printf("%d %lld %lld %d %d %d %d %d %d %d %d %d %d %d\n", p.seg_shift, (long long)p.n_work, (long long)p.cap_tparts, p.l2_chunks, chunks, len,
            sga::tile_parts_in_doubt(p), sga::tile_parts_may_be_in_doubt(dtype, p.total_bytes),
            (int)sga::leftover_workgroups(L, H), merge_of(H), p.l2_chunks != 0 && dtype == SGA_F16 ? -1 : 0,
            sga::l2_chunks(L, d, dtype) && L <= sga::kSharedMaxKeys && sga::shared_chunks(p, nnz, L, dtype, 1 << 16, 2),
-           possible(L, H, nnz, dtype, d));
+           possible(L, H, nnz, dtype, d), (int)sga::first_xcd((uint32_t)L, (int)deg));
   }
   return 0;
 }
@@ -170,3 +170,18 @@ def test_workspaces_tell_whether_split_rows_may_share_key_blocks(plans):
                         assert not any(possible for _, _, possible in found), (L, H, d)
                         refused += 1
     assert used > 200 and refused > 5
+
+
+def test_only_rows_of_few_chunks_start_at_an_xcd_of_their_own(plans):
+    """Up to four chunks: eight neighbouring rows put the same number of chunks on every XCD.  From five on chunk c
+    of every row is on XCD c % 8, so that an L2 sees one part of the keys."""
+    for z in list(range(1, 18)) + [24, 25, 63, 64, 100, 1024]:
+        starts = [x for x, in plans([(s, 0, 1, 0, 64, z) for s in range(1, 65)], 13, 14)]
+        load = [0] * 8
+        for first in starts:
+            for c in range(z):
+                load[(first + c) % 8] += 1
+        if z <= 4:
+            assert len(set(load)) == 1, (z, load)
+        else:
+            assert set(starts) == {0}, z
