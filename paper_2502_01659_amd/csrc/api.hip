@@ -239,6 +239,7 @@ sga_status run_explicit_call(const void* Q, const void* K, const void* V, const 
     a.plan_tiles_cover_all = (plan->flags & SGA_GRAPH_TILES_COVER_ALL) != 0;
     a.plan_no_tiles = (int64_t)plan->tiles_left == (L + kTile - 1) / kTile;
     a.plan_long_rows = (plan->flags & SGA_GRAPH_ROW_CHUNKS_FIT) ? plan->long_rows : 0;
+    a.plan_rows_share = (plan->flags & SGA_GRAPH_ROWS_SHARE_KEYS) != 0;
     return launch_tile_explicit(a);
   }
   // (the per-row kernels alone use the workspace for split rows only, and no row of up to kSplitThreshold
@@ -376,6 +377,9 @@ sga_status sga_graph_prepare(const int64_t* row_ptr, const int32_t* col_idx, int
   const bool chunks_fit = (int64_t)p.row_chunks <= pl.cap_items;
   p.flags = (parts_fit ? SGA_GRAPH_TILE_PARTS_FIT : 0) | (chunks_fit ? SGA_GRAPH_ROW_CHUNKS_FIT : 0) |
             (p.tiles_left == 0 && parts_fit ? SGA_GRAPH_TILES_COVER_ALL : 0);
+  if (chunks_fit && shared_chunks_possible(L, H, d, dtype, workspace_bytes) &&
+      shared_chunks(pl, nnz, L, dtype, p.long_rows, ctr[split_is_fine(pl, ctr) ? kCtrMaxChunksFine : kCtrMaxChunks]))
+    p.flags |= SGA_GRAPH_ROWS_SHARE_KEYS;
   p.row_ptr = row_ptr; p.col_idx = col_idx;
   p.workspace = workspace; p.workspace_bytes = workspace_bytes;
   *plan_out = p;

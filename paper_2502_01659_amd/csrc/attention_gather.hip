@@ -313,10 +313,10 @@ __global__ __launch_bounds__(256) void split_prepass_kernel(const int64_t* __res
   record_split_row(row_ptr, i, pl, ws);
 }
 
-// The list of long rows that this call uses: the finer split if all its chunks fit.
+// The list of long rows that this call uses.
 __device__ __forceinline__ const int4* long_rows(const WorkspacePlan& pl, const void* ws, uint32_t& max_chunks) {
   const uint32_t* ctr = reinterpret_cast<const uint32_t*>(ws);
-  const bool fine = (int64_t)ctr[kCtrFineNeeded] <= pl.cap_items;
+  const bool fine = split_is_fine(pl, ctr);
   max_chunks = ctr[fine ? kCtrMaxChunksFine : kCtrMaxChunks];
   return reinterpret_cast<const int4*>(static_cast<const char*>(ws) + pl.off_long) + (fine ? pl.cap_items : 0);
 }
@@ -1103,8 +1103,7 @@ sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
   const bool mark = !skip_tiled || (a.prepared && a.plan_no_tiles);
   const bool mark_chunks = mark && a.prepared && a.plan_long_rows > 0;
   const bool fused = D >= kHeadDim && skip_tiled && !a.prepared;     // (nothing known about what is left)
-  const bool may_share = split && (!a.prepared || a.plan_long_rows >= kSharedMinRows) &&
-                         shared_chunks_possible(a.L, a.H, a.d, a.dtype, a.ws_bytes);
+  const bool may_share = split && (a.prepared ? a.plan_rows_share : shared_chunks_possible(a.L, a.H, a.d, a.dtype, a.ws_bytes));
   if constexpr (D >= kHeadDim) {
     if (fused) {
       const unsigned n_merge = merge_tiles(a) * kTile;
@@ -1121,9 +1120,9 @@ sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
     if (mark && !mark_chunks) profile_mark_end(a.stream);
   }
   if (split && (!a.prepared || a.plan_long_rows > 0)) {
-    if (!fused) {
+    if (mark_chunks) profile_mark_begin(a.stream, may_share ? "shared_chunk_kernel" : "gather_chunk_kernel");
+    if (!fused && !(a.prepared && may_share)) {
       const unsigned chunk_wgs = skip_tiled && a.H >= 8 ? 128 : 1024;
-      if (mark_chunks) profile_mark_begin(a.stream, "gather_chunk_kernel");
       hipLaunchKernelGGL((gather_chunk_kernel<T, D>), dim3(chunk_wgs, (unsigned)a.H), dim3(256), 0, a.stream, Q,
                          K, V, a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes, may_share ? 1 : 0);
     }

@@ -290,8 +290,13 @@ __host__ __device__ inline int64_t leftover_workgroups(int64_t L, int32_t H) {
   return ((rows < full ? rows : full) + 7) & ~int64_t(7);
 }
 
+// The finer split is taken if all its chunks fit (ctr: the counters of the workspace).
+__host__ __device__ inline bool split_is_fine(const WorkspacePlan& p, const uint32_t* ctr) {
+  return (int64_t)ctr[kCtrFineNeeded] <= p.cap_items;
+}
+
 // Which calls run shared_chunk_kernel: those of dense enough random rows.  The host asks whether the mask may be one
-// (shared_chunks_possible), the chunk kernels of such a call then look at the mask itself (shared_chunks).
+// (shared_chunks_possible), the chunk kernels of such a call then look at the mask itself (shared_chunks); a plan knows.
 // Where rows are cut by L2 share the other kernel reads K and V from its XCD's L2, and the line lies at an 18th of
 // the pairs for fp32 (us, that / this kernel, L = 24,576, d = 64: 4.5 % 620 / 651, 5 % 627 / 625, 5.5 % 675 / 655,
 // 10 % 1,287 / 880; L = 12,001, 10 % 317 / 259; d = 128, L = 13,001, 10 % 668 / 603); fp16 stays there (L = 24,576,
@@ -479,6 +484,7 @@ struct AttnArgs {
   bool plan_tiles_cover_all;   // no row is left to the per-row kernels
   bool plan_no_tiles;          // no tile qualified: the tile kernels have nothing to do
   uint32_t plan_long_rows;     // split rows among the leftover rows whose chunk items fit
+  bool plan_rows_share;        // ... and shared_chunk_kernel computes them
 };
 
 // Global -> LDS copy of 16 bytes per lane without passing through registers: lane l's 16 bytes

@@ -11,7 +11,7 @@ import pytest
 
 import paper_2502_01659_amd as sga
 from sga_inputs import (MaskSpec, KIND_SLIDING, KIND_DILATED, KIND_GLOBAL_LOCAL, KIND_BIGBIRD, KIND_NONLOCAL,
-                        numpy_qkv, Workload)
+                        numpy_qkv, torch_qkv, Workload)
 from oracle import reference as R
 from gpu_util import TOL, to_device, max_err
 
@@ -239,3 +239,30 @@ def test_dense_mask_stays_on_the_tiles():
     O = sga.attention_forward_prepared(Q, K, V, rp, ci, 0.125, plan, ws)
     O2 = sga.attention_forward_implicit(Q, K, V, spec, 0.125)
     assert (O - O2).abs().max().item() <= TOL["f32"]
+
+
+@pytest.mark.parametrize("dtype,L,H,kernel", [("f32", 12001, 1, "shared_chunk_kernel"), ("f16", 13001, 1, "gather_chunk_kernel"),
+                                              ("f32", 6001, 1, "gather_csr_kernel")])
+def test_prepared_call_runs_the_chunk_kernel_its_plan_names(dtype, L, H, kernel):
+    """A random mask of 11 %: a plan says which kernel computes the chunks of its split rows (fp32: the one that shares
+    key blocks; fp16 rows cut by L2 share: the per-row one; L = 6,001: none is split), the benchmark hook
+    names that kernel, and the bits are those of the call without a plan."""
+    import torch
+    print("case", dtype, L, H, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    mask = torch.rand((L, L), generator=g, device="cuda") < 0.11
+    rp = torch.zeros(L + 1, dtype=torch.int64, device="cuda")
+    rp[1:] = mask.sum(1).cumsum(0)
+    ci = mask.nonzero()[:, 1].to(torch.int32).contiguous()
+    Q, K, V = torch_qkv(H, L, 64, dtype, 0.5, 6, "cuda:0")
+    ws = sga.alloc_workspace(L, H, 64, dtype, ci.numel())
+    O1 = sga.attention_forward(Q, K, V, rp, ci, 0.125, workspace=ws)
+    plan = sga.graph_prepare(rp, ci, H, 64, dtype, ws)
+    assert bool(plan.flags & sga.GRAPH_ROWS_SHARE_KEYS) == (kernel == "shared_chunk_kernel")
+    assert sga.sga_profile_enable(1) == 0
+    O2 = sga.attention_forward_prepared(Q, K, V, rp, ci, 0.125, plan, ws)
+    status, ms = sga.sga_profile_collect()
+    name = sga.sga_profile_last_kernel()
+    sga.sga_profile_enable(0)
+    assert status == 0 and len(ms) == 1 and name == kernel
+    assert torch.equal(O1, O2)
