@@ -889,15 +889,19 @@ __global__ __attribute__((amdgpu_waves_per_eu((D == 64 ? 8 : 4), (D == 64 ? 8 : 
       reinterpret_cast<uint32_t*>(planes + i * S::kPlane + S::kKeys * S::kRowBytes)[threadIdx.x] = 0;
   }
   const uint32_t cohorts = (n_long + S::kRows - 1) / S::kRows;
-  // as in gather_chunk_kernel: chunk c on XCD c % 8, or, where there are fewer than 8, all units on all XCDs in turn
-  const bool few = max_chunks < 8;
-  const uint64_t n_units = few ? (uint64_t)cohorts * max_chunks : 8 * (uint64_t)cohorts * ((max_chunks + 7) / 8);
-  for (uint64_t u = blockIdx.x; u < n_units; u += gridDim.x) {
-    const uint32_t cohort = (uint32_t)(few ? u / max_chunks : (u >> 3) % cohorts);
-    const int c = (int)(few ? u % max_chunks : (u & 7) + 8 * ((u >> 3) / cohorts));
+  // by L2 share chunk c on XCD c % 8 as in gather_chunk_kernel, else all units on all XCDs in turn, the chunks of
+  // the 64 rows on as many workgroups (their numbers are an odd number apart, the grid is a power of two): one row of
+  // many chunks among rows of two would keep one busy for 3 ms (random 8 %, L = 32,768, fp32, us: without such a
+  // row 1,135; with one of all keys, every chunk c on XCD c % 8 4,935, its chunks on one workgroup 4,270, so 1,440)
+  const bool by_share = pl.l2_chunks != 0;
+  const uint32_t n_units = by_share ? 8 * cohorts * ((max_chunks + 7) / 8) : cohorts * max_chunks;
+  for (uint32_t u = blockIdx.x; u < n_units; u += gridDim.x) {
+    const uint32_t c = by_share ? (u & 7) + 8 * ((u >> 3) / cohorts) : u / cohorts;
+    const uint32_t cohort = by_share ? (u >> 3) % cohorts : (u + (cohorts & 1 ? 0 : c)) % cohorts;
     const uint32_t r = cohort * S::kRows + threadIdx.x / 16;
     const int4 rec = r < n_long ? lr[r] : make_int4(0, 0, 0, 0);        // {row, first partial slot, chunks, chunk length}
-    const bool active = c < rec.z;
+    const bool active = (int)c < rec.z;
+    if (!__syncthreads_or(active)) continue;          // (no row of the 64 has that many chunks)
     const int64_t r0 = row_ptr[rec.x];
     const int deg = (int)(row_ptr[rec.x + 1] - r0);
     const int32_t* cols = col_idx + r0;

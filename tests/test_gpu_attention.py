@@ -411,7 +411,7 @@ def test_rows_split_into_a_few_chunks(d, dtype):
         _close(O[h].cpu().numpy()[rows], lse[h].cpu().numpy()[rows], O_ref, lse_ref, dtype)
 
 
-@pytest.mark.parametrize("d,dtype,L,H", [(64, "f32", 9001, 1), (64, "f32", 16321, 2), (64, "f16", 18017, 2),
+@pytest.mark.parametrize("d,dtype,L,H", [(64, "f32", 9001, 1), (64, "f32", 18001, 2), (64, "f16", 18017, 2),
                                          (128, "f32", 8961, 1), (128, "f32", 18001, 1), (128, "f16", 18049, 1)])
 @pytest.mark.parametrize("even", [True, False])
 def test_many_split_rows_share_their_key_blocks(d, dtype, L, H, even):
@@ -467,9 +467,55 @@ def test_many_split_rows_share_their_key_blocks(d, dtype, L, H, even):
                                                V[h].astype(np.float64), mask, 0.125)
             _close(O[h].cpu().numpy()[rows], lse[h].cpu().numpy()[rows], O_ref, lse_ref, dtype)
     plan = sga.graph_prepare(drp, dci, H, d, dtype, ws)
+    assert plan.flags & sga.GRAPH_ROWS_SHARE_KEYS and plan.long_rows >= 2048
+    assert plan.row_chunks == (8 if H * L * 8 * (d + 4) * 4 <= 64 << 20 else 2) * plan.long_rows
     O3 = sga.attention_forward_prepared(dQ, dK, dV, drp, dci, 0.125, plan, ws)
     torch.cuda.synchronize()
     assert torch.equal(O3, O2)
+
+
+@pytest.mark.parametrize("d,dtype,H", [(64, "f32", 2), (64, "f16", 2), (128, "f32", 1)])
+def test_rows_of_many_chunks_among_rows_of_two(d, dtype, H):
+    """Two rows with every and with half the keys as neighbours, 12 and 6 chunks, among rows of two that share their key
+    blocks: every row against the same call without a workspace, the two and some others against the dense oracle."""
+    import torch
+    L = 23041
+    print("case long rows", d, dtype, H, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(83)
+    rp = torch.zeros(L + 1, dtype=torch.int64, device="cuda")
+    cols, deg = [], []
+    for r0 in range(0, L, 1024):
+        block = torch.rand((min(1024, L - r0), L), generator=g, device="cuda") < 0.0945      # (the tiles of the two rows stay below 128 edges a block)
+        if r0 == 0:
+            block[5] = True
+        if r0 == 9 * 1024:
+            block[77] = torch.arange(L, device="cuda") % 2 == 0
+        deg.append(block.sum(1))
+        cols.append(block.nonzero()[:, 1].to(torch.int32))
+    rp[1:] = torch.cat(deg).cumsum(0)
+    ci = torch.cat(cols).contiguous()
+    Q, K, V = numpy_qkv(H, L, d, dtype, 0.6, 34)
+    dQ, dK, dV = to_device(Q, K, V)
+    ws = sga.alloc_workspace(L, H, d, dtype, ci.numel())
+    plan = sga.graph_prepare(rp, ci, H, d, dtype, ws)
+    assert plan.flags & sga.GRAPH_ROWS_SHARE_KEYS and plan.row_chunks == 2 * (plan.long_rows - 2) + 12 + 6
+    O, lse = sga.attention_forward_prepared(dQ, dK, dV, rp, ci, 0.125, plan, ws, want_lse=True)
+    O1, lse1 = sga.attention_forward(dQ, dK, dV, rp, ci, 0.125, path=sga.PATH_GATHER, want_lse=True)
+    torch.cuda.synchronize()
+    assert (O.float() - O1.float()).abs().max().item() <= 2 * TOL[dtype]
+    assert (lse - lse1).abs().max().item() <= 2 * LSE_TOL[dtype]
+    rows = np.array([0, 5, 6, 9 * 1024 + 76, 9 * 1024 + 77, L - 1])
+    start = rp.cpu().numpy()
+    mask = np.zeros((len(rows), L), dtype=bool)
+    for k, i in enumerate(rows):
+        mask[k, ci[start[i]:start[i + 1]].cpu().numpy()] = True
+    for h in range(H):
+        O_ref, lse_ref = R.attention_dense(Q[h][rows].astype(np.float64), K[h].astype(np.float64),
+                                           V[h].astype(np.float64), mask, 0.125)
+        _close(O[h].cpu().numpy()[rows], lse[h].cpu().numpy()[rows], O_ref, lse_ref, dtype)
+    O2 = sga.attention_forward(dQ, dK, dV, rp, ci, 0.125, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(O, O2)
 
 
 def test_explicit_and_implicit_paths_agree():
