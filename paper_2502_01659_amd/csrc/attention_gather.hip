@@ -1013,13 +1013,15 @@ __global__ __attribute__((amdgpu_waves_per_eu((D == 64 ? 8 : 4), (D == 64 ? 8 : 
 
 // What the tile path leaves over, in one launch for the call that does not know whether there is anything
 // (none reads what another writes): the first n_merge workgroups of a head merge the tiles' segments,
-// the others take the leftover rows and then the chunks of the split rows.  (n_merge and the others
-// are multiples of 8, so that the chunks keep their XCDs.)  An empty launch costs 3 to 6
+// the next n_rows take the leftover rows, the others the chunks of the split rows.  (n_merge and
+// n_rows are multiples of 8, so that the chunk workgroups keep their XCDs.)  An empty launch costs 3 to 6
 // us of a small call: +-32, L = 4,096, fp32, mask build and forward, in three launches 42.0 us, in two 38.9.
-// The same workgroups for rows and chunks: a chip-full for either, whichever a call has, and no more to start for
-// one that has neither.  (us, 1,024 workgroups of a head more for the chunks / L / 32 over the heads more / these:
-// random 10 %, fp16, L = 13,001 290 / 443 / 298, two heads 489 / 949 / 510, L = 24,576 907 / 1,085 / 890; +-16,
-// fp32, L = 4,096, eight heads 51.9 / 49.2 / 44.1, L = 16,384, one head 49.6 / 39.4 / 36.7.)
+// The chunks have as many workgroups as the chip holds twice (leftover_chunk_workgroups), however short the sequence:
+// in a scattered mask every row is split (us, 10 %, fp16, L = 13,001, two heads: with L / 32 over the heads 949,
+// with 512 a head 520, with 1,024 a head 505), and idle ones cost less than the launch they spare (+-16, fp32,
+// L = 4,096, eight heads 51.9 in launches of their own, 40.7 so).  Workgroups that take rows first and chunks then
+// bring keys of the whole range into the L2s that the chunks of others share (10 % below the diagonal, fp32, L = 24,576:
+// 977 against 814).
 // Four wavefronts per SIMD: fp32 at d = 256 has registers for five, which start on a second head's K and V
 // while the first is in the L2s (11.5 %, L = 9,001, two heads 3,182 against 2,932).
 template <typename T, int D>
@@ -1027,17 +1029,18 @@ __global__ __attribute__((amdgpu_waves_per_eu(1, 4))) __launch_bounds__(256) voi
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
     float* __restrict__ lse, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
     int64_t L, float scale, void* ws, size_t ws_bytes, int use_split, int may_share, int accumulate,
-    uint32_t n_merge) {
+    uint32_t n_merge, uint32_t n_rows) {
   if (blockIdx.x < n_merge) {
     tile_merge_body<T, D>(O, lse, row_ptr, L, ws, ws_bytes, accumulate, blockIdx.x / kTile, n_merge / kTile,
                           blockIdx.x % kTile, kTile);
     return;
   }
-  gather_csr_body<T, D>(Q, K, V, O, lse, row_ptr, col_idx, L, scale, ws, ws_bytes, use_split, 1, accumulate,
-                        blockIdx.x - n_merge, gridDim.x - n_merge);
-  if (use_split)
-    gather_chunk_body<T, D>(Q, K, V, row_ptr, col_idx, L, scale, ws, ws_bytes, may_share, blockIdx.x - n_merge,
-                            gridDim.x - n_merge);
+  if (blockIdx.x < n_merge + n_rows)
+    gather_csr_body<T, D>(Q, K, V, O, lse, row_ptr, col_idx, L, scale, ws, ws_bytes, use_split, 1, accumulate,
+                          blockIdx.x - n_merge, n_rows);
+  else
+    gather_chunk_body<T, D>(Q, K, V, row_ptr, col_idx, L, scale, ws, ws_bytes, may_share, blockIdx.x - n_merge - n_rows,
+                            gridDim.x - n_merge - n_rows);
 }
 
 // Rows of up to kMaxSplit chunks: one wavefront per (long row, head) combines the row's partials
@@ -1110,10 +1113,10 @@ sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
   const bool may_share = split && (a.prepared ? a.plan_rows_share : shared_chunks_possible(a.L, a.H, a.d, a.dtype, a.ws_bytes));
   if constexpr (D >= kHeadDim) {
     if (fused) {
-      const unsigned n_merge = merge_tiles(a) * kTile;
-      hipLaunchKernelGGL((leftovers_kernel<T, D>), dim3(n_merge + (unsigned)nwg, (unsigned)a.H), dim3(256), 0, a.stream, Q, K, V, O,
+      const unsigned n_merge = merge_tiles(a) * kTile, n_chunks = split ? (unsigned)leftover_chunk_workgroups(a.H) : 0;
+      hipLaunchKernelGGL((leftovers_kernel<T, D>), dim3(n_merge + (unsigned)nwg + n_chunks, (unsigned)a.H), dim3(256), 0, a.stream, Q, K, V, O,
                          a.lse, a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes, split ? 1 : 0, may_share ? 1 : 0,
-                         a.accumulate ? 1 : 0, n_merge);
+                         a.accumulate ? 1 : 0, n_merge, (unsigned)nwg);
     }
   }
   if (!fused && !(a.prepared && a.plan_long_rows == a.L)) {       // (a prepared graph all of whose rows are split: 19 us of L = 24,576)

@@ -332,6 +332,12 @@ inline bool shared_chunks_possible(int64_t L, int32_t H, int32_t d, int32_t dtyp
   return rows <= L && room(without > least ? without : least, false);
 }
 
+// ... and over the chunks of its split rows: two rounds of the 1,024 that the chip holds of leftovers_kernel
+__host__ __device__ inline int64_t leftover_chunk_workgroups(int32_t H) {
+  const int64_t full = 2048 / H > 128 ? 2048 / H : 128;
+  return (full + 7) & ~int64_t(7);
+}
+
 // First work item of tile t: f(t) = t + row_ptr[min(32t, L)] / S.
 __device__ __forceinline__ int64_t work_first(const int64_t* __restrict__ row_ptr, int64_t L,
                                               int sh, int64_t t) {

@@ -31,7 +31,7 @@ int main() {
     sga::row_split_shape(deg, p, false, chunks, len);
     printf("%d %lld %lld %d %d %d %d %d %d %d %d %d %d %d\n", p.seg_shift, (long long)p.n_work, (long long)p.cap_tparts, p.l2_chunks, chunks, len,
            sga::tile_parts_in_doubt(p), sga::tile_parts_may_be_in_doubt(dtype, p.total_bytes),
-           (int)sga::leftover_workgroups(L, H), merge_of(H), p.l2_chunks != 0 && dtype == SGA_F16 ? -1 : 0,
+           (int)(sga::leftover_workgroups(L, H) | sga::leftover_chunk_workgroups(H) << 16), merge_of(H), p.l2_chunks != 0 && dtype == SGA_F16 ? -1 : 0,
            sga::l2_chunks(L, d, dtype) && L <= sga::kSharedMaxKeys && sga::shared_chunks(p, nnz, L, dtype, 1 << 16, 2),
            possible(L, H, nnz, dtype, d), (int)sga::first_xcd((uint32_t)L, (int)deg));
   }
@@ -130,14 +130,16 @@ def test_doubtful_calls_are_recognised_by_their_workspace(plans):
 
 
 def test_rows_left_over_have_a_chip_full_of_workgroups(plans):
-    """Without a plan the same workgroups take the rows that the tiles leave over and the chunks of split rows.  In a
-    scattered mask those are all rows: a wavefront each, or the 1,024 workgroups that the chip holds; chunk c
-    runs on XCD c % 8, which a multiple of 8 keeps."""
+    """Without a plan one launch takes the rows that the tiles leave over and the chunks of split rows.  In a scattered
+    mask the one or the other are all rows: a wavefront each, or a chip full; chunk c runs on XCD c % 8, which
+    multiples of 8 keep."""
     cases = [(L, L * L // 20, H, dtype, 64) for dtype in (0, 1) for H in (1, 2, 4, 8, 64, 1000)
              for L in (1, 31, 2049, 3001, 5000, 13001, 16384, 24576, 1 << 20)]
-    for (L, _, H, _, _), (wgs,) in zip(cases, plans(cases, 8, 9)):
-        assert wgs % 8 == 0 and 4 * wgs >= min(L, 4096 // H), (L, H, wgs)
-        assert wgs * H <= 2048 + 264 * H, (L, H, wgs)
+    for (L, _, H, _, _), (both,) in zip(cases, plans(cases, 8, 9)):
+        rows, chunks = both & 0xFFFF, both >> 16
+        assert rows % 8 == 0 and 4 * rows >= min(L, 4096 // H), (L, H, rows)
+        assert chunks % 8 == 0 and chunks * H >= 1024, (L, H, chunks)
+        assert rows * H <= 2048 + 264 * H and chunks * H <= 2048 + 136 * H, (L, H, rows, chunks)
 
 
 def test_idle_merge_workgroups_do_not_grow_with_the_heads(plans):
