@@ -300,17 +300,18 @@ __global__ __launch_bounds__(256) void clear_workspace_kernel(void* ws, size_t w
     next[i] = 0;          // claim counters of the heads
 }
 
-// One thread per row, see record_split_row: the rows of a call on the per-row kernels alone, or (after_tiles) the rows
+// One thread per row, see record_split_rows: the rows of a call on the per-row kernels alone, or (after_tiles) the rows
 // that the tile path left over where the CSR -> tile pass could not tell (tile_parts_in_doubt).
 __global__ __launch_bounds__(256) void split_prepass_kernel(const int64_t* __restrict__ row_ptr,
                                                             int64_t L, int32_t H, int32_t dtype,
                                                             int32_t d, void* ws, size_t ws_bytes, int after_tiles) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= L || row_ptr[i + 1] - row_ptr[i] <= kSplitThreshold / 2) return;      // (no rule splits a row this short)
+  bool mine = i < L && row_ptr[i + 1] - row_ptr[i] > kSplitThreshold / 2;      // (no rule splits a shorter row)
+  if (!__any(mine)) return;
   const WorkspacePlan pl = plan_workspace(L, H, row_ptr[L], dtype, d);
-  if (pl.total_bytes > ws_bytes) return;
-  if (after_tiles && (!tile_parts_in_doubt(pl) || tile_handled(pl, ws, row_ptr, L, i / kTile))) return;
-  record_split_row(row_ptr, i, pl, ws);
+  if (pl.total_bytes > ws_bytes || (after_tiles && !tile_parts_in_doubt(pl))) return;
+  if (mine && after_tiles) mine = !tile_handled(pl, ws, row_ptr, L, i / kTile);
+  record_split_rows(row_ptr, i, mine, pl, ws);
 }
 
 // The list of long rows that this call uses.

@@ -1914,8 +1914,8 @@ __global__ __launch_bounds__(256) void tile_analyze_kernel(const int64_t* __rest
       }
     }
     // the tile's rows that the per-row kernels split (L > kSplitThreshold; see tile_parts_in_doubt)
-    if (L > kSplitThreshold && !tile_parts_in_doubt(pl) && __any(gives_up) && lane < kTile && row < L)
-      record_split_row(row_ptr, row, pl, ws);
+    if (L > kSplitThreshold && !tile_parts_in_doubt(pl) && __any(gives_up))
+      record_split_rows(row_ptr, row, lane < kTile && row < L, pl, ws);
   }
 }
 

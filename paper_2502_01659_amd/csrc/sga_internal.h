@@ -126,18 +126,17 @@ __host__ __device__ inline int seg_shift(int32_t dtype, int64_t nnz, int32_t H, 
 // tpartials           cap_tparts x H x max(1, d / 64) x kTilePartialFloats floats
 // work_next           H x uint32: claims of tile work items made so far of each head (dynamic scheduling)
 enum WsCounter : int {
-  kCtrChunksNeeded = 0,   // sum of chunk counts of all long rows
-  kCtrItemsAlloc = 1,     // bump allocator over the partial slots of split rows
-  kCtrLongRows = 2,       // number of long rows recorded
+  kCtrChunksNeeded = 0,   // sum of chunk counts of all long rows, handing out their partial slots
+  kCtrFineNeeded = 1,     // the same for the finer split (see row_split_shape); one 64-bit word with the former
   kCtrTilePartsNeeded = 3,  // sum of segment counts of all multi-segment tiles
   kCtrTilePartsAlloc = 4,   // bump allocator over tile partial slots
   kCtrTilesBad = 5,         // tiles whose block lists overflowed (left to the gather path)
   kCtrMultiTiles = 6,       // multi-segment tiles recorded in the merge list
-  kCtrMaxChunks = 7,        // most chunks any split row has (bounds the chunk kernel's unit loop)
-  kCtrFineNeeded = 8,       // the same three for the finer split (see row_split_shape)
-  kCtrFineAlloc = 9,
-  kCtrMaxChunksFine = 10,
   kCtrMultiItems = 11,      // groups of up to four segment items (see TileItem::group)
+  // (the second cache line: atomics on one line wait for each other)
+  kCtrLongRows = 32,        // number of long rows recorded
+  kCtrMaxChunks = 34,       // most chunks any split row has (bounds the chunk kernel's unit loop), ...
+  kCtrMaxChunksFine = 35,   // ... in the finer split; one 64-bit word with the former
   kNumCounters = 64
 };
 
@@ -408,28 +407,55 @@ __device__ __forceinline__ bool tiles_cover_everything(const WorkspacePlan& pl, 
   return ctr[kCtrTilesBad] == 0 && (int64_t)ctr[kCtrTilePartsNeeded] <= pl.cap_tparts;
 }
 
-// Row i of the per-row path's preparation: a row that is split reserves its partial slots and enters the
-// list of long rows.
-__device__ __forceinline__ void record_split_row(const int64_t* __restrict__ row_ptr, int64_t i, const WorkspacePlan& pl,
-                                                 void* ws) {
-  const int64_t deg = row_ptr[i + 1] - row_ptr[i];
-  if (!row_is_split(deg, pl)) return;
-  uint32_t* ctr = reinterpret_cast<uint32_t*>(ws);
-  int32_t n, len, nf, lenf;
-  row_split_shape(deg, pl, false, n, len);
-  row_split_shape(deg, pl, true, nf, lenf);
-  if (nf <= n) {
-    nf = n;
-    lenf = len;
+// The per-row path's preparation of a wavefront's rows (lane: row i, if mine): those that are split reserve their
+// partial slots and enter the list of long rows.  All lanes call it.  Atomics on one counter follow each other
+// 12 ns apart whatever they come from, so a wavefront issues two, and two more where it raises a maximum (24,576
+// split rows, the CSR -> tile pass, us: none recorded 28, seven atomics per wavefront 89, so 60).
+__device__ __forceinline__ void record_split_rows(const int64_t* __restrict__ row_ptr, int64_t i, bool mine,
+                                                  const WorkspacePlan& pl, void* ws) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t deg = mine ? row_ptr[i + 1] - row_ptr[i] : 0;
+  int32_t n = 0, len = 0, nf = 0, lenf = 0;
+  if (row_is_split(deg, pl)) {
+    row_split_shape(deg, pl, false, n, len);
+    row_split_shape(deg, pl, true, nf, lenf);
+    if (nf <= n) {
+      nf = n;
+      lenf = len;
+    }
   }
-  atomicAdd(&ctr[kCtrChunksNeeded], (uint32_t)n);
-  atomicMax(&ctr[kCtrMaxChunks], (uint32_t)n);
-  atomicAdd(&ctr[kCtrFineNeeded], (uint32_t)nf);
-  atomicMax(&ctr[kCtrMaxChunksFine], (uint32_t)nf);
-  const uint32_t base = atomicAdd(&ctr[kCtrItemsAlloc], (uint32_t)n);
-  const uint32_t basef = atomicAdd(&ctr[kCtrFineAlloc], (uint32_t)nf);
-  if ((int64_t)base + n > pl.cap_items) return;
-  const uint32_t slot = atomicAdd(&ctr[kCtrLongRows], 1u);
+  if (!__any(n > 0)) return;
+  int32_t sum = n, sumf = nf, most = n, mostf = nf;      // up to this lane
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const int32_t t = __shfl_up(sum, off, kWave), tf = __shfl_up(sumf, off, kWave);
+    const int32_t u = __shfl_up(most, off, kWave), uf = __shfl_up(mostf, off, kWave);
+    if (lane >= off) {
+      sum += t;
+      sumf += tf;
+      most = max(most, u);
+      mostf = max(mostf, uf);
+    }
+  }
+  uint32_t* ctr = reinterpret_cast<uint32_t*>(ws);
+  uint32_t base = 0, basef = 0, slot = 0;
+  if (lane == kWave - 1) {
+    const unsigned long long both = atomicAdd(reinterpret_cast<unsigned long long*>(&ctr[kCtrChunksNeeded]),
+                                              (unsigned long long)(uint32_t)sumf << 32 | (uint32_t)sum);
+    base = (uint32_t)both;
+    basef = (uint32_t)(both >> 32);
+    const unsigned long long seen = __hip_atomic_load(reinterpret_cast<unsigned long long*>(&ctr[kCtrMaxChunks]),
+                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((uint32_t)seen < (uint32_t)most) atomicMax(&ctr[kCtrMaxChunks], (uint32_t)most);
+    if ((uint32_t)(seen >> 32) < (uint32_t)mostf) atomicMax(&ctr[kCtrMaxChunksFine], (uint32_t)mostf);
+  }
+  base = __shfl(base, kWave - 1, kWave) + (uint32_t)(sum - n);
+  basef = __shfl(basef, kWave - 1, kWave) + (uint32_t)(sumf - nf);
+  const bool fits = n > 0 && (int64_t)base + n <= pl.cap_items;
+  const uint64_t all = __ballot(fits);
+  if (lane == 0) slot = atomicAdd(&ctr[kCtrLongRows], (uint32_t)__popcll(all));
+  slot = __shfl(slot, 0, kWave) + (uint32_t)__popcll(all & ((uint64_t(1) << lane) - 1));
+  if (!fits) return;
   int4* lr = reinterpret_cast<int4*>(static_cast<char*>(ws) + pl.off_long);
   lr[slot] = make_int4((int)i, (int)base, n, len);
   // (read only if the finer chunks of every row fit, and then basef + nf <= cap_items)
