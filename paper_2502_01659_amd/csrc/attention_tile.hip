@@ -3728,7 +3728,8 @@ __device__ __forceinline__ void softmax_block_deferred(floatx16 sv, float c, boo
 // that took W > 64 before has two, each of which waits for its first blocks, its Q and its output alone.
 // (blocks start at the workgroup's first key, W below it: sub-tile w covers blocks w .. w + (31 + 2W) / 32
 // of them, and in the first workgroups of a class, where the window is cut at key 0, at most
-// 2 * ceil(W / 32) + 1: kWaveBlocks = 5 up to W = 64, 7 up to 96, 9 up to 128, 11 up to 160, 17 up to 256)
+// 2 * ceil(W / 32) + 1: kWaveBlocks = 5 up to W = 64, 7 up to 96, 9 up to 128, 11 up to 160, 17 up to 256; a class
+// of few tokens has fewer, see subtile_blocks)
 // L = 1,048,576, 4 heads, us, band kernel -> this: W = 65 737 -> 446, 96 756 -> 475, 128 837 -> 558,
 // 144 872 -> 600, 160 923 -> 719, 192 980 -> 797, 256 1,076 -> 952; beyond, one workgroup per CU: 288
 // 1,136 -> 1,665.  W = 64 (2.1 GB, 5.1 TB/s): 412.
@@ -4067,6 +4068,7 @@ sga_status run_tile_implicit(const AttnArgs& a) {
   const int acc = a.accumulate ? 1 : 0;
   if (a.dtype == SGA_F32) clear_unselected_rows<float>(a); else clear_unselected_rows<__half>(a);
   const int64_t nb_max = (4 * kTile - 1 + 2 * (int64_t)a.window) / kTile + 1;   // key blocks of 128 queries
+  const int64_t staged = staged_blocks(a.window, Lc);
   const bool kv = wg && nb_max >= kKvMinBlocks;
   const char* window_kernel = kv ? "tile_window_kv_kernel" : wg ? "tile_window_wg_kernel"
                               : pair ? "tile_window_band_kernel" : "tile_window_kernel";
@@ -4078,21 +4080,21 @@ sga_status run_tile_implicit(const AttnArgs& a) {
       Lq = (shape.seg_len + s - 1) / s;
       Lr = (last_len + s - 1) / s;
     }
-    const int64_t wave_blocks = 2 * ((a.window + kTile - 1) / kTile) + 1;
+    const int64_t wave_blocks = subtile_blocks(a.window, Lc);
     const auto kv_kernel = wave_blocks <= 5   ? tile_window_kv_kernel<5>
                            : wave_blocks <= 7 ? tile_window_kv_kernel<7>
                            : wave_blocks <= 9 ? tile_window_kv_kernel<9>
                            : wave_blocks <= 11 ? tile_window_kv_kernel<11> : tile_window_kv_kernel<17>;
     if (kv)
-      hipLaunchKernelGGL(kv_kernel, grid, dim3(256), (size_t)nb_max * CoreF16::kBlockBytes,
+      hipLaunchKernelGGL(kv_kernel, grid, dim3(256), (size_t)staged * CoreF16::kBlockBytes,
                          a.stream, static_cast<const __half*>(a.Q), static_cast<const __half*>(a.K),
                          static_cast<const __half*>(a.V), static_cast<__half*>(a.O), a.lse, a.L,
-                         (int64_t)a.window, s, n_groups, a.scale, acc, (int)nb_max, shape.seg_len, Lq, Lr);
+                         (int64_t)a.window, s, n_groups, a.scale, acc, (int)staged, shape.seg_len, Lq, Lr);
     else
-      hipLaunchKernelGGL(tile_window_wg_kernel, grid, dim3(256), (size_t)nb_max * 2 * CoreF16::kBlockBytes,
+      hipLaunchKernelGGL(tile_window_wg_kernel, grid, dim3(256), (size_t)staged * 2 * CoreF16::kBlockBytes,
                          a.stream, static_cast<const __half*>(a.Q), static_cast<const __half*>(a.K),
                          static_cast<const __half*>(a.V), static_cast<__half*>(a.O), a.lse, a.L,
-                         (int64_t)a.window, s, n_groups, a.scale, acc, (int)nb_max, shape.seg_len, Lq, Lr);
+                         (int64_t)a.window, s, n_groups, a.scale, acc, (int)staged, shape.seg_len, Lq, Lr);
   } else if (pair) {
     hipLaunchKernelGGL(tile_window_band_kernel, grid, dim3(256), 0, a.stream,
                        static_cast<const __half*>(a.Q), static_cast<const __half*>(a.K),

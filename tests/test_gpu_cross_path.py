@@ -256,6 +256,26 @@ def test_staged_windows_agree_with_row_kernels(window, kind, L, stride):
     _agree(O1, l1, O2, l2, "f16", 2.0)
 
 
+@pytest.mark.parametrize("tokens", [33, 66, 96, 97, 130, 160, 161, 192, 193, 224, 225, 256, 257, 258])
+@pytest.mark.parametrize("stride", [1, 3])
+def test_staged_classes_agree_with_row_kernels(tokens, stride):
+    """fp16 2-D dilated blocks of so many selected rows, which all see each other: LDS and registers are those of the
+    class and not of the window, on both sides of every number of blocks; the last block of the sequence is
+    a short one.  Forward, and continuing a state."""
+    import torch
+    spec = MaskSpec(KIND_DILATED_2D, tokens * stride * 5 + 41, block=tokens * stride, stride=stride)
+    print("case", spec, flush=True)
+    Q, K, V = torch_qkv(2, spec.L, 64, "f16", 0.8, tokens, "cuda:0")
+    O1, l1 = sga.attention_forward_implicit(Q, K, V, spec, 0.125, path=sga.PATH_TILE, want_lse=True)
+    O2, l2 = sga.attention_forward_implicit(Q, K, V, spec, 0.125, path=sga.PATH_GATHER, want_lse=True)
+    torch.cuda.synchronize()
+    _agree(O1, l1, O2, l2, "f16")
+    sga.attention_accumulate_implicit(Q, K, V, spec, 0.125, O1, l1, path=sga.PATH_TILE)
+    sga.attention_accumulate_implicit(Q, K, V, spec, 0.125, O2, l2, path=sga.PATH_GATHER)
+    torch.cuda.synchronize()
+    _agree(O1, l1, O2, l2, "f16", 2.0)
+
+
 @pytest.mark.parametrize("case", range(11))
 def test_d128_wide_bands_agree_with_row_kernels(case):
     """fp16, d = 128, windows wide enough and calls large enough for the kernel that gives a

@@ -29,11 +29,12 @@ int main() {
     const sga::WorkspacePlan p = sga::plan_workspace(L, H, nnz, dtype, d);
     int chunks, len;
     sga::row_split_shape(deg, p, false, chunks, len);
-    printf("%d %lld %lld %d %d %d %d %d %d %d %d %d %d %d\n", p.seg_shift, (long long)p.n_work, (long long)p.cap_tparts, p.l2_chunks, chunks, len,
+    printf("%d %lld %lld %d %d %d %d %d %d %d %d %d %d %d %d\n", p.seg_shift, (long long)p.n_work, (long long)p.cap_tparts, p.l2_chunks, chunks, len,
            sga::tile_parts_in_doubt(p), sga::tile_parts_may_be_in_doubt(dtype, p.total_bytes),
            (int)(sga::leftover_workgroups(L, H) | sga::leftover_chunk_workgroups(H) << 16), merge_of(H), p.l2_chunks != 0 && dtype == SGA_F16 ? -1 : 0,
            sga::l2_chunks(L, d, dtype) && L <= sga::kSharedMaxKeys && sga::shared_chunks(p, nnz, L, dtype, 1 << 16, 2),
-           possible(L, H, nnz, dtype, d), (int)sga::first_xcd((uint32_t)L, (int)deg));
+           possible(L, H, nnz, dtype, d), (int)sga::first_xcd((uint32_t)L, (int)deg),
+           (int)(sga::staged_blocks(deg, L) << 8 | sga::subtile_blocks(deg, L)));
   }
   return 0;
 }
@@ -187,3 +188,21 @@ def test_only_rows_of_few_chunks_start_at_an_xcd_of_their_own(plans):
             assert len(set(load)) == 1, (z, load)
         else:
             assert set(starts) == {0}, z
+
+
+def test_staged_windows_have_room_for_their_blocks_and_no_more(plans):
+    """The key blocks that tile_window_wg_kernel and tile_window_kv_kernel copy and meet, counted as they count them,
+    for every workgroup and sub-tile of a class of Lc tokens: the most there are is what they are given."""
+    shapes = [(Lc, W) for Lc in list(range(1, 70)) + [96, 97, 128, 129, 130, 160, 161, 192, 193, 224, 225, 256, 257, 258, 300, 400, 900, 2000]
+              for W in (1, 5, 16, 31, 32, 33, 63, 64, 65, 80, 96, 97, 128, 129, 144, 160, 161, 200, 255, 256) if W < Lc]
+    for (Lc, W), (word,) in zip(shapes, plans([(Lc, 0, 1, 1, 64, W) for Lc, W in shapes], 14, 15)):
+        most = most_sub = 0
+        for q0 in range(0, Lc, 128):
+            first, last = max(q0 - W, 0), min(q0 + 127 + W, Lc - 1)
+            most = max(most, (last - first) // 32 + 1)
+            for u0 in range(q0, min(q0 + 128, Lc), 32):
+                lo, hi = max(u0 - W, first), min(u0 + 31 + W, last)
+                most_sub = max(most_sub, (hi - first) // 32 - (lo - first) // 32 + 1)
+        staged, sub = word >> 8, word & 255
+        assert most <= staged <= max(4, (Lc + 31) // 32) and most_sub <= sub <= (Lc + 31) // 32, (Lc, W, staged, sub)
+        assert staged <= (127 + 2 * W) // 32 + 1 or staged == 4, (Lc, W)
