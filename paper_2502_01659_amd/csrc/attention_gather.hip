@@ -890,15 +890,15 @@ __global__ __attribute__((amdgpu_waves_per_eu((D == 64 ? 8 : 4), (D == 64 ? 8 : 
       reinterpret_cast<uint32_t*>(planes + i * S::kPlane + S::kKeys * S::kRowBytes)[threadIdx.x] = 0;
   }
   const uint32_t cohorts = (n_long + S::kRows - 1) / S::kRows;
-  // by L2 share chunk c on XCD c % 8 as in gather_chunk_kernel, else all units on all XCDs in turn, the chunks of
-  // the 64 rows on as many workgroups (their numbers are an odd number apart, the grid is a power of two): one row of
-  // many chunks among rows of two would keep one busy for 3 ms (random 8 %, L = 32,768, fp32, us: without such a
-  // row 1,135; with one of all keys, every chunk c on XCD c % 8 4,935, its chunks on one workgroup 4,270, so 1,440)
-  const bool by_share = pl.l2_chunks != 0;
-  const uint32_t n_units = by_share ? 8 * cohorts * ((max_chunks + 7) / 8) : cohorts * max_chunks;
+  // All units go round all workgroups, the chunks of the 64 rows to as many of them (their numbers are an odd number
+  // apart, the grid is a power of two): one row of many chunks among rows of two would keep one busy for 3 ms
+  // (random 8 %, L = 32,768, fp32, us: without such a row 1,135; with one of all keys, every chunk c on XCD c % 8 4,935,
+  // its chunks on one workgroup 4,270, so 1,440).  No part of the keys has an XCD of its own, as it has in
+  // gather_chunk_kernel: 64 rows share each copy, and masks denser in a part of the keys would leave XCDs
+  // idle (12 % of the right half only, L = 24,576, fp32 876 -> 508; uniform 10 % 821 / 827, L = 12,001 241 / 236).
+  const uint32_t n_units = cohorts * max_chunks;
   for (uint32_t u = blockIdx.x; u < n_units; u += gridDim.x) {
-    const uint32_t c = by_share ? (u & 7) + 8 * ((u >> 3) / cohorts) : u / cohorts;
-    const uint32_t cohort = by_share ? (u >> 3) % cohorts : (u + (cohorts & 1 ? 0 : c)) % cohorts;
+    const uint32_t c = u / cohorts, cohort = (u + (cohorts & 1 ? 0 : c)) % cohorts;
     const uint32_t r = cohort * S::kRows + threadIdx.x / 16;
     const int4 rec = r < n_long ? lr[r] : make_int4(0, 0, 0, 0);        // {row, first partial slot, chunks, chunk length}
     const bool active = (int)c < rec.z;

@@ -474,6 +474,33 @@ def test_many_split_rows_share_their_key_blocks(d, dtype, L, H, even):
     assert torch.equal(O3, O2)
 
 
+@pytest.mark.parametrize("d,L", [(64, 16001), (128, 15003)])
+def test_shared_key_blocks_of_one_sided_masks(d, L):
+    """Rows cut by L2 share whose neighbours all lie in the last third of the keys, or nearly all in the first
+    eighth: most parts of the keys are empty, one holds most edges.  Against the same call without a workspace."""
+    import torch
+    print("case one-sided", d, L, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(84)
+    j = torch.arange(L, device="cuda")
+    for fill in (torch.where(j >= L - L // 3, 0.23, 0.0), torch.where(j < L // 8, 0.34, 0.022)):
+        rp = torch.zeros(L + 1, dtype=torch.int64, device="cuda")
+        cols, deg = [], []
+        for r0 in range(0, L, 1024):
+            block = torch.rand((min(1024, L - r0), L), generator=g, device="cuda") < fill
+            block &= (j[None, :] // 32 + (r0 + torch.arange(block.shape[0], device="cuda"))[:, None] // 32) % 5 > 0
+            deg.append(block.sum(1))
+            cols.append(block.nonzero()[:, 1].to(torch.int32))
+        rp[1:] = torch.cat(deg).cumsum(0)
+        ci = torch.cat(cols).contiguous()
+        Q, K, V = (torch.from_numpy(x).cuda() for x in numpy_qkv(1, L, d, "f32", 0.6, 35))
+        ws = sga.alloc_workspace(L, 1, d, "f32", ci.numel())
+        O, lse = sga.attention_forward(Q, K, V, rp, ci, 0.125, workspace=ws, path=sga.PATH_GATHER, want_lse=True)
+        O1, lse1 = sga.attention_forward(Q, K, V, rp, ci, 0.125, path=sga.PATH_GATHER, want_lse=True)
+        torch.cuda.synchronize()
+        assert (O - O1).abs().max().item() <= 2 * TOL["f32"]
+        assert (lse - lse1).abs().max().item() <= 2 * LSE_TOL["f32"]
+
+
 @pytest.mark.parametrize("d,dtype,H", [(64, "f32", 2), (64, "f16", 2), (128, "f32", 1)])
 def test_rows_of_many_chunks_among_rows_of_two(d, dtype, H):
     """Two rows with every and with half the keys as neighbours, 12 and 6 chunks, among rows of two that share their key
