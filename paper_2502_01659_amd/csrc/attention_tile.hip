@@ -3692,7 +3692,7 @@ __global__ __launch_bounds__(256) void tile_window_wg_kernel(
     return;
   }
   // every wavefront is done with the staged blocks: their space takes the four output tiles
-  // (at least 4 K and 4 V blocks are allocated, 32 KB)
+  // (see staged_blocks)
   __syncthreads();
   if (active)
     finish_tile_rows<__half>(O + hoff, lse_h, s * u0 + p, s, Lc - u0 < kTile ? (int)(Lc - u0) : kTile, st,
@@ -3849,7 +3849,7 @@ __global__ __launch_bounds__(256) void tile_window_kv_kernel(
     if (active) finish_tile<__half>(O + hoff, lse_h, qrow, qrow, exists, st, h, true);
     return;
   }
-  // every wavefront is done with the staged blocks: their space takes the four output tiles
+  // every wavefront is done with the staged blocks: their space takes the four output tiles (see staged_blocks)
   __syncthreads();
   if (active)
     finish_tile_rows<__half>(O + hoff, lse_h, s * u0 + p, s, Lc - u0 < kTile ? (int)(Lc - u0) : kTile, st,
@@ -4068,8 +4068,9 @@ sga_status run_tile_implicit(const AttnArgs& a) {
   const int acc = a.accumulate ? 1 : 0;
   if (a.dtype == SGA_F32) clear_unselected_rows<float>(a); else clear_unselected_rows<__half>(a);
   const int64_t nb_max = (4 * kTile - 1 + 2 * (int64_t)a.window) / kTile + 1;   // key blocks of 128 queries
-  const int64_t staged = staged_blocks(a.window, Lc);
   const bool kv = wg && nb_max >= kKvMinBlocks;
+  const int64_t staged = staged_blocks(a.window, Lc, kv ? 1 : 2);
+  static_assert(CoreF16::kBlockBytes == kStagedBlockBytes && CoreF16::kTileBytes == kOutTileBytes, "see staged_blocks");
   const char* window_kernel = kv ? "tile_window_kv_kernel" : wg ? "tile_window_wg_kernel"
                               : pair ? "tile_window_band_kernel" : "tile_window_kernel";
   if (wg || pair) profile_mark_begin(a.stream, window_kernel);

@@ -282,15 +282,20 @@ __host__ __device__ inline uint32_t first_xcd(uint32_t s, int32_t z) {
   return z <= kXcdTurnChunks ? s * (uint32_t)z & 7u : 0u;
 }
 
-// fp16 windows staged in LDS: key blocks that a workgroup of 128 consecutive queries of a class of Lc tokens copies
-// (at least the four whose space its output tiles take), and blocks that one of its 32-query sub-tiles meets
+// fp16 windows staged in LDS: key blocks that a workgroup of 128 consecutive queries of a class of Lc tokens copies, and
+// blocks that one of its 32-query sub-tiles meets
 // (blocks start at the first key of the workgroup's window, or at key 0 where that cuts it).  A class holds
 // ceil(Lc / 32): in 2-D dilated masks W = Lc - 1, and LDS and registers for 2W keys halved the
 // workgroups per CU (L = 262,144, 4 heads, us, band kernel / sized by W / so: Lc = 130 175 / 153 / 136, 160 133 / 167 / 121,
-// 192 133 / 161 / 120, 257 221 / 219 / 176).
-__host__ __device__ inline int64_t staged_blocks(int64_t W, int64_t Lc) {
+// 192 133 / 161 / 120, 257 221 / 219 / 176).  sets: LDS blocks per key block (2: K beside V; 1: K and V in turn).  The four
+// output tiles leave through the same space, 4.5 blocks.
+constexpr int kStagedBlockBytes = kTile * kHeadDim * 2;
+constexpr int kOutTileBytes = kTile * (kHeadDim * 2 + 16);
+__host__ __device__ inline int64_t staged_blocks(int64_t W, int64_t Lc, int sets) {
   const int64_t window = (4 * kTile - 1 + 2 * W) / kTile + 1, held = (Lc + kTile - 1) / kTile;
-  return window < held ? window : held < 4 ? 4 : held;
+  const int64_t out = (4 * kOutTileBytes + sets * kStagedBlockBytes - 1) / (sets * kStagedBlockBytes);
+  const int64_t keys = window < held ? window : held;
+  return keys < out ? out : keys;
 }
 __host__ __device__ inline int64_t subtile_blocks(int64_t W, int64_t Lc) {
   const int64_t window = 2 * ((W + kTile - 1) / kTile) + 1, held = (Lc + kTile - 1) / kTile;

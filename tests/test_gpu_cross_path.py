@@ -256,7 +256,7 @@ def test_staged_windows_agree_with_row_kernels(window, kind, L, stride):
     _agree(O1, l1, O2, l2, "f16", 2.0)
 
 
-@pytest.mark.parametrize("tokens", [33, 66, 96, 97, 130, 160, 161, 192, 193, 224, 225, 256, 257, 258])
+@pytest.mark.parametrize("tokens", [33, 66, 96, 97, 115, 128, 130, 160, 161, 192, 193, 224, 225, 256, 257, 258])
 @pytest.mark.parametrize("stride", [1, 3])
 def test_staged_classes_agree_with_row_kernels(tokens, stride):
     """fp16 2-D dilated blocks of so many selected rows, which all see each other: LDS and registers are those of the

@@ -34,7 +34,7 @@ int main() {
            (int)(sga::leftover_workgroups(L, H) | sga::leftover_chunk_workgroups(H) << 16), merge_of(H), p.l2_chunks != 0 && dtype == SGA_F16 ? -1 : 0,
            sga::l2_chunks(L, d, dtype) && L <= sga::kSharedMaxKeys && sga::shared_chunks(p, nnz, L, dtype, 1 << 16, 2),
            possible(L, H, nnz, dtype, d), (int)sga::first_xcd((uint32_t)L, (int)deg),
-           (int)(sga::staged_blocks(deg, L) << 8 | sga::subtile_blocks(deg, L)));
+           (int)(sga::staged_blocks(deg, L, 1) << 16 | sga::staged_blocks(deg, L, 2) << 8 | sga::subtile_blocks(deg, L)));
   }
   return 0;
 }
@@ -192,7 +192,8 @@ def test_only_rows_of_few_chunks_start_at_an_xcd_of_their_own(plans):
 
 def test_staged_windows_have_room_for_their_blocks_and_no_more(plans):
     """The key blocks that tile_window_wg_kernel and tile_window_kv_kernel copy and meet, counted as they count them,
-    for every workgroup and sub-tile of a class of Lc tokens: the most there are is what they are given."""
+    for every workgroup and sub-tile of a class of Lc tokens: the most there are is what they are given.  The space also
+    holds the output tiles of the four wavefronts, 32 rows of 144 bytes each."""
     shapes = [(Lc, W) for Lc in list(range(1, 70)) + [96, 97, 128, 129, 130, 160, 161, 192, 193, 224, 225, 256, 257, 258, 300, 400, 900, 2000]
               for W in (1, 5, 16, 31, 32, 33, 63, 64, 65, 80, 96, 97, 128, 129, 144, 160, 161, 200, 255, 256) if W < Lc]
     for (Lc, W), (word,) in zip(shapes, plans([(Lc, 0, 1, 1, 64, W) for Lc, W in shapes], 14, 15)):
@@ -203,6 +204,9 @@ def test_staged_windows_have_room_for_their_blocks_and_no_more(plans):
             for u0 in range(q0, min(q0 + 128, Lc), 32):
                 lo, hi = max(u0 - W, first), min(u0 + 31 + W, last)
                 most_sub = max(most_sub, (hi - first) // 32 - (lo - first) // 32 + 1)
-        staged, sub = word >> 8, word & 255
-        assert most <= staged <= max(4, (Lc + 31) // 32) and most_sub <= sub <= (Lc + 31) // 32, (Lc, W, staged, sub)
-        assert staged <= (127 + 2 * W) // 32 + 1 or staged == 4, (Lc, W)
+        sub = word & 255
+        assert most_sub <= sub <= (Lc + 31) // 32, (Lc, W, sub)
+        for sets, staged in ((1, word >> 16), (2, word >> 8 & 255)):
+            out = -(-4 * 32 * 144 // (sets * 4096))
+            assert max(most, out) <= staged <= max(out, (Lc + 31) // 32), (Lc, W, sets, staged)
+            assert staged <= max(out, (127 + 2 * W) // 32 + 1), (Lc, W, sets, staged)
