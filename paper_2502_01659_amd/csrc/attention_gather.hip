@@ -1030,9 +1030,10 @@ __global__ __attribute__((amdgpu_waves_per_eu((D == 64 ? 8 : 4), (D == 64 ? 8 : 
 // bring keys of the whole range into the L2s that the chunks of others share (10 % below the diagonal, fp32, L = 24,576:
 // 977 against 814).
 // Four wavefronts per SIMD: fp32 at d = 256 has registers for five, which start on a second head's K and V
-// while the first is in the L2s (11.5 %, L = 9,001, two heads 3,182 against 2,932).
+// while the first is in the L2s (11.5 %, L = 9,001, two heads 3,182 against 2,932).  At d = 128 three, as the row kernel
+// has, for the same reason (6 %, L = 12,001, us: 545 with four, 504 so; 5 %, L = 20,000, two heads 3,627, 3,460).
 template <typename T, int D>
-__global__ __attribute__((amdgpu_waves_per_eu(1, 4))) __launch_bounds__(256) void leftovers_kernel(
+__global__ __attribute__((amdgpu_waves_per_eu(1, sizeof(T) == 4 && D == 128 ? 3 : 4))) __launch_bounds__(256) void leftovers_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
     float* __restrict__ lse, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
     int64_t L, float scale, void* ws, size_t ws_bytes, int use_split, int may_share, int accumulate,
