@@ -378,7 +378,7 @@ sga_status sga_graph_prepare(const int64_t* row_ptr, const int32_t* col_idx, int
   p.flags = (parts_fit ? SGA_GRAPH_TILE_PARTS_FIT : 0) | (chunks_fit ? SGA_GRAPH_ROW_CHUNKS_FIT : 0) |
             (p.tiles_left == 0 && parts_fit ? SGA_GRAPH_TILES_COVER_ALL : 0);
   if (chunks_fit && shared_chunks_possible(L, H, d, dtype, workspace_bytes) &&
-      shared_chunks(pl, nnz, L, dtype, p.long_rows, ctr[split_is_fine(pl, ctr) ? kCtrMaxChunksFine : kCtrMaxChunks]))
+      shared_chunks(pl, nnz, L, H, d, dtype, ctr))
     p.flags |= SGA_GRAPH_ROWS_SHARE_KEYS;
   p.row_ptr = row_ptr; p.col_idx = col_idx;
   p.workspace = workspace; p.workspace_bytes = workspace_bytes;

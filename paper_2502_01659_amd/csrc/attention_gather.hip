@@ -649,7 +649,7 @@ __device__ __forceinline__ void gather_chunk_body(
   const WorkspacePlan pl = plan_workspace(L, H, row_ptr[L], dtype, D);
   uint32_t max_chunks;
   const int4* lr = long_rows(pl, ws, max_chunks);
-  if (may_share && shared_chunks(pl, row_ptr[L], L, dtype, n_long, max_chunks)) return;      // (shared_chunk_kernel)
+  if (may_share && shared_chunks(pl, row_ptr[L], L, H, D, dtype, reinterpret_cast<const uint32_t*>(ws))) return;      // (shared_chunk_kernel)
   float* partials = reinterpret_cast<float*>(static_cast<char*>(ws) + pl.off_partials);
   const int lane = threadIdx.x & (kWave - 1);
   const int waves = blockDim.x / kWave;
@@ -724,6 +724,7 @@ struct SharedChunk {
   static constexpr int kThreads = 1024;
   static constexpr int kKeys = kRowBytes > 256 ? 64 : 128;   // 66 KB for K and V of a block (fp16, d = 64: 33)
   static constexpr int kRows = kThreads / 16;
+  static_assert(kRows == kSharedRows, "see shared_chunks");
   static constexpr int kBatch = 4;                           // edges whose rows are read together (registers)
   static constexpr int kPlane = (kKeys + 1) * kRowBytes;     // the row of zeros behind the block stands in for edges that are not there
 
@@ -882,7 +883,7 @@ __global__ __attribute__((amdgpu_waves_per_eu((D == 64 ? 8 : 4), (D == 64 ? 8 : 
   const WorkspacePlan pl = plan_workspace(L, H, row_ptr[L], dtype, D);
   uint32_t max_chunks;
   const int4* lr = long_rows(pl, ws, max_chunks);
-  if (!shared_chunks(pl, row_ptr[L], L, dtype, n_long, max_chunks)) return;
+  if (!shared_chunks(pl, row_ptr[L], L, H, D, dtype, reinterpret_cast<const uint32_t*>(ws))) return;
   float* partials = reinterpret_cast<float*>(static_cast<char*>(ws) + pl.off_partials);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int lane = threadIdx.x & (kWave - 1), l16 = lane & 15;
@@ -1144,8 +1145,7 @@ sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
     if constexpr (D == 64 || D == 128) {
       if (may_share) {
         using S = SharedChunk<T, D>;
-        const unsigned wgs = D == 64 ? 512 : 256;        // what the chip holds
-        hipLaunchKernelGGL((shared_chunk_kernel<T, D>), dim3(wgs, (unsigned)a.H), dim3(S::kThreads), 0, a.stream, Q, K, V,
+        hipLaunchKernelGGL((shared_chunk_kernel<T, D>), dim3(shared_places(D), (unsigned)a.H), dim3(S::kThreads), 0, a.stream, Q, K, V,
                            a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes);
       }
     }

@@ -411,8 +411,8 @@ def test_rows_split_into_a_few_chunks(d, dtype):
         _close(O[h].cpu().numpy()[rows], lse[h].cpu().numpy()[rows], O_ref, lse_ref, dtype)
 
 
-@pytest.mark.parametrize("d,dtype,L,H", [(64, "f32", 9001, 1), (64, "f32", 18001, 2), (64, "f16", 18017, 2),
-                                         (128, "f32", 8961, 1), (128, "f32", 18001, 1), (128, "f16", 18049, 1)])
+@pytest.mark.parametrize("d,dtype,L,H", [(64, "f32", 9001, 1), (64, "f32", 18001, 2), (64, "f16", 18017, 4),
+                                         (128, "f32", 8961, 1), (128, "f32", 18001, 1), (128, "f16", 18049, 2)])
 @pytest.mark.parametrize("even", [True, False])
 def test_many_split_rows_share_their_key_blocks(d, dtype, L, H, even):
     """Random rows dense enough for shared_chunk_kernel, cut into 2 and into 8 chunks: lengths that end inside a

@@ -22,6 +22,19 @@ int merge_of(int H) {
   a.H = H;
   return (int)sga::merge_tiles(a);
 }
+bool share(const sga::WorkspacePlan& p, long long nnz, long long L, int H, int d, int dtype, uint32_t rows) {      // rows of two chunks
+  uint32_t ctr[sga::kNumCounters] = {};
+  ctr[sga::kCtrLongRows] = rows;
+  ctr[sga::kCtrChunksNeeded] = 2 * rows;
+  ctr[sga::kCtrFineNeeded] = 0xFFFFFFFF;         // (the finer split has no room)
+  ctr[sga::kCtrMaxChunks] = 2;
+  return sga::shared_chunks(p, nnz, L, H, d, dtype, ctr);
+}
+int least_shared(const sga::WorkspacePlan& p, long long nnz, long long L, int H, int d, int dtype) {
+  uint32_t rows = 64;
+  while (rows < 1 << 16 && !share(p, nnz, L, H, d, dtype, rows)) rows += 64;
+  return (int)rows;
+}
 int main() {
   long long L, nnz, deg;
   int H, dtype, d;
@@ -29,12 +42,13 @@ int main() {
     const sga::WorkspacePlan p = sga::plan_workspace(L, H, nnz, dtype, d);
     int chunks, len;
     sga::row_split_shape(deg, p, false, chunks, len);
-    printf("%d %lld %lld %d %d %d %d %d %d %d %d %d %d %d %d\n", p.seg_shift, (long long)p.n_work, (long long)p.cap_tparts, p.l2_chunks, chunks, len,
+    printf("%d %lld %lld %d %d %d %d %d %d %d %d %d %d %d %d %d\n", p.seg_shift, (long long)p.n_work, (long long)p.cap_tparts, p.l2_chunks, chunks, len,
            sga::tile_parts_in_doubt(p), sga::tile_parts_may_be_in_doubt(dtype, p.total_bytes),
            (int)(sga::leftover_workgroups(L, H) | sga::leftover_chunk_workgroups(H) << 16), merge_of(H), p.l2_chunks != 0 && dtype == SGA_F16 ? -1 : 0,
-           sga::l2_chunks(L, d, dtype) && L <= sga::kSharedMaxKeys && sga::shared_chunks(p, nnz, L, dtype, 1 << 16, 2),
+           sga::l2_chunks(L, d, dtype) && L <= sga::kSharedMaxKeys && share(p, nnz, L, H, d, dtype, 1 << 16),
            possible(L, H, nnz, dtype, d), (int)sga::first_xcd((uint32_t)L, (int)deg),
-           (int)(sga::staged_blocks(deg, L, 1) << 16 | sga::staged_blocks(deg, L, 2) << 8 | sga::subtile_blocks(deg, L)));
+           (int)(sga::staged_blocks(deg, L, 1) << 16 | sga::staged_blocks(deg, L, 2) << 8 | sga::subtile_blocks(deg, L)),
+           least_shared(p, nnz, L, H, d, dtype));
   }
   return 0;
 }
@@ -210,3 +224,13 @@ def test_staged_windows_have_room_for_their_blocks_and_no_more(plans):
             out = -(-4 * 32 * 144 // (sets * 4096))
             assert max(most, out) <= staged <= max(out, (Lc + 31) // 32), (Lc, W, sets, staged)
             assert staged <= max(out, (127 + 2 * W) // 32 + 1), (Lc, W, sets, staged)
+
+
+def test_rows_share_key_blocks_where_they_fill_the_chip(plans):
+    """The least number of rows of two chunks that share their key blocks (2,048 at any rate): with 64 to a workgroup and
+    all heads, the chunks are enough for a quarter (fp32) or all (fp16) of the 512 (d = 64) or 256 (d = 128) places."""
+    L = 32768
+    cases = [(L, L * L // 10, H, dtype, d) for H in (1, 2, 4, 16) for dtype in (0, 1) for d in (64, 128)]
+    for (_, _, H, dtype, d), (least,) in zip(cases, plans(cases, 15, 16)):
+        places = (512 if d == 64 else 256) // (1 if dtype else 4)
+        assert least == max(2048, 32 * places // H), (H, dtype, d, least)
