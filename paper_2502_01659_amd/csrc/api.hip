@@ -237,6 +237,7 @@ sga_status run_explicit_call(const void* Q, const void* K, const void* V, const 
     a.prepared = true;
     a.plan_multi_tiles = parts_fit ? plan->multi_tiles : 0;
     a.plan_tiles_cover_all = (plan->flags & SGA_GRAPH_TILES_COVER_ALL) != 0;
+    a.plan_rows_left = parts_fit ? (int64_t)plan->tiles_left * kTile : L;
     a.plan_no_tiles = (int64_t)plan->tiles_left == (L + kTile - 1) / kTile;
     a.plan_long_rows = (plan->flags & SGA_GRAPH_ROW_CHUNKS_FIT) ? plan->long_rows : 0;
     a.plan_rows_share = (plan->flags & SGA_GRAPH_ROWS_SHARE_KEYS) != 0;

@@ -1112,7 +1112,7 @@ sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
     launch_split_prepass(a, skip_tiled);
   // after the tile path only leftover rows remain: a grid of about one chip-full of wavefronts
   // over all heads strides over the rows (it returns at once when the tiles covered everything)
-  const int64_t nwg = skip_tiled ? leftover_workgroups(a.L, a.H) : (a.L + 3) / 4;
+  const int64_t nwg = skip_tiled ? leftover_workgroups(a.prepared ? a.plan_rows_left : a.L, a.H) : (a.L + 3) / 4;
   const dim3 grid((unsigned)nwg, (unsigned)a.H);
   // the benchmark hook brackets the kernel that does the work: the row kernel, or the chunk
   // kernel where a prepared graph has found every row left to it split

@@ -303,9 +303,10 @@ __host__ __device__ inline int64_t subtile_blocks(int64_t W, int64_t Lc) {
 }
 
 // Workgroups (of four wavefronts) of a head that stride over what the tile path leaves over: about one chip-full over
-// the heads, a multiple of 8 so that workgroup i runs on XCD i % 8 behind any other such number.
-__host__ __device__ inline int64_t leftover_workgroups(int64_t L, int32_t H) {
-  const int64_t rows = (L + 3) / 4, full = 2048 / H > 256 ? 2048 / H : 256;
+// the heads, a multiple of 8 so that workgroup i runs on XCD i % 8 behind any other such number; fewer where a prepared
+// graph knows that there are not so many rows (one global token, L = 1,000, fp32, d = 256, 32 heads, us: 243 -> 210).
+__host__ __device__ inline int64_t leftover_workgroups(int64_t rows_left, int32_t H) {
+  const int64_t rows = (rows_left + 3) / 4, full = 2048 / H > 256 ? 2048 / H : 256;
   return ((rows < full ? rows : full) + 7) & ~int64_t(7);
 }
 
@@ -544,6 +545,7 @@ struct AttnArgs {
   bool prepared;
   uint32_t plan_multi_tiles;   // multi-segment tiles whose partial states fit (0: no merge launch)
   bool plan_tiles_cover_all;   // no row is left to the per-row kernels
+  int64_t plan_rows_left;      // at most so many rows are left to the per-row kernels
   bool plan_no_tiles;          // no tile qualified: the tile kernels have nothing to do
   uint32_t plan_long_rows;     // split rows among the leftover rows whose chunk items fit
   bool plan_rows_share;        // ... and shared_chunk_kernel computes them
