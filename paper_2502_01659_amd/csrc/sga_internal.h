@@ -326,10 +326,12 @@ __host__ __device__ inline bool split_is_fine(const WorkspacePlan& p, const uint
 // 3.4 % 6,947 -> 3,313 / 3,825 -> 3,900; d = 128, L = 24,576, 10 % 4,971 -> 1,627 / 2,844 -> 1,360); with fewer edges
 // to a step the sums lose accuracy (L = 90,001, 2.5 %, fp32: 3.7e-7 against 3.4e-7).
 // A unit of it (a chunk of 64 rows and a head) is a workgroup's work of 100 to 250 us, and few of them leave the chip idle
-// where the other kernel has a wavefront per chunk: it has to have units for a quarter of its places (fp32) or for all
-// (fp16).  (Rows of 10 % below window rows, two chunks each, prepared, us, that / this kernel by places filled: fp32, d = 64, an
-// 8th 322 / 341, a quarter 457 / 400 and 642 / 599, a half 588 / 483 and 1,125 / 615; d = 128, all 4,095 / 1,445; fp16, d = 64, an
-// 8th 199 / 289, a quarter 272 / 332 and 409 / 544, a half 387 / 442 and 716 / 570, all 678 / 659; d = 128, a half 450 / 484, all 686 / 590.)
+// where the other kernel has a wavefront per chunk.  Rows of 10 % below window rows, prepared, us, that / this kernel by the
+// share of its places that the units fill.  Chunks of 2,048 edges (two a row): fp32, d = 64, a quarter 642 / 599, 3/8
+// 476 / 476, a half 588 / 483 and 1,125 / 615; d = 128, all 4,095 / 1,445; fp16, d = 64, a quarter 409 / 544, a half
+// 387 / 442 and 716 / 570, all 678 / 659; d = 128, all 686 / 590.  The finer split of a few rows, ten chunks and more, each on
+// its XCD: fp32, d = 64, 0.8 328 / 341, 1.25 457 / 390; d = 128, 5 1,724 / 1,265; fp16 0.8 199 / 289, 1.25 272 / 325, d = 128,
+// 2.5 450 / 483.
 constexpr int64_t kSharedMaxKeys = int64_t(1) << 16;
 constexpr uint32_t kSharedMinRows = 2048;
 constexpr int64_t kSharedFillByShare = 18;
@@ -338,11 +340,11 @@ __host__ __device__ constexpr int64_t shared_fill(int32_t dtype) { return dtype 
 __host__ __device__ constexpr unsigned shared_places(int32_t d) { return d == 64 ? 512 : 256; }   // workgroups that the chip holds
 __host__ __device__ inline bool shared_chunks(const WorkspacePlan& pl, int64_t nnz, int64_t L, int32_t H, int32_t d,
                                               int32_t dtype, const uint32_t* ctr) {
-  if (pl.l2_chunks && dtype == SGA_F16) return false;
-  const bool fine = split_is_fine(pl, ctr);
+  const bool fine = split_is_fine(pl, ctr), finer = fine && !pl.l2_chunks;      // (by L2 share both splits are one)
+  if ((pl.l2_chunks || finer) && dtype == SGA_F16) return false;
   const int64_t chunks = (int64_t)ctr[fine ? kCtrFineNeeded : kCtrChunksNeeded] * H;
   return ctr[fine ? kCtrMaxChunksFine : kCtrMaxChunks] <= (uint32_t)kMaxSplit && ctr[kCtrLongRows] >= kSharedMinRows &&
-         chunks * (dtype == SGA_F32 ? 4 : 1) >= (int64_t)kSharedRows * shared_places(d) &&
+         chunks * (dtype == SGA_F32 && !finer ? 4 : 1) >= (int64_t)kSharedRows * shared_places(d) &&
          nnz / L >= L / (pl.l2_chunks ? kSharedFillByShare : shared_fill(dtype));
 }
 // False where no mask that this workspace was sized for can take shared_chunks: an empty launch costs a

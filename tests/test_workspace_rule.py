@@ -22,17 +22,19 @@ int merge_of(int H) {
   a.H = H;
   return (int)sga::merge_tiles(a);
 }
-bool share(const sga::WorkspacePlan& p, long long nnz, long long L, int H, int d, int dtype, uint32_t rows) {      // rows of two chunks
+bool share(const sga::WorkspacePlan& p, long long nnz, long long L, int H, int d, int dtype, uint32_t rows,
+           bool finer = false) {      // rows of two chunks, or of ten
   uint32_t ctr[sga::kNumCounters] = {};
   ctr[sga::kCtrLongRows] = rows;
   ctr[sga::kCtrChunksNeeded] = 2 * rows;
-  ctr[sga::kCtrFineNeeded] = 0xFFFFFFFF;         // (the finer split has no room)
+  ctr[sga::kCtrFineNeeded] = finer ? 10 * rows : 0xFFFFFFFF;         // (no room for it)
   ctr[sga::kCtrMaxChunks] = 2;
+  ctr[sga::kCtrMaxChunksFine] = 10;
   return sga::shared_chunks(p, nnz, L, H, d, dtype, ctr);
 }
-int least_shared(const sga::WorkspacePlan& p, long long nnz, long long L, int H, int d, int dtype) {
+int least_shared(const sga::WorkspacePlan& p, long long nnz, long long L, int H, int d, int dtype, bool finer) {
   uint32_t rows = 64;
-  while (rows < 1 << 16 && !share(p, nnz, L, H, d, dtype, rows)) rows += 64;
+  while (rows < 8192 && !share(p, nnz, L, H, d, dtype, rows, finer)) rows += 64;
   return (int)rows;
 }
 int main() {
@@ -42,13 +44,13 @@ int main() {
     const sga::WorkspacePlan p = sga::plan_workspace(L, H, nnz, dtype, d);
     int chunks, len;
     sga::row_split_shape(deg, p, false, chunks, len);
-    printf("%d %lld %lld %d %d %d %d %d %d %d %d %d %d %d %d %d\n", p.seg_shift, (long long)p.n_work, (long long)p.cap_tparts, p.l2_chunks, chunks, len,
+    printf("%d %lld %lld %d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", p.seg_shift, (long long)p.n_work, (long long)p.cap_tparts, p.l2_chunks, chunks, len,
            sga::tile_parts_in_doubt(p), sga::tile_parts_may_be_in_doubt(dtype, p.total_bytes),
            (int)(sga::leftover_workgroups(L, H) | sga::leftover_chunk_workgroups(H) << 16), merge_of(H), p.l2_chunks != 0 && dtype == SGA_F16 ? -1 : 0,
            sga::l2_chunks(L, d, dtype) && L <= sga::kSharedMaxKeys && share(p, nnz, L, H, d, dtype, 1 << 16),
            possible(L, H, nnz, dtype, d), (int)sga::first_xcd((uint32_t)L, (int)deg),
            (int)(sga::staged_blocks(deg, L, 1) << 16 | sga::staged_blocks(deg, L, 2) << 8 | sga::subtile_blocks(deg, L)),
-           least_shared(p, nnz, L, H, d, dtype));
+           least_shared(p, nnz, L, H, d, dtype, false), least_shared(p, nnz, L, H, d, dtype, true));
   }
   return 0;
 }
@@ -228,9 +230,12 @@ def test_staged_windows_have_room_for_their_blocks_and_no_more(plans):
 
 def test_rows_share_key_blocks_where_they_fill_the_chip(plans):
     """The least number of rows of two chunks that share their key blocks (2,048 at any rate): with 64 to a workgroup and
-    all heads, the chunks are enough for a quarter (fp32) or all (fp16) of the 512 (d = 64) or 256 (d = 128) places."""
+    all heads, the chunks are enough for a quarter (fp32) or all (fp16) of the 512 (d = 64) or 256 (d = 128) places.
+    Rows of the finer split, here of ten chunks: fp32 only, and all of the places."""
     L = 32768
-    cases = [(L, L * L // 10, H, dtype, d) for H in (1, 2, 4, 16) for dtype in (0, 1) for d in (64, 128)]
-    for (_, _, H, dtype, d), (least,) in zip(cases, plans(cases, 15, 16)):
-        places = (512 if d == 64 else 256) // (1 if dtype else 4)
-        assert least == max(2048, 32 * places // H), (H, dtype, d, least)
+    cases = [(L, L * L // 10, H, dtype, d) for H in (2, 4, 8, 16) for dtype in (0, 1) for d in (64, 128)]
+    cases.append((L, L * L // 10, 1, 0, 64))
+    for (_, _, H, dtype, d), (least, finer) in zip(cases, plans(cases, 15, 17)):
+        places = 512 if d == 64 else 256
+        assert least == max(2048, 32 * places // (1 if dtype else 4) // H), (H, dtype, d, least)
+        assert finer == (8192 if dtype else max(2048, -(-places * 64 // (10 * H * 64)) * 64)), (H, dtype, d, finer)
