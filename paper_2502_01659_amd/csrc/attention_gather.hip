@@ -711,8 +711,9 @@ __global__ __launch_bounds__(256) void gather_chunk_kernel(
 // edges, the chunks of 64 rows spread over half as many blocks again (1,164 us).  The products of a step
 // are added to the row's state at once: 24 additions per chunk at that density where a group of
 // gather_chunk_kernel does 77.
-// That case: 1,276 -> 835 us (880 in a loop of nothing else), error 2.2e-7 -> 1.9e-7.  Bound by the vector unit (busy 88 % of the time): 13 of
-// 16 slots of a step hold an edge, and four rows of a wavefront wait for the longest.  d = 64: one buffer, two
+// That case: 1,276 -> 835 us (880 in a loop of nothing else), error 2.2e-7 -> 1.9e-7.  Bound by the vector unit (busy 88 % of the time): a
+// row has 12.8 edges in a block, but the four rows of a wavefront take 1.45 steps of 16 for them, as many as the longest
+// row; of the slots in the fours that a step does not skip 72 % hold an edge.  d = 64: one buffer, two
 // workgroups per CU, 64 registers (7 spill outside the steps); two buffers and one workgroup 1,061 us.
 //
 // A row's steps are cut at its own key blocks (multiples of kKeys) and nowhere else, so its result does not
