@@ -47,6 +47,8 @@ constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kMinusHuge = -1.0e30f;
 constexpr int kFullBit = 1 << 30;
 constexpr int kBitmapBlocks = 32;   // key blocks per window of the CSR -> tile pass's bitmap walk
+constexpr int kScoutColumns = 1024;  // longest rows that the CSR -> tile pass compares with the first of their tile, ...
+constexpr int kScoutRuns = 8;        // ... and most runs of consecutive columns they may have
 constexpr int kBitmapAfter = 4;     // ... which takes over after this many blocks if all but one had scattered columns
 constexpr int kBitmapUnits = 2;     // ... each lane taking this many units of 16 columns at a time
 
@@ -1584,10 +1586,10 @@ __device__ __forceinline__ WorkId locate_work(const int64_t* __restrict__ row_pt
 // lane r < 32 walks row 32t + r.  A 32-way merge by key block id: every round takes the
 // smallest block id at the head of any row and lets each row consume its columns inside that
 // block into a 32-bit word.  A row whose remaining columns are consecutive integers (windows,
-// global rows) is walked arithmetically without reading col_idx again; otherwise a run of
-// consecutive columns up to the end of the block costs two loads, and only scattered columns
+// global rows) is walked arithmetically without reading col_idx again, and so are rows of one shape (below);
+// otherwise a run of consecutive columns up to the end of the block costs two loads, and only scattered columns
 // are read one by one.
-__global__ __launch_bounds__(256) void tile_analyze_kernel(const int64_t* __restrict__ row_ptr,
+__global__ __attribute__((amdgpu_waves_per_eu(4, 4))) __launch_bounds__(256) void tile_analyze_kernel(const int64_t* __restrict__ row_ptr,
                                                            const int32_t* __restrict__ col_idx,
                                                            int64_t L, int32_t H, int32_t dtype,
                                                            int32_t d, void* ws, size_t ws_bytes) {
@@ -1651,13 +1653,151 @@ __global__ __launch_bounds__(256) void tile_analyze_kernel(const int64_t* __rest
     // column is kept), so a row of a few runs turns arithmetic once its last run is reached
     int run_lo = 0, run_hi = -1;
     bool arith = false;
+    const int c_first = pos < end ? col_idx[pos] : -1;
     const int c_last = pos < end ? col_idx[end - 1] : -1;
     int nblk = 0;
     bool overflow = false;
     int consumed = 0;                   // edges of this lane's row in the blocks written so far
     int scattered = 0;                  // blocks so far in which some row's columns were read one by one
     bool by_bitmap = false;
-    while (true) {
+    auto write_block = [&](int b, uint32_t word) {
+      const bool full = __all(lane >= kTile || word == ~0u);
+      if (lane < kTile) pair_mask[(slot0 + nblk) * kTile + lane] = word;
+      if (lane == 0) pair_blk[slot0 + nblk] = b | (full ? kFullBit : 0);
+      ++nblk;
+    };
+    // Every row is down to one run of consecutive columns lo .. hi (some) or to nothing: writes the rest of the list and
+    // returns true if there is none, or if the runs' block ranges overlap or touch.  The remaining blocks then are
+    // the whole range from the first to the last, and each row's word follows from its run alone: no minimum per block.
+    auto close_runs = [&](bool some, int run_lo, int run_hi) -> bool {
+      const int blo = first_half_min(some ? run_lo >> 5 : INT32_MAX);
+      if (blo == INT32_MAX) return true;
+      const int bhi = first_half_max(some ? run_hi >> 5 : -1);
+      const int lo_max = first_half_max(some ? run_lo >> 5 : -1);
+      const int hi_min = first_half_min(some ? run_hi >> 5 : INT32_MAX);
+      if (lo_max > hi_min + 1) return false;
+      for (int b = blo; b <= bhi; ++b) {
+        if (nblk >= cap) {
+          overflow = true;
+          break;
+        }
+        const int lo = run_lo - (b << 5) > 0 ? run_lo - (b << 5) : 0;
+        const int hi = run_hi - (b << 5) < 31 ? run_hi - (b << 5) : 31;
+        write_block(b, some && lo <= hi ? (~0u >> (31 - hi)) & (~0u << lo) : 0u);
+      }
+      return true;
+    };
+    // A list that averages under kProbeEdges edges per block over its first kProbeBlocks blocks
+    // is given up at once (scattered columns: the rows go to the per-row kernels) instead
+    // of being walked until its slots run out.  Like the slot rule this depends on the mask
+    // alone.
+    auto too_thin = [&]() -> bool {
+      if (nblk != kProbeBlocks) return false;
+      int total = lane < kTile ? consumed : 0;
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off, kWave);
+      return total < kProbeBlocks * kProbeEdges;
+    };
+    // Rows of one shape: as many columns in every row, in the same few runs of consecutive ones (block masks; global columns
+    // beside a window).  The first row is read whole, with coalesced loads; of the others the first and last column of
+    // each run, all requested together, show the rest, since a list is sorted and free of duplicates.  The list then
+    // follows without another load: three dependent ones in place of two or more per block.  (BigBird mask of 64-token
+    // blocks, L = 1,048,576, us of this kernel: 551 -> 385, 2.06 -> 1.53 GB of col_idx; it waits for memory, at
+    // four wavefronts per SIMD: five and six spill and gain nothing, and a list written with scalar code where all rows are
+    // equal, at 40 % fewer vector instructions, takes as long.  Looking ahead along each row by itself, at the ends of the
+    // 2nd, 4th, 6th and 8th key block, 460: it brings in lines that are gone again before the walk reaches them.)
+    int n_runs = 0;
+    if (!__all(pos >= end || c_last - c_first == end - 1 - pos)) {
+      const int deg = (int)(end - pos < kScoutColumns + 1 ? end - pos : kScoutColumns + 1);
+      const int deg0 = __builtin_amdgcn_readfirstlane(deg);
+      if (row_first + kTile <= L && deg0 <= kScoutColumns && __all(lane >= kTile || deg == deg0)) {
+        const int64_t at0 = uniform64(pos);
+        int cc[kScoutColumns / kWave];
+#pragma unroll
+        for (int k = 0; k < kScoutColumns / kWave; ++k) {
+          const int e = k * kWave + lane;
+          cc[k] = k * kWave < deg0 ? col_idx[at0 + (e < deg0 ? e : deg0 - 1)] : 0;
+        }
+        int at[kScoutRuns + 1];              // the runs' first entries (uniform)
+#pragma unroll
+        for (int k = 0; k < kScoutColumns / kWave; ++k) {
+          if (k * kWave >= deg0) break;
+          int before = __shfl_up(cc[k], 1, kWave);
+          if (lane == 0) before = k > 0 ? __builtin_amdgcn_readlane(cc[k > 0 ? k - 1 : 0], kWave - 1) : INT32_MIN;
+          uint64_t starts = __builtin_amdgcn_ballot_w64(k * kWave + lane < deg0 && cc[k] != before + 1);
+          while (starts && n_runs <= kScoutRuns) {
+            const int e = k * kWave + (int)__builtin_ctzll(starts);
+            starts &= starts - 1;
+#pragma unroll
+            for (int i = 0; i < kScoutRuns; ++i)
+              if (i == n_runs) at[i] = e;
+            ++n_runs;
+          }
+        }
+        if (n_runs <= kScoutRuns) {
+          bool same = true;
+          int lo[kScoutRuns], hi[kScoutRuns], len[kScoutRuns];
+#pragma unroll
+          for (int i = 0; i < kScoutRuns; ++i) {
+            const int e = i < n_runs ? at[i] : 0;
+            const int next = i + 1 < n_runs ? at[i + 1] : deg0;
+            len[i] = (i < n_runs ? next : 1) - e;
+            lo[i] = col_idx[(lane < kTile ? pos : at0) + e];
+            hi[i] = col_idx[(lane < kTile ? pos : at0) + e + len[i] - 1];
+          }
+#pragma unroll
+          for (int i = 0; i < kScoutRuns; ++i) {
+            same = same && hi[i] - lo[i] == len[i] - 1;
+          }
+          same = __all(same);
+          if (same) {
+#pragma unroll
+            for (int i = 0; i < kScoutRuns; ++i) {
+              if (lane < kTile) bm[i * kTile + lane] = (uint32_t)lo[i];
+              if (lane == 0) bm[kScoutRuns * kTile + i] = (uint32_t)len[i];
+            }
+          } else {
+            n_runs = 0;
+          }
+        } else {
+          n_runs = 0;
+        }
+      }
+    }
+    if (n_runs > 0) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // (one wavefront: its LDS operations complete in order)
+      const int deg = lane < kTile ? (int)(end - pos) : 0;
+      int i = lane < kTile ? 0 : n_runs;
+      run_lo = c_first;
+      run_hi = run_lo + (int)bm[kScoutRuns * kTile] - 1;
+      while (true) {
+        if (__all(i >= n_runs || c_last - run_lo == deg - consumed - 1) && close_runs(i < n_runs, run_lo, c_last)) break;
+        const int b = first_half_min(i < n_runs ? run_lo >> 5 : INT32_MAX);
+        if (b == INT32_MAX) break;
+        if (nblk >= cap) {
+          overflow = true;
+          break;
+        }
+        uint32_t word = 0;
+        while (i < n_runs && run_lo >> 5 == b) {
+          const int last = (b << 5) + 31;
+          word |= (~0u >> (31 - ((run_hi < last ? run_hi : last) & 31))) & (~0u << (run_lo & 31));
+          if (run_hi > last) {
+            run_lo = last + 1;
+          } else if (++i < n_runs) {
+            run_lo = (int)bm[i * kTile + lane];
+            run_hi = run_lo + (int)bm[kScoutRuns * kTile + i] - 1;
+          }
+        }
+        write_block(b, word);
+        consumed += __builtin_popcount(word);
+        if (too_thin()) {
+          overflow = true;
+          break;
+        }
+      }
+    }
+    while (n_runs == 0) {
       int cur = INT32_MAX;
       if (!arith && pos < end) {
         const int c0 = col_idx[pos];
@@ -1675,28 +1815,7 @@ __global__ __launch_bounds__(256) void tile_analyze_kernel(const int64_t* __rest
         // Every row is down to one run of consecutive columns (or to nothing).  If the runs'
         // block ranges overlap or touch, the remaining blocks are the whole range from the first
         // to the last, and each row's word follows from its run alone: no minimum per block.
-        const bool some = arith && run_lo <= run_hi;
-        const int blo = first_half_min(some ? run_lo >> 5 : INT32_MAX);
-        if (blo == INT32_MAX) break;
-        const int bhi = first_half_max(some ? run_hi >> 5 : -1);
-        const int lo_max = first_half_max(some ? run_lo >> 5 : -1);
-        const int hi_min = first_half_min(some ? run_hi >> 5 : INT32_MAX);
-        if (lo_max <= hi_min + 1) {
-          for (int b = blo; b <= bhi; ++b) {
-            if (nblk >= cap) {
-              overflow = true;
-              break;
-            }
-            const int lo = run_lo - (b << 5) > 0 ? run_lo - (b << 5) : 0;
-            const int hi = run_hi - (b << 5) < 31 ? run_hi - (b << 5) : 31;
-            const uint32_t word = some && lo <= hi ? (~0u >> (31 - hi)) & (~0u << lo) : 0u;
-            const bool full = __all(lane >= kTile || word == ~0u);
-            if (lane < kTile) pair_mask[(slot0 + nblk) * kTile + lane] = word;
-            if (lane == 0) pair_blk[slot0 + nblk] = b | (full ? kFullBit : 0);
-            ++nblk;
-          }
-          break;
-        }
+        if (close_runs(arith && run_lo <= run_hi, run_lo, run_hi)) break;
       }
       const int b = first_half_min(cur);
       if (b == INT32_MAX) break;
@@ -1750,10 +1869,7 @@ __global__ __launch_bounds__(256) void tile_analyze_kernel(const int64_t* __rest
           }
         }
       }
-      const bool full = __all(lane >= kTile || word == ~0u);
-      if (lane < kTile) pair_mask[(slot0 + nblk) * kTile + lane] = word;
-      if (lane == 0) pair_blk[slot0 + nblk] = b | (full ? kFullBit : 0);
-      ++nblk;
+      write_block(b, word);
       consumed += __builtin_popcount(word);
       if (__any(one_by_one)) ++scattered;
       // Scattered columns in nearly all of the first blocks: the rest of the list is made by
@@ -1763,18 +1879,9 @@ __global__ __launch_bounds__(256) void tile_analyze_kernel(const int64_t* __rest
         by_bitmap = true;
         break;
       }
-      if (nblk == kProbeBlocks) {
-        // A list that averages under kProbeEdges edges per block over its first kProbeBlocks blocks
-        // is given up at once (scattered columns: the rows go to the per-row kernels) instead
-        // of being walked until its slots run out.  Like the slot rule this depends on the mask
-        // alone.
-        int total = lane < kTile ? consumed : 0;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off, kWave);
-        if (total < kProbeBlocks * kProbeEdges) {
-          overflow = true;
-          break;
-        }
+      if (too_thin()) {
+        overflow = true;
+        break;
       }
     }
     if (by_bitmap) {
@@ -1866,19 +1973,11 @@ __global__ __launch_bounds__(256) void tile_analyze_kernel(const int64_t* __rest
             overflow = true;
             break;
           }
-          const bool full = __all(lane >= kTile || word == ~0u);
-          if (lane < kTile) pair_mask[(slot0 + nblk) * kTile + lane] = word;
-          if (lane == 0) pair_blk[slot0 + nblk] = (b0 + k) | (full ? kFullBit : 0);
-          ++nblk;
+          write_block(b0 + k, word);
           consumed += __builtin_popcount(word);
-          if (nblk == kProbeBlocks) {                    // (the same test as in the walk above)
-            int sum = consumed;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, kWave);
-            if (sum < kProbeBlocks * kProbeEdges) {
-              overflow = true;
-              break;
-            }
+          if (too_thin()) {
+            overflow = true;
+            break;
           }
         }
         if (overflow) break;
@@ -4135,12 +4234,14 @@ sga_status run_tile_implicit(const AttnArgs& a) {
 }  // namespace
 
 // The CSR -> tile pass is a chain of dependent loads per item: one wavefront per tile and a
-// margin for the extra segments keeps every item's chain in flight at once.
+// margin for the extra segments keeps every item's chain in flight at once; from the fourfold of what the chip holds on,
+// wavefronts that go on to further items save the start of others (BigBird mask of 32-token blocks, L = 524,288, mask
+// build and forward, us, at most 16,384 workgroups / 4,096: 425 / 405; +-300, L = 300,000 318 / 310).
 void launch_tile_analyze(const AttnArgs& a) {
   const int64_t n_tiles = (a.L + kTile - 1) / kTile;
   int64_t nwg_analyze = n_tiles + 64;
   if (nwg_analyze < 2048) nwg_analyze = 2048;
-  if (nwg_analyze > 16384) nwg_analyze = 16384;
+  if (nwg_analyze > 4096) nwg_analyze = 4096;
   hipLaunchKernelGGL(tile_analyze_kernel, dim3((unsigned)nwg_analyze), dim3(256), 0, a.stream, a.row_ptr,
                      a.col_idx, a.L, a.H, a.dtype, a.d, a.ws, a.ws_bytes);
 }
