@@ -2805,14 +2805,22 @@ __device__ __forceinline__ void nonlocal_cols(const T* __restrict__ Q, const T* 
   finish_tile<T>(O + hoff, lse ? lse + hd * L : nullptr, i, i, mine, st, h, accumulate != 0);
 }
 
-// ... and the g global rows: one wavefront per (tile of global rows, range c of key blocks), which leaves
-// the partial state of its rows over its range in the layout nonlocal_merge_kernel reads
-// (row-major: D accumulators, m, l per (row, range, head)).
+// ... and the g global rows: one workgroup per (tile of global rows, range c of key blocks), a quarter of the range per
+// wavefront.  The four states are merged in LDS, in wavefront order, and leave as
+// the partial state of the tile's rows over the range in the layout nonlocal_merge_kernel reads
+// (row-major: D accumulators, m, l per (row, range, head)).  (A wavefront with a range of its own took twice to four times as
+// many blocks one after the other, 2 us each in fp32: three global tokens, L = 35,000, one head, kernel and merge
+// 28 + 5.6 us, 16 + 5.5 so; both calls: L = 200,000, 16 tokens, fp32 206 -> 135, fp16 68 -> 51; L = 65,536, 8 heads,
+// fp16 127 -> 124.)
 template <typename T, int kPipe>
 __device__ __forceinline__ void nonlocal_rows(const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
                                               int64_t L, int64_t W, int64_t g, int64_t tile, int64_t c, int64_t n_ranges,
                                               int64_t blocks_per_range, float scale, float* __restrict__ partials,
-                                              int lane, char* lds) {
+                                              int lane, int wave, char* lds_all) {
+  constexpr int kLds = CoreFor<T, kPipe>::type::template lds_bytes<kPipe>();
+  constexpr int kStateBytes = kTile * kHeadDim * 4;          // a wavefront's accumulators; its m and l of the rows follow
+  static_assert(kStateBytes + 2 * kTile * 4 <= kLds, "a wavefront's state fits its LDS");
+  char* const lds = lds_all + wave * kLds;
   const int n = lane & 31, h = lane >> 5;
   const int64_t hd = blockIdx.y, H = gridDim.y;
   const int64_t row0 = tile * kTile;
@@ -2820,26 +2828,59 @@ __device__ __forceinline__ void nonlocal_rows(const T* __restrict__ Q, const T* 
   const int64_t nb_total = (L + kTile - 1) / kTile;
   const int64_t kb0 = c * blocks_per_range;
   const int64_t kb1 = kb0 + blocks_per_range < nb_total ? kb0 + blocks_per_range : nb_total;
+  const int nb = (int)(kb1 > kb0 ? kb1 - kb0 : 0);
   const NonlocalBlocks<true> src{L, g, W, row0, kb0};
   const int64_t i = row0 + n;
   typename CoreFor<T, kPipe>::type core;
   core.load_q(Q + hoff + (i < L ? i : L - 1) * kHeadDim, h, scale < 0.f);
   TileState st;
   st.init();
-  core.template run<kPipe>(K + hoff, V + hoff, src, 0, (int)(kb1 > kb0 ? kb1 - kb0 : 0), softmax_factor(scale),
+  core.template run<kPipe>(K + hoff, V + hoff, src, nb * wave / 4, nb * (wave + 1) / 4, softmax_factor(scale),
                            lane, st, lds);
-  if (i >= g) return;
   const float l = st.l + other_half(st.l, h);
-  float* p = partials + ((i * n_ranges + c) * H + hd) * (kHeadDim + 4);
+  wait_loads_except<0>();                  // (nothing of this wavefront still lands in its LDS)
+  wait_lds_reads();
+  __builtin_amdgcn_wave_barrier();
+  // (the 16-byte chunks of a row swizzled)
 #pragma unroll
   for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      *reinterpret_cast<float4*>(p + cb * 32 + 8 * q + 4 * h) =
+      *reinterpret_cast<float4*>(lds + n * (kHeadDim * 4) + (((cb * 8 + 2 * q + h) ^ (n & 15)) * 16)) =
           make_float4(st.o[cb][4 * q], st.o[cb][4 * q + 1], st.o[cb][4 * q + 2], st.o[cb][4 * q + 3]);
   if (h == 0) {
-    p[kHeadDim] = st.m;
-    p[kHeadDim + 1] = l;
+    reinterpret_cast<float*>(lds + kStateBytes)[n] = st.m;
+    reinterpret_cast<float*>(lds + kStateBytes)[kTile + n] = l;
+  }
+  __syncthreads();
+  const int t = wave * kWave + lane, chunk = t & 15;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int r = (t >> 4) + 16 * k;
+    if (row0 + r >= g) continue;
+    float m[4], M = kMinusHuge, sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      m[w] = reinterpret_cast<const float*>(lds_all + w * kLds + kStateBytes)[r];
+      M = fmaxf(M, m[w]);
+    }
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float e = __builtin_amdgcn_exp2f(m[w] - M);
+      const float4 o = *reinterpret_cast<const float4*>(lds_all + w * kLds + r * (kHeadDim * 4) + ((chunk ^ (r & 15)) * 16));
+      sum = __builtin_fmaf(reinterpret_cast<const float*>(lds_all + w * kLds + kStateBytes)[kTile + r], e, sum);
+      acc.x = __builtin_fmaf(o.x, e, acc.x);
+      acc.y = __builtin_fmaf(o.y, e, acc.y);
+      acc.z = __builtin_fmaf(o.z, e, acc.z);
+      acc.w = __builtin_fmaf(o.w, e, acc.w);
+    }
+    float* p = partials + (((row0 + r) * n_ranges + c) * H + hd) * (kHeadDim + 4);
+    *reinterpret_cast<float4*>(p + 4 * chunk) = acc;
+    if (chunk == 0) {
+      p[kHeadDim] = M;
+      p[kHeadDim + 1] = sum;
+    }
   }
 }
 
@@ -2858,11 +2899,9 @@ __global__ __launch_bounds__(256, 2) void tile_nonlocal_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   char* lds = lds_all + wave * kLds;
   if (blockIdx.x < row_wgs) {
-    const uint32_t unit = blockIdx.x * 4 + wave;             // (tile, range), ranges of a tile together
-    const uint32_t tile = unit / n_ranges;
-    if ((int64_t)tile * kTile >= g) return;
-    nonlocal_rows<T, kPipe>(Q, K, V, L, W, g, tile, unit - tile * n_ranges, n_ranges, blocks_per_range, scale, partials,
-                            lane, lds);
+    const uint32_t tile = blockIdx.x / n_ranges;             // (ranges of a tile together)
+    nonlocal_rows<T, kPipe>(Q, K, V, L, W, g, tile, blockIdx.x - tile * n_ranges, n_ranges, blocks_per_range, scale,
+                            partials, lane, wave, lds_all);
   } else {
     nonlocal_cols<T, kPipe>(Q, K, V, O, lse, L, W, g, (int64_t)(blockIdx.x - row_wgs) * 4 + wave, scale, accumulate,
                             lane, lds);
@@ -4278,7 +4317,7 @@ void run_tile_nonlocal(const AttnArgs& a, int64_t g, float* partials, int32_t* n
     per = (n_tiles + max_ranges - 1) / max_ranges;
     if (per < 8) per = 8;
     ranges = (n_tiles + per - 1) / per;
-    row_wgs = (g_tiles * ranges + 3) / 4;
+    row_wgs = g_tiles * ranges;
   }
   *n_chunks = (int32_t)ranges;
   if (row_wgs + col_wgs == 0) return;
