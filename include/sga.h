@@ -293,7 +293,9 @@ enum {
   SGA_GRAPH_TILES_COVER_ALL = 1,   /* every row is produced by the tile kernels               */
   SGA_GRAPH_TILE_PARTS_FIT = 2,    /* the partial states of the multi-segment tiles fit       */
   SGA_GRAPH_ROW_CHUNKS_FIT = 4,    /* the chunk items of the split rows fit                   */
-  SGA_GRAPH_ROWS_SHARE_KEYS = 8    /* ... and are computed by the kernel that shares key blocks */
+  SGA_GRAPH_ROWS_SHARE_KEYS = 8,   /* ... and are computed by the kernel that shares key blocks */
+  SGA_GRAPH_ROWS_EVEN = 16         /* no tile qualified, no row is split, and none has more than 64
+                                      neighbours beyond twice the average, which is at most 256 */
 };
 
 sga_status sga_graph_prepare(const int64_t* row_ptr, const int32_t* col_idx, int64_t L, int32_t H,

@@ -13,7 +13,7 @@ from .binding import (SgaError, PATH_AUTO, PATH_GATHER, PATH_TILE, PATH_TILE_SPL
                       sga_attention_forward, sga_attention_forward_implicit,
                       sga_status_string, sga_profile_enable, sga_profile_collect, sga_profile_last_kernel,
                       GraphPlan, GRAPH_TILES_COVER_ALL, GRAPH_TILE_PARTS_FIT, GRAPH_ROW_CHUNKS_FIT,
-                      GRAPH_ROWS_SHARE_KEYS, graph_prepare, attention_forward_prepared, attention_accumulate_prepared,
+                      GRAPH_ROWS_SHARE_KEYS, GRAPH_ROWS_EVEN, graph_prepare, attention_forward_prepared, attention_accumulate_prepared,
                       sga_graph_prepare, sga_attention_forward_prepared,
                       sga_attention_accumulate_prepared,
                       sga_static_scratch_init, sga_static_scratch_bytes, sga_attention_forward_static)
@@ -27,7 +27,7 @@ __all__ = [
     "sga_mask_nnz", "sga_build_mask", "sga_validate_csr", "sga_workspace_bytes",
     "sga_attention_forward", "sga_attention_forward_implicit", "sga_status_string",
     "sga_profile_enable", "sga_profile_collect", "sga_profile_last_kernel",
-    "GraphPlan", "GRAPH_TILES_COVER_ALL", "GRAPH_TILE_PARTS_FIT", "GRAPH_ROW_CHUNKS_FIT", "GRAPH_ROWS_SHARE_KEYS",
+    "GraphPlan", "GRAPH_TILES_COVER_ALL", "GRAPH_TILE_PARTS_FIT", "GRAPH_ROW_CHUNKS_FIT", "GRAPH_ROWS_SHARE_KEYS", "GRAPH_ROWS_EVEN",
     "graph_prepare", "attention_forward_prepared", "attention_accumulate_prepared",
     "sga_graph_prepare", "sga_attention_forward_prepared", "sga_attention_accumulate_prepared",
     "sga_static_scratch_init", "sga_static_scratch_bytes", "sga_attention_forward_static",

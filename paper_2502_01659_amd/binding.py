@@ -48,7 +48,7 @@ class GraphPlan(ctypes.Structure):
     ]
 
 
-GRAPH_TILES_COVER_ALL, GRAPH_TILE_PARTS_FIT, GRAPH_ROW_CHUNKS_FIT, GRAPH_ROWS_SHARE_KEYS = 1, 2, 4, 8
+GRAPH_TILES_COVER_ALL, GRAPH_TILE_PARTS_FIT, GRAPH_ROW_CHUNKS_FIT, GRAPH_ROWS_SHARE_KEYS, GRAPH_ROWS_EVEN = 1, 2, 4, 8, 16
 
 
 def lib_path():

@@ -240,6 +240,7 @@ sga_status run_explicit_call(const void* Q, const void* K, const void* V, const 
     a.plan_rows_left = parts_fit ? (int64_t)plan->tiles_left * kTile : L;
     a.plan_no_tiles = (int64_t)plan->tiles_left == (L + kTile - 1) / kTile;
     a.plan_long_rows = (plan->flags & SGA_GRAPH_ROW_CHUNKS_FIT) ? plan->long_rows : 0;
+    a.plan_rows_even = (plan->flags & SGA_GRAPH_ROWS_EVEN) != 0;
     a.plan_rows_share = (plan->flags & SGA_GRAPH_ROWS_SHARE_KEYS) != 0;
     return launch_tile_explicit(a);
   }
@@ -360,6 +361,7 @@ sga_status sga_graph_prepare(const int64_t* row_ptr, const int32_t* col_idx, int
   clear_workspace(a, true);
   launch_tile_analyze(a);
   if (L > kSplitThreshold && tile_parts_in_doubt(pl)) launch_split_prepass(a, true);
+  launch_longest_row(a);
   uint32_t ctr[kNumCounters];
   if (hipGetLastError() != hipSuccess ||
       hipMemcpyAsync(ctr, workspace, sizeof(ctr), hipMemcpyDeviceToHost, st) != hipSuccess ||
@@ -381,6 +383,8 @@ sga_status sga_graph_prepare(const int64_t* row_ptr, const int32_t* col_idx, int
   if (chunks_fit && shared_chunks_possible(L, H, d, dtype, workspace_bytes) &&
       shared_chunks(pl, nnz, L, H, d, dtype, ctr))
     p.flags |= SGA_GRAPH_ROWS_SHARE_KEYS;
+  if ((int64_t)p.tiles_left == pl.n_tiles && p.long_rows == 0 && rows_of_one_length(nnz, L, ctr[kCtrLongestRow]))
+    p.flags |= SGA_GRAPH_ROWS_EVEN;
   p.row_ptr = row_ptr; p.col_idx = col_idx;
   p.workspace = workspace; p.workspace_bytes = workspace_bytes;
   *plan_out = p;

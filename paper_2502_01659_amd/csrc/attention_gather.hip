@@ -208,23 +208,29 @@ __device__ __forceinline__ void attend_columns(const T* __restrict__ Kh, const T
   }
 }
 
+// st and another state of the same row, as one.
+template <int VEC>
+__device__ __forceinline__ void merge_state(State<VEC>& st, const State<VEC>& other) {
+  const float mn = fmaxf(st.m, other.m);
+  const float a1 = __builtin_amdgcn_exp2f(st.m - mn);
+  const float a2 = __builtin_amdgcn_exp2f(other.m - mn);
+  st.l = __builtin_fmaf(st.l, a1, other.l * a2);
+#pragma unroll
+  for (int c = 0; c < VEC; ++c) st.acc[c] = __builtin_fmaf(st.acc[c], a1, other.acc[c] * a2);
+  st.m = mn;
+}
+
 // Merge the G lane-group states of a wavefront; afterwards every group holds the row's state.
 template <int LPK, int VEC>
 __device__ __forceinline__ void merge_groups(State<VEC>& st) {
 #pragma unroll
   for (int off = LPK; off < kWave; off <<= 1) {
-    const float m2 = __shfl_xor(st.m, off, kWave);
-    const float l2 = __shfl_xor(st.l, off, kWave);
-    const float mn = fmaxf(st.m, m2);
-    const float a1 = __builtin_amdgcn_exp2f(st.m - mn);
-    const float a2 = __builtin_amdgcn_exp2f(m2 - mn);
-    st.l = st.l * a1 + l2 * a2;
+    State<VEC> other;
+    other.m = __shfl_xor(st.m, off, kWave);
+    other.l = __shfl_xor(st.l, off, kWave);
 #pragma unroll
-    for (int c = 0; c < VEC; ++c) {
-      const float o = __shfl_xor(st.acc[c], off, kWave);
-      st.acc[c] = st.acc[c] * a1 + o * a2;
-    }
-    st.m = mn;
+    for (int c = 0; c < VEC; ++c) other.acc[c] = __shfl_xor(st.acc[c], off, kWave);
+    merge_state(st, other);
   }
 }
 
@@ -237,13 +243,13 @@ __device__ __forceinline__ void load_query(const T* Qrow, float scale, int lane,
   for (int k = 0; k < Row<T, D>::VEC; ++k) q[k] *= c;
 }
 
-// Normalise and store a row; with `accumulate` the row continues the (O, lse) state already
+// Normalise and store a row whose whole state the lanes of a group hold (cl: the lane's place in it; store: this
+// group writes); with `accumulate` the row continues the (O, lse) state already
 // in the output buffers (sequential composition on one state, Section V-F).
 template <typename T, int D>
-__device__ __forceinline__ void finish_row(T* Orow, float* lse_i, int lane,
-                                           State<Row<T, D>::VEC>& st, bool accumulate) {
-  constexpr int LPK = Row<T, D>::LPK, VEC = Row<T, D>::VEC;
-  merge_groups<LPK, VEC>(st);
+__device__ __forceinline__ void finish_merged(T* Orow, float* lse_i, int cl, bool store,
+                                              const State<Row<T, D>::VEC>& st, bool accumulate) {
+  constexpr int VEC = Row<T, D>::VEC;
   const bool empty = !(st.l > 0.f);
   float inv = empty ? 0.f : 1.0f / st.l;
   float lse_row = empty ? -INFINITY : (st.m + __builtin_amdgcn_logf(st.l)) * kLn2;
@@ -257,16 +263,23 @@ __device__ __forceinline__ void finish_row(T* Orow, float* lse_i, int lane,
   float o[VEC];
 #pragma unroll
   for (int c = 0; c < VEC; ++c) o[c] = st.acc[c] * inv;
-  if (lane < LPK) {
-    if (accumulate) {
-      float old[VEC];
-      Row<T, D>::load(Orow + lane * VEC, old);
+  if (!store) return;
+  if (accumulate) {
+    float old[VEC];
+    Row<T, D>::load(Orow + cl * VEC, old);
 #pragma unroll
-      for (int c = 0; c < VEC; ++c) o[c] = __builtin_fmaf(w_prev, old[c], o[c]);
-    }
-    Row<T, D>::store(Orow + lane * VEC, o);
+    for (int c = 0; c < VEC; ++c) o[c] = __builtin_fmaf(w_prev, old[c], o[c]);
   }
-  if (lse_i && lane == 0) *lse_i = lse_row;
+  Row<T, D>::store(Orow + cl * VEC, o);
+  if (lse_i && cl == 0) *lse_i = lse_row;
+}
+
+template <typename T, int D>
+__device__ __forceinline__ void finish_row(T* Orow, float* lse_i, int lane,
+                                           State<Row<T, D>::VEC>& st, bool accumulate) {
+  constexpr int LPK = Row<T, D>::LPK;
+  merge_groups<LPK, Row<T, D>::VEC>(st);
+  finish_merged<T, D>(Orow, lse_i, lane % LPK, lane < LPK, st, accumulate);
 }
 
 __host__ __device__ inline void split_shape(int64_t deg, int chunk, int32_t& nchunks, int32_t& len) {
@@ -425,6 +438,70 @@ __global__ __launch_bounds__(256) void gather_csr_kernel(
     int accumulate) {
   gather_csr_body<T, D>(Q, K, V, O, lse, row_ptr, col_idx, L, scale, ws, ws_bytes, use_split, skip_tiled,
                         accumulate, blockIdx.x, gridDim.x);
+}
+
+// Prepared graphs of short rows of about one length and no tiles, K and V beyond one L2 (even_rows): a row per group of
+// LPK lanes, so that a wavefront takes G rows at once and four times (fp32, d = 64) as many rows are under way.  All
+// of them read their sorted neighbours from the first key to the last at about the same pace, so a key that one row has
+// brought into an L2 is still there for the others.  The arithmetic is gather_csr_body's: there group g of a wavefront
+// takes every G-th edge from g on and the groups' states are merged, here one group holds those G states in turn;
+// the bits are the same, and so are those of the call without a plan.  Bound by what misses the L2s (6.4 TB/s) where K and V
+// are several times an L2: 35,000 rows of 35 neighbours, fp32, d = 64 77 -> 73 us; by the L2s below that: random 1 %,
+// L = 24,576, fp32, d = 64 247 -> 177 us, d = 128 613 -> 571; fp16, d = 128 250 -> 178; L = 8,000, four heads, fp32, d = 64
+// 92 -> 65.  Registers for four wavefronts per SIMD; with more, the G states spill (six: 277 us,
+// eight: 422 of the 177).
+template <typename T, int D>
+__global__ __attribute__((amdgpu_waves_per_eu(4))) __launch_bounds__(256) void gather_even_rows_kernel(
+    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
+    float* __restrict__ lse, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int64_t L, float scale,
+    int accumulate) {
+  constexpr int LPK = Row<T, D>::LPK, VEC = Row<T, D>::VEC, G = kWave / LPK;
+  constexpr int kStep = G * kUnroll;
+  static_assert(LPK % kStep == 0, "a group's columns are a whole number of steps");
+  const int lane = threadIdx.x & (kWave - 1), cl = lane % LPK;
+  const int64_t i = ((int64_t)blockIdx.x * 4 + threadIdx.x / kWave) * G + lane / LPK;
+  if (i >= L) return;
+  const int64_t h = blockIdx.y, hoff = h * L * D;
+  const int64_t r0 = row_ptr[i];
+  const int deg = (int)(row_ptr[i + 1] - r0);
+  const int32_t* cols = col_idx + r0;
+  const char* Kb = reinterpret_cast<const char*>(K + hoff);
+  const char* Vb = reinterpret_cast<const char*>(V + hoff);
+  float q[VEC];
+  load_query<T, D>(Q + hoff + i * D, scale, lane, q);
+  State<VEC> st[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g) st[g].init();
+  int32_t cur = deg > 0 ? cols[min(cl, deg - 1)] : 0;
+  for (int base = 0; base < deg; base += LPK) {
+    const int32_t nxt = cols[min(base + LPK + cl, deg - 1)];
+#pragma unroll 1
+    for (int sub = 0; sub < LPK; sub += kStep) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        if (base + sub + g < deg) {
+          float kf[kUnroll][VEC], vf[kUnroll][VEC];
+          bool valid[kUnroll];
+#pragma unroll
+          for (int u = 0; u < kUnroll; ++u) {
+            const int el = sub + u * G + g;
+            valid[u] = base + el < deg;
+            const uint32_t off = (uint32_t)__shfl(cur, el, LPK) * (uint32_t)(D * sizeof(T)) + (uint32_t)(cl * VEC * sizeof(T));
+            Row<T, D>::load(reinterpret_cast<const T*>(Kb + off), kf[u]);
+            Row<T, D>::load(reinterpret_cast<const T*>(Vb + off), vf[u]);
+          }
+          attend_loaded<LPK, VEC>(q, kf, vf, valid, st[g]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    cur = nxt;
+  }
+#pragma unroll
+  for (int n = 1; n < G; n <<= 1)
+#pragma unroll
+    for (int g = 0; g < G; g += 2 * n) merge_state(st[g], st[g + n]);
+  finish_merged<T, D>(O + hoff + i * D, lse ? lse + h * L + i : nullptr, cl, true, st[0], accumulate != 0);
 }
 
 template <typename T, int D>
@@ -1132,6 +1209,16 @@ sga_status run_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {
     }
   }
   if (!fused && !(a.prepared && a.plan_long_rows == a.L)) {       // (a prepared graph all of whose rows are split: 19 us of L = 24,576)
+    if constexpr (kWave / Row<T, D>::LPK > 1 && kWave / Row<T, D>::LPK <= 4) {
+      if (a.prepared && a.plan_rows_even && even_rows(a.L, a.H, D, a.dtype)) {
+        constexpr int kRows = 4 * kWave / Row<T, D>::LPK;
+        profile_mark_begin(a.stream, "gather_even_rows_kernel");
+        hipLaunchKernelGGL((gather_even_rows_kernel<T, D>), dim3((unsigned)((a.L + kRows - 1) / kRows), (unsigned)a.H), dim3(256),
+                           0, a.stream, Q, K, V, O, a.lse, a.row_ptr, a.col_idx, a.L, a.scale, a.accumulate ? 1 : 0);
+        profile_mark_end(a.stream);
+        return hip_status(hipGetLastError());
+      }
+    }
     if (mark && !mark_chunks) profile_mark_begin(a.stream, "gather_csr_kernel");
     hipLaunchKernelGGL((gather_csr_kernel<T, D>), grid, dim3(256), 0, a.stream, Q, K, V, O, a.lse,
                        a.row_ptr, a.col_idx, a.L, a.scale, a.ws, a.ws_bytes, split ? 1 : 0,
@@ -1177,6 +1264,27 @@ void clear_workspace(const AttnArgs& a, bool tile_flags) {
 void launch_split_prepass(const AttnArgs& a, bool after_tiles) {
   hipLaunchKernelGGL(split_prepass_kernel, dim3((unsigned)((a.L + 255) / 256)), dim3(256), 0, a.stream,
                      a.row_ptr, a.L, a.H, a.dtype, a.d, a.ws, a.ws_bytes, after_tiles ? 1 : 0);
+}
+
+namespace {
+// The length of the longest row, into a counter (graph preparation only).
+__global__ __launch_bounds__(256) void longest_row_kernel(const int64_t* __restrict__ row_ptr, int64_t L, uint32_t* ctr) {
+  int64_t most = 0;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < L; i += (int64_t)gridDim.x * 256) {
+    const int64_t deg = row_ptr[i + 1] - row_ptr[i];
+    most = deg > most ? deg : most;
+  }
+  int longest = (int)most;                 // (a row has at most L < 2^31 neighbours)
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) longest = max(longest, __shfl_xor(longest, off, kWave));
+  if ((threadIdx.x & (kWave - 1)) == 0) atomicMax(&ctr[kCtrLongestRow], (uint32_t)longest);
+}
+}  // namespace
+
+void launch_longest_row(const AttnArgs& a) {
+  const int64_t wgs = (a.L + 255) / 256;
+  hipLaunchKernelGGL(longest_row_kernel, dim3((unsigned)(wgs < 512 ? wgs : 512)), dim3(256), 0, a.stream, a.row_ptr, a.L,
+                     static_cast<uint32_t*>(a.ws));
 }
 
 sga_status launch_gather_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled) {

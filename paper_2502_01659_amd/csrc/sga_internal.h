@@ -133,6 +133,7 @@ enum WsCounter : int {
   kCtrTilesBad = 5,         // tiles whose block lists overflowed (left to the gather path)
   kCtrMultiTiles = 6,       // multi-segment tiles recorded in the merge list
   kCtrMultiItems = 11,      // groups of up to four segment items (see TileItem::group)
+  kCtrLongestRow = 12,      // neighbours of the longest row (written when a graph is prepared)
   // (the second cache line: atomics on one line wait for each other)
   kCtrLongRows = 32,        // number of long rows recorded
   kCtrMaxChunks = 34,       // most chunks any split row has (bounds the chunk kernel's unit loop), ...
@@ -308,6 +309,19 @@ __host__ __device__ inline int64_t subtile_blocks(int64_t W, int64_t Lc) {
 __host__ __device__ inline int64_t leftover_workgroups(int64_t rows_left, int32_t H) {
   const int64_t rows = (rows_left + 3) / 4, full = 2048 / H > 256 ? 2048 / H : 256;
   return ((rows < full ? rows : full) + 7) & ~int64_t(7);
+}
+
+// Calls on a prepared graph of even rows (no tile, none split, none longer than twice the average and 64 neighbours, at most
+// 256 on average) that gather_even_rows_kernel takes: K and V of a head beyond one L2 and rows for four wavefronts per SIMD
+// (fp32, d = 64).  Longer rows gain nothing (3 %, L = 16,000: fp32, d = 64 183 / 182, fp16, d = 128 194.6 / 198.4).
+// (us, a wavefront per row / that: random 1 %, fp32, d = 64, L = 8,000 21 / 26, four heads 92 / 65; d = 128, L = 17,000, 0.6 %
+// 179 / 166; fp16, d = 128, L = 50,000, 0.1 % 154 / 156.)
+inline bool rows_of_one_length(int64_t nnz, int64_t L, int64_t longest) {
+  return nnz / L <= 256 && longest <= 2 * (nnz / L) + 64;
+}
+inline bool even_rows(int64_t L, int32_t H, int32_t d, int32_t dtype) {
+  const int64_t bytes = L * d * (dtype == SGA_F32 ? 4 : 2);
+  return L * H >= 16384 && 2 * bytes > kL2FitBytes && bytes < int64_t(1) << 32;      // (32-bit offsets)
 }
 
 // The finer split is taken if all its chunks fit (ctr: the counters of the workspace).
@@ -550,6 +564,7 @@ struct AttnArgs {
   int64_t plan_rows_left;      // at most so many rows are left to the per-row kernels
   bool plan_no_tiles;          // no tile qualified: the tile kernels have nothing to do
   uint32_t plan_long_rows;     // split rows among the leftover rows whose chunk items fit
+  bool plan_rows_even;         // every row is left to them, none is split and all are of about one length
   bool plan_rows_share;        // ... and shared_chunk_kernel computes them
 };
 
@@ -577,6 +592,7 @@ void clear_workspace(const AttnArgs& a, bool tile_flags);
 // skip_tiled: rows whose 32-row tile was produced by the tile path (tile_bad == 0 in the
 // workspace) are skipped, and a small grid strides over the rows; without a prepared graph the same
 // launch merges the tiles' segments.
+void launch_longest_row(const AttnArgs& a);
 sga_status launch_gather_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled);
 sga_status launch_gather_implicit(const AttnArgs& a);
 
