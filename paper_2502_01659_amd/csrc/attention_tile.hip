@@ -3502,6 +3502,148 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) voi
   }
 }
 
+// The same for one 32-query sub-tile per wavefront, 128 queries per workgroup: 128 registers and a ring of four blocks (32 KB)
+// let four wavefronts of four workgroups share a SIMD where tile_window_band_kernel has two.  That kernel reads every
+// operand from LDS once for two sub-tiles, but a wavefront issues a vector instruction every five cycles at best, so two
+// of them leave the vector unit half idle, and each workgroup waits for its first blocks and its output with one other
+// beside it.  This one is bound by power where it runs long (1.48 GHz at +-1,359 where the other has 1.98, with 18 % fewer
+// cycles): there the two are level, and from about 140 blocks per workgroup on the other is 4 to 5 % faster (see
+// strip_is_faster).  us, that / this: one head, L = 400,000, W = 260 133 / 94, 400 152 / 124, 1,000 285 / 260; L = 30,000,
+// W = 500 41 / 23, 2,000 94 / 60; L = 8,000, W = 400 34 / 20; 2-D blocks of 1,100, L = 100,000, 8 heads 138 / 112.
+// (Eight wavefronts on a ring of eight blocks: W = 260 320 where this has 289; without the scores one block ahead
+// 293; two groups of four wavefronts that swap matrix and vector work at barriers, 64 queries each, L = 1,600,000,
+// +-1,359: 1,350 -> 1,635.)
+constexpr int kStripWaves = 4, kStripSlots = 4;
+constexpr int kStripAhead = kStripSlots - 1;      // the slot written holds the block retired by the barrier before
+__global__ __attribute__((amdgpu_waves_per_eu(4, 4))) __launch_bounds__(kStripWaves * kWave) void tile_window_strip_kernel(
+    const __half* __restrict__ Q, const __half* __restrict__ K, const __half* __restrict__ V,
+    __half* __restrict__ O, float* __restrict__ lse, int64_t L, int64_t W, int64_t s, int64_t n_groups,
+    float scale, int accumulate, int64_t seg_len) {
+  constexpr int kSlotBytes = 2 * CoreF16::kBlockBytes;       // K block, then V block
+  constexpr int kQueries = kStripWaves * kTile, kCopies = 2;      // copies per wavefront and block: 1 KB of K, 1 KB of V
+  constexpr int kRing = kStripSlots * kSlotBytes, kOut = kStripWaves * CoreF16::kTileBytes;
+  __shared__ __attribute__((aligned(16))) char ring[kRing];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int n = lane & 31, h = lane >> 5;
+  const int64_t chunk = gridDim.x / 8;
+  const int64_t bid = (int64_t)(blockIdx.x % 8) * chunk + blockIdx.x / 8;
+  WindowSlot slot;
+  if (!locate_window_slot(bid, L, s, n_groups, seg_len, slot)) return;      // (the whole workgroup leaves)
+  const int64_t p = slot.p, Lc = slot.Lc;
+  const int64_t q0 = slot.grp * kQueries;
+  if (q0 >= Lc) return;
+  const int64_t hd = blockIdx.y;
+  const int64_t hoff = hd * L * kHeadDim;
+  const int64_t u0 = q0 + (int64_t)wave * kTile;
+  const int64_t vfirst = q0 - W > 0 ? q0 - W : 0;
+  const int64_t vlast = q0 + kQueries - 1 + W < Lc - 1 ? q0 + kQueries - 1 + W : Lc - 1;
+  const int nblk = (int)((vlast - vfirst) / kTile + 1);
+  // a wavefront whose queries lie past the end of the class (u0 >= Lc) still copies and meets the
+  // barriers; classify() then reports no block as its own
+  const WindowBlocks src{vfirst, Lc, s, p, u0, W};
+  const int64_t u = u0 + n;
+  const bool exists = u < Lc;
+  const int64_t qrow = s * (exists ? u : Lc - 1) + p;
+  CoreF16 core;
+  core.load_q(Q + hoff + qrow * kHeadDim, h, scale < 0.f);
+  wait_loads_except<0>();            // Q has arrived: from here on only the ring's copies are counted
+  core.q_arrived();
+  // this wavefront's share of a block: keys 8w .. 8w+7 (the K chunks swizzled as CoreF16::read_k expects)
+  const int r_own = 8 * wave + (lane >> 3), c_own = lane & 7;
+  const char* Kb = reinterpret_cast<const char*>(K + hoff) + (c_own ^ (r_own & 7)) * 16;
+  const char* Vb = reinterpret_cast<const char*>(V + hoff) + c_own * 16;
+  auto issue = [&](int kb) {
+    const int kc = kb < nblk ? kb : nblk - 1;
+    int64_t v = vfirst + (int64_t)kc * kTile + r_own;
+    v = v < Lc ? v : Lc - 1;                               // keys past the end re-read the last one (masked off)
+    const int64_t at = (s * v + p) * (kHeadDim * 2);
+    char* dst = ring + (kb % kStripSlots) * kSlotBytes + wave * 1024;
+    copy16_to_lds_untracked(Kb + at, dst);
+    copy16_to_lds_untracked(Vb + at, dst + CoreF16::kBlockBytes);
+  };
+  TileState st;
+  st.init();
+  const float c = softmax_factor(scale);
+  const char* vt0 = CoreF16::vt_base(ring + CoreF16::kBlockBytes, lane, h);
+  // The barrier that opens block kb: every wavefront has waited for its own copies of blocks kb and kb+1 (the scores of
+  // kb+1 are taken one block ahead), and everyone is done with block kb-1, whose slot takes the next copy.
+  auto publish = [&](int kb) {
+    wait_loads_except<kCopies * (kStripAhead - 2)>();
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    issue(kb + kStripAhead);
+  };
+  int k_lo = 0, k_hi = nblk;
+  while (k_lo < nblk && src.classify(k_lo) != 2) ++k_lo;
+  while (k_hi > k_lo && src.classify(k_hi - 1) != 2) --k_hi;
+  auto scores = [&](int kb, floatx16& sv) {
+    half8 kf[4];
+    CoreF16::read_k(ring + (kb % kStripSlots) * kSlotBytes, n, h, kf);
+    sv = floatx16{0};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) sv = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[t], core.qf[t], sv, 0, 0, 0);
+  };
+  auto weigh = [&](int kb, const half8 (&ph)[2]) {
+    const char* vt = vt0 + (kb % kStripSlots) * kSlotBytes;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const half8 va0 = CoreF16::read_va(vt, u, 0), va1 = CoreF16::read_va(vt, u, 1);
+      st.o[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va0, ph[u], st.o[0], 0, 0, 0);
+      st.o[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va1, ph[u], st.o[1], 0, 0, 0);
+    }
+  };
+  // a block on the edge of (or outside) this wavefront's window
+  auto edge = [&](int kb) {
+    publish(kb);
+    const int cls = src.classify(kb);
+    if (cls) {
+      floatx16 sv;
+      half8 ph[2];
+      scores(kb, sv);
+      softmax_block_h(sv, c, cls == 2, cls == 2 ? ~0u : src.get(kb, n).word, h, st, ph);
+      weigh(kb, ph);
+    }
+  };
+  static_assert(kRing >= kOut, "the output tiles fit the ring");
+  for (int kb = 0; kb < kStripAhead; ++kb) issue(kb);
+  int kb = 0;
+  for (; kb < k_lo; ++kb) edge(kb);
+  // interior blocks, the scores of block kb+1 ahead of the numerators and PV products of block kb
+  if (kb + 1 < k_hi) {
+    floatx16 s_cur, s_next;
+    publish(kb);
+    scores(kb, s_cur);
+    for (; kb + 2 < k_hi; kb += 2) {
+      half8 ph[2];
+      scores(kb + 1, s_next);
+      softmax_block_h(s_cur, c, true, 0, h, st, ph);
+      weigh(kb, ph);
+      publish(kb + 1);
+      scores(kb + 2, s_cur);
+      softmax_block_h(s_next, c, true, 0, h, st, ph);
+      weigh(kb + 1, ph);
+      publish(kb + 2);
+    }
+    half8 ph[2];
+    softmax_block_h(s_cur, c, true, 0, h, st, ph);
+    weigh(kb, ph);
+    ++kb;
+  }
+  for (; kb < k_hi; ++kb) edge(kb);
+  for (; kb < nblk; ++kb) edge(kb);
+  // every copy has landed and every wavefront is done with the ring: its space takes the output tiles
+  wait_loads_except<0>();
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  if (u0 >= Lc) return;
+  float* lse_h = lse ? lse + hd * L : nullptr;
+  if (accumulate) {
+    finish_tile<__half>(O + hoff, lse_h, qrow, qrow, exists, st, h, true);
+  } else {
+    const int64_t left = Lc - u0;
+    finish_tile_rows<__half>(O + hoff, lse_h, s * u0 + p, s, left < kTile ? (int)left : kTile, st, lane, ring + wave * CoreF16::kTileBytes);
+  }
+}
+
 // fp16 window masks, wide bands, d = 128: the ring of tile_window_band_kernel with key blocks of
 // 128 channels.  A block is staged as four 64-channel blocks in the layout CoreF16 reads (K
 // channels 0..63, K 64..127, V 0..63, V 64..127: 16 KB), once per workgroup of 128 queries; a
@@ -4187,6 +4329,21 @@ sga_status run_tile_implicit_wide(const AttnArgs& a) {
   return SGA_ERR_UNSUPPORTED;
 }
 
+// fp16 windows beyond the staged ones: true where tile_window_strip_kernel (128 queries per workgroup) is expected to beat
+// tile_window_band_kernel (256).  A CU takes its workgroups of either kind at about one pace, alone or with others: a key
+// block costs 0.59 us of the latter, 0.324 of the former, and a call 16 and 5 us around its blocks.  (us measured, band / strip,
+// where the two estimates are close: L = 100,000, W = 2,100 154 / 157, 1,700 129.9 / 128.5; L = 400,000, W = 2,100 529 / 517;
+// L = 1,600,000, W = 1,359 1,322 / 1,332, 700 804 / 756; L = 16,384, 16 heads, W = 2,000 302 / 316; L = 20,000, 8 heads,
+// W = 2,100 236 / 207; L = 65,536, W = 16,383 636 / 665; L = 1,000,000, W = 5,000 2,760 / 2,896.)
+bool strip_is_faster(int64_t W, int64_t Lc, int64_t classes) {
+  const int64_t held = (Lc + kTile - 1) / kTile;
+  const auto cost = [&](int64_t queries, double per_block, double around) {
+    const int64_t wgs = (Lc + queries - 1) / queries * classes, met = (queries - 1 + 2 * W) / kTile + 1;
+    return per_block * (double)((wgs + 255) / 256) * (double)(met < held ? met : held) + around;
+  };
+  return cost(4 * kTile, 0.324, 5.0) < cost(8 * kTile, 0.59, 16.0);
+}
+
 sga_status run_tile_implicit(const AttnArgs& a) {
   if (a.d != kHeadDim)
     return a.dtype == SGA_F32 ? run_tile_implicit_wide<float>(a) : run_tile_implicit_wide<__half>(a);
@@ -4196,7 +4353,8 @@ sga_status run_tile_implicit(const AttnArgs& a) {
   // fp16, 128 queries' key range fits the LDS at two workgroups per CU or more: one workgroup stages
   // it once (128 queries per workgroup, as in the fp32 kernel); wider fp16 windows: 64 queries per wavefront
   const bool wg = a.dtype == SGA_F16 && a.window <= kKvMaxWindow;
-  const bool pair = a.dtype == SGA_F16 && !wg;
+  const bool strip = a.dtype == SGA_F16 && !wg && strip_is_faster(a.window, Lc, shape.n_slots * a.H);
+  const bool pair = a.dtype == SGA_F16 && !wg && !strip;
   const int64_t per_wave = pair ? 2 * kTile : kTile;
   const int64_t n_tiles = (Lc + per_wave - 1) / per_wave;
   const int64_t n_groups = (n_tiles + 3) / 4;           // workgroups per class
@@ -4210,8 +4368,9 @@ sga_status run_tile_implicit(const AttnArgs& a) {
   const int64_t staged = staged_blocks(a.window, Lc, kv ? 1 : 2);
   static_assert(CoreF16::kBlockBytes == kStagedBlockBytes && CoreF16::kTileBytes == kOutTileBytes, "see staged_blocks");
   const char* window_kernel = kv ? "tile_window_kv_kernel" : wg ? "tile_window_wg_kernel"
+                              : strip ? "tile_window_strip_kernel"
                               : pair ? "tile_window_band_kernel" : "tile_window_kernel";
-  if (wg || pair) profile_mark_begin(a.stream, window_kernel);
+  if (wg || strip || pair) profile_mark_begin(a.stream, window_kernel);
   if (wg) {
     int64_t Lq = a.L / s, Lr = a.L % s;             // class lengths, see the kernel
     if (shape.seg_len > 0) {
@@ -4234,6 +4393,11 @@ sga_status run_tile_implicit(const AttnArgs& a) {
                          a.stream, static_cast<const __half*>(a.Q), static_cast<const __half*>(a.K),
                          static_cast<const __half*>(a.V), static_cast<__half*>(a.O), a.lse, a.L,
                          (int64_t)a.window, s, n_groups, a.scale, acc, (int)staged, shape.seg_len, Lq, Lr);
+  } else if (strip) {
+    hipLaunchKernelGGL(tile_window_strip_kernel, grid, dim3(kStripWaves * kWave), 0, a.stream,
+                       static_cast<const __half*>(a.Q), static_cast<const __half*>(a.K),
+                       static_cast<const __half*>(a.V), static_cast<__half*>(a.O), a.lse, a.L,
+                       (int64_t)a.window, s, n_groups, a.scale, acc, shape.seg_len);
   } else if (pair) {
     hipLaunchKernelGGL(tile_window_band_kernel, grid, dim3(256), 0, a.stream,
                        static_cast<const __half*>(a.Q), static_cast<const __half*>(a.K),
