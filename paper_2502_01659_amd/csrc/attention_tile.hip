@@ -319,6 +319,7 @@ __device__ __forceinline__ void softmax_block(floatx16 sv, float c, const BlockI
 
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float float2v __attribute__((ext_vector_type(2)));
+typedef float float4v __attribute__((ext_vector_type(4)));
 
 // softmax_block for fp16 storage, in three steps that callers with two independent sub-tiles
 // interleave.  The numerators leave as the B operand of the PV products: rounded to fp16 two at a
@@ -362,6 +363,13 @@ __device__ __forceinline__ void rescale_state(TileState& st, float bm) {
     st.o[1][r] *= alpha;
   }
 }
+// kMatrixSum: the pairs are not summed by v_dot2_f32_f16, which no matrix instruction overlaps with, but by four 4 x 4 x 4
+// products with ones, whose lane l holds the sum of its own four numerators.  (Two wavefronts of one SIMD, one issuing matrix
+// products, the other the instruction, us alone / alone / together: dot2 242 / 244 / 489, packed conversion 236 / 237 /
+// 243, exp2 253 / 253 / 330.  Kernels of two wavefronts per SIMD with interior loops gain 1 to 3 %: +-1,359, L = 1,600,000
+// 1,366 -> 1,342 us; d = 128, +-2,048, L = 32,768, 32 heads 2,394 -> 2,368, +-200, L = 200,000, 4 heads 332 -> 323.  The others,
+// with four wavefronts per SIMD or masked blocks, do not, and tile_attend_f16_kernel loses 4 % on random masks.)
+template <bool kMatrixSum = false>
 __device__ __forceinline__ void numerators_h(const floatx16& sv, float c, TileState& st, half8 (&ph)[2]) {
   const float neg_m = -st.m;
   const half2v ones = {(_Float16)1.0f, (_Float16)1.0f};
@@ -371,9 +379,19 @@ __device__ __forceinline__ void numerators_h(const floatx16& sv, float c, TileSt
     const float2v p2 = {__builtin_amdgcn_exp2f(__builtin_fmaf(sv[r], c, neg_m)),
                         __builtin_amdgcn_exp2f(__builtin_fmaf(sv[r + 1], c, neg_m))};
     const half2v hp = __builtin_convertvector(p2, half2v);
-    l = __builtin_amdgcn_fdot2(hp, ones, l, false);
+    if constexpr (!kMatrixSum) l = __builtin_amdgcn_fdot2(hp, ones, l, false);
     ph[r / 8][r % 8] = hp[0];
     ph[r / 8][r % 8 + 1] = hp[1];
+  }
+  if constexpr (kMatrixSum) {
+    const half4 four_ones = {(_Float16)1.0f, (_Float16)1.0f, (_Float16)1.0f, (_Float16)1.0f};
+    float4v sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int r = 0; r < 16; r += 4) {
+      const half4 four = {ph[r / 8][r % 8], ph[r / 8][r % 8 + 1], ph[r / 8][r % 8 + 2], ph[r / 8][r % 8 + 3]};
+      sum = __builtin_amdgcn_mfma_f32_4x4x4f16(four_ones, four, sum, 0, 0, 0);
+    }
+    l += sum[0];
   }
   st.l = l;
 }
@@ -402,15 +420,15 @@ __device__ __forceinline__ void softmax_pair_h(const floatx16& s_a, const floatx
                                                TileState& sta, TileState& stb, half8 (&pha)[2],
                                                half8 (&phb)[2]) {
   const float la = sta.l, lb = stb.l;
-  numerators_h(s_a, c, sta, pha);
-  numerators_h(s_b, c, stb, phb);
+  numerators_h<true>(s_a, c, sta, pha);
+  numerators_h<true>(s_b, c, stb, phb);
   if (__any(sum_overflowed(sta) || sum_overflowed(stb))) {
     sta.l = la;
     stb.l = lb;
     rescale_state(sta, block_max(s_a, c, h));
     rescale_state(stb, block_max(s_b, c, h));
-    numerators_h(s_a, c, sta, pha);
-    numerators_h(s_b, c, stb, phb);
+    numerators_h<true>(s_a, c, sta, pha);
+    numerators_h<true>(s_b, c, stb, phb);
   }
 }
 
@@ -3743,7 +3761,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) voi
   auto weigh = [&](int kb, floatx16& sv) {
     half8 ph[2];
     const float l_before = st.l;
-    numerators_h(sv, c, st, ph);
+    numerators_h<true>(sv, c, st, ph);
     if (__any(sum_overflowed(st))) {
       st.l = l_before;
       const float m_before = st.m;
@@ -3754,7 +3772,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) voi
         st_hi.o[0][r] *= alpha;
         st_hi.o[1][r] *= alpha;
       }
-      numerators_h(sv, c, st, ph);
+      numerators_h<true>(sv, c, st, ph);
     }
     const char* vt = vt0 + (kb % kBand128Slots) * kSlotBytes;
 #pragma unroll
