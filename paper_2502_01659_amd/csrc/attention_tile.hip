@@ -4300,6 +4300,17 @@ int choose_window_split(const AttnArgs& a, int64_t tile_heads, int64_t resident,
   return (int)want;
 }
 
+// fp16 windows at d = 128: true where tile_window_band128_kernel, with so many workgroups of 128 queries that meet so many key
+// blocks, beats tile_window_wide_kernel, whose workgroups hold one 32-query tile.  That one runs 1,024 tiles at a time and cuts
+// fewer than 512 into ranges of their keys; the former takes 0.65 us a block and 7 us around them.  (us, wide / band128,
+// one head unless stated.  Up to 128 workgroups: L = 8,000, W = 2,000 60 / 87, 500 33 / 31; L = 16,000, W = 200 18 / 20, 400 30 / 27,
+// 8,000 297 / 308.  Up to 256: L = 20,000, W = 300 26 / 24, 4,000 216 / 164; L = 30,000, W = 100 15.7 / 16.4, 200 22 / 20, 1,000
+// 78 / 51; three heads, L = 16,384, W = 2,000 294 / 133.  Beyond: L = 60,000, W = 64 24 / 19, 130 35 / 24; L = 40,000,
+// W = 10,000 959 / 565.)
+bool band128_is_faster(int64_t wgs, int64_t blocks) {
+  return wgs >= 512 || (wgs > 256 && blocks >= 8) || (wgs > 128 && blocks >= 20);
+}
+
 template <typename T, int kD>
 sga_status run_tile_implicit_wide_d(const AttnArgs& a) {
   const int64_t s = a.stride;
@@ -4312,11 +4323,11 @@ sga_status run_tile_implicit_wide_d(const AttnArgs& a) {
   clear_unselected_rows<T>(a);
   const int acc = a.accumulate ? 1 : 0;
   if constexpr (DtypeOf<T>::code == SGA_F16 && kD == 128) {
-    // wide bands on a call with workgroups enough to fill the chip: one wavefront per 32 queries
-    // with all 128 channels, key blocks staged once per 128 queries
+    // one wavefront per 32 queries with all 128 channels, key blocks staged once per 128 queries
     const int64_t n_groups = (n_tiles + 3) / 4;
     const int64_t n_wg128 = (n_groups * shape.n_slots + 7) / 8 * 8;
-    if (n_groups * shape.n_slots * a.H >= 512) {
+    const int64_t met = (4 * kTile - 1 + 2 * (int64_t)a.window) / kTile + 1;
+    if (band128_is_faster(n_groups * shape.n_slots * a.H, met < n_tiles ? met : n_tiles)) {
       profile_mark_begin(a.stream, "tile_window_band128_kernel");
       hipLaunchKernelGGL(tile_window_band128_kernel, dim3((unsigned)n_wg128, (unsigned)a.H), dim3(256), 0, a.stream,
                          static_cast<const __half*>(a.Q), static_cast<const __half*>(a.K),

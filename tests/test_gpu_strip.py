@@ -46,3 +46,25 @@ def test_wide_windows_agree_with_row_kernels(case):
     sga.attention_accumulate_implicit(Q, K, V, spec, scale, O3, l3)
     assert ((O3.float() - O1.float()).abs() / (1 + O1.float().abs())).max().item() <= 2 * TOL["f16"]
     assert (l3 - l1)[seen].sub(0.6931472).abs().max().item() <= 2 * LSE_TOL["f16"]
+
+
+@pytest.mark.parametrize("L,H,W,kernel", [
+    (16384, 1, 300, "tile_window_wide_kernel"), (16385, 1, 300, "tile_window_band128_kernel"),       # 128 and 129 workgroups
+    (16500, 1, 240, "tile_window_wide_kernel"), (16500, 1, 255, "tile_window_band128_kernel"),       # 19 and 20 blocks
+    (8200, 4, 48, "tile_window_wide_kernel"), (8200, 4, 60, "tile_window_band128_kernel"),           # 260 workgroups, 7 and 8 blocks
+    (700, 44, 3000, "tile_window_band128_kernel"), (16384, 4, 1, "tile_window_band128_kernel")])     # classes of 22 blocks; 512 workgroups
+def test_d128_windows_agree_with_row_kernels(L, H, W, kernel):
+    """Both kernels of d = 128 on both sides of each line between them."""
+    import torch
+    spec = MaskSpec(KIND_SLIDING, L, window=W)
+    print("case", L, H, W, flush=True)
+    Q, K, V = torch_qkv(H, L, 128, "f16", 1.0, L + W, "cuda:0")
+    assert sga.sga_profile_enable(1) == 0
+    O1, l1 = sga.attention_forward_implicit(Q, K, V, spec, 0.088, want_lse=True)
+    torch.cuda.synchronize()
+    name = sga.sga_profile_last_kernel()
+    sga.sga_profile_enable(0)
+    assert name == kernel
+    O2, l2 = sga.attention_forward_implicit(Q, K, V, spec, 0.088, path=sga.PATH_GATHER, want_lse=True)
+    assert ((O1.float() - O2.float()).abs() / (1 + O2.float().abs())).max().item() <= 2 * TOL["f16"]
+    assert (l1 - l2).abs().max().item() <= 2 * LSE_TOL["f16"]
