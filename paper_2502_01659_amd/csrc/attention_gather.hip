@@ -848,6 +848,22 @@ __device__ __forceinline__ void unrolled(const F& f) {
   }
 }
 
+// lo + its partner's lo in one half of every 16 lanes, hi + its partner's hi in the other: lanes l and l ^ 8 (lanes 8 to 15
+// take hi), lanes l and 7 - l of every eight (lanes 4 to 7 take hi).  Two instructions in place of an addition and two
+// selections; s_nop: two states lie between the write of a register and its use across lanes.  (Random 10 %, L = 24,576,
+// us, fp32 824 -> 810, two heads fp16 1,518 -> 1,482.  Products with V that take the numerator across lanes
+// themselves, to save the copy, lose 4 %, fp16 13 %: such an instruction takes longer than the plain one.)
+__device__ __forceinline__ float add_halves8(float lo, float hi) {
+  float x = lo + dpp<0x128>(lo);                                  // row_ror:8
+  asm("s_nop 1\n\tv_add_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xc" : "+v"(x) : "v"(hi));
+  return x;
+}
+__device__ __forceinline__ float add_halves4(float lo, float hi) {
+  float x = lo + dpp<0x141>(lo);                                  // row_half_mirror
+  asm("s_nop 1\n\tv_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa" : "+v"(x) : "v"(hi));
+  return x;
+}
+
 // One step of a row's 16 lanes: up to 16 edges, lane e holding edge e (valid), its row `off` bytes into K and
 // V.  held: the valid lanes of the wavefront (a prefix of every 16).
 template <typename T, int D, bool kLds>
@@ -886,15 +902,14 @@ __device__ __forceinline__ void attend_step(const char* Kb, const char* Vb, uint
     if (held & (0x0100010001000100ull << g)) {
       unrolled<S::kBatch>([&](auto i) {
         constexpr int u = g + decltype(i)::value;
-        const float upper = product(std::integral_constant<int, u + 8>{});
-        a[u] = (l16 & 8 ? upper : a[u]) + dpp<0x128>(l16 & 8 ? a[u] : upper);                     // row_ror:8
+        a[u] = add_halves8(a[u], product(std::integral_constant<int, u + 8>{}));
       });
     } else {
       unrolled<S::kBatch>([&](auto i) { a[g + decltype(i)::value] += dpp<0x128>(a[g + decltype(i)::value]); });
     }
   });
 #pragma unroll
-  for (int u = 0; u < 4; ++u) b[u] = (l16 & 4 ? a[u + 4] : a[u]) + dpp<0x141>(l16 & 4 ? a[u] : a[u + 4]);   // row_half_mirror
+  for (int u = 0; u < 4; ++u) b[u] = add_halves4(a[u], a[u + 4]);
 #pragma unroll
   for (int u = 0; u < 2; ++u) c[u] = (l16 & 2 ? b[u + 2] : b[u]) + dpp<0x4E>(l16 & 2 ? b[u] : b[u + 2]);    // quad_perm [2,3,0,1]
   const float sum = (l16 & 1 ? c[1] : c[0]) + dpp<0xB1>(l16 & 1 ? c[0] : c[1]);                             // quad_perm [1,0,3,2]
