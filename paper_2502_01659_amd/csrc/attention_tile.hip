@@ -2365,6 +2365,84 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) voi
   }
 }
 
+// fp32 windows of calls that leave most SIMDs without a second wavefront: kShare wavefronts (2 or 4) take a tile, each a
+// range of its key blocks, and the first one merges their states through LDS, in wavefront order (see window_share).
+template <int kShare>
+__global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) void tile_window_share_kernel(
+    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, float* __restrict__ O,
+    float* __restrict__ lse, int64_t L, int64_t W, int64_t s, int64_t n_groups, float scale, int accumulate,
+    int64_t seg_len) {
+  constexpr int kLds = CoreF32::lds_bytes<kPipeRegK>(), kTiles = 4 / kShare;
+  static_assert(34 * kWave * 4 <= kLds, "a wavefront's state fits its LDS");
+  __shared__ __attribute__((aligned(16))) char lds_all[4 * kLds];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int n = lane & 31, h = lane >> 5, part = wave % kShare;
+  char* lds = lds_all + wave * kLds;
+  const int64_t chunk = gridDim.x / 8;
+  const int64_t bid = (int64_t)(blockIdx.x % 8) * chunk + blockIdx.x / 8;
+  WindowSlot slot;
+  if (!locate_window_slot(bid, L, s, n_groups, seg_len, slot)) return;      // (the whole workgroup leaves)
+  const int64_t p = slot.p, Lc = slot.Lc;
+  const int64_t u0 = (slot.grp * kTiles + wave / kShare) * kTile;
+  const bool active = u0 < Lc;                     // (a wavefront without queries still meets the barrier)
+  const int64_t hd = blockIdx.y;
+  const int64_t hoff = hd * L * kHeadDim;
+  const int64_t u = u0 + n;
+  const bool exists = u < Lc;
+  const int64_t qrow = s * (exists ? u : Lc - 1) + p;
+  TileState st;
+  st.init();
+  if (active) {
+    const int64_t vlo = u0 - W > 0 ? u0 - W : 0;
+    const int64_t vhi = u0 + kTile - 1 + W < Lc - 1 ? u0 + kTile - 1 + W : Lc - 1;
+    const WindowBlocks src{vlo, Lc, s, p, u0, W};
+    const int nblk = (int)((vhi - vlo) / kTile + 1);
+    CoreF32 core;
+    core.load_q(Q + hoff + qrow * kHeadDim, h, scale < 0.f);
+    core.run<kPipeRegK>(K + hoff, V + hoff, src, nblk * part / kShare, nblk * (part + 1) / kShare, softmax_factor(scale),
+                        lane, st, lds);
+  }
+  float* mine = reinterpret_cast<float*>(lds) + lane;
+  if (part > 0) {
+    wait_loads_except<0>();                // (nothing of this wavefront still lands in its LDS)
+    wait_lds_reads();
+    __builtin_amdgcn_wave_barrier();
+    mine[0] = st.m;
+    mine[kWave] = st.l;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      mine[(2 + r) * kWave] = st.o[0][r];
+      mine[(18 + r) * kWave] = st.o[1][r];
+    }
+  }
+  __syncthreads();
+  if (part > 0 || !active) return;
+  // (one common maximum, so that each state is scaled once)
+  float m = st.m, weight[kShare];
+#pragma unroll
+  for (int w = 1; w < kShare; ++w) m = __builtin_fmaxf(m, mine[w * (kLds / 4)]);
+  weight[0] = __builtin_amdgcn_exp2f(st.m - m);
+  st.m = m;
+  st.l *= weight[0];
+#pragma unroll
+  for (int w = 1; w < kShare; ++w) {
+    weight[w] = __builtin_amdgcn_exp2f(mine[w * (kLds / 4)] - m);
+    st.l = __builtin_fmaf(mine[w * (kLds / 4) + kWave], weight[w], st.l);
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    st.o[0][r] *= weight[0];
+    st.o[1][r] *= weight[0];
+#pragma unroll
+    for (int w = 1; w < kShare; ++w) {
+      st.o[0][r] = __builtin_fmaf(mine[w * (kLds / 4) + (2 + r) * kWave], weight[w], st.o[0][r]);
+      st.o[1][r] = __builtin_fmaf(mine[w * (kLds / 4) + (18 + r) * kWave], weight[w], st.o[1][r]);
+    }
+  }
+  finish_tile<float>(O + hoff, lse ? lse + hd * L : nullptr, qrow, qrow, exists, st, h, accumulate != 0);
+}
+
 // ---- fp32 storage, key blocks shared by a workgroup ------------------------------------------------
 // Four tiles (one per wavefront) walk one list of key blocks together.  Each block of K and V is
 // loaded once per workgroup, split once (16 values per thread), and left in LDS as six planes of
@@ -4358,6 +4436,20 @@ sga_status run_tile_implicit_wide(const AttnArgs& a) {
   return SGA_ERR_UNSUPPORTED;
 }
 
+// Wavefronts per tile of an fp32 window call that tile_window_f32_kernel leaves, in tile_window_share_kernel (1: none,
+// tile_window_kernel): shorter chains of blocks (2 us each for a wavefront alone) as long as the chip holds all
+// wavefronts at once, two per SIMD.  Tiles of fewer than four blocks gain nothing.  Ranges of keys that workgroups
+// take (nsplit) stay where they leave no less than half a chain: their sums of several states are as exact, if slower.
+// (us, 1 / 2 / 4, one head: L = 8,000, W = 50 16.6 / 12.4 / 12.1, 200 35.6 / 19.2 / 13.3, 400 61 / 31 / 19.4; L = 16,000,
+// W = 100 23.2 / 13.5 / 14.8, 400 61 / 31 / 31; L = 35,000, W = 50 25.6 / 24.6 / 27.7, 200 56 / 46 / 43; L = 50,000, W = 50
+// 26.4 / 30.0 / 36.4, 200 57.2 / 58.5 / 58.4; four heads, L = 16,000, W = 50 29.3 / 31.0 / 41.1.  12 is what the host takes for
+// a call.  Two ranges and their merge / 4: L = 8,000, W = 600 53.5 / 25.3, error against 64 bits 1.70e-7 / 1.62e-7; three
+// ranges / 4: W = 1,000 51.9 / 37.1, 1.735e-7 / 1.740e-7.)
+int window_share(int64_t tiles, int64_t blocks, int nsplit) {
+  const int share = blocks < 4 ? 1 : tiles <= 320 ? 4 : tiles <= 1152 ? 2 : 1;
+  return nsplit == 1 || share >= 2 * nsplit ? share : 1;
+}
+
 // fp16 windows beyond the staged ones: true where tile_window_strip_kernel (128 queries per workgroup) is expected to beat
 // tile_window_band_kernel (256).  A CU takes its workgroups of either kind at about one pace, alone or with others: a key
 // block costs 0.59 us of the latter, 0.324 of the former, and a call 16 and 5 us around its blocks.  (us measured, band / strip,
@@ -4443,6 +4535,20 @@ sga_status run_tile_implicit(const AttnArgs& a) {
     const int64_t class_blocks = (Lc + kTile - 1) / kTile;
     const int64_t steps = n_groups * shape.n_slots * a.H * (nb_max < class_blocks ? nb_max : class_blocks);
     const bool shared = !a.split && steps >= kSharedSteps;
+    const int64_t tiles = (Lc + kTile - 1) / kTile, mine = (kTile - 1 + 2 * (int64_t)a.window) / kTile + 1;
+    const int share = a.split || shared ? 1
+                      : window_share(tiles * shape.n_slots * a.H, mine < class_blocks ? mine : class_blocks, nsplit);
+    if (share > 1) {
+      const int64_t ng = (tiles * share + 3) / 4;
+      const dim3 share_grid((unsigned)((ng * shape.n_slots + 7) / 8 * 8), (unsigned)a.H);
+      profile_mark_begin(a.stream, "tile_window_share_kernel");
+      hipLaunchKernelGGL(share == 4 ? tile_window_share_kernel<4> : tile_window_share_kernel<2>, share_grid, dim3(256), 0,
+                         a.stream, static_cast<const float*>(a.Q), static_cast<const float*>(a.K),
+                         static_cast<const float*>(a.V), static_cast<float*>(a.O), a.lse, a.L, (int64_t)a.window, s, ng,
+                         a.scale, acc, shape.seg_len);
+      profile_mark_end(a.stream);
+      return hip_status(hipGetLastError());
+    }
     if (shared) window_kernel = "tile_window_f32_kernel";
     profile_mark_begin(a.stream, window_kernel);
     auto kernel = a.split ? tile_window_kernel<float, kPipeSplit>

@@ -1,0 +1,51 @@
+"""fp32 windows of calls with few tiles: two or four wavefronts per tile, against the per-row kernels."""
+import pytest
+
+import paper_2502_01659_amd as sga
+from sga_inputs import MaskSpec, KIND_SLIDING, KIND_DILATED, KIND_DILATED_2D, torch_qkv
+from gpu_util import TOL, LSE_TOL
+
+pytestmark = pytest.mark.gpu
+SHARE, ONE, GROUP = "tile_window_share_kernel", "tile_window_kernel", "tile_window_f32_kernel"
+
+
+@pytest.mark.parametrize("spec,H,kernel", [
+    (MaskSpec(KIND_SLIDING, 97, window=33), 1, SHARE),            # four blocks, the last of one key; a tile of one query
+    (MaskSpec(KIND_SLIDING, 96, window=400), 1, ONE),             # three blocks: the class holds no more
+    (MaskSpec(KIND_SLIDING, 1000, window=32), 2, ONE),            # three blocks inside
+    (MaskSpec(KIND_SLIDING, 1001, window=49), 2, SHARE),          # five blocks for four wavefronts, fewer at the ends
+    (MaskSpec(KIND_SLIDING, 10240, window=100), 1, SHARE),        # 320 tiles: four wavefronts each
+    (MaskSpec(KIND_SLIDING, 10241, window=100), 1, SHARE),        # 321: two
+    (MaskSpec(KIND_SLIDING, 4601, window=60), 8, SHARE),          # 1,152 tiles
+    (MaskSpec(KIND_SLIDING, 4609, window=60), 8, ONE),            # 1,160
+    (MaskSpec(KIND_SLIDING, 4001, window=700), 1, SHARE),         # two ranges of keys would be the other form,
+    (MaskSpec(KIND_SLIDING, 4001, window=1000), 1, ONE),          # three are
+    (MaskSpec(KIND_DILATED, 3001, window=70, stride=3), 1, SHARE),
+    (MaskSpec(KIND_DILATED_2D, 3000, block=601, stride=2), 2, SHARE),
+    (MaskSpec(KIND_SLIDING, 40000, window=200), 8, GROUP)])
+def test_wavefronts_that_share_a_tile(spec, H, kernel):
+    import torch
+    L = spec.L
+    scale = -0.125 if H == 2 else 0.125
+    print("case", spec, H, flush=True)
+    Q, K, V = torch_qkv(H, L, 64, "f32", 1.0, L, "cuda:0")
+    ws = sga.alloc_workspace(L, H, 64, "f32", -1)
+    assert sga.sga_profile_enable(1) == 0
+    O1, l1 = sga.attention_forward_implicit(Q, K, V, spec, scale, workspace=ws, want_lse=True)
+    torch.cuda.synchronize()
+    name = sga.sga_profile_last_kernel()
+    sga.sga_profile_enable(0)
+    assert name == kernel
+    O2, l2 = sga.attention_forward_implicit(Q, K, V, spec, scale, path=sga.PATH_GATHER, want_lse=True)
+    assert ((O1 - O2).abs() / (1 + O2.abs())).max().item() <= 2 * TOL["f32"]
+    seen = torch.isfinite(l2)
+    assert torch.equal(torch.isfinite(l1), seen) and (l1 - l2)[seen].abs().max().item() <= 2 * LSE_TOL["f32"]
+    # continued, and with values whose split is not exact (computed again with fp32 products, per wavefront)
+    O3, l3 = O1.clone(), l1.clone()
+    sga.attention_accumulate_implicit(Q, K, V, spec, scale, O3, l3, workspace=ws)
+    assert ((O3 - O1).abs() / (1 + O1.abs())).max().item() <= 2 * TOL["f32"]
+    K[:, L // 2] *= 1e-36
+    V[:, L // 3] = 1e-37
+    O4 = sga.attention_forward_implicit(Q, K, V, spec, scale, workspace=ws)
+    O5 = sga.attention_forward_implicit(Q, K, V, spec, scale, path=sga.PATH_GATHER)
+    assert ((O4 - O5).abs() / (1 + O5.abs())).max().item() <= 2 * TOL["f32"]
