@@ -902,6 +902,19 @@ struct CoreF32T {
     }
   }
 
+  // The slices of a wide tile for one of several ranges of its blocks in one workgroup: sum_slices waits for the whole
+  // workgroup, so every wavefront meets `longest` (>= k1 - k0) barriers.
+  template <typename Src>
+  __device__ void run_range(const float* __restrict__ Kh, const float* __restrict__ Vh, const Src& src, int k0, int k1,
+                            int longest, float c, int lane, TileState& st, char* lds) {
+    if (k0 < k1) run_split(Kh, Vh, src, k0, k1, c, lane, st, lds);
+    for (int k = k1 - k0; k < longest; ++k) __syncthreads();
+    if (!__syncthreads_or(k0 < k1 && again(st))) return;
+    st.init();
+    if (k0 < k1) run_exact(Kh, Vh, src, k0, k1, c, lane, st, lds);
+    for (int k = k1 - k0; k < longest; ++k) __syncthreads();
+  }
+
   // Orow = acc * inv, or w_prev * Orow + acc * inv when the call continues an earlier state.
   __device__ static void store_row(float* Orow, const TileState& st, float inv, float w_prev,
                                    bool accumulate, int h) {
@@ -2365,6 +2378,50 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) voi
   }
 }
 
+// The state of a wavefront, left in its LDS for another one to add (kShareBytes of it).
+constexpr int kShareBytes = 34 * kWave * 4;
+__device__ __forceinline__ void leave_state(const TileState& st, char* lds, int lane) {
+  wait_loads_except<0>();                // (nothing of this wavefront still lands in its LDS)
+  wait_lds_reads();
+  __builtin_amdgcn_wave_barrier();
+  float* mine = reinterpret_cast<float*>(lds) + lane;
+  mine[0] = st.m;
+  mine[kWave] = st.l;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    mine[(2 + r) * kWave] = st.o[0][r];
+    mine[(18 + r) * kWave] = st.o[1][r];
+  }
+}
+
+// Adds the states left at lds + kStep, lds + 2 kStep, ... to st (one common maximum, so that each is scaled once).
+template <int kShare, int kStep>
+__device__ __forceinline__ void add_states(TileState& st, const char* lds, int lane) {
+  const float* other = reinterpret_cast<const float*>(lds) + lane;
+  constexpr int step = kStep / 4;
+  float m = st.m, weight[kShare];
+#pragma unroll
+  for (int w = 1; w < kShare; ++w) m = __builtin_fmaxf(m, other[w * step]);
+  weight[0] = __builtin_amdgcn_exp2f(st.m - m);
+  st.m = m;
+  st.l *= weight[0];
+#pragma unroll
+  for (int w = 1; w < kShare; ++w) {
+    weight[w] = __builtin_amdgcn_exp2f(other[w * step] - m);
+    st.l = __builtin_fmaf(other[w * step + kWave], weight[w], st.l);
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    st.o[0][r] *= weight[0];
+    st.o[1][r] *= weight[0];
+#pragma unroll
+    for (int w = 1; w < kShare; ++w) {
+      st.o[0][r] = __builtin_fmaf(other[w * step + (2 + r) * kWave], weight[w], st.o[0][r]);
+      st.o[1][r] = __builtin_fmaf(other[w * step + (18 + r) * kWave], weight[w], st.o[1][r]);
+    }
+  }
+}
+
 // fp32 windows of calls that leave most SIMDs without a second wavefront: kShare wavefronts (2 or 4) take a tile, each a
 // range of its key blocks, and the first one merges their states through LDS, in wavefront order (see window_share).
 template <int kShare>
@@ -2373,7 +2430,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) voi
     float* __restrict__ lse, int64_t L, int64_t W, int64_t s, int64_t n_groups, float scale, int accumulate,
     int64_t seg_len) {
   constexpr int kLds = CoreF32::lds_bytes<kPipeRegK>(), kTiles = 4 / kShare;
-  static_assert(34 * kWave * 4 <= kLds, "a wavefront's state fits its LDS");
+  static_assert(kShareBytes <= kLds, "a wavefront's state fits its LDS");
   __shared__ __attribute__((aligned(16))) char lds_all[4 * kLds];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -2403,43 +2460,10 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) voi
     core.run<kPipeRegK>(K + hoff, V + hoff, src, nblk * part / kShare, nblk * (part + 1) / kShare, softmax_factor(scale),
                         lane, st, lds);
   }
-  float* mine = reinterpret_cast<float*>(lds) + lane;
-  if (part > 0) {
-    wait_loads_except<0>();                // (nothing of this wavefront still lands in its LDS)
-    wait_lds_reads();
-    __builtin_amdgcn_wave_barrier();
-    mine[0] = st.m;
-    mine[kWave] = st.l;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      mine[(2 + r) * kWave] = st.o[0][r];
-      mine[(18 + r) * kWave] = st.o[1][r];
-    }
-  }
+  if (part > 0) leave_state(st, lds, lane);
   __syncthreads();
   if (part > 0 || !active) return;
-  // (one common maximum, so that each state is scaled once)
-  float m = st.m, weight[kShare];
-#pragma unroll
-  for (int w = 1; w < kShare; ++w) m = __builtin_fmaxf(m, mine[w * (kLds / 4)]);
-  weight[0] = __builtin_amdgcn_exp2f(st.m - m);
-  st.m = m;
-  st.l *= weight[0];
-#pragma unroll
-  for (int w = 1; w < kShare; ++w) {
-    weight[w] = __builtin_amdgcn_exp2f(mine[w * (kLds / 4)] - m);
-    st.l = __builtin_fmaf(mine[w * (kLds / 4) + kWave], weight[w], st.l);
-  }
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    st.o[0][r] *= weight[0];
-    st.o[1][r] *= weight[0];
-#pragma unroll
-    for (int w = 1; w < kShare; ++w) {
-      st.o[0][r] = __builtin_fmaf(mine[w * (kLds / 4) + (2 + r) * kWave], weight[w], st.o[0][r]);
-      st.o[1][r] = __builtin_fmaf(mine[w * (kLds / 4) + (18 + r) * kWave], weight[w], st.o[1][r]);
-    }
-  }
+  add_states<kShare, kLds>(st, lds, lane);
   finish_tile<float>(O + hoff, lse ? lse + hd * L : nullptr, qrow, qrow, exists, st, h, accumulate != 0);
 }
 
@@ -3133,6 +3157,55 @@ __global__ __launch_bounds__(kD) void tile_window_wide_kernel(
                            lds_all + slice * kLds);
   finish_tile_wide<T, kD>(O + hoff, lse ? lse + hd * L : nullptr, qrow, exists, st, h, slice,
                           accumulate != 0);
+}
+
+// fp32 windows at d = 128 and 256 of calls with few tiles: kShare groups of kD / 64 wavefronts per tile, each for a range
+// of its key blocks; the first group merges their states through LDS (see window_share_wide).
+template <int kD, int kShare>
+__global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kD * kShare) void tile_window_wide_share_kernel(
+    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, float* __restrict__ O,
+    float* __restrict__ lse, int64_t L, int64_t W, int64_t s, int64_t n_tiles, float scale, int accumulate,
+    int64_t seg_len) {
+  using Core = CoreF32T<kD>;
+  constexpr int kSlices = kD / kHeadDim, kLds = Core::template lds_bytes<kPipeRegK>();
+  static_assert(kShareBytes <= kLds, "a wavefront's state fits its LDS");
+  __shared__ __attribute__((aligned(16))) char lds_all[kShare * (kSlices * kLds + SliceExchange<kD>::kBytes)];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int slice = wave % kSlices, part = wave / kSlices;
+  const int n = lane & 31, h = lane >> 5;
+  char* lds = lds_all + wave * kLds;
+  const int64_t chunk = gridDim.x / 8;
+  const int64_t bid = (int64_t)(blockIdx.x % 8) * chunk + blockIdx.x / 8;
+  WindowSlot slot;
+  if (!locate_window_slot(bid, L, s, n_tiles, seg_len, slot)) return;       // (the whole workgroup leaves)
+  const int64_t p = slot.p, Lc = slot.Lc;
+  const int64_t u0 = slot.grp * kTile;
+  if (u0 >= Lc) return;
+  const int64_t hd = blockIdx.y;
+  const int64_t hoff = hd * L * kD + slice * kHeadDim;
+  const int64_t vlo = u0 - W > 0 ? u0 - W : 0;
+  const int64_t vhi = u0 + kTile - 1 + W < Lc - 1 ? u0 + kTile - 1 + W : Lc - 1;
+  const WindowBlocks src{vlo, Lc, s, p, u0, W};
+  const int nblk = (int)((vhi - vlo) / kTile + 1);
+  const int64_t u = u0 + n;
+  const bool exists = u < Lc;
+  const int64_t qrow = s * (exists ? u : Lc - 1) + p;
+  Core core;
+  core.xchg.init(lds_all + kShare * kSlices * kLds + part * SliceExchange<kD>::kBytes, slice);
+  core.load_q(Q + hoff + qrow * kD, h, scale < 0.f);
+  TileState st;
+  st.init();
+  core.run_range(K + hoff, V + hoff, src, nblk * part / kShare, nblk * (part + 1) / kShare, (nblk + kShare - 1) / kShare,
+                 softmax_factor(scale), lane, st, lds);
+  if (part > 0) leave_state(st, lds, lane);
+  __syncthreads();
+  if (part > 0) {
+    if (accumulate) __syncthreads();     // (the one of finish_tile_wide)
+    return;
+  }
+  add_states<kShare, kSlices * kLds>(st, lds, lane);
+  finish_tile_wide<float, kD>(O + hoff, lse ? lse + hd * L : nullptr, qrow, exists, st, h, slice, accumulate != 0);
 }
 
 // fp16, d = 128, explicit masks: one wavefront per work item with all 128 channels of its 32
@@ -4389,6 +4462,18 @@ bool band128_is_faster(int64_t wgs, int64_t blocks) {
   return wgs >= 512 || (wgs > 256 && blocks >= 8) || (wgs > 128 && blocks >= 20);
 }
 
+// Groups of kSlices wavefronts per tile of an fp32 window call at d = 64 kSlices, in tile_window_wide_share_kernel (1: none,
+// tile_window_wide_kernel), as window_share: a CU holds eight wavefronts, two groups want six blocks (with five d = 256 gains
+// nothing and d = 128 no accuracy).  (us, one group / shared, one head: d = 128, L = 8,000 (four groups), W = 50 16.4 / 13.5, 200 36.5 /
+// 22.6, 400 63.4 / 33.7, 600 (two ranges of keys and their merge) 84 / 45; L = 16,000 (two), W = 100 33.5 / 23.7, 400 95 / 59;
+// d = 256, L = 8,000 (two), W = 50 19.7 / 19.5, 200 42.4 / 36.1, 400 75.5 / 60.8.)
+template <int kSlices>
+int window_share_wide(int64_t tiles, int64_t blocks, int nsplit) {
+  const int most = tiles > 1024 / kSlices ? 1 : tiles > 512 / kSlices || kSlices == 4 ? 2 : 4;
+  const int share = blocks < (most == 4 ? 4 : 6) ? 1 : most;
+  return nsplit == 1 || share >= 2 * nsplit ? share : 1;
+}
+
 template <typename T, int kD>
 sga_status run_tile_implicit_wide_d(const AttnArgs& a) {
   const int64_t s = a.stride;
@@ -4417,6 +4502,21 @@ sga_status run_tile_implicit_wide_d(const AttnArgs& a) {
   }
   float* parts = nullptr;
   const int nsplit = choose_window_split(a, n_wg * a.H, 2048 / kSlices, &parts);
+  if constexpr (DtypeOf<T>::code == SGA_F32) {
+    const int64_t met = (kTile - 1 + 2 * (int64_t)a.window) / kTile + 1;
+    const int share = window_share_wide<kSlices>(n_tiles * shape.n_slots * a.H, met < n_tiles ? met : n_tiles, nsplit);
+    if (share > 1) {
+      auto kernel = tile_window_wide_share_kernel<kD, 2>;
+      if constexpr (kSlices == 2)
+        if (share == 4) kernel = tile_window_wide_share_kernel<kD, 4>;
+      profile_mark_begin(a.stream, "tile_window_wide_share_kernel");
+      hipLaunchKernelGGL(kernel, dim3((unsigned)n_wg, (unsigned)a.H), dim3(kD * share), 0, a.stream,
+                         static_cast<const float*>(a.Q), static_cast<const float*>(a.K), static_cast<const float*>(a.V),
+                         static_cast<float*>(a.O), a.lse, a.L, (int64_t)a.window, s, n_tiles, a.scale, acc, shape.seg_len);
+      profile_mark_end(a.stream);
+      return hip_status(hipGetLastError());
+    }
+  }
   profile_mark_begin(a.stream, "tile_window_wide_kernel");
   hipLaunchKernelGGL((tile_window_wide_kernel<T, kD, kPipe>), dim3((unsigned)(n_wg * nsplit), (unsigned)a.H),
                      dim3(kD), 0, a.stream, static_cast<const T*>(a.Q), static_cast<const T*>(a.K),

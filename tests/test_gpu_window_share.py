@@ -49,3 +49,48 @@ def test_wavefronts_that_share_a_tile(spec, H, kernel):
     O4 = sga.attention_forward_implicit(Q, K, V, spec, scale, workspace=ws)
     O5 = sga.attention_forward_implicit(Q, K, V, spec, scale, path=sga.PATH_GATHER)
     assert ((O4 - O5).abs() / (1 + O5.abs())).max().item() <= 2 * TOL["f32"]
+
+
+WIDE, WIDE_SHARE = "tile_window_wide_kernel", "tile_window_wide_share_kernel"
+
+
+@pytest.mark.parametrize("spec,H,d,kernel", [
+    (MaskSpec(KIND_SLIDING, 97, window=33), 1, 128, WIDE_SHARE),
+    (MaskSpec(KIND_SLIDING, 96, window=400), 1, 256, WIDE),
+    (MaskSpec(KIND_SLIDING, 1001, window=49), 2, 128, WIDE_SHARE),
+    (MaskSpec(KIND_SLIDING, 1001, window=64), 2, 256, WIDE),              # five blocks
+    (MaskSpec(KIND_SLIDING, 1001, window=65), 2, 256, WIDE_SHARE),        # six
+    (MaskSpec(KIND_SLIDING, 8192, window=100), 1, 128, WIDE_SHARE),       # 256 tiles: four groups each
+    (MaskSpec(KIND_SLIDING, 8193, window=100), 1, 128, WIDE_SHARE),       # 257: two
+    (MaskSpec(KIND_SLIDING, 4096, window=100), 4, 128, WIDE_SHARE),       # 512
+    (MaskSpec(KIND_SLIDING, 4097, window=100), 4, 128, WIDE),             # 516
+    (MaskSpec(KIND_SLIDING, 8192, window=100), 1, 256, WIDE_SHARE),       # 256: two
+    (MaskSpec(KIND_SLIDING, 8193, window=100), 1, 256, WIDE),
+    (MaskSpec(KIND_SLIDING, 4001, window=1000), 1, 128, WIDE),            # three ranges of keys
+    (MaskSpec(KIND_DILATED, 3001, window=70, stride=3), 1, 128, WIDE_SHARE),
+    (MaskSpec(KIND_DILATED_2D, 3000, block=601, stride=2), 2, 256, WIDE_SHARE)])
+def test_groups_that_share_a_wide_tile(spec, H, d, kernel):
+    import torch
+    L = spec.L
+    scale = -0.125 if H == 2 else 0.125
+    print("case", spec, H, d, flush=True)
+    Q, K, V = torch_qkv(H, L, d, "f32", 1.0, L, "cuda:0")
+    ws = sga.alloc_workspace(L, H, d, "f32", -1)
+    assert sga.sga_profile_enable(1) == 0
+    O1, l1 = sga.attention_forward_implicit(Q, K, V, spec, scale, workspace=ws, want_lse=True)
+    torch.cuda.synchronize()
+    name = sga.sga_profile_last_kernel()
+    sga.sga_profile_enable(0)
+    assert name == kernel
+    O2, l2 = sga.attention_forward_implicit(Q, K, V, spec, scale, path=sga.PATH_GATHER, want_lse=True)
+    assert ((O1 - O2).abs() / (1 + O2.abs())).max().item() <= 2 * TOL["f32"]
+    seen = torch.isfinite(l2)
+    assert torch.equal(torch.isfinite(l1), seen) and (l1 - l2)[seen].abs().max().item() <= 2 * LSE_TOL["f32"]
+    O3, l3 = O1.clone(), l1.clone()
+    sga.attention_accumulate_implicit(Q, K, V, spec, scale, O3, l3, workspace=ws)
+    assert ((O3 - O1).abs() / (1 + O1.abs())).max().item() <= 2 * TOL["f32"]
+    K[:, L // 2] *= 1e-36
+    V[:, L // 3] = 1e-37
+    O4 = sga.attention_forward_implicit(Q, K, V, spec, scale, workspace=ws)
+    O5 = sga.attention_forward_implicit(Q, K, V, spec, scale, path=sga.PATH_GATHER)
+    assert ((O4 - O5).abs() / (1 + O5.abs())).max().item() <= 2 * TOL["f32"]
