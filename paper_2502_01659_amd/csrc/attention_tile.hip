@@ -1146,6 +1146,14 @@ struct CoreF16T {
     run_ldsk(Kh, Vh, src, k0, k1, c, lane, st, lds);
   }
 
+  // (see CoreF32T::run_range)
+  template <typename Src>
+  __device__ void run_range(const __half* __restrict__ Kh, const __half* __restrict__ Vh, const Src& src, int k0, int k1,
+                            int longest, float c, int lane, TileState& st, char* lds) {
+    run_ldsk(Kh, Vh, src, k0, k1, c, lane, st, lds);
+    for (int k = k1 - k0; k < longest; ++k) __syncthreads();
+  }
+
   __device__ static void store_row(__half* Orow, const TileState& st, float inv, float w_prev,
                                    bool accumulate, int h) {
 #pragma unroll
@@ -3159,15 +3167,16 @@ __global__ __launch_bounds__(kD) void tile_window_wide_kernel(
                           accumulate != 0);
 }
 
-// fp32 windows at d = 128 and 256 of calls with few tiles: kShare groups of kD / 64 wavefronts per tile, each for a range
+// Windows at d = 128 and 256 of calls with few tiles: kShare groups of kD / 64 wavefronts per tile, each for a range
 // of its key blocks; the first group merges their states through LDS (see window_share_wide).
-template <int kD, int kShare>
+template <typename T, int kD, int kShare>
 __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kD * kShare) void tile_window_wide_share_kernel(
-    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, float* __restrict__ O,
+    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
     float* __restrict__ lse, int64_t L, int64_t W, int64_t s, int64_t n_tiles, float scale, int accumulate,
     int64_t seg_len) {
-  using Core = CoreF32T<kD>;
-  constexpr int kSlices = kD / kHeadDim, kLds = Core::template lds_bytes<kPipeRegK>();
+  using Core = typename WideCoreOf<T, kD>::type;
+  constexpr int kPipe = DtypeOf<T>::code == SGA_F16 ? kPipeLdsK : kPipeRegK;
+  constexpr int kSlices = kD / kHeadDim, kLds = Core::template lds_bytes<kPipe>();
   static_assert(kShareBytes <= kLds, "a wavefront's state fits its LDS");
   __shared__ __attribute__((aligned(16))) char lds_all[kShare * (kSlices * kLds + SliceExchange<kD>::kBytes)];
   const int lane = threadIdx.x & (kWave - 1);
@@ -3205,7 +3214,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kD * kSh
     return;
   }
   add_states<kShare, kSlices * kLds>(st, lds, lane);
-  finish_tile_wide<float, kD>(O + hoff, lse ? lse + hd * L : nullptr, qrow, exists, st, h, slice, accumulate != 0);
+  finish_tile_wide<T, kD>(O + hoff, lse ? lse + hd * L : nullptr, qrow, exists, st, h, slice, accumulate != 0);
 }
 
 // fp16, d = 128, explicit masks: one wavefront per work item with all 128 channels of its 32
@@ -4462,15 +4471,20 @@ bool band128_is_faster(int64_t wgs, int64_t blocks) {
   return wgs >= 512 || (wgs > 256 && blocks >= 8) || (wgs > 128 && blocks >= 20);
 }
 
-// Groups of kSlices wavefronts per tile of an fp32 window call at d = 64 kSlices, in tile_window_wide_share_kernel (1: none,
-// tile_window_wide_kernel), as window_share: a CU holds eight wavefronts, two groups want six blocks (with five d = 256 gains
-// nothing and d = 128 no accuracy).  (us, one group / shared, one head: d = 128, L = 8,000 (four groups), W = 50 16.4 / 13.5, 200 36.5 /
-// 22.6, 400 63.4 / 33.7, 600 (two ranges of keys and their merge) 84 / 45; L = 16,000 (two), W = 100 33.5 / 23.7, 400 95 / 59;
-// d = 256, L = 8,000 (two), W = 50 19.7 / 19.5, 200 42.4 / 36.1, 400 75.5 / 60.8.)
-template <int kSlices>
+// Groups of d / 64 wavefronts per tile of a window call, in tile_window_wide_share_kernel (1: none, tile_window_wide_kernel),
+// as window_share: a CU holds eight wavefronts, two groups want six blocks (with five d = 256 gains nothing and d = 128 no
+// accuracy).  fp16 takes four groups or none: sums of two ranges are no more exact than of one (2.956e-4 -> 2.962e-4), of four
+// they are; below ten blocks its calls wait for the host.
+// (us, one group / shared, one head: fp32, d = 128, L = 8,000 (four groups), W = 50 16.4 / 13.5, 200 36.5 / 22.6, 400 63.4 / 33.7, 600 (two
+// ranges of keys and their merge) 84 / 45; L = 16,000 (two), W = 100 33.5 / 23.7, 400 95 / 59; d = 256, L = 8,000 (two), W = 50
+// 19.7 / 19.5, 200 42.4 / 36.1, 400 75.5 / 60.8; fp16, d = 128, L = 8,000, W = 100 12.0 / 12.4, 200 15.5 / 12.2, 400 25.4 / 13.5, 600
+// 36.1 / 17.9; two groups, not taken: L = 16,000, W = 400 29.9 / 20.7, d = 256, L = 8,000 32.5 / 24.3.)
+template <typename T, int kD>
 int window_share_wide(int64_t tiles, int64_t blocks, int nsplit) {
-  const int most = tiles > 1024 / kSlices ? 1 : tiles > 512 / kSlices || kSlices == 4 ? 2 : 4;
-  const int share = blocks < (most == 4 ? 4 : 6) ? 1 : most;
+  constexpr bool kF32 = DtypeOf<T>::code == SGA_F32;
+  constexpr int64_t kPairs = 1024 * kHeadDim / kD;       // tiles whose two groups the chip holds at once
+  const int most = kD == 128 && tiles <= kPairs / 2 ? 4 : kF32 && tiles <= kPairs ? 2 : 1;
+  const int share = blocks < (kF32 ? most == 4 ? 4 : 6 : 10) ? 1 : most;
   return nsplit == 1 || share >= 2 * nsplit ? share : 1;
 }
 
@@ -4502,17 +4516,18 @@ sga_status run_tile_implicit_wide_d(const AttnArgs& a) {
   }
   float* parts = nullptr;
   const int nsplit = choose_window_split(a, n_wg * a.H, 2048 / kSlices, &parts);
-  if constexpr (DtypeOf<T>::code == SGA_F32) {
-    const int64_t met = (kTile - 1 + 2 * (int64_t)a.window) / kTile + 1;
-    const int share = window_share_wide<kSlices>(n_tiles * shape.n_slots * a.H, met < n_tiles ? met : n_tiles, nsplit);
+  const int64_t met = (kTile - 1 + 2 * (int64_t)a.window) / kTile + 1;
+  const int share = window_share_wide<T, kD>(n_tiles * shape.n_slots * a.H, met < n_tiles ? met : n_tiles, nsplit);
+  if constexpr (DtypeOf<T>::code == SGA_F32 || kD == 128) {
     if (share > 1) {
-      auto kernel = tile_window_wide_share_kernel<kD, 2>;
-      if constexpr (kSlices == 2)
-        if (share == 4) kernel = tile_window_wide_share_kernel<kD, 4>;
+      void (*kernel)(const T*, const T*, const T*, T*, float*, int64_t, int64_t, int64_t, int64_t, float, int, int64_t) = nullptr;
+      if constexpr (kD == 128) kernel = tile_window_wide_share_kernel<T, kD, 4>;
+      if constexpr (DtypeOf<T>::code == SGA_F32)
+        if (share == 2) kernel = tile_window_wide_share_kernel<T, kD, 2>;
       profile_mark_begin(a.stream, "tile_window_wide_share_kernel");
       hipLaunchKernelGGL(kernel, dim3((unsigned)n_wg, (unsigned)a.H), dim3(kD * share), 0, a.stream,
-                         static_cast<const float*>(a.Q), static_cast<const float*>(a.K), static_cast<const float*>(a.V),
-                         static_cast<float*>(a.O), a.lse, a.L, (int64_t)a.window, s, n_tiles, a.scale, acc, shape.seg_len);
+                         static_cast<const T*>(a.Q), static_cast<const T*>(a.K), static_cast<const T*>(a.V),
+                         static_cast<T*>(a.O), a.lse, a.L, (int64_t)a.window, s, n_tiles, a.scale, acc, shape.seg_len);
       profile_mark_end(a.stream);
       return hip_status(hipGetLastError());
     }

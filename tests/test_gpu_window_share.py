@@ -94,3 +94,35 @@ def test_groups_that_share_a_wide_tile(spec, H, d, kernel):
     O4 = sga.attention_forward_implicit(Q, K, V, spec, scale, workspace=ws)
     O5 = sga.attention_forward_implicit(Q, K, V, spec, scale, path=sga.PATH_GATHER)
     assert ((O4 - O5).abs() / (1 + O5.abs())).max().item() <= 2 * TOL["f32"]
+
+
+@pytest.mark.parametrize("spec,H,d,kernel", [
+    (MaskSpec(KIND_SLIDING, 8192, window=129), 1, 128, WIDE_SHARE),       # ten blocks, 256 tiles
+    (MaskSpec(KIND_SLIDING, 8192, window=128), 1, 128, WIDE),             # nine
+    (MaskSpec(KIND_SLIDING, 8193, window=129), 1, 128, WIDE),             # 257 tiles
+    (MaskSpec(KIND_SLIDING, 321, window=400), 3, 128, WIDE_SHARE),        # eleven blocks, all of them in every tile
+    (MaskSpec(KIND_SLIDING, 4001, window=600), 1, 128, WIDE_SHARE),
+    (MaskSpec(KIND_SLIDING, 4001, window=1000), 1, 128, WIDE),            # three ranges of keys
+    (MaskSpec(KIND_SLIDING, 8001, window=400), 1, 256, WIDE),
+    (MaskSpec(KIND_DILATED, 3001, window=170, stride=3), 1, 128, WIDE_SHARE),
+    (MaskSpec(KIND_DILATED_2D, 3000, block=1001, stride=3), 2, 128, WIDE_SHARE)])
+def test_groups_that_share_a_wide_tile_fp16(spec, H, d, kernel):
+    import torch
+    L = spec.L
+    scale = -0.125 if H == 2 else 0.125
+    print("case", spec, H, d, flush=True)
+    Q, K, V = torch_qkv(H, L, d, "f16", 0.5, L, "cuda:0")
+    ws = sga.alloc_workspace(L, H, d, "f16", -1)
+    assert sga.sga_profile_enable(1) == 0
+    O1, l1 = sga.attention_forward_implicit(Q, K, V, spec, scale, workspace=ws, want_lse=True)
+    torch.cuda.synchronize()
+    name = sga.sga_profile_last_kernel()
+    sga.sga_profile_enable(0)
+    assert name == kernel
+    O2, l2 = sga.attention_forward_implicit(Q, K, V, spec, scale, path=sga.PATH_GATHER, want_lse=True)
+    assert ((O1.float() - O2.float()).abs() / (1 + O2.float().abs())).max().item() <= 2 * TOL["f16"]
+    seen = torch.isfinite(l2)
+    assert torch.equal(torch.isfinite(l1), seen) and (l1 - l2)[seen].abs().max().item() <= 2 * LSE_TOL["f16"]
+    O3, l3 = O1.clone(), l1.clone()
+    sga.attention_accumulate_implicit(Q, K, V, spec, scale, O3, l3, workspace=ws)
+    assert ((O3.float() - O1.float()).abs() / (1 + O1.float().abs())).max().item() <= 2 * TOL["f16"]
