@@ -4462,7 +4462,8 @@ int choose_window_split(const AttnArgs& a, int64_t tile_heads, int64_t resident,
 
 // fp16 windows at d = 128: true where tile_window_band128_kernel, with so many workgroups of 128 queries that meet so many key
 // blocks, beats tile_window_wide_kernel, whose workgroups hold one 32-query tile.  That one runs 1,024 tiles at a time and cuts
-// fewer than 512 into ranges of their keys; the former takes 0.65 us a block and 7 us around them.  (us, wide / band128,
+// fewer than 512 into ranges of their keys; the former takes 0.65 us a block and 7 us around them.  Calls of at most 64
+// workgroups (256 tiles) may take window_share_wide's groups instead (W = 400 13.5).  (us, wide / band128,
 // one head unless stated.  Up to 128 workgroups: L = 8,000, W = 2,000 60 / 87, 500 33 / 31; L = 16,000, W = 200 18 / 20, 400 30 / 27,
 // 8,000 297 / 308.  Up to 256: L = 20,000, W = 300 26 / 24, 4,000 216 / 164; L = 30,000, W = 100 15.7 / 16.4, 200 22 / 20, 1,000
 // 78 / 51; three heads, L = 16,384, W = 2,000 294 / 133.  Beyond: L = 60,000, W = 64 24 / 19, 130 35 / 24; L = 40,000,
