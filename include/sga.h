@@ -294,7 +294,8 @@ enum {
   SGA_GRAPH_TILE_PARTS_FIT = 2,    /* the partial states of the multi-segment tiles fit       */
   SGA_GRAPH_ROW_CHUNKS_FIT = 4,    /* the chunk items of the split rows fit                   */
   SGA_GRAPH_ROWS_SHARE_KEYS = 8,   /* ... and are computed by the kernel that shares key blocks */
-  SGA_GRAPH_ROWS_EVEN = 16         /* no tile qualified, no row is split, and none has more than 64
+  SGA_GRAPH_ROWS_EVEN = 16         /* no tile qualified, no row is split, the rows' lengths vary no more than
+                                      evenly spread ones do, and none has more than 64
                                       neighbours beyond twice the average, which is at most 256 */
 };
 

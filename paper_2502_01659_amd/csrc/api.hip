@@ -2,6 +2,7 @@
 #include "sga_internal.h"
 
 #include <atomic>
+#include <cstring>
 #include <vector>
 
 using namespace sga;
@@ -361,7 +362,7 @@ sga_status sga_graph_prepare(const int64_t* row_ptr, const int32_t* col_idx, int
   clear_workspace(a, true);
   launch_tile_analyze(a);
   if (L > kSplitThreshold && tile_parts_in_doubt(pl)) launch_split_prepass(a, true);
-  launch_longest_row(a);
+  launch_row_lengths(a);
   uint32_t ctr[kNumCounters];
   if (hipGetLastError() != hipSuccess ||
       hipMemcpyAsync(ctr, workspace, sizeof(ctr), hipMemcpyDeviceToHost, st) != hipSuccess ||
@@ -383,7 +384,10 @@ sga_status sga_graph_prepare(const int64_t* row_ptr, const int32_t* col_idx, int
   if (chunks_fit && shared_chunks_possible(L, H, d, dtype, workspace_bytes) &&
       shared_chunks(pl, nnz, L, H, d, dtype, ctr))
     p.flags |= SGA_GRAPH_ROWS_SHARE_KEYS;
-  if ((int64_t)p.tiles_left == pl.n_tiles && p.long_rows == 0 && rows_of_one_length(nnz, L, ctr[kCtrLongestRow]))
+  uint64_t squares;
+  std::memcpy(&squares, ctr + kCtrLengthSquares, sizeof(squares));
+  if ((int64_t)p.tiles_left == pl.n_tiles && p.long_rows == 0 &&
+      rows_of_one_length(nnz, L, ctr[kCtrLongestRow], squares))
     p.flags |= SGA_GRAPH_ROWS_EVEN;
   p.row_ptr = row_ptr; p.col_idx = col_idx;
   p.workspace = workspace; p.workspace_bytes = workspace_bytes;

@@ -449,7 +449,9 @@ __global__ __launch_bounds__(256) void gather_csr_kernel(
 // are several times an L2: 35,000 rows of 35 neighbours, fp32, d = 64 77 -> 73 us; by the L2s below that: random 1 %,
 // L = 24,576, fp32, d = 64 247 -> 177 us, d = 128 613 -> 571; fp16, d = 128 250 -> 178; L = 8,000, four heads, fp32, d = 64
 // 92 -> 65.  Registers for four wavefronts per SIMD; with more, the G states spill (six: 277 us,
-// eight: 422 of the 177).
+// eight: 422 of the 177).  Which of eight neighbouring workgroups takes which rows turns from eight to eight: else lengths
+// that alternate every 64 rows (fp32, d = 64) leave the long rows to four of the XCDs (11 and 58 neighbours, L = 50,000
+// 140 -> 112 us, a wavefront per row 111).
 template <typename T, int D>
 __global__ __attribute__((amdgpu_waves_per_eu(4))) __launch_bounds__(256) void gather_even_rows_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
@@ -459,7 +461,9 @@ __global__ __attribute__((amdgpu_waves_per_eu(4))) __launch_bounds__(256) void g
   constexpr int kStep = G * kUnroll;
   static_assert(LPK % kStep == 0, "a group's columns are a whole number of steps");
   const int lane = threadIdx.x & (kWave - 1), cl = lane % LPK;
-  const int64_t i = ((int64_t)blockIdx.x * 4 + threadIdx.x / kWave) * G + lane / LPK;
+  const unsigned eight = blockIdx.x & ~7u;
+  const unsigned wg = eight + 8 <= gridDim.x ? eight + ((blockIdx.x + (blockIdx.x >> 3)) & 7) : blockIdx.x;
+  const int64_t i = ((int64_t)wg * 4 + threadIdx.x / kWave) * G + lane / LPK;
   if (i >= L) return;
   const int64_t h = blockIdx.y, hoff = h * L * D;
   const int64_t r0 = row_ptr[i];
@@ -1282,23 +1286,32 @@ void launch_split_prepass(const AttnArgs& a, bool after_tiles) {
 }
 
 namespace {
-// The length of the longest row, into a counter (graph preparation only).
-__global__ __launch_bounds__(256) void longest_row_kernel(const int64_t* __restrict__ row_ptr, int64_t L, uint32_t* ctr) {
+// The length of the longest row and the sum of the squared lengths, into counters (graph preparation only).
+__global__ __launch_bounds__(256) void row_lengths_kernel(const int64_t* __restrict__ row_ptr, int64_t L, uint32_t* ctr) {
   int64_t most = 0;
+  unsigned long long squares = 0;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < L; i += (int64_t)gridDim.x * 256) {
     const int64_t deg = row_ptr[i + 1] - row_ptr[i];
     most = deg > most ? deg : most;
+    const unsigned long long n = deg < 65535 ? deg : 65535;      // (the sum stays below 2^63; such rows are not even ones)
+    squares += n * n;
   }
   int longest = (int)most;                 // (a row has at most L < 2^31 neighbours)
 #pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) longest = max(longest, __shfl_xor(longest, off, kWave));
-  if ((threadIdx.x & (kWave - 1)) == 0) atomicMax(&ctr[kCtrLongestRow], (uint32_t)longest);
+  for (int off = 1; off < kWave; off <<= 1) {
+    longest = max(longest, __shfl_xor(longest, off, kWave));
+    squares += __shfl_xor(squares, off, kWave);
+  }
+  if ((threadIdx.x & (kWave - 1)) == 0) {
+    atomicMax(&ctr[kCtrLongestRow], (uint32_t)longest);
+    atomicAdd(reinterpret_cast<unsigned long long*>(&ctr[kCtrLengthSquares]), squares);
+  }
 }
 }  // namespace
 
-void launch_longest_row(const AttnArgs& a) {
+void launch_row_lengths(const AttnArgs& a) {
   const int64_t wgs = (a.L + 255) / 256;
-  hipLaunchKernelGGL(longest_row_kernel, dim3((unsigned)(wgs < 512 ? wgs : 512)), dim3(256), 0, a.stream, a.row_ptr, a.L,
+  hipLaunchKernelGGL(row_lengths_kernel, dim3((unsigned)(wgs < 512 ? wgs : 512)), dim3(256), 0, a.stream, a.row_ptr, a.L,
                      static_cast<uint32_t*>(a.ws));
 }
 

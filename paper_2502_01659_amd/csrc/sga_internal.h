@@ -134,6 +134,7 @@ enum WsCounter : int {
   kCtrMultiTiles = 6,       // multi-segment tiles recorded in the merge list
   kCtrMultiItems = 11,      // groups of up to four segment items (see TileItem::group)
   kCtrLongestRow = 12,      // neighbours of the longest row (written when a graph is prepared)
+  kCtrLengthSquares = 14,   // sum of the squares of the rows' lengths, 64 bits (likewise)
   // (the second cache line: atomics on one line wait for each other)
   kCtrLongRows = 32,        // number of long rows recorded
   kCtrMaxChunks = 34,       // most chunks any split row has (bounds the chunk kernel's unit loop), ...
@@ -314,10 +315,18 @@ __host__ __device__ inline int64_t leftover_workgroups(int64_t rows_left, int32_
 // Calls on a prepared graph of even rows (no tile, none split, none longer than twice the average and 64 neighbours, at most
 // 256 on average) that gather_even_rows_kernel takes: K and V of a head beyond one L2 and rows for four wavefronts per SIMD
 // (fp32, d = 64).  Longer rows gain nothing (3 %, L = 16,000: fp32, d = 64 183 / 182, fp16, d = 128 194.6 / 198.4).
-// (us, a wavefront per row / that: random 1 %, fp32, d = 64, L = 8,000 21 / 26, four heads 92 / 65; d = 128, L = 17,000, 0.6 %
-// 179 / 166; fp16, d = 128, L = 50,000, 0.1 % 154 / 156.)
-inline bool rows_of_one_length(int64_t nnz, int64_t L, int64_t longest) {
-  return nnz / L <= 256 && longest <= 2 * (nnz / L) + 64;
+// The lengths vary no more than evenly spread ones do (a variance of a third of the squared average; random neighbours add
+// the average), since a wavefront stays until the longest of its rows ends and a small call until its longest row does:
+// rows of 0.05 and of 1.95 times the average, 64 of each in turn, average 128, L = 16,500, fp32, d = 64 68 / 87,
+// d = 128 139 / 200, average 245 208 / 353.
+// (us, a wavefront per row / that.  Equal lengths, average 35, fp32, d = 64, L = 8,192, two heads 25.8 / 19.5, L = 24,576
+// 48.7 / 43.7, L = 100,000 236 / 234; random neighbours, average 70, L = 24,576, fp32, d = 64 88 / 77, d = 128 206 / 195, fp16,
+// d = 128 88 / 77, d = 256 206 / 195; L = 100,000, in that order 462 / 456, 974 / 943, 462 / 458, 963 / 946.  Lengths between 0.4 and
+// 1.6 times the average, fp32, d = 64: average 70, L = 35,000 143 / 136; average 245, L = 8,192, two heads, where the longest
+// rows decide 98 / 110.)
+inline bool rows_of_one_length(int64_t nnz, int64_t L, int64_t longest, uint64_t squares) {
+  const double mean = (double)nnz / (double)L;
+  return nnz / L <= 256 && longest <= 2 * (nnz / L) + 64 && (double)squares / (double)L <= mean * mean * 4.0 / 3.0 + mean;
 }
 inline bool even_rows(int64_t L, int32_t H, int32_t d, int32_t dtype) {
   const int64_t bytes = L * d * (dtype == SGA_F32 ? 4 : 2);
@@ -592,7 +601,7 @@ void clear_workspace(const AttnArgs& a, bool tile_flags);
 // skip_tiled: rows whose 32-row tile was produced by the tile path (tile_bad == 0 in the
 // workspace) are skipped, and a small grid strides over the rows; without a prepared graph the same
 // launch merges the tiles' segments.
-void launch_longest_row(const AttnArgs& a);
+void launch_row_lengths(const AttnArgs& a);
 sga_status launch_gather_explicit(const AttnArgs& a, bool allow_split, bool skip_tiled);
 sga_status launch_gather_implicit(const AttnArgs& a);
 

@@ -70,3 +70,24 @@ def test_rows_of_uneven_length_keep_a_wavefront_each():
     O = sga.attention_forward_prepared(Q, K, V, rp, ci, 0.125, plan, ws)
     want, _ = C.attend_gathered(Q[0, at].cpu().numpy(), K[0].cpu().numpy()[long], V[0].cpu().numpy()[long], 0.125)
     assert np.abs(O[0, at].cpu().numpy() - want).max() <= 1e-5
+
+
+@pytest.mark.parametrize("lo,hi,run,even", [
+    (5, 195, 64, False), (5, 195, 1, False), (60, 140, 64, True), (100, 100, 1, True), (36, 164, 1024, False)])
+def test_rows_of_two_lengths(lo, hi, run, even):
+    """`run` rows of one length, then as many of the other.  None is longer than twice the average and 64, but a variance
+    above a third of the squared average (100) plus the average is a mix that a row per lane group slows down."""
+    import torch
+    L, H, d = 16450, 1, 64
+    rng = np.random.default_rng(lo + run)
+    deg = np.where((np.arange(L) // run) % 2 == 1, hi, lo)
+    cols = [np.sort(rng.choice(L, size=n, replace=False)).astype(np.int32) for n in deg]
+    rp = np.zeros(L + 1, dtype=np.int64)
+    rp[1:] = np.cumsum(deg)
+    rp, ci = torch.from_numpy(rp).cuda(), torch.from_numpy(np.concatenate(cols)).cuda()
+    Q, K, V = torch_qkv(H, L, d, "f32", 0.7, 5, "cuda:0")
+    ws = sga.alloc_workspace(L, H, d, "f32", ci.numel())
+    O1 = sga.attention_forward(Q, K, V, rp, ci, 0.125, workspace=ws)
+    plan = sga.graph_prepare(rp, ci, H, d, "f32", ws)
+    assert bool(plan.flags & sga.GRAPH_ROWS_EVEN) == even
+    assert torch.equal(O1, sga.attention_forward_prepared(Q, K, V, rp, ci, 0.125, plan, ws))
