@@ -1692,8 +1692,17 @@ __global__ __attribute__((amdgpu_waves_per_eu(4, 4))) __launch_bounds__(256) voi
     // column is kept), so a row of a few runs turns arithmetic once its last run is reached
     int run_lo = 0, run_hi = -1;
     bool arith = false;
+    const int64_t pos_first = pos;
     const int c_first = pos < end ? col_idx[pos] : -1;
     const int c_last = pos < end ? col_idx[end - 1] : -1;
+    const int deg = (int)(end - pos < kScoutColumns + 1 ? end - pos : kScoutColumns + 1);
+    const int deg0 = __builtin_amdgcn_readfirstlane(deg);
+    const bool one_length = row_first + kTile <= L && deg0 > 1 && deg0 <= kScoutColumns && __all(lane >= kTile || deg == deg0);
+    int c_second = 0, c_before_last = 0;                  // (requested with the former two)
+    if (one_length && lane < kTile) {
+      c_second = col_idx[pos + 1];
+      c_before_last = col_idx[end - 2];
+    }
     int nblk = 0;
     bool overflow = false;
     int consumed = 0;                   // edges of this lane's row in the blocks written so far
@@ -1745,11 +1754,11 @@ __global__ __attribute__((amdgpu_waves_per_eu(4, 4))) __launch_bounds__(256) voi
     // four wavefronts per SIMD: five and six spill and gain nothing, and a list written with scalar code where all rows are
     // equal, at 40 % fewer vector instructions, takes as long.  Looking ahead along each row by itself, at the ends of the
     // 2nd, 4th, 6th and 8th key block, 460: it brings in lines that are gone again before the walk reaches them.)
+    // Scattered columns do not come here though the rows be of one length (it would cost their calls 1.2 us of 22 to 50): the
+    // first or the last two columns of every row have to be neighbours.
     int n_runs = 0;
-    if (!__all(pos >= end || c_last - c_first == end - 1 - pos)) {
-      const int deg = (int)(end - pos < kScoutColumns + 1 ? end - pos : kScoutColumns + 1);
-      const int deg0 = __builtin_amdgcn_readfirstlane(deg);
-      if (row_first + kTile <= L && deg0 <= kScoutColumns && __all(lane >= kTile || deg == deg0)) {
+    if (one_length && !__all(lane >= kTile || c_last - c_first == deg - 1)) {
+      if (__all(lane >= kTile || c_second - c_first == 1 || c_last - c_before_last == 1)) {
         const int64_t at0 = uniform64(pos);
         int cc[kScoutColumns / kWave];
 #pragma unroll
@@ -1839,7 +1848,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(4, 4))) __launch_bounds__(256) voi
     while (n_runs == 0) {
       int cur = INT32_MAX;
       if (!arith && pos < end) {
-        const int c0 = col_idx[pos];
+        const int c0 = pos == pos_first ? c_first : col_idx[pos];
         if ((int64_t)c_last - c0 == end - 1 - pos) {
           arith = true;
           run_lo = c0;

@@ -54,6 +54,10 @@ def _masks():
         row[inside] = False
         row[np.flatnonzero(~row & (np.arange(L) > inside + 64))[0]] = True
     out["a hole in a run"] = split
+    out["scattered, as many in every row"] = _rows([1] * 20, 9, 0, 15)
+    out["single columns at both ends"] = _rows([1, 64, 90, 1], 10, 0, 16)      # (read run by run)
+    out["a single column first"] = _rows([1, 64, 90], 10, 0, 17)
+    out["a single column last"] = _rows([64, 90, 1], 10, 1, 18)
     empty = _rows([64, 32], 10, 0, 14)
     empty[::17] = False
     out["empty rows"] = empty
