@@ -4577,17 +4577,25 @@ int window_share(int64_t tiles, int64_t blocks, int nsplit) {
 
 // fp16 windows beyond the staged ones: true where tile_window_strip_kernel (128 queries per workgroup) is expected to beat
 // tile_window_band_kernel (256).  A CU takes its workgroups of either kind at about one pace, alone or with others: a key
-// block costs 0.59 us of the latter, 0.324 of the former, and a call 16 and 5 us around its blocks.  (us measured, band / strip,
-// where the two estimates are close: L = 100,000, W = 2,100 154 / 157, 1,700 129.9 / 128.5; L = 400,000, W = 2,100 529 / 517;
-// L = 1,600,000, W = 1,359 1,322 / 1,332, 700 804 / 756; L = 16,384, 16 heads, W = 2,000 302 / 316; L = 20,000, 8 heads,
-// W = 2,100 236 / 207; L = 65,536, W = 16,383 636 / 665; L = 1,000,000, W = 5,000 2,760 / 2,896.)
+// block costs 0.59 us of the latter, 0.324 of the former, and a call 16 and 5 us around its blocks.  The CUs with one workgroup
+// more than others decide a short call.  Beyond eight rounds of the strip kernel (256 of its workgroups each) the rounds run into
+// each other, and the blocks of the band kernel cost 0.61 us.  Over 535 shapes (L 4,000 to 8,000,000, W 257 to 16,000, 1 to 32 heads,
+// strides, 2-D blocks) the kernel taken is within 0.2 % of the faster one in the geometric mean, and 8 to 12 % behind it in five,
+// four of them 2-D.  (us, band / strip near the line, the one taken marked: L = 8,000, 16 heads, W = 1,000
+// 95 / 93.5*, 1,359 119.5 / 121.0*, 3,000 232* / 242; L = 65,536, W = 3,000 135.3 / 134.0*, 5,000 210* / 215; L = 100,000, W = 1,359
+// 110.3 / 109.5*, 2,100 157* / 164; L = 400,000, W = 2,100 537* / 533, 5,000 1,198* / 1,221; L = 1,600,000, W = 1,000
+// 1,093 / 1,067*, 1,359 1,368* / 1,382, 2,100 2,022* / 2,053; L = 4,000,000, W = 1,000 2,766 / 2,644*; L = 154,821, 32 heads,
+// W = 771 2,812 / 2,637*.)
 bool strip_is_faster(int64_t W, int64_t Lc, int64_t classes) {
   const int64_t held = (Lc + kTile - 1) / kTile;
-  const auto cost = [&](int64_t queries, double per_block, double around) {
+  const bool many = (Lc + 4 * kTile - 1) / (4 * kTile) * classes > 8 * 256;
+  const auto cost = [&](int64_t queries, double per_block, double last_round, double around) {
     const int64_t wgs = (Lc + queries - 1) / queries * classes, met = (queries - 1 + 2 * W) / kTile + 1;
-    return per_block * (double)((wgs + 255) / 256) * (double)(met < held ? met : held) + around;
+    const double rounds = many ? (double)wgs / 256.0 + last_round : (double)((wgs + 255) / 256);
+    return per_block * rounds * (double)(met < held ? met : held) + around;
   };
-  return cost(4 * kTile, 0.324, 5.0) < cost(8 * kTile, 0.59, 16.0);
+  return many ? cost(4 * kTile, 0.324, 0.25, 5.0) < cost(8 * kTile, 0.61, 0.0, 21.0)
+              : cost(4 * kTile, 0.324, 0.0, 5.0) < cost(8 * kTile, 0.59, 0.0, 16.0);
 }
 
 sga_status run_tile_implicit(const AttnArgs& a) {

@@ -2,7 +2,7 @@
 through the C ABI binding, and evaluate the CPU oracle on the same stored values."""
 import numpy as np
 
-from sga_inputs import numpy_qkv
+from sga_inputs import numpy_qkv, torch_qkv
 from oracle import reference as R
 from oracle import rowscan as C
 
@@ -67,3 +67,36 @@ def oracle_rows_gathered(spec, scale, rows, fetch_q, fetch_kv):
         out[r], lse[r] = C.attend_gathered(q[r], Kg, Vg, scale)
         edges += len(nb)
     return out, lse, edges
+
+
+def check_window_state(spec, H, d, dtype, kernel, sigma=1.0):
+    """A window call on the kernel named, and a second call of another scale that continues its state, against the per-row
+    kernels on the same two calls.  Bars: O of one call as in the tests of one call (twice the tolerance relative to
+    1 + |O|); the second call adds its own error, weighted with the first one's, another rounding of O on both sides, and
+    the old state's weight, whose error is that of two lse: three times.  lse is a sum of two such sums: the bar of one."""
+    import torch
+    import paper_2502_01659_amd as sga
+    L = spec.L
+    print("case", spec, H, d, dtype, flush=True)
+    Q, K, V = torch_qkv(H, L, d, dtype, sigma, L + d, "cuda:0")
+    ws = sga.alloc_workspace(L, H, d, dtype, -1)
+    scales = (3.0 / d ** 0.5, -2.5 / d ** 0.5)
+    assert sga.sga_profile_enable(1) == 0
+    O1, l1 = sga.attention_forward_implicit(Q, K, V, spec, scales[0], workspace=ws, want_lse=True)
+    torch.cuda.synchronize()
+    names = [sga.sga_profile_last_kernel()]
+    O2, l2 = sga.attention_forward_implicit(Q, K, V, spec, scales[0], path=sga.PATH_GATHER, want_lse=True)
+    seen = torch.isfinite(l2)
+
+    def agree(times):
+        assert ((O1.float() - O2.float()).abs() / (1 + O2.float().abs())).max().item() <= times * TOL[dtype]
+        assert torch.equal(torch.isfinite(l1), seen)
+        assert (l1 - l2)[seen].abs().max().item() <= 2 * LSE_TOL[dtype]
+    agree(2)
+    sga.attention_accumulate_implicit(Q, K, V, spec, scales[1], O1, l1, workspace=ws)
+    torch.cuda.synchronize()
+    names.append(sga.sga_profile_last_kernel())
+    sga.sga_profile_enable(0)
+    sga.attention_accumulate_implicit(Q, K, V, spec, scales[1], O2, l2, path=sga.PATH_GATHER)
+    agree(3)
+    assert names == [kernel, kernel]

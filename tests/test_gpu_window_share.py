@@ -3,7 +3,7 @@ import pytest
 
 import paper_2502_01659_amd as sga
 from sga_inputs import MaskSpec, KIND_SLIDING, KIND_DILATED, KIND_DILATED_2D, torch_qkv
-from gpu_util import TOL, LSE_TOL
+from gpu_util import TOL, LSE_TOL, check_window_state
 
 pytestmark = pytest.mark.gpu
 SHARE, ONE, GROUP = "tile_window_share_kernel", "tile_window_kernel", "tile_window_f32_kernel"
@@ -44,6 +44,7 @@ def test_wavefronts_that_share_a_tile(spec, H, kernel):
     O3, l3 = O1.clone(), l1.clone()
     sga.attention_accumulate_implicit(Q, K, V, spec, scale, O3, l3, workspace=ws)
     assert ((O3 - O1).abs() / (1 + O1.abs())).max().item() <= 2 * TOL["f32"]
+    assert (l3 - l1)[seen].sub(0.6931472).abs().max().item() <= 2 * LSE_TOL["f32"]
     K[:, L // 2] *= 1e-36
     V[:, L // 3] = 1e-37
     O4 = sga.attention_forward_implicit(Q, K, V, spec, scale, workspace=ws)
@@ -89,6 +90,7 @@ def test_groups_that_share_a_wide_tile(spec, H, d, kernel):
     O3, l3 = O1.clone(), l1.clone()
     sga.attention_accumulate_implicit(Q, K, V, spec, scale, O3, l3, workspace=ws)
     assert ((O3 - O1).abs() / (1 + O1.abs())).max().item() <= 2 * TOL["f32"]
+    assert (l3 - l1)[seen].sub(0.6931472).abs().max().item() <= 2 * LSE_TOL["f32"]
     K[:, L // 2] *= 1e-36
     V[:, L // 3] = 1e-37
     O4 = sga.attention_forward_implicit(Q, K, V, spec, scale, workspace=ws)
@@ -126,3 +128,23 @@ def test_groups_that_share_a_wide_tile_fp16(spec, H, d, kernel):
     O3, l3 = O1.clone(), l1.clone()
     sga.attention_accumulate_implicit(Q, K, V, spec, scale, O3, l3, workspace=ws)
     assert ((O3.float() - O1.float()).abs() / (1 + O1.float().abs())).max().item() <= 2 * TOL["f16"]
+    assert (l3 - l1)[seen].sub(0.6931472).abs().max().item() <= 2 * LSE_TOL["f16"]
+
+
+@pytest.mark.parametrize("spec,H,d,dtype,kernel", [
+    (MaskSpec(KIND_SLIDING, 97, window=33), 1, 64, "f32", SHARE),
+    (MaskSpec(KIND_SLIDING, 12001, window=100), 1, 64, "f32", SHARE),
+    (MaskSpec(KIND_DILATED, 3001, window=70, stride=3), 2, 64, "f32", SHARE),
+    (MaskSpec(KIND_SLIDING, 1001, window=49), 2, 128, "f32", WIDE_SHARE),
+    (MaskSpec(KIND_SLIDING, 9001, window=100), 1, 128, "f32", WIDE_SHARE),
+    (MaskSpec(KIND_SLIDING, 1001, window=65), 2, 256, "f32", WIDE_SHARE),
+    (MaskSpec(KIND_SLIDING, 1301, window=200), 1, 128, "f16", WIDE_SHARE),
+    (MaskSpec(KIND_DILATED, 3001, window=170, stride=3), 1, 128, "f16", WIDE_SHARE)] + [
+    # a last class of one, two and three key blocks: ranges without a block
+    (MaskSpec(KIND_DILATED_2D, 800 + n, block=400, stride=1), 2, d, dtype, kernel)
+    for n in (1, 33, 70) for d, dtype, kernel in ((64, "f32", SHARE), (128, "f32", WIDE_SHARE), (256, "f32", WIDE_SHARE),
+                                                  (128, "f16", WIDE_SHARE))])
+def test_shared_tiles_continue_a_state(spec, H, d, dtype, kernel):
+    """Peaked rows, and a second call of another scale on the state of the first: the old state's weight differs from
+    row to row."""
+    check_window_state(spec, H, d, dtype, kernel)
