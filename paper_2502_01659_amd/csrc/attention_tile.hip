@@ -2411,37 +2411,47 @@ __device__ __forceinline__ void leave_state(const TileState& st, char* lds, int 
   }
 }
 
-// Adds the states left at lds + kStep, lds + 2 kStep, ... to st (one common maximum, so that each is scaled once).
-template <int kShare, int kStep>
+// Adds the states left at lds + kStep, lds + 2 kStep, ... to st (one common maximum, so that each is scaled once).  Sum: double
+// for fp32 tiles of four blocks, whose ranges are so short that the additions and weights of the merge, rounded to 32 bits, would
+// show.  (Error against 64 bits, means of 24 inputs, W = 33: d = 64 one range 1.297e-7, two in 32 bits 1.310e-7, in
+// 64 1.289e-7; d = 128 one range 1.316e-7, four 1.318e-7, 1.276e-7; from five blocks on 32 bits are enough, W = 52 1.361e-7, 1.357e-7.
+// 64 bits cost 0.23 us of 9.3 for two states, 0.5 of 11 for four.)
+template <int kShare, int kStep, typename Sum>
 __device__ __forceinline__ void add_states(TileState& st, const char* lds, int lane) {
   const float* other = reinterpret_cast<const float*>(lds) + lane;
   constexpr int step = kStep / 4;
-  float m = st.m, weight[kShare];
+  float m = st.m;
+  Sum weight[kShare];
 #pragma unroll
   for (int w = 1; w < kShare; ++w) m = __builtin_fmaxf(m, other[w * step]);
-  weight[0] = __builtin_amdgcn_exp2f(st.m - m);
-  st.m = m;
-  st.l *= weight[0];
+  auto weigh = [&](float of) -> Sum {
+    if constexpr (sizeof(Sum) == 8) return exp2((Sum)of - (Sum)m);
+    else return __builtin_amdgcn_exp2f(of - m);
+  };
+  weight[0] = weigh(st.m);
 #pragma unroll
-  for (int w = 1; w < kShare; ++w) {
-    weight[w] = __builtin_amdgcn_exp2f(other[w * step] - m);
-    st.l = __builtin_fmaf(other[w * step + kWave], weight[w], st.l);
-  }
+  for (int w = 1; w < kShare; ++w) weight[w] = weigh(other[w * step]);
+  st.m = m;
+  auto sum = [&](float& own, int at) {
+    Sum x = own * weight[0];
+#pragma unroll
+    for (int w = 1; w < kShare; ++w) x = __builtin_elementwise_fma((Sum)other[w * step + at], weight[w], x);
+    own = (float)x;
+  };
+  sum(st.l, kWave);
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
-    st.o[0][r] *= weight[0];
-    st.o[1][r] *= weight[0];
-#pragma unroll
-    for (int w = 1; w < kShare; ++w) {
-      st.o[0][r] = __builtin_fmaf(other[w * step + (2 + r) * kWave], weight[w], st.o[0][r]);
-      st.o[1][r] = __builtin_fmaf(other[w * step + (18 + r) * kWave], weight[w], st.o[1][r]);
-    }
+    float own[2] = {st.o[0][r], st.o[1][r]};
+    sum(own[0], (2 + r) * kWave);
+    sum(own[1], (18 + r) * kWave);
+    st.o[0][r] = own[0];
+    st.o[1][r] = own[1];
   }
 }
 
 // fp32 windows of calls that leave most SIMDs without a second wavefront: kShare wavefronts (2 or 4) take a tile, each a
 // range of its key blocks, and the first one merges their states through LDS, in wavefront order (see window_share).
-template <int kShare>
+template <int kShare, typename Sum>
 __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) void tile_window_share_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, float* __restrict__ O,
     float* __restrict__ lse, int64_t L, int64_t W, int64_t s, int64_t n_groups, float scale, int accumulate,
@@ -2480,7 +2490,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) voi
   if (part > 0) leave_state(st, lds, lane);
   __syncthreads();
   if (part > 0 || !active) return;
-  add_states<kShare, kLds>(st, lds, lane);
+  add_states<kShare, kLds, Sum>(st, lds, lane);
   finish_tile<float>(O + hoff, lse ? lse + hd * L : nullptr, qrow, qrow, exists, st, h, accumulate != 0);
 }
 
@@ -3178,7 +3188,7 @@ __global__ __launch_bounds__(kD) void tile_window_wide_kernel(
 
 // Windows at d = 128 and 256 of calls with few tiles: kShare groups of kD / 64 wavefronts per tile, each for a range
 // of its key blocks; the first group merges their states through LDS (see window_share_wide).
-template <typename T, int kD, int kShare>
+template <typename T, int kD, int kShare, typename Sum>
 __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kD * kShare) void tile_window_wide_share_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
     float* __restrict__ lse, int64_t L, int64_t W, int64_t s, int64_t n_tiles, float scale, int accumulate,
@@ -3222,7 +3232,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kD * kSh
     if (accumulate) __syncthreads();     // (the one of finish_tile_wide)
     return;
   }
-  add_states<kShare, kSlices * kLds>(st, lds, lane);
+  add_states<kShare, kSlices * kLds, Sum>(st, lds, lane);
   finish_tile_wide<T, kD>(O + hoff, lse ? lse + hd * L : nullptr, qrow, exists, st, h, slice, accumulate != 0);
 }
 
@@ -4527,13 +4537,16 @@ sga_status run_tile_implicit_wide_d(const AttnArgs& a) {
   float* parts = nullptr;
   const int nsplit = choose_window_split(a, n_wg * a.H, 2048 / kSlices, &parts);
   const int64_t met = (kTile - 1 + 2 * (int64_t)a.window) / kTile + 1;
-  const int share = window_share_wide<T, kD>(n_tiles * shape.n_slots * a.H, met < n_tiles ? met : n_tiles, nsplit);
+  const int64_t blocks = met < n_tiles ? met : n_tiles;
+  const int share = window_share_wide<T, kD>(n_tiles * shape.n_slots * a.H, blocks, nsplit);
   if constexpr (DtypeOf<T>::code == SGA_F32 || kD == 128) {
     if (share > 1) {
       void (*kernel)(const T*, const T*, const T*, T*, float*, int64_t, int64_t, int64_t, int64_t, float, int, int64_t) = nullptr;
-      if constexpr (kD == 128) kernel = tile_window_wide_share_kernel<T, kD, 4>;
+      if constexpr (kD == 128) kernel = tile_window_wide_share_kernel<T, kD, 4, float>;
+      if constexpr (kD == 128 && DtypeOf<T>::code == SGA_F32)
+        if (blocks == 4) kernel = tile_window_wide_share_kernel<T, kD, 4, double>;            // (see add_states)
       if constexpr (DtypeOf<T>::code == SGA_F32)
-        if (share == 2) kernel = tile_window_wide_share_kernel<T, kD, 2>;
+        if (share == 2) kernel = tile_window_wide_share_kernel<T, kD, 2, float>;
       profile_mark_begin(a.stream, "tile_window_wide_share_kernel");
       hipLaunchKernelGGL(kernel, dim3((unsigned)n_wg, (unsigned)a.H), dim3(kD * share), 0, a.stream,
                          static_cast<const T*>(a.Q), static_cast<const T*>(a.K), static_cast<const T*>(a.V),
@@ -4669,14 +4682,16 @@ sga_status run_tile_implicit(const AttnArgs& a) {
     const int64_t steps = n_groups * shape.n_slots * a.H * (nb_max < class_blocks ? nb_max : class_blocks);
     const bool shared = !a.split && steps >= kSharedSteps;
     const int64_t tiles = (Lc + kTile - 1) / kTile, mine = (kTile - 1 + 2 * (int64_t)a.window) / kTile + 1;
-    const int share = a.split || shared ? 1
-                      : window_share(tiles * shape.n_slots * a.H, mine < class_blocks ? mine : class_blocks, nsplit);
+    const int64_t blocks = mine < class_blocks ? mine : class_blocks;
+    const int share = a.split || shared ? 1 : window_share(tiles * shape.n_slots * a.H, blocks, nsplit);
     if (share > 1) {
       const int64_t ng = (tiles * share + 3) / 4;
       const dim3 share_grid((unsigned)((ng * shape.n_slots + 7) / 8 * 8), (unsigned)a.H);
       profile_mark_begin(a.stream, "tile_window_share_kernel");
-      hipLaunchKernelGGL(share == 4 ? tile_window_share_kernel<4> : tile_window_share_kernel<2>, share_grid, dim3(256), 0,
-                         a.stream, static_cast<const float*>(a.Q), static_cast<const float*>(a.K),
+      auto share_kernel = share == 4    ? tile_window_share_kernel<4, float>
+                          : blocks == 4 ? tile_window_share_kernel<2, double>            // (see add_states)
+                                        : tile_window_share_kernel<2, float>;
+      hipLaunchKernelGGL(share_kernel, share_grid, dim3(256), 0, a.stream, static_cast<const float*>(a.Q), static_cast<const float*>(a.K),
                          static_cast<const float*>(a.V), static_cast<float*>(a.O), a.lse, a.L, (int64_t)a.window, s, ng,
                          a.scale, acc, shape.seg_len);
       profile_mark_end(a.stream);
