@@ -4575,16 +4575,21 @@ sga_status run_tile_implicit_wide(const AttnArgs& a) {
 }
 
 // Wavefronts per tile of an fp32 window call that tile_window_f32_kernel leaves, in tile_window_share_kernel (1: none,
-// tile_window_kernel): shorter chains of blocks (2 us each for a wavefront alone) as long as the chip holds all
-// wavefronts at once, two per SIMD.  Tiles of fewer than four blocks gain nothing.  Ranges of keys that workgroups
-// take (nsplit) stay where they leave no less than half a chain: their sums of several states are as exact, if slower.
-// (us, 1 / 2 / 4, one head: L = 8,000, W = 50 16.6 / 12.4 / 12.1, 200 35.6 / 19.2 / 13.3, 400 61 / 31 / 19.4; L = 16,000,
-// W = 100 23.2 / 13.5 / 14.8, 400 61 / 31 / 31; L = 35,000, W = 50 25.6 / 24.6 / 27.7, 200 56 / 46 / 43; L = 50,000, W = 50
-// 26.4 / 30.0 / 36.4, 200 57.2 / 58.5 / 58.4; four heads, L = 16,000, W = 50 29.3 / 31.0 / 41.1.  12 is what the host takes for
-// a call.  Two ranges and their merge / 4: L = 8,000, W = 600 53.5 / 25.3, error against 64 bits 1.70e-7 / 1.62e-7; three
+// tile_window_kernel): shorter chains of blocks.  A wavefront takes 2.1 us a block alone on its SIMD, two take 3.5 for one
+// each.  Four per tile: up to 320 tiles, where a quarter of the SIMDs have two of them (up to 256 none).  Two per tile: up to
+// 1,536 tiles, where three wavefronts of half the blocks follow each other on a SIMD (3.5 + 2.1 times half of them)
+// instead of two of all of them (3.5 times all); beyond, four do, and lose.  Tiles of four and five blocks, which gain 2 to
+// 6 % there, keep to 1,152; those of fewer gain nothing.  Ranges of keys that workgroups take (nsplit) stay where they
+// leave no less than half a chain: their sums of several states are as exact, if slower.
+// (us of the kernel, 1 / 2 / 4.  250 tiles, 4 blocks 14.0 / 9.2 / 7.1, 14 35.1 / 19.5 / 13.9, 26 60.3 / 31.3 / 20.7; 320 tiles, 4
+// 14.1 / 9.4 / 10.0, 14 35.0 / 20.0 / 19.7, 26 60.3 / 32.1 / 30.1; 375, 4 14.2 / 9.5 / 10.1, 26 60.6 / 32.5 / 30.5; 1,024, 5
+// 17.7 / 17.5 / 22.0, 26 63.9 / 55.4 / 58.4; 1,094, 5 25.8 / 24.9 / 27.2, 20 75.5 / 62.6 / 56.3; 1,188, 5 26.0 / 25.5 / 27.8, 14
+// 56.0 / 47.0 / 44.6; 1,500, four heads, 6 29.9 / 27.3 / 32.7, 14 56.9 / 49.6 / 53.8; 1,536, 6 30.1 / 27.6 / 32.9, 14
+// 56.8 / 49.1 / 53.0; 1,563, 6 29.9 / 32.0 / 36.2, 14 57.3 / 58.5 / 58.9.  Errors against 64 bits, 1 / 2: 6 blocks 1.39e-7 / 1.39e-7, 14
+// 1.58e-7 / 1.51e-7, 20 1.66e-7 / 1.56e-7.  Two ranges and their merge / 4: L = 8,000, W = 600 53.5 / 25.3, 1.70e-7 / 1.62e-7; three
 // ranges / 4: W = 1,000 51.9 / 37.1, 1.735e-7 / 1.740e-7.)
 int window_share(int64_t tiles, int64_t blocks, int nsplit) {
-  const int share = blocks < 4 ? 1 : tiles <= 320 ? 4 : tiles <= 1152 ? 2 : 1;
+  const int share = blocks < 4 ? 1 : tiles <= 320 ? 4 : tiles <= (blocks < 6 ? 1152 : 1536) ? 2 : 1;
   return nsplit == 1 || share >= 2 * nsplit ? share : 1;
 }
 

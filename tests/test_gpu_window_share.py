@@ -18,6 +18,9 @@ SHARE, ONE, GROUP = "tile_window_share_kernel", "tile_window_kernel", "tile_wind
     (MaskSpec(KIND_SLIDING, 10241, window=100), 1, SHARE),        # 321: two
     (MaskSpec(KIND_SLIDING, 4601, window=60), 8, SHARE),          # 1,152 tiles
     (MaskSpec(KIND_SLIDING, 4609, window=60), 8, ONE),            # 1,160
+    (MaskSpec(KIND_SLIDING, 4096, window=64), 12, ONE),           # 1,536 of five blocks
+    (MaskSpec(KIND_SLIDING, 4096, window=65), 12, SHARE),         # of six
+    (MaskSpec(KIND_SLIDING, 4097, window=65), 12, ONE),           # 1,548
     (MaskSpec(KIND_SLIDING, 4001, window=700), 1, SHARE),         # two ranges of keys would be the other form,
     (MaskSpec(KIND_SLIDING, 4001, window=1000), 1, ONE),          # three are
     (MaskSpec(KIND_DILATED, 3001, window=70, stride=3), 1, SHARE),
