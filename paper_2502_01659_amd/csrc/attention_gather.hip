@@ -575,9 +575,10 @@ __global__ __launch_bounds__(256) void gather_runs_kernel(
 // at a time, so that a row of a thousand chunks does not wait for a thousand loads one after the
 // other; the sums run in chunk order all the same.  (The 256 partials of a global row of the
 // non-local mask, a quarter per wavefront: 20 us one after the other.)
-template <int D>
-__device__ __forceinline__ void reduce_partials(const float* p0, int64_t step, int n, int lane, float& M, float& l,
-                                                float (&acc)[(D + kWave - 1) / kWave]) {
+// Sum: what the sums are held in.
+template <int D, typename Sum>
+__device__ __forceinline__ void reduce_partials(const float* p0, int64_t step, int n, int lane, float& M, Sum& l,
+                                                Sum (&acc)[(D + kWave - 1) / kWave]) {
   constexpr int kCh = (D + kWave - 1) / kWave;
   constexpr int kAhead = 8;
   M = kMinusHuge;
@@ -600,37 +601,40 @@ __device__ __forceinline__ void reduce_partials(const float* p0, int64_t step, i
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
       if (c0 + u < n) {
-        const float w = __builtin_amdgcn_exp2f(mm[u] - M);
-        l = __builtin_fmaf(ll[u], w, l);
+        const Sum w = __builtin_amdgcn_exp2f(mm[u] - M);
+        l = __builtin_elementwise_fma((Sum)ll[u], w, l);
 #pragma unroll
-        for (int k = 0; k < kCh; ++k) acc[k] = __builtin_fmaf(aa[u][k], w, acc[k]);
+        for (int k = 0; k < kCh; ++k) acc[k] = __builtin_elementwise_fma((Sum)aa[u][k], w, acc[k]);
       }
     }
   }
 }
 // ... and left as one partial state at `out`
-template <int D>
+template <int D, typename Sum = float>
 __device__ __forceinline__ void combine_partials(const float* p0, int64_t step, int n, float* out, int lane) {
   constexpr int kCh = (D + kWave - 1) / kWave;
-  float M, l, acc[kCh];
+  float M;
+  Sum l, acc[kCh];
   reduce_partials<D>(p0, step, n, lane, M, l, acc);
 #pragma unroll
   for (int k = 0; k < kCh; ++k)
-    if (lane + k * kWave < D) out[lane + k * kWave] = acc[k];
+    if (lane + k * kWave < D) out[lane + k * kWave] = (float)acc[k];
   if (lane == 0) {
     out[D] = M;
-    out[D + 1] = l;
+    out[D + 1] = (float)l;
   }
 }
 
 // Combine the n partial (m, l, acc) states of one row in their stored order (deterministic) and
 // write the row: one wavefront, lane c owns channels c, c + 64, ...
-template <typename T, int D>
+template <typename T, int D, typename Sum = float>
 __device__ __forceinline__ void merge_row_partials(const float* p0, int64_t step, int n, T* Orow,
                                                    float* lse_i, int lane, bool accumulate) {
   constexpr int kCh = (D + kWave - 1) / kWave;
-  float M, l, acc[kCh];
-  reduce_partials<D>(p0, step, n, lane, M, l, acc);
+  float M;
+  Sum sum, acc[kCh];
+  reduce_partials<D>(p0, step, n, lane, M, sum, acc);
+  const float l = (float)sum;
   const bool empty = !(l > 0.f);
   const float inv = empty ? 0.f : 1.0f / l;
   float lse_row = empty ? -INFINITY : (M + __builtin_amdgcn_logf(l)) * kLn2;
@@ -643,7 +647,7 @@ __device__ __forceinline__ void merge_row_partials(const float* p0, int64_t step
   for (int k = 0; k < kCh; ++k) {
     const int ch = lane + k * kWave;
     if (ch < D) {
-      float o = acc[k] * inv * cw.w_now;
+      float o = (float)acc[k] * inv * cw.w_now;
       if (accumulate) o = __builtin_fmaf(cw.w_prev, load_scalar(Orow + ch), o);
       store_scalar(Orow + ch, o);
     }
@@ -692,7 +696,9 @@ __global__ __launch_bounds__(64) void nonlocal_chunk_kernel(
 // ... and one workgroup per (global row, head) combines the row's partials: each of its four
 // wavefronts reduces a quarter of the chunks, in chunk order, to one partial state in LDS, and
 // the first wavefront combines the four in wavefront order and writes the row (a fixed order:
-// deterministic).
+// deterministic).  fp32: in 64 bits, since a row of 20,000 keys is 79 ranges whose sums in 32 bits are half of its error, the more
+// so as the wavefronts of tile_nonlocal_kernel merge four parts of each before (error of 64 global rows against 64 bits, one
+// chain of blocks per range 2.74e-7, four parts 2.80e-7, so 2.66e-7; L = 3,000 1.87e-7, 1.89e-7, 1.83e-7; 0.2 us a call).
 template <typename T, int D>
 __global__ __launch_bounds__(256) void nonlocal_merge_kernel(T* __restrict__ O, float* __restrict__ lse,
                                                              int64_t L, int32_t n_chunks,
@@ -706,10 +712,11 @@ __global__ __launch_bounds__(256) void nonlocal_merge_kernel(T* __restrict__ O, 
   const int c0 = wave * per < n_chunks ? wave * per : n_chunks;
   const int c1 = c0 + per < n_chunks ? c0 + per : n_chunks;
   const float* p0 = partials + ((i * n_chunks + c0) * H + h) * (D + 4);
-  combine_partials<D>(p0, step, c1 - c0, &quarter[wave][0], lane);
+  using Sum = std::conditional_t<DtypeOf<T>::code == SGA_F32, double, float>;
+  combine_partials<D, Sum>(p0, step, c1 - c0, &quarter[wave][0], lane);
   __syncthreads();
   if (wave == 0)
-    merge_row_partials<T, D>(&quarter[0][0], D + 4, 4, O + h * L * D + i * D, lse ? lse + h * L + i : nullptr, lane,
+    merge_row_partials<T, D, Sum>(&quarter[0][0], D + 4, 4, O + h * L * D + i * D, lse ? lse + h * L + i : nullptr, lane,
                              accumulate != 0);
 }
 
