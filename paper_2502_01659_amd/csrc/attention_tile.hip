@@ -366,9 +366,11 @@ __device__ __forceinline__ void rescale_state(TileState& st, float bm) {
 // kMatrixSum: the pairs are not summed by v_dot2_f32_f16, which no matrix instruction overlaps with, but by four 4 x 4 x 4
 // products with ones, whose lane l holds the sum of its own four numerators.  (Two wavefronts of one SIMD, one issuing matrix
 // products, the other the instruction, us alone / alone / together: dot2 242 / 244 / 489, packed conversion 236 / 237 /
-// 243, exp2 253 / 253 / 330.  Kernels of two wavefronts per SIMD with interior loops gain 1 to 3 %: +-1,359, L = 1,600,000
-// 1,366 -> 1,342 us; d = 128, +-2,048, L = 32,768, 32 heads 2,394 -> 2,368, +-200, L = 200,000, 4 heads 332 -> 323.  The others,
-// with four wavefronts per SIMD or masked blocks, do not, and tile_attend_f16_kernel loses 4 % on random masks.)
+// 243, exp2 253 / 253 / 330.  Kernels of two wavefronts per SIMD with interior loops take 3.4 % fewer cycles (+-1,359, L =
+// 1,600,000 2.93M -> 2.84M), most of which a lower clock takes back (1.97 -> 1.90 GHz): medians of 15 alternations, us, +-1,359
+// 1,377 -> 1,360; +-2,000, L = 400,000, 4 heads 1,901 -> 1,884; +-3,000, L = 400,000 761 -> 761; d = 128, +-2,048, L = 32,768, 32 heads
+// 2,461 -> 2,437, +-200, L = 200,000, 4 heads 340 -> 331, +-32, L = 300,000, 4 heads 264 -> 257.  The others, with four
+// wavefronts per SIMD or masked blocks, do not gain, and tile_attend_f16_kernel loses 4 % on random masks.)
 template <bool kMatrixSum = false>
 __device__ __forceinline__ void numerators_h(const floatx16& sv, float c, TileState& st, half8 (&ph)[2]) {
   const float neg_m = -st.m;
@@ -3703,10 +3705,11 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(256) voi
 // let four wavefronts of four workgroups share a SIMD where tile_window_band_kernel has two.  That kernel reads every
 // operand from LDS once for two sub-tiles, but a wavefront issues a vector instruction every five cycles at best, so two
 // of them leave the vector unit half idle, and each workgroup waits for its first blocks and its output with one other
-// beside it.  This one is bound by power where it runs long (1.48 GHz at +-1,359 where the other has 1.98, with 18 % fewer
-// cycles): there the two are level, and from about 140 blocks per workgroup on the other is 4 to 5 % faster (see
-// strip_is_faster).  us, that / this: one head, L = 400,000, W = 260 133 / 94, 400 152 / 124, 1,000 285 / 260; L = 30,000,
-// W = 500 41 / 23, 2,000 94 / 60; L = 8,000, W = 400 34 / 20; 2-D blocks of 1,100, L = 100,000, 8 heads 138 / 112.
+// beside it.  This one is bound by power where it runs long (+-1,359, L = 1,600,000: 2.45M cycles at 1.69 GHz, the other
+// 2.84M at 1.90): there the two are level, and from about 140 blocks per workgroup on the other is 2 to 8 % faster (see
+// strip_is_faster).  us, that / this: one head, L = 400,000, W = 257 134 / 99, 400 152 / 128, 1,000 288 / 270; L = 1,600,000, W = 257
+// 482 / 399, 400 555 / 513; L = 30,000, W = 577 43 / 26, 2,100 98 / 65; L = 8,000, W = 400 34 / 20; 2-D blocks of 1,100, L =
+// 1,600,000 653 / 635.
 // (Eight wavefronts on a ring of eight blocks: W = 260 320 where this has 289; without the scores one block ahead
 // 293; two groups of four wavefronts that swap matrix and vector work at barriers, 64 queries each, L = 1,600,000,
 // +-1,359: 1,350 -> 1,635.)
@@ -4623,7 +4626,7 @@ sga_status run_tile_implicit(const AttnArgs& a) {
   const WindowShape shape = window_shape(a);
   const int64_t Lc = shape.Lc;
   // fp16, 128 queries' key range fits the LDS at two workgroups per CU or more: one workgroup stages
-  // it once (128 queries per workgroup, as in the fp32 kernel); wider fp16 windows: 64 queries per wavefront
+  // it once (128 queries per workgroup, as in the fp32 kernel); wider fp16 windows: 32 or 64 queries per wavefront
   const bool wg = a.dtype == SGA_F16 && a.window <= kKvMaxWindow;
   const bool strip = a.dtype == SGA_F16 && !wg && strip_is_faster(a.window, Lc, shape.n_slots * a.H);
   const bool pair = a.dtype == SGA_F16 && !wg && !strip;
