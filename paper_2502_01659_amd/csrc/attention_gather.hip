@@ -698,7 +698,7 @@ __global__ __launch_bounds__(64) void nonlocal_chunk_kernel(
 // the first wavefront combines the four in wavefront order and writes the row (a fixed order:
 // deterministic).  fp32: in 64 bits, since a row of 20,000 keys is 79 ranges whose sums in 32 bits are half of its error, the more
 // so as the wavefronts of tile_nonlocal_kernel merge four parts of each before (error of 64 global rows against 64 bits, one
-// chain of blocks per range 2.74e-7, four parts 2.80e-7, so 2.66e-7; L = 3,000 1.87e-7, 1.89e-7, 1.83e-7; 0.2 us a call).
+// chain of blocks per range 2.74e-7, four parts 2.80e-7, so 2.66e-7; L = 3,000 1.87e-7, 1.89e-7, 1.83e-7; 0.1 us a call, 0.7 where 137 ranges are summed).
 template <typename T, int D>
 __global__ __launch_bounds__(256) void nonlocal_merge_kernel(T* __restrict__ O, float* __restrict__ lse,
                                                              int64_t L, int32_t n_chunks,
